@@ -9,6 +9,7 @@ import functools
 import math
 
 import torch
+import torch.nn.functional as F
 
 from paper_2302_00282_amd import xenos as X
 from workloads import cnn_graphs as wg
@@ -110,9 +111,9 @@ class Model:
             self.session.close()
 
 
-def prepare(case, seed):
-    """Parameters by the recipe of `workloads.cnn_graphs` (He-normal weights, BN statistics around one, input U[-1, 1]), drawn on the
-    GPU; then the plan of the graph, bound to its device memory."""
+def _drawn(case, seed):
+    """The graph with its parameters (NumPy arrays on the host) and the input on the GPU, by the recipe of `workloads.cnn_graphs`:
+    He-normal weights, BN statistics around one, input U[-1, 1], drawn on the GPU."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
 
@@ -132,7 +133,13 @@ def prepare(case, seed):
             else:
                 value = normal(zeros.shape, 0.1)
             op.params[key] = value.cpu().numpy()
-    return Model(graph, case, uniform(graph.input_shape, -1.0, 1.0))
+    return graph, uniform(graph.input_shape, -1.0, 1.0)
+
+
+def prepare(case, seed):
+    """The plan of the drawn graph, bound to its device memory."""
+    graph, x = _drawn(case, seed)
+    return Model(graph, case, x)
 
 
 def run(state):
@@ -167,3 +174,50 @@ def tolerance(case):
     if case["compute"] == "f32":
         return {"rel": 5e-6, "max": 2e-5}
     return {"rel": 1.5e-2, "max": 6e-2}
+
+
+def _plain(op, ins):
+    """One operator of the graph in torch, in the type of its inputs."""
+    a, x = op.attrs, ins[0]
+    p = {k: torch.from_numpy(v).to(x.device, x.dtype) for k, v in op.params.items()}
+    per_channel = lambda k: p[k].view(1, -1, 1, 1)
+    if op.kind == "conv":
+        return F.conv2d(x, p["weight"], p.get("bias"), stride=a["stride"], padding=a["pad"], groups=a["groups"])
+    if op.kind in ("fc", "matmul"):
+        return F.linear(x.flatten(1), p["weight"].flatten(1), p.get("bias"))[:, :, None, None]
+    if op.kind == "bias":
+        return x + per_channel("bias")
+    if op.kind == "bn":
+        return (x - per_channel("mean")) / torch.sqrt(per_channel("var") + a["eps"]) * per_channel("gamma") + per_channel("beta")
+    if op.kind == "relu":
+        return x.clamp_min(0)
+    if op.kind == "maxpool":
+        return F.max_pool2d(x, a["k"], a["stride"], a["pad"], ceil_mode=bool(a["ceil"]))
+    if op.kind == "gap":
+        return x.mean((2, 3), keepdim=True)
+    if op.kind == "add":
+        return ins[0] + ins[1]
+    if op.kind == "concat":
+        return torch.cat(ins, 1)
+    if op.kind == "slice":
+        return x[:, a["c_begin"]:a["c_begin"] + a["out_c"]]
+    assert op.kind == "shuffle", op.kind
+    n, c, h, w = x.shape
+    return x.view(n, a["groups"], c // a["groups"], h, w).transpose(1, 2).reshape(n, c, h, w)
+
+
+def exact(case, seed):
+    """The pass operator by operator in float64, a few images at a time."""
+    graph, x = _drawn(case, seed)
+    last = {t: i for i, op in enumerate(graph.ops) for t in op.inputs}
+    parts = []
+    for rows in x.split(128 if case["family"] == "matmul" else 4):
+        live = {0: rows.double()}
+        for i, op in enumerate(graph.ops):
+            live[i + 1] = _plain(op, [live[t] for t in op.inputs])
+            for t in set(op.inputs):
+                if last[t] == i and t != graph.output:
+                    del live[t]
+        parts.append(live[graph.output])
+    y = torch.cat(parts)
+    return y.permute(0, 2, 3, 1).contiguous() if FORMATS[case["io"]][1] == X.XENOS_NHWC else y
