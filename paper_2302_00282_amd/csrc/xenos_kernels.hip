@@ -28,6 +28,7 @@ __host__ __device__ constexpr int lds_conv_bytes() { return cmax(2 * (BM + BN) *
 // producer hands its result to the pointwise consumer in the consumer's channel-first order).
 template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE, bool DWPRO = false>
 __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE;
   constexpr int WAVES_N = BN / WN;
@@ -583,6 +584,7 @@ __device__ __forceinline__ float quad_add(float v) {
 // leave most compute units idle (7x7 and 14x14 at batch 32).
 template <typename T, int MODE, int PWID, int BN, bool PART = false>
 __global__ __launch_bounds__(V2_NT) void conv3x3_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
   constexpr int BM = V2_BM, NTH = V2_NT;
@@ -1248,6 +1250,7 @@ constexpr int PR_LDS = PR_OFF_STAGE + PR_NW * 64 * PR_SPW;
 
 template <int MODE, bool PMAX>
 __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   constexpr int BM = PR_BM, NTH = PR_NT, CE = 8;
   constexpr int ROWS = MODE == M_FLAT ? BM : BM / 4;               // staged rows: pixels, or pooled windows
   constexpr int NI = (PR_INMAX * 4 + NTH - 1) / NTH;               // input elements per thread
@@ -1583,6 +1586,7 @@ static int launch_pair(const ConvArgs& a, int dtype, hipStream_t st) {
 constexpr int FC_NW = 4, FC_NT = 64 * FC_NW, FC_BN = 32 * FC_NW, FC_DEPTH = 4;
 
 __global__ __launch_bounds__(FC_NT, 2) void fc_stream_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l31 = lane & 31, lhalf = lane >> 5;
   // Reduction shared out across workgroups (a.ksplit >= 1: a workgroup owns 128 channels, a wavefront 32 of them, and share z
@@ -1692,6 +1696,7 @@ static int launch_fc(const ConvArgs& a, int dtype, hipStream_t st) {
 // ---------------------------------------------------------------------------------------------
 template <typename T, int KB>
 __global__ __launch_bounds__(NT, sizeof(T) == 2 ? 4 : 2) void stem_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   __shared__ __align__(16) float s_scale[KB * 32];
   __shared__ __align__(16) float s_shift[KB * 32];
@@ -1891,6 +1896,7 @@ static_assert(sl_inpos(3) == 576 && sl_inpos(7) == 672, "the same limits as stem
 // which spills), 24 channels padded to 32: 28.3 -> 23.5 us with four)
 template <int KB, int NSTEP, bool POOL>
 __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void stem_lds_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   constexpr int K = KB * 32;
   constexpr int SPITCH = K * 2 + 16;                               // staging row pitch (odd number of 16-byte slots)
   constexpr int CPP = K * 2 / 16, PPI = 64 / CPP;                  // 16-byte chunks per output pixel, pixels per store instruction
@@ -2162,6 +2168,7 @@ __host__ __device__ constexpr int dwpw_lds(int cp, int esz) { return 64 * dwpw_p
 // the others; measured 2 % on a network of such chains at batch 32, four wavefronts spill and lose)
 template <typename T>
 __global__ __launch_bounds__(NT, 3) void dwpw_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
   constexpr int BM = 64, BN = 64;
@@ -2491,6 +2498,7 @@ size_t dwpw_lds_bytes(int panel_channels, int esz) { return (size_t)dwpw_lds(pan
 // item instead of three 64-bit ones, which cost more than the nine taps).
 template <typename T, bool K3, typename IDX>
 __global__ __launch_bounds__(NT) void dw_kernel(const DwArgs a) {
+  FETCH_ARGS(DwArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE;
   const int cv = a.C / CE;
@@ -2561,6 +2569,7 @@ int launch_dw(const DwArgs& a, int dtype, void* stream) {
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(NT) void splitk_finish_kernel(const SplitKArgs a) {
+  FETCH_ARGS(SplitKArgs);
   using tr = Tr<T>;
   // the shares of one output element, added in index order.  Eight loads are requested before the first is added: a
   // loop of load-then-add pays one cache latency per share (32 shares: 5 us for the plain pass, 20 us for the averaging
@@ -2650,6 +2659,7 @@ int launch_splitk_finish(const SplitKArgs& a, int dtype, void* stream) {
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(NT) void elt_kernel(const EltArgs a) {
+  FETCH_ARGS(EltArgs);
   using tr = Tr<T>;
   const long long total = a.pixels * a.C;
   for (long long idx = (long long)blockIdx.x * NT + threadIdx.x; idx < total; idx += (long long)gridDim.x * NT) {
@@ -2665,6 +2675,7 @@ __global__ __launch_bounds__(NT) void elt_kernel(const EltArgs a) {
 
 template <typename T>
 __global__ __launch_bounds__(NT) void elt_vec_kernel(const EltArgs a) {
+  FETCH_ARGS(EltArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE;
   const int cv = a.C / CE;

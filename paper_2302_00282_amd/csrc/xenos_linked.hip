@@ -178,6 +178,7 @@ __host__ __device__ constexpr int pwdw_lds(int positions, int esz) { return posi
 
 template <typename T>
 __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
   constexpr int BM = PD_BM, BN = PD_BN;
@@ -361,6 +362,7 @@ __host__ __device__ constexpr int fire_lds(int positions, int S, int esz, int po
 
 template <typename T, bool POOL, int TAPS1>
 __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, ESZ = (int)sizeof(T);
   constexpr int STP = fire_stg_pitch(ESZ), CBP = fire_cb_pitch(ESZ);
