@@ -1251,9 +1251,10 @@ struct Planner {
             double e = 0;
             for (int wch = 0; wch < 2; ++wch) {
               const int taps = wch ? 9 : 1;
-              const double copy = 0.7 + 0.15 * (64.0 * taps * S * p.esz / 4096.0);
-              const double gemm = px_chunks * (0.5 + (p.dt == DT_BF16 ? 0.028 : 0.11) * taps * kgs);
-              e += ((nt[wch] - z + shares - 1) / shares) * (copy + gemm + 0.9 + (pool ? 1.5 : 0.0));
+              const bool b16 = p.dt == DT_BF16;
+              const double copy = b16 ? 0.3 : 0.7 + 0.15 * (64.0 * taps * S * p.esz / 4096.0);
+              const double gemm = px_chunks * (0.5 + (b16 ? 0.016 : 0.11) * taps * kgs);
+              e += ((nt[wch] - z + shares - 1) / shares) * (copy + gemm + (b16 ? 0.4 : 0.9) + (pool ? 1.5 : 0.0));
             }
             ex_total += e; ex_longest = std::max(ex_longest, e);
           }
@@ -1313,7 +1314,9 @@ struct Planner {
         for (int c = 0; c < S; ++c)
           for (int t = 0; t < taps; ++t) {
             const float v = eg.weight[((size_t)k * S + c) * taps + t];
-            const size_t o = ((size_t)k * taps + t) * S + c;
+            // (bf16: in fragment order, [32-channel block][tap][k-group of 16][lane = 32 * (half of the group) + channel][8])
+            const size_t o = p.dt == DT_BF16 ? ((((size_t)(k / 32) * taps + t) * (S / 16) + c / 16) * 64 + (c % 16 / 8) * 32 + k % 32) * 8 + c % 8
+                                             : ((size_t)k * taps + t) * S + c;
             if (p.dt == DT_BF16) ((uint16_t*)base)[o] = f2bf_host(v); else ((float*)base)[o] = v;
           }
       push_affine(we.af, Epad, &st.fire_scale_off[which], &st.fire_shift_off[which]);

@@ -354,14 +354,22 @@ __host__ __device__ constexpr int fire_sq_pitch(int S, int esz) { return S * esz
 __host__ __device__ constexpr int fire_w_pitch(int taps, int S, int esz) { return taps * S * esz + 16; }
 __host__ __device__ constexpr int fire_stg_pitch(int esz) { return 32 * esz + 16; }
 __host__ __device__ constexpr int fire_cb_pitch(int esz) { return 64 * esz + 16; }
-// LDS: squeeze block | max(GEMM stages, one 3x3 weight tile) | 4 per-wavefront staging slices | pooled form: conv block of a channel tile
+// LDS, fp32: squeeze block | max(GEMM stages, one 3x3 weight tile) | 4 per-wavefront staging slices | pooled form: conv block of
+// a channel tile.  bf16: squeeze block | GEMM stages, whose space the staging slices and the conv block take over afterwards.
 __host__ __device__ constexpr int fire_lds(int positions, int S, int esz, int pool_positions) {
-  return positions * fire_sq_pitch(S, esz) + cmax(PG_STAGES_BYTES, 64 * fire_w_pitch(9, S, esz)) + 4 * 32 * fire_stg_pitch(esz) +
-         pool_positions * fire_cb_pitch(esz);
+  return esz == 2 ? positions * fire_sq_pitch(S, esz) + cmax(PG_STAGES_BYTES, 4 * 32 * fire_stg_pitch(esz) + pool_positions * fire_cb_pitch(esz))
+                  : positions * fire_sq_pitch(S, esz) + cmax(PG_STAGES_BYTES, 64 * fire_w_pitch(9, S, esz)) + 4 * 32 * fire_stg_pitch(esz) +
+                        pool_positions * fire_cb_pitch(esz);
 }
 
-template <typename T, bool POOL, int TAPS1>
-__global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
+// KGS (bf16): S / 16, the MFMA k-groups of a tap.  The weights of a wavefront's 32 expand channels, 1 or 9 taps x KGS fragments
+// packed in fragment order, then go from memory straight into registers and stay there for all pixel chunks of the tile: the
+// first 1x1 tile's are requested before phase 1 and the first 3x3 tile's behind it, so their latency passes under the GEMMs,
+// phase 2 has no barrier (unpooled) and reads only pixel fragments from LDS.  Staged through LDS, a 3x3 tile over 64 channels
+// cost a copy of 3.2 us before its first MFMA and twice the fragment reads.  0 (fp32, whose fragments do not fit the registers):
+// the weights of a tile are copied to LDS.
+template <typename T, bool POOL, int TAPS1, int KGS>
+__global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, ESZ = (int)sizeof(T);
@@ -383,8 +391,9 @@ __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
   unsigned char* s_sq = smem;
   unsigned char* s_b = smem + PH * PWd * SQP;
   const int bbytes = 64 * fire_w_pitch(9, S, ESZ);
-  unsigned char* s_stg = s_b + (bbytes > PG_STAGES_BYTES ? bbytes : PG_STAGES_BYTES) + wave * 32 * STP;
-  unsigned char* s_cb = s_b + (bbytes > PG_STAGES_BYTES ? bbytes : PG_STAGES_BYTES) + 4 * 32 * STP;   // POOL: [conv pixel][64 channels]
+  unsigned char* s_free = KGS > 0 ? s_b : s_b + (bbytes > PG_STAGES_BYTES ? bbytes : PG_STAGES_BYTES);
+  unsigned char* s_stg = s_free + wave * 32 * STP;
+  unsigned char* s_cb = s_free + 4 * 32 * STP;                     // POOL: [conv pixel][64 channels]
   const int tiles_sp = a.tiles_y * a.tiles_x;
   const int npix = CH * CW;
 
@@ -402,6 +411,21 @@ __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
       const u32x4_t z = {0u, 0u, 0u, 0u};
       for (int i = tid; i < PH * PWd * (SQP / 16); i += NT) *(u32x4_t*)(s_sq + i * 16) = z;
     }
+    // KGS > 0: this wavefront's weight fragments of the first tile of each part
+    u32x4_t w0[KGS > 0 ? KGS : 1];
+    auto load_w = [&](int which, int j, auto& w) __attribute__((always_inline)) {
+      constexpr int NF = sizeof(w) / sizeof(u32x4_t);
+      if (a.fire_E[which] > 0) {
+        const u32x4_t* src = (const u32x4_t*)a.fire_w[which] + (j * 64 < a.fire_E[which] ? j * 2 + wave_n : 0) * NF * 64 + lane;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) w[f] = src[f * 64];
+      } else {                                                     // (not left undefined: the registers would be kept over the whole kernel)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) w[f] = u32x4_t{0u, 0u, 0u, 0u};
+      }
+    };
+    if constexpr (KGS > 0) load_w(0, gz, w0);
+
     // ---- phase 1: the squeeze chain of the block, into LDS -------------------------------------------------
     // (scale and shift of this lane's channels are the same for every chunk: requested once)
     f32x4_t qsc[4], qsh[4];
@@ -449,11 +473,154 @@ __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
     __syncthreads();                                               // the block is complete, the GEMM stages are free
 
     // ---- phase 2: this workgroup's expand tiles -----------------------------------------------------------
+    // epilogue of a wavefront's 32 pixels x 32 channels of chunk mc of channel tile j
+    auto tile_epilogue = [&](int which, int j, int mc, const f32x16_t& acc) __attribute__((always_inline)) {
+      const int E = a.fire_E[which];
+      const float lo = a.fire_relu[which] ? 0.f : -3.4028235e38f;
+      // finished values change hands inside the wavefront only
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int c = g * 8 + lhalf * 4, kk = j * 64 + wave_n * 32 + c;
+        const f32x4_t sc = *(const f32x4_t*)(a.fire_scale[which] + kk), sh = *(const f32x4_t*)(a.fire_shift[which] + kk);
+        float y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
+        if constexpr (sizeof(T) == 2) {
+          uint2 o;
+          o.x = f2bf2(y[0], y[1]);
+          o.y = f2bf2(y[2], y[3]);
+          *(uint2*)(s_stg + l31 * STP + c * 2) = o;
+        } else {
+          *(u32x4_t*)(s_stg + l31 * STP + c * 4) = u32x4_t{__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 32 * G / 64; ++u) {
+        const int idx = lane + u * 64, r = idx / G, cg = idx - r * G;
+        const int mr = mc * 64 + wave_m * 32 + r;
+        const int k0 = j * 64 + wave_n * 32 + cg * CE;
+        u32x4_t v;
+        if constexpr (sizeof(T) == 2) {
+          const uint2 lo8 = *(const uint2*)(s_stg + r * STP + cg * 16), hi8 = *(const uint2*)(s_stg + r * STP + cg * 16 + 8);
+          v = u32x4_t{lo8.x, lo8.y, hi8.x, hi8.y};
+        } else {
+          v = *(const u32x4_t*)(s_stg + r * STP + cg * 16);
+        }
+        if (mr < npix && k0 < E) {
+          const int qy = mr / CW, qx = mr - qy * CW;
+          if constexpr (POOL) {
+            *(u32x4_t*)(s_cb + mr * CBP + (wave_n * 32 + cg * CE) * ESZ) = v;
+          } else {
+            const int oy = oy0 + qy, ox = ox0 + qx;
+            if (oy < a.H && ox < a.W)
+              *(u32x4_t*)((T*)a.fire_out[which] + (long long)n * a.fire_sN[which] + (long long)(oy * a.W + ox) * a.fire_sP[which] + k0) = v;
+          }
+        }
+      }
+    };
+    // POOL: the windows of channel tile j out of its conv block
+    auto tile_pool = [&](int which, int j) __attribute__((always_inline)) {
+      const int E = a.fire_E[which];
+      __syncthreads();                                         // the conv block of this channel tile is complete
+      // one thread = one 16-byte channel group of one pooling window; windows are clipped to the map (never empty)
+      constexpr int CG = 64 / CE;
+      for (int idx = tid; idx < a.pph * a.ppw * CG; idx += NT) {
+        const int q = idx / CG, cg = idx - q * CG, k0 = j * 64 + cg * CE;
+        const int qy = q / a.ppw, qx = q - qy * a.ppw;
+        const int gy = ty * a.pph + qy, gx = tx * a.ppw + qx;
+        if (gy >= a.PH || gx >= a.PW || k0 >= E) continue;
+        float mx[CE];
+#pragma unroll
+        for (int e = 0; e < CE; ++e) mx[e] = -INFINITY;
+        if (a.pk == 3) {
+          // all nine reads of the window are issued before the first maximum (elements outside the map read the
+          // window's first element, which is inside, once more): as a loop over rows and columns the stage paid one
+          // LDS latency per element, 3 of the 21 us of a pooled module's workgroup at batch 32
+          u32x4_t wv9[9];
+#pragma unroll
+          for (int t9 = 0; t9 < 9; ++t9) {
+            const int cy = qy * a.ps + t9 / 3, cx = qx * a.ps + t9 % 3;
+            const bool in = oy0 + cy < a.H && ox0 + cx < a.W;   // (no padding: windows start inside the map)
+            wv9[t9] = *(const u32x4_t*)(s_cb + (in ? cy * CW + cx : qy * a.ps * CW + qx * a.ps) * CBP + cg * 16);
+          }
+#pragma unroll
+          for (int t9 = 0; t9 < 9; ++t9) {
+            float x[CE];
+            tr::unpack(wv9[t9], x);
+#pragma unroll
+            for (int e = 0; e < CE; ++e) mx[e] = fmx_raw(mx[e], x[e]);
+          }
+        } else {
+          for (int r = 0; r < a.pk; ++r)
+            for (int c = 0; c < a.pk; ++c) {
+              const int cy = qy * a.ps + r, cx = qx * a.ps + c;
+              const int oy = oy0 + cy, ox = ox0 + cx;
+              if (oy < 0 || oy >= a.H || ox < 0 || ox >= a.W) continue;
+              float x[CE];
+              tr::unpack(*(const u32x4_t*)(s_cb + (cy * CW + cx) * CBP + cg * 16), x);
+#pragma unroll
+              for (int e = 0; e < CE; ++e) mx[e] = fmx_raw(mx[e], x[e]);
+            }
+        }
+        *(u32x4_t*)((T*)a.fire_out[which] + (long long)n * a.fire_sN[which] + (long long)(gy * a.PW + gx) * a.fire_sP[which] + k0) = tr::pack(mx);
+      }
+      __syncthreads();                                             // the conv block is rewritten by the next tile
+    };
+    // block position of the first tap of this lane's pixel in chunk mc: the 1x1 expand reads the pixel itself, the 3x3 its window
+    auto first_tap = [&](int which, int mc) __attribute__((always_inline)) -> const unsigned char* {
+      const int m = mc * 64 + wave_m * 32 + l31;
+      const int mm = m < npix ? m : 0;
+      const int py = mm / CW, px = mm - py * CW;
+      return s_sq + ((py + (which ? 0 : ring)) * PWd + px + (which ? 0 : ring)) * SQP + lhalf * 16;
+    };
+    if constexpr (KGS > 0) {
+      // the tiles gz, gz + tiles_n, ... of one part; w holds the fragments of the first
+      auto tiles = [&](int which, auto& w) __attribute__((always_inline)) {
+        constexpr int TAPS = sizeof(w) / sizeof(u32x4_t) / KGS;
+#pragma unroll 1
+        for (int j = gz; j * 64 < a.fire_E[which]; j += a.tiles_n) {
+          if (j != gz) load_w(which, j, w);
+#pragma unroll 1
+          for (int mc = 0; mc * 64 < npix; ++mc) {
+            const unsigned char* pa = first_tap(which, mc);
+            f32x16_t acc;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+            // pixel fragments one group of taps ahead; the barriers keep the scheduler from requesting all of them at once, which
+            // takes the registers of the second workgroup
+            constexpr int GT = TAPS == 9 && KGS <= 2 ? 3 : 1, NG = TAPS / GT;
+            u32x4_t fa[2][GT * KGS];
+            auto fetch = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+              for (int f = 0; f < GT * KGS; ++f) {
+                const int tap = g * GT + f / KGS;
+                fa[g & 1][f] = *(const u32x4_t*)(pa + ((tap / 3) * PWd + tap % 3) * SQP + (f % KGS) * 32);
+              }
+            };
+            fetch(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+              if (g + 1 < NG) fetch(g + 1);
+#pragma unroll
+              for (int f = 0; f < GT * KGS; ++f)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w[g * GT * KGS + f]), __builtin_bit_cast(bf16x8_t, fa[g & 1][f]), acc, 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            tile_epilogue(which, j, mc, acc);
+          }
+          if constexpr (POOL) tile_pool(which, j);
+        }
+      };
+      u32x4_t w1[9 * KGS];
+      load_w(1, gz, w1);
+      tiles(0, w0);
+      tiles(1, w1);
+      __syncthreads();                                             // the squeeze block and the stages are rewritten
+    } else {
 #pragma unroll 1
     for (int which = 0; which < 2; ++which) {                      // 0: the 1x1 expand, 1: the 3x3 expand
       const int taps = which ? 9 : 1, E = a.fire_E[which];
       const int WP = fire_w_pitch(taps, S, ESZ), wrow_b = taps * S * ESZ;   // LDS pitch and bytes of a channel's weights
-      const float lo = a.fire_relu[which] ? 0.f : -3.4028235e38f;
 #pragma unroll 1
       for (int j = gz; j * 64 < E; j += a.tiles_n) {
         {   // the tile's weights: 64 channels x taps x S, contiguous in memory (rows beyond E are zero)
@@ -479,11 +646,7 @@ __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
         __syncthreads();
 #pragma unroll 1
         for (int mc = 0; mc * 64 < npix; ++mc) {
-          const int m = mc * 64 + wave_m * 32 + l31;
-          const int mm = m < npix ? m : 0;
-          const int py = mm / CW, px = mm - py * CW;
-          // block position of the pixel's first tap: the 1x1 expand reads the pixel itself, the 3x3 its window
-          const unsigned char* pa = s_sq + ((py + (which ? 0 : ring)) * PWd + px + (which ? 0 : ring)) * SQP + lhalf * 16;
+          const unsigned char* pa = first_tap(which, mc);
           const unsigned char* pb = s_b + (wave_n * 32 + l31) * WP + lhalf * 16;
           f32x16_t acc;
 #pragma unroll
@@ -494,117 +657,46 @@ __global__ __launch_bounds__(NT) void fire_kernel(const ConvArgs a) {
             const unsigned char* tb = pb + tap * S * ESZ;
             for (int kg = 0; kg < kgs; ++kg) {
               const u32x4_t fa = *(const u32x4_t*)(ta + kg * 32), fb = *(const u32x4_t*)(tb + kg * 32);
-              if constexpr (sizeof(T) == 2) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb), __builtin_bit_cast(bf16x8_t, fa), acc, 0, 0, 0);
-              } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[e]), __uint_as_float(fa[e]), acc, 0, 0, 0);
-              }
+              for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[e]), __uint_as_float(fa[e]), acc, 0, 0, 0);
             }
           }
-          // epilogue of the wavefront's 32 pixels x 32 channels: finished values change hands inside the wavefront only
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int c = g * 8 + lhalf * 4, kk = j * 64 + wave_n * 32 + c;
-            const f32x4_t sc = *(const f32x4_t*)(a.fire_scale[which] + kk), sh = *(const f32x4_t*)(a.fire_shift[which] + kk);
-            float y[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
-            if constexpr (sizeof(T) == 2) {
-              uint2 o;
-              o.x = f2bf2(y[0], y[1]);
-              o.y = f2bf2(y[2], y[3]);
-              *(uint2*)(s_stg + l31 * STP + c * 2) = o;
-            } else {
-              *(u32x4_t*)(s_stg + l31 * STP + c * 4) = u32x4_t{__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3])};
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 32 * G / 64; ++u) {
-            const int idx = lane + u * 64, r = idx / G, cg = idx - r * G;
-            const int mr = mc * 64 + wave_m * 32 + r;
-            const int k0 = j * 64 + wave_n * 32 + cg * CE;
-            u32x4_t v;
-            if constexpr (sizeof(T) == 2) {
-              const uint2 lo8 = *(const uint2*)(s_stg + r * STP + cg * 16), hi8 = *(const uint2*)(s_stg + r * STP + cg * 16 + 8);
-              v = u32x4_t{lo8.x, lo8.y, hi8.x, hi8.y};
-            } else {
-              v = *(const u32x4_t*)(s_stg + r * STP + cg * 16);
-            }
-            if (mr < npix && k0 < E) {
-              const int qy = mr / CW, qx = mr - qy * CW;
-              if constexpr (POOL) {
-                *(u32x4_t*)(s_cb + mr * CBP + (wave_n * 32 + cg * CE) * ESZ) = v;
-              } else {
-                const int oy = oy0 + qy, ox = ox0 + qx;
-                if (oy < a.H && ox < a.W)
-                  *(u32x4_t*)((T*)a.fire_out[which] + (long long)n * a.fire_sN[which] + (long long)(oy * a.W + ox) * a.fire_sP[which] + k0) = v;
-              }
-            }
-          }
+          tile_epilogue(which, j, mc, acc);
         }
-        if constexpr (POOL) {
-          __syncthreads();                                         // the conv block of this channel tile is complete
-          // one thread = one 16-byte channel group of one pooling window; windows are clipped to the map (never empty)
-          constexpr int CG = 64 / CE;
-          for (int idx = tid; idx < a.pph * a.ppw * CG; idx += NT) {
-            const int q = idx / CG, cg = idx - q * CG, k0 = j * 64 + cg * CE;
-            const int qy = q / a.ppw, qx = q - qy * a.ppw;
-            const int gy = ty * a.pph + qy, gx = tx * a.ppw + qx;
-            if (gy >= a.PH || gx >= a.PW || k0 >= E) continue;
-            float mx[CE];
-#pragma unroll
-            for (int e = 0; e < CE; ++e) mx[e] = -INFINITY;
-            if (a.pk == 3) {
-              // all nine reads of the window are issued before the first maximum (elements outside the map read the
-              // window's first element, which is inside, once more): as a loop over rows and columns the stage paid one
-              // LDS latency per element, 3 of the 21 us of a pooled module's workgroup at batch 32
-              u32x4_t wv9[9];
-#pragma unroll
-              for (int t9 = 0; t9 < 9; ++t9) {
-                const int cy = qy * a.ps + t9 / 3, cx = qx * a.ps + t9 % 3;
-                const bool in = oy0 + cy < a.H && ox0 + cx < a.W;   // (no padding: windows start inside the map)
-                wv9[t9] = *(const u32x4_t*)(s_cb + (in ? cy * CW + cx : qy * a.ps * CW + qx * a.ps) * CBP + cg * 16);
-              }
-#pragma unroll
-              for (int t9 = 0; t9 < 9; ++t9) {
-                float x[CE];
-                tr::unpack(wv9[t9], x);
-#pragma unroll
-                for (int e = 0; e < CE; ++e) mx[e] = fmx_raw(mx[e], x[e]);
-              }
-            } else {
-              for (int r = 0; r < a.pk; ++r)
-                for (int c = 0; c < a.pk; ++c) {
-                  const int cy = qy * a.ps + r, cx = qx * a.ps + c;
-                  const int oy = oy0 + cy, ox = ox0 + cx;
-                  if (oy < 0 || oy >= a.H || ox < 0 || ox >= a.W) continue;
-                  float x[CE];
-                  tr::unpack(*(const u32x4_t*)(s_cb + (cy * CW + cx) * CBP + cg * 16), x);
-#pragma unroll
-                  for (int e = 0; e < CE; ++e) mx[e] = fmx_raw(mx[e], x[e]);
-                }
-            }
-            *(u32x4_t*)((T*)a.fire_out[which] + (long long)n * a.fire_sN[which] + (long long)(gy * a.PW + gx) * a.fire_sP[which] + k0) = tr::pack(mx);
-          }
-        }
-        __syncthreads();                                           // the weight tile (and the conv block) are rewritten
+        if constexpr (POOL) tile_pool(which, j);
+        else __syncthreads();                                      // the weight tile is rewritten
       }
+    }
     }
   }
 }
 
-template <typename T, bool POOL, int TAPS1>
-static int launch_fire_inst(const ConvArgs& a, int lds, hipStream_t st) {
+template <typename T, bool POOL, int TAPS1, int KGS>
+static int launch_fire_kgs(const ConvArgs& a, int lds, hipStream_t st) {
   static int raised = 0;
   if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)fire_kernel<T, POOL, TAPS1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipError_t e = hipFuncSetAttribute((const void*)fire_kernel<T, POOL, TAPS1, KGS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return (int)e;
     raised = lds;
   }
-  hipLaunchKernelGGL((fire_kernel<T, POOL, TAPS1>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
+  hipLaunchKernelGGL((fire_kernel<T, POOL, TAPS1, KGS>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
+}
+
+template <typename T, bool POOL, int TAPS1>
+static int launch_fire_inst(const ConvArgs& a, int lds, hipStream_t st) {
+  if constexpr (sizeof(T) == 2) {
+    switch (a.K / 16) {
+      case 1: return launch_fire_kgs<T, POOL, TAPS1, 1>(a, lds, st);
+      case 2: return launch_fire_kgs<T, POOL, TAPS1, 2>(a, lds, st);
+      case 3: return launch_fire_kgs<T, POOL, TAPS1, 3>(a, lds, st);
+      case 4: return launch_fire_kgs<T, POOL, TAPS1, 4>(a, lds, st);
+    }
+    return (int)hipErrorInvalidValue;
+  } else {
+    return launch_fire_kgs<T, POOL, TAPS1, 0>(a, lds, st);
+  }
 }
 
 template <typename T>
