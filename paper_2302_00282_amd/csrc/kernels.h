@@ -65,6 +65,9 @@ static const int kPwDwChannels = 64, kPwDwMaxPositions = 400;
 // as one chain: the squeeze output of a tile (+ halo, at most kFireMaxPositions positions, at most 64 channels) stays in LDS
 static const int kFireCfg = 10;
 static const int kFireMaxPositions = 400;
+// Configuration index of the kernel that runs pointwise -> depthwise 3x3 -> pointwise as one chain, a tile of output pixels x all
+// channels per workgroup
+static const int kUnitCfg = 11;
 static const int kFcWgPerCu = 1;
 static const int kFcDirectSteps = 16;   // reductions of at most this many 64-element steps are not shared out (no summing pass)    // workgroups per compute unit the reduction split of such a chain aims at
 static const int kPairChannels = 64, kPairRed = 48;
@@ -89,6 +92,7 @@ struct ConvArgs {
   int in_f32;            // scalar loader: input elements are fp32 (graph input) instead of the compute type
   int K, R, S, stride, pad, OH, OW;
   int Kred, Kred_pad;    // R*S*C and its padding to the reduction step
+  int wfrag;             // weights in fragment order: [32-channel block][step][k-group][lane][16 bytes]
   int kchunk;            // reduction order: 1 = (channel chunk, r, s, channel in chunk), needs C % step == 0; 0 = (r, s, c)
   int mode;              // M_*
   int relu, has_res;
@@ -126,6 +130,11 @@ struct ConvArgs {
   const void* fire_w[2]; const float* fire_scale[2]; const float* fire_shift[2];
   void* fire_out[2]; long long fire_sN[2], fire_sP[2];
   int fire_E[2], fire_relu[2];
+  // linked unit (unit_kernel): this chain is the second pointwise convolution of pointwise -> depthwise 3x3 -> pointwise; `in` is
+  // the input of the first (unit_C channels, weights fire_w[0] in fragment order with a reduction padded to unit_kred, epilogue
+  // fire_scale / fire_shift / fire_relu[0]), C the channels of the depthwise convolution (dw_*) over the dw_H x dw_W map,
+  // th x tw the tile of output pixels
+  int unit, unit_C, unit_kred;
   // reduction split across workgroups (ksplit >= 1, M_FLAT only; 0 = none): share z covers steps [z*steps_per_split, ...)
   // and writes raw fp32 sums to part[z][m][k] (row pitch part_ld); a splitk_finish pass completes the chain
   int ksplit, steps_per_split, part_ld;
@@ -208,6 +217,9 @@ size_t probe_out_bytes(int num_cu);
 // pointwise -> depthwise kernel (xenos_linked.hip)
 int launch_pwdw(const ConvArgs& a, int dtype, void* stream);
 size_t pwdw_lds_bytes(int th, int tw, int stride, int esz);
+// pointwise -> depthwise -> pointwise kernel (xenos_unit.hip)
+int launch_unit(const ConvArgs& a, int dtype, void* stream);
+size_t unit_lds_bytes(int th, int tw, int stride, int c1, int c, int esz);
 // Fire-module kernel (xenos_linked.hip); conv_h x conv_w = conv-output pixels of a tile
 int launch_fire(const ConvArgs& a, int dtype, void* stream);
 size_t fire_lds_bytes(int conv_h, int conv_w, int S, int esz, int pooled, int ring = 1);   // ring: halo of the block (1 with a 3x3 part)

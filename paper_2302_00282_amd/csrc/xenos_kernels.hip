@@ -2437,10 +2437,10 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
   if (cfg < kHaloCfg && a.xcd_m != 1 && a.xcd_m != 2 && a.xcd_m != 4 && a.xcd_m != 8) return (int)hipErrorInvalidValue;
   if (a.ksplit >= 1 && (a.mode != M_FLAT || !a.part || a.steps_per_split < 1 || (a.dw_w && a.dw_panel <= 0))) return (int)hipErrorInvalidValue;
   if (a.ileave) {
-    // the interleaving store exists in the pixel-major epilogues of the general kernel and of the depthwise-panel kernel;
+    // the interleaving store exists in the pixel-major epilogues of the general, the depthwise-panel and the unit kernel;
     // it moves whole 16-byte groups
     const int ce = dtype == DT_BF16 ? 8 : 4, esz = dtype == DT_BF16 ? 2 : 4;
-    if (cfg >= kHaloCfg || a.mode != M_FLAT || a.has_res || a.ksplit >= 1 || a.pair || !a.res || a.out_f32 || a.out_sK != 1 ||
+    if ((cfg >= kHaloCfg && cfg != kUnitCfg) || a.mode != M_FLAT || a.has_res || a.ksplit >= 1 || a.pair || !a.res || a.out_f32 || a.out_sK != 1 ||
         (a.ileave != 1 && a.ileave != 2) || a.K % ce != 0 || a.out_sP % ce != 0 || a.out_sN % ce != 0 || a.res_sP % ce != 0 || a.res_sN % ce != 0 ||
         ((uintptr_t)a.out % 16) != 0 || ((uintptr_t)a.res % 16) != 0 || a.out_sP < 2 * a.K || a.res_sP < a.K || esz * ce != 16)
       return (int)hipErrorInvalidValue;
@@ -2457,6 +2457,10 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
   if (cfg == kFireCfg || a.fire) {
     if (cfg != kFireCfg || !a.fire || scalar_loader) return (int)hipErrorInvalidValue;
     return launch_fire(a, dtype, st);
+  }
+  if (cfg == kUnitCfg || a.unit) {
+    if (cfg != kUnitCfg || !a.unit || scalar_loader) return (int)hipErrorInvalidValue;
+    return launch_unit(a, dtype, st);
   }
   if (cfg == kPwDwCfg || a.pwdw) {
     if (cfg != kPwDwCfg || !a.pwdw || scalar_loader) return (int)hipErrorInvalidValue;

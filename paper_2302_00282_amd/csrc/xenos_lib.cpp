@@ -175,6 +175,9 @@ void write_plan_json(xenos_plan& p);
 // ---------------------------------------------------------------------------------------------
 // Planner
 // ---------------------------------------------------------------------------------------------
+// Fewest output pixels (all images) of a chain on unit_kernel
+constexpr long long kUnitMinPixels = 1024;
+
 struct Planner {
   const xenos_graph& g;
   xenos_plan& p;
@@ -370,6 +373,10 @@ struct Planner {
     int k = 0, stride = 0, pad = 0, H = 0, W = 0, relu = 0;
     double flops = 0;
     long long bytes_w = 0;
+    // the depthwise chain's own producer, a pointwise chain linked in front of it (unit_kernel): v_in is then its input
+    bool unit = false;
+    long long pw_w_off = -1, pw_scale_off = -1, pw_shift_off = -1;
+    int pw_C = 0, pw_kred = 0, pw_relu = 0, th = 0, tw = 0;
   } dwpro;
 
   // A first-layer 3x3 chain waiting to be linked into the 3x3 convolution that consumes it (link level 3; Table 1,
@@ -793,19 +800,19 @@ struct Planner {
     auto kidx = [&](int c, int rs) -> size_t {
       return kchunk ? ((size_t)(c / bke) * R * S + rs) * bke + c % bke : (size_t)rs * C + c;
     };
-    if (st.fc_stream) {
-      // Weight-streaming kernel: the fragments of a 32-channel block are stored in the order its wavefront loads them,
-      // [block][step of 64][k-group of 16][lane = 32 * (half of the k-group) + channel][8 elements], so every load
-      // instruction reads 1 KB of consecutive memory and a block's share of the reduction is one sequential stream
-      const int nsteps = kred_pad / 64;
-      uint16_t* dst = (uint16_t*)base;
+    if (st.fc_stream || st.conv.wfrag) {
+      // Fragment order: the operands of a 32-channel block are stored as a wavefront loads them, [block][128-byte step]
+      // [k-group of 32 bytes][lane = 32 * (half of the k-group) + channel][16 bytes], so every load instruction reads 1 KB of
+      // consecutive memory and a block's share of the reduction is one sequential stream
+      const size_t nsteps = kred_pad / bke;
       for (int k = 0; k < K; ++k) {
         const float* src = o.weight.data() + (size_t)k * Csrc * R * S;
         for (int c = 0; c < Csrc; ++c)
           for (int rs = 0; rs < R * S; ++rs) {
-            const size_t kk = (size_t)rs * C + c;
-            const size_t step = kk / 64, g = (kk % 64) / 16, half = (kk % 16) / 8, e = kk % 8;
-            dst[(((((size_t)(k / 32) * nsteps + step) * 4 + g) * 64 + half * 32 + k % 32) * 8) + e] = f2bf_host(src[wch(c) * R * S + rs]);
+            const size_t at = kidx(c, rs) * p.esz, in_step = at % kRowBytes;
+            unsigned char* dst = base + ((((k / 32) * nsteps + at / kRowBytes) * 4 + in_step / 32) * 64 + (in_step % 32) / 16 * 32 + k % 32) * 16 + in_step % 16;
+            const float v = src[wch(c) * R * S + rs];
+            if (p.dt == DT_BF16) *(uint16_t*)dst = f2bf_host(v); else *(float*)dst = v;
           }
       }
       st.bytes_w = (long long)K * R * S * Csrc * p.esz;
@@ -1124,6 +1131,92 @@ struct Planner {
     if (nd2.groups != 1 || nd2.kh != 1 || nd2.kw != 1 || nd2.stride_h != 1 || nd2.pad_h != 0) return true;
     (void)i;
     return pwdw_consumer(nx) >= 0;
+  }
+
+  // ---- link level 3, pointwise -> depthwise -> pointwise (unit_kernel) --------------------------------------------
+  // The pointwise convolution behind depthwise node dn (= pwdw_consumer(i)) if all three can run as one chain: a plain 1x1
+  // chain of its own (no shortcut, no pooling) that stores 16-byte channel groups, or finishes a two-group shuffle whose other
+  // part exists already.  A pointwise convolution that hands on to the next depthwise one stays out (see pwdw_wanted), and so
+  // do few pixels, which are better spread over the units by channel tiles too, as two chains.  Returns the node or -1.
+  int unit_consumer(int i, int dn) const {
+    const Shape os = tshape[dn + 1];
+    if ((long long)os.n * os.h * os.w < kUnitMinPixels) return -1;
+    const int src = nodes[i].in[0] - 1;
+    if (src >= 0 && nodes[src].kind == XENOS_OP_SHUFFLE && fold_shuffle[src]) return -1;
+    const ChainWalk w2 = walk_chain(dn);
+    if (w2.cur == out_tid || placed.count(w2.cur) || fin.count(w2.cur)) return -1;
+    const int pw = single_consumer(w2.cur);
+    if (pw < 0 || nodes[pw].kind != XENOS_OP_CONV || node_step[pw] >= 0) return -1;
+    const xenos_op_desc& pd = desc(nodes[pw]);
+    if (pd.groups != 1 || pd.kh != 1 || pd.kw != 1 || pd.stride_h != 1 || pd.pad_h != 0 || pd.out_c % p.ce != 0) return -1;
+    const int next_dw = pwdw_consumer(pw);
+    if (next_dw >= 0 && pwdw_wanted(pw, next_dw)) return -1;
+    const ChainWalk w3 = walk_chain(pw);
+    if (w3.has_res || w3.pool_node >= 0) return -1;
+    const auto f = fin.find(w3.cur);
+    if (f != fin.end()) {
+      if (!available(f->second.other)) return -1;
+    } else {
+      const auto pl = placed.find(w3.cur);
+      if (pl != placed.end() && (pl->second.c_stride != 1 || pl->second.c_off % p.ce != 0)) return -1;
+      if (w3.cur == out_tid && !ext_is_internal(p.out)) return -1;
+    }
+    return pw;
+  }
+
+  // Tile of output pixels of a unit chain.  A workgroup's time in microseconds: start-up and the latencies of its phases, the
+  // two GEMMs (a wavefront takes 64 rows x 32 channels at a time), the stencil; the longest queue of a unit decides.
+  bool choose_unit_tile(int c1, const Shape& os, const Shape& ms, int s, int K, int* bth, int* btw) const {
+    const int C = ms.c, num_cu = std::max(1, p.hw.num_cu);
+    const size_t lds_cap = std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
+    if (C / p.ce > 512) return false;
+    const double kg = p.dt == DT_BF16 ? 0.045 : 0.18;               // a k-group of 64 rows x 32 channels
+    double best = 1e300;
+    for (int th = 1; th <= os.h; ++th)
+      for (int tw = 1; tw <= os.w; ++tw) {
+        const int PH = (th - 1) * s + 3, PW = (tw - 1) * s + 3, npx = th * tw;
+        const size_t lds = unit_lds_bytes(th, tw, s, c1, C, p.esz);
+        if (lds > lds_cap) break;
+        const int npos = std::min(PH, ms.h) * std::min(PW, ms.w);
+        auto rounds = [&](int rows, int ch) { return (double)(((rows + 63) / 64) * ((ch + 31) / 32) + 7) / 8; };
+        const double cost = 4.0 + kg * (std::ceil(rounds(npos, C)) * ((c1 * p.esz + 31) / 32) + std::ceil(rounds(npx, K)) * ((C * p.esz + 31) / 32)) +
+                            0.4 * std::ceil((double)npx * (C / p.ce) / 512) + 0.25 * std::ceil((double)npos * (c1 / p.ce) / 2048);
+        const double tiles = (double)((os.h + th - 1) / th) * ((os.w + tw - 1) / tw) * os.n;
+        const double t = p.opts.split ? std::max(std::ceil(tiles / num_cu), 1.0) * cost + tiles * cost / (8.0 * num_cu) : tiles * cost;
+        if (t < best - 1e-9) { best = t; *bth = th; *btw = tw; }
+      }
+    return best < 1e300;
+  }
+
+  // Hands the pointwise and the depthwise chain to the pointwise chain behind them (planned as the step of all three).
+  xenos_status plan_unit(int i, const ChainWalk& w1, int dn, int pw2, int th, int tw) {
+    const Shape is = tshape[nodes[i].in[0]], ms = tshape[i + 1], os = tshape[dn + 1];
+    const xenos_op_desc& dd = desc(nodes[dn]);
+    const ChainWalk w2 = walk_chain(dn);
+    dwpro = DwPro{};
+    dwpro.active = dwpro.unit = true;
+    dwpro.v_in = tview[nodes[i].in[0]];
+    dwpro.ops.push_back(nodes[i].src);
+    for (int ab : w1.absorbed) dwpro.ops.push_back(nodes[ab].src);
+    dwpro.ops.push_back(nodes[dn].src);
+    for (int ab : w2.absorbed) dwpro.ops.push_back(nodes[ab].src);
+    Step first;
+    first.conv.wfrag = 1;
+    dwpro.pw_C = std::max(is.c, p.views[dwpro.v_in].cphys);        // (padding channels multiply zero weights)
+    pack_dense(first, g.ops[nodes[i].src], is.c, dwpro.pw_C, 1, 1, ms.c);
+    dwpro.pw_w_off = first.w_off; dwpro.pw_kred = first.conv.Kred_pad; dwpro.pw_relu = w1.relu;
+    push_affine(w1.af, (ms.c + 127) / 128 * 128, &dwpro.pw_scale_off, &dwpro.pw_shift_off);
+    dwpro.w_off = pack_depthwise(g.ops[nodes[dn].src], ms.c, 9);
+    push_affine(w2.af, ms.c, &dwpro.scale_off, &dwpro.shift_off);
+    dwpro.k = 3; dwpro.stride = dd.stride_h; dwpro.pad = 1; dwpro.H = ms.h; dwpro.W = ms.w; dwpro.relu = w2.relu;
+    dwpro.th = th; dwpro.tw = tw;
+    dwpro.flops = 2.0 * ms.n * ms.h * ms.w * (double)ms.c * is.c + 2.0 * os.n * os.h * os.w * (double)os.c * 9;
+    dwpro.bytes_w = first.bytes_w + 9ll * ms.c * p.esz;
+    const int mark = (int)p.steps.size();
+    node_step[i] = node_step[dn] = mark;
+    for (int ab : w1.absorbed) node_step[ab] = mark;
+    for (int ab : w2.absorbed) node_step[ab] = mark;
+    return plan_node(pw2);
   }
 
   // Tile of depthwise output pixels for a pointwise -> depthwise chain: the GEMM runs over the block positions inside
@@ -1518,6 +1611,14 @@ struct Planner {
               return plan_fire(i, walk, fm);
           }
           const int dn = pwdw_consumer(i);
+          if (dn >= 0) {
+            const View& iv0 = p.views[tview[nd.in[0]]];
+            int th, tw;
+            const int pw2 = unit_consumer(i, dn);
+            if (pw2 >= 0 && iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
+                choose_unit_tile(std::max(is.c, iv0.cphys), tshape[dn + 1], tshape[i + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, &th, &tw))
+              return plan_unit(i, walk, dn, pw2, th, tw);
+          }
           if (dn >= 0 && pwdw_wanted(i, dn)) {
             const View& iv0 = p.views[tview[nd.in[0]]];
             if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0)
@@ -1555,6 +1656,11 @@ struct Planner {
           st.dw_w_off = pro.w_off; st.dw_scale_off = pro.scale_off; st.dw_shift_off = pro.shift_off;
           a.dw_k = pro.k; a.dw_stride = pro.stride; a.dw_pad = pro.pad; a.dw_H = pro.H; a.dw_W = pro.W; a.dw_relu = pro.relu;
           a.dw_sN = iv.sN; a.dw_sP = iv.sP;
+          if (pro.unit) {
+            a.unit = 1; a.unit_C = pro.pw_C; a.unit_kred = pro.pw_kred; a.fire_relu[0] = pro.pw_relu; a.wfrag = 1;
+            a.in_sH = iv.sP * pro.W;
+            st.fire_w_off[0] = pro.pw_w_off; st.fire_scale_off[0] = pro.pw_scale_off; st.fire_shift_off[0] = pro.pw_shift_off;
+          }
           a.dw_w = (const void*)1;           // marks the chain for the split planner; patched at launch
         }
         // The first-layer kernels compute 32 or 64 channels: another channel count (24 in the ShuffleNet graph) is padded
@@ -1674,6 +1780,26 @@ struct Planner {
         if (has_res) {
           const View& rv = p.views[st.v_in2];
           a.vec_res = K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0;
+        }
+        if (a.unit) {
+          if (!a.vec_out || a.mode != M_FLAT || has_res) return fail(XENOS_EUNSUPPORTED, "%s: output of the unit's chain is not aligned", st.name.c_str());
+          a.th = pro.th; a.tw = pro.tw;
+          a.tiles_y = (a.OH + a.th - 1) / a.th; a.tiles_x = (a.OW + a.tw - 1) / a.tw;
+          a.tiles_m = a.ntiles = a.N * a.tiles_y * a.tiles_x;
+          a.tiles_n = 1; a.xcd_m = 8;
+          a.grid = p.opts.split ? std::max(1, std::min(a.ntiles, 4 * std::max(1, p.hw.num_cu))) : 1;
+          st.cfg = kUnitCfg;
+          st.lds = unit_lds_bytes(a.th, a.tw, a.dw_stride, a.unit_C, a.C, p.esz);
+          st.flops = 2.0 * a.N * a.OH * a.OW * (double)K * is.c + pro.flops;
+          st.bytes_w += pro.bytes_w;
+          st.bytes_in = view_bytes(st.v_in); st.bytes_out = view_bytes(st.v_out);
+          if (a.ileave) st.bytes_res = view_bytes(st.v_in2);
+          const int sidx = (int)p.steps.size();
+          node_step[i] = sidx;
+          for (int ab : absorbed) node_step[ab] = sidx;
+          node_final[last] = 1;
+          add_step(st);
+          return XENOS_OK;
         }
         if (dw_panel_fits && a.mode == M_FLAT && (a.vec_out || st.gap_finish)) {
           // depthwise panel on chip: as many input channels as fit the unit's private memory beside the weight stages
@@ -2095,11 +2221,11 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg fc_tc{32, kFcChannels, 32, 32};
       const TileCfg stem_lds_tc{kStemLdsTh * kStemLdsTw, c.K, 32, c.K};
       const TileCfg pwdw_tc{64, kPwDwChannels, 32, 32};
-      const TileCfg& tc = s.cfg == kPwDwCfg || s.cfg == kFireCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
+      const TileCfg& tc = s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
                "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d",
-               kModeNames[c.mode], s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
+               kModeNames[c.mode], s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.unit ? "unit" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
                c.PH, c.PW, c.pool, c.relu, c.has_res, tc.bm, tc.bn, c.tiles_m, c.tiles_n, c.grid, s.lds, c.pph, c.ppw, c.patch_h,
                c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave);
       j += buf;
@@ -2159,6 +2285,11 @@ xenos_status launch_step(xenos_plan& p, const Step& s, const void* d_in_, void* 
       a.dw_w = s.dw_w_off >= 0 ? (const void*)(wb + s.dw_w_off) : nullptr;
       a.dw_scale = s.dw_scale_off >= 0 ? (const float*)(wb + s.dw_scale_off) : nullptr;
       a.dw_shift = s.dw_shift_off >= 0 ? (const float*)(wb + s.dw_shift_off) : nullptr;
+      if (a.unit) {
+        a.fire_w[0] = wb + s.fire_w_off[0];
+        a.fire_scale[0] = (const float*)(wb + s.fire_scale_off[0]);
+        a.fire_shift[0] = (const float*)(wb + s.fire_shift_off[0]);
+      }
       if (a.fire) {
         for (int e = 0; e < 2; ++e) {
           const bool has = a.fire_E[e] > 0;

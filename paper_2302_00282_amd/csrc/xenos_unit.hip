@@ -1,0 +1,306 @@
+// gfx950 (CDNA4) kernel of a depthwise-separable unit as one chain (Table 1, ConvX -> ConvY twice; Section 2.2):
+//
+//  unit_kernel   pointwise (1x1) chain -> depthwise 3x3 chain -> pointwise chain, both intermediate tensors on chip.
+//
+// A workgroup owns TH x TW output pixels of one image and ALL output channels: the depthwise convolution works per channel,
+// but the second pointwise convolution sums over all of them.  It stages the input block (the pixels the tile's windows
+// cover, all input channels) in LDS, runs the first GEMM of the positions inside the map into the LDS block the stencil reads
+// (rounded to the storage type as a stored tensor would be; positions outside the map stay zero, the padding of the depthwise
+// convolution; neighbouring tiles recompute the shared border), runs the stencil into the operand panel of the second GEMM,
+// and that GEMM's epilogue stores the output, alternating with the other half of a shuffled concat where the unit ends in one.
+//
+// Bound: latency.  As two launches (1x1 convolution; depthwise -> pointwise, whose depthwise panel every 64-channel tile of the
+// output recomputed) a 176-channel 14x14 unit at batch 32 took 8.4 + 18.2 us for 0.8 GFLOP and 7 MB; all output channels in
+// one workgroup take the recomputation out, and both weight matrices, packed in fragment order, go from the cache straight
+// into the registers of the wavefront that multiplies them, UN_RING k-groups ahead: no barrier inside a GEMM, four per tile.
+#include "device_common.h"
+
+namespace xenos {
+
+constexpr int UN_NT = 512, UN_NW = UN_NT / 64;   // eight wavefronts
+constexpr int UN_RING = 12;                      // weight fragments in flight per wavefront: 12 KB
+
+// LDS row of c channels: whole 32-byte k-groups and one odd 16-byte slot
+__host__ __device__ constexpr int unit_pitch(int c, int esz) { return (c * esz + 31) / 32 * 32 + 16; }
+__host__ __device__ constexpr int unit_stg_pitch(int esz) { return 32 * esz + 16; }
+// input block, later the stencil's panel | block the stencil reads, later the staging slices of the wavefronts
+__host__ __device__ constexpr int unit_lds_a(int positions, int pixels, int c1, int c, int esz) {
+  return cmax(positions * unit_pitch(c1, esz), pixels * unit_pitch(c, esz));
+}
+__host__ __device__ constexpr int unit_lds_b(int positions, int c, int esz) {
+  return cmax(positions * unit_pitch(c, esz), UN_NW * 32 * unit_stg_pitch(esz));
+}
+
+// Transposed GEMM of `nrows` LDS rows (pitch bytes apart, nkg k-groups of 32 bytes each) with ncb blocks of 32 channels, a
+// wavefront per 64 rows x 32 channels.  w: fragments [block][kgs][lane] of 16 bytes.  pre(block, row0) runs before a block's
+// reduction, epi(block, row0, acc) receives each finished 32 x 32 part: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3)
+// of the block in acc[4 g ..].
+template <typename T, typename PreFn, typename EpiFn>
+__device__ __forceinline__ void unit_gemm(const u32x4_t* w, int kgs, int nkg, const unsigned char* s_rows, int pitch, int nrows, int ncb, PreFn pre, EpiFn epi) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l31 = lane & 31, lhalf = lane >> 5;
+  const int ngr = (nrows + 63) / 64;
+#pragma unroll 1
+  for (int u = wave; u < ncb * ngr; u += UN_NW) {
+    const int rg = u / ncb, cb = u - rg * ncb, row0 = rg * 64;
+    const bool two = row0 + 32 < nrows;                            // (uniform)
+    const u32x4_t* wp = w + (long long)cb * kgs * 64 + lane;
+    u32x4_t rb[UN_RING];
+#pragma unroll
+    for (int d = 0; d < UN_RING; ++d) rb[d] = wp[(d < nkg ? d : nkg - 1) * 64];
+    pre(cb, row0);
+    // (rows past the end read the last row; their results are not stored)
+    const unsigned char* pa0 = s_rows + (row0 + l31 < nrows ? row0 + l31 : nrows - 1) * pitch + lhalf * 16;
+    const unsigned char* pa1 = s_rows + (row0 + 32 + l31 < nrows ? row0 + 32 + l31 : nrows - 1) * pitch + lhalf * 16;
+    f32x16_t acc0, acc1;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { acc0[e] = 0.f; acc1[e] = 0.f; }
+    auto round = [&](int k0, auto MORE) __attribute__((always_inline)) {
+#pragma unroll
+      for (int d = 0; d < UN_RING; ++d) {
+        if (k0 + d < nkg) {                                        // (uniform)
+          const u32x4_t fa0 = *(const u32x4_t*)(pa0 + (k0 + d) * 32), fa1 = *(const u32x4_t*)(pa1 + (k0 + d) * 32);
+          if constexpr (sizeof(T) == 2) {
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d]), __builtin_bit_cast(bf16x8_t, fa0), acc0, 0, 0, 0);
+            if (two) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d]), __builtin_bit_cast(bf16x8_t, fa1), acc1, 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d][e]), __uint_as_float(fa0[e]), acc0, 0, 0, 0);
+            if (two) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d][e]), __uint_as_float(fa1[e]), acc1, 0, 0, 0);
+            }
+          }
+        }
+        if constexpr (decltype(MORE)::value) rb[d] = wp[(k0 + UN_RING + d < nkg ? k0 + UN_RING + d : nkg - 1) * 64];
+      }
+    };
+    int k0 = 0;
+#pragma unroll 1
+    for (; k0 + UN_RING < nkg; k0 += UN_RING) round(k0, std::true_type());
+    round(k0, std::false_type());
+    epi(cb, row0, acc0);
+    if (two) epi(cb, row0 + 32, acc1);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
+  FETCH_ARGS(ConvArgs);
+  using tr = Tr<T>;
+  constexpr int CE = tr::CE, ESZ = (int)sizeof(T);
+  constexpr int STP = unit_stg_pitch(ESZ), G = 32 * ESZ / 16, STG_IT = 32 * G / 64;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, lhalf = lane >> 5;
+  const u32x4_t z = {0u, 0u, 0u, 0u};
+
+  const int s = a.dw_stride, C = a.C, C1 = a.unit_C;
+  const int PH = (a.th - 1) * s + 3, PWd = (a.tw - 1) * s + 3, P = PH * PWd, npx = a.th * a.tw;
+  const int PX = unit_pitch(C1, ESZ), PM = unit_pitch(C, ESZ);
+  unsigned char* s_x = smem;                                       // input block [position inside the map][C1], later [pixel][C]
+  unsigned char* s_mid = smem + unit_lds_a(P, npx, C1, C, ESZ);    // [block position][C]
+  unsigned char* s_stg = s_mid + wave * 32 * STP;
+  const int tiles_sp = a.tiles_y * a.tiles_x;
+  const int cgs = C / CE, pgs = UN_NT / cgs;                       // stencil: a thread keeps its channel group, pgs pixels side by side
+  const int cg = tid % cgs, pg = tid / cgs;
+  const bool dw_on = pg < pgs;
+
+  for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    const int n = t / tiles_sp, rr = t - n * tiles_sp, ty = rr / a.tiles_x, tx = rr - ty * a.tiles_x;
+    const int oy0 = ty * a.th, ox0 = tx * a.tw;
+    const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
+    const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.dw_H ? iy0 + PH : a.dw_H;
+    const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.dw_W ? ix0 + PWd : a.dw_W;
+    const int wv = x_hi - x_lo, npos = (y_hi - y_lo) * wv;          // the part of the block inside the map (never empty)
+
+    // ---- the input block, all channels; k-groups are filled up with zeros ---------------------------------
+    {
+      const int cpr = (PX - 16) / 16, total = npos * cpr;
+      constexpr int U = 4;                                         // requests before the first LDS write
+      for (int i0 = tid; i0 < total; i0 += U * UN_NT) {
+        u32x4_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * UN_NT < total ? i0 + u * UN_NT : total - 1;
+          const int r = i / cpr, c = i - r * cpr, py = r / wv, px = r - py * wv;
+          const bool ok = c * CE < C1;
+          v[u] = *(const u32x4_t*)((const T*)a.in + (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW + (ok ? c * CE : 0));
+          if (!ok) v[u] = z;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * UN_NT, r = i / cpr, c = i - r * cpr;
+          if (i < total) *(u32x4_t*)(s_x + r * PX + c * 16) = v[u];
+        }
+      }
+    }
+    if (npos < P)                                                  // the zero padding of the depthwise convolution
+      for (int i = tid; i < P * (PM / 16); i += UN_NT) *(u32x4_t*)(s_mid + i * 16) = z;
+    // this thread's depthwise weights
+    u32x4_t dww[9];
+#pragma unroll
+    for (int t9 = 0; t9 < 9; ++t9) dww[t9] = *(const u32x4_t*)((const T*)a.dw_w + (long long)t9 * C + cg * CE);
+    __syncthreads();
+
+    f32x4_t sc[4], sh[4];                                          // scale and shift of the lane's channels
+    // ---- first pointwise chain, into the stencil's block ----------------------------------------------------
+    unit_gemm<T>((const u32x4_t*)a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, s_x, PX, npos, (C + 31) / 32,
+      [&](int cb, int) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          sc[g] = *(const f32x4_t*)(a.fire_scale[0] + cb * 32 + g * 8 + lhalf * 4);
+          sh[g] = *(const f32x4_t*)(a.fire_shift[0] + cb * 32 + g * 8 + lhalf * 4);
+        }
+      },
+      [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
+        const int m = row0 + l31;
+        if (m >= npos) return;
+        const int py = m / wv, px = m - py * wv;
+        unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * PM;
+        const float lo = a.fire_relu[0] ? 0.f : -3.4028235e38f;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = cb * 32 + g * 8 + lhalf * 4;
+          if (c >= C) continue;
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
+          if constexpr (sizeof(T) == 2) {
+            uint2 o;
+            o.x = f2bf2(y[0], y[1]);
+            o.y = f2bf2(y[2], y[3]);
+            *(uint2*)(dst + c * 2) = o;
+          } else {
+            *(f32x4_t*)(dst + c * 4) = f32x4_t{y[0], y[1], y[2], y[3]};
+          }
+        }
+      });
+    __syncthreads();                                               // the block is complete, the input block is free
+
+    // ---- depthwise chain, into the operand panel of the second GEMM -----------------------------------------
+    if (dw_on) {
+      float dsc[CE], dsh[CE];
+#pragma unroll
+      for (int e = 0; e < CE; e += 4) {
+        *(f32x4_t*)&dsc[e] = *(const f32x4_t*)(a.dw_scale + cg * CE + e);
+        *(f32x4_t*)&dsh[e] = *(const f32x4_t*)(a.dw_shift + cg * CE + e);
+      }
+      for (int q = pg; q < npx; q += pgs) {
+        const int qy = q / a.tw, qx = q - qy * a.tw;
+        const unsigned char* src = s_mid + ((qy * s) * PWd + qx * s) * PM + cg * 16;
+        u32x4_t xr[9];
+#pragma unroll
+        for (int t9 = 0; t9 < 9; ++t9) xr[t9] = *(const u32x4_t*)(src + ((t9 / 3) * PWd + t9 % 3) * PM);
+        float d[CE];
+#pragma unroll
+        for (int e = 0; e < CE; ++e) d[e] = 0.f;
+#pragma unroll
+        for (int t9 = 0; t9 < 9; ++t9) {
+          float x[CE], w[CE];
+          tr::unpack(xr[t9], x);
+          tr::unpack(dww[t9], w);
+#pragma unroll
+          for (int e = 0; e < CE; ++e) d[e] = fmaf(x[e], w[e], d[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < CE; ++e) {
+          const float y = d[e] * dsc[e] + dsh[e];
+          d[e] = a.dw_relu ? fmx(y, 0.f) : y;
+        }
+        *(u32x4_t*)(s_x + q * PM + cg * 16) = tr::pack(d);
+      }
+    }
+    if (C * ESZ % 32 != 0)                                         // the other half of the last k-group
+      for (int q = tid; q < npx; q += UN_NT) *(u32x4_t*)(s_x + q * PM + C * ESZ) = z;
+    __syncthreads();                                               // the panel is complete, the block is free
+
+    // ---- second pointwise chain -------------------------------------------------------------------------------
+    unit_gemm<T>((const u32x4_t*)a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, s_x, PM, npx, (a.K + 31) / 32,
+      [&](int cb, int) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          sc[g] = *(const f32x4_t*)(a.scale + cb * 32 + g * 8 + lhalf * 4);
+          sh[g] = *(const f32x4_t*)(a.shift + cb * 32 + g * 8 + lhalf * 4);
+        }
+      },
+      [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
+        // finished values change hands inside the wavefront only (LDS serves its requests in order)
+        const float lo = a.relu ? 0.f : -3.4028235e38f;
+        u32x4_t oth[STG_IT];
+        long long dst[STG_IT];
+#pragma unroll
+        for (int u = 0; u < STG_IT; ++u) {
+          const int idx = lane + u * 64, r = idx / G, g16 = idx - r * G;
+          const int q = row0 + r, qy = q / a.tw, qx = q - qy * a.tw, oy = oy0 + qy, ox = ox0 + qx, k0 = cb * 32 + g16 * CE;
+          const bool ok = q < npx && oy < a.OH && ox < a.OW && k0 < a.K;
+          const long long p = (long long)oy * a.OW + ox;
+          dst[u] = ok ? (long long)n * a.out_sN + p * a.out_sP + (a.ileave ? 2 * k0 : k0) : -1;
+          oth[u] = a.ileave && ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = g * 8 + lhalf * 4;
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
+          if constexpr (sizeof(T) == 2) {
+            uint2 o;
+            o.x = f2bf2(y[0], y[1]);
+            o.y = f2bf2(y[2], y[3]);
+            *(uint2*)(s_stg + l31 * STP + c * 2) = o;
+          } else {
+            *(f32x4_t*)(s_stg + l31 * STP + c * 4) = f32x4_t{y[0], y[1], y[2], y[3]};
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < STG_IT; ++u) {
+          const int idx = lane + u * 64, r = idx / G, g16 = idx - r * G;
+          const u32x4_t mine = *(const u32x4_t*)(s_stg + r * STP + g16 * 16);
+          if (dst[u] < 0) continue;
+          if (a.ileave) ileave_store<T>((T*)a.out + dst[u], mine, oth[u], a.ileave == 1);
+          else *(u32x4_t*)((T*)a.out + dst[u]) = mine;
+        }
+      });
+    __syncthreads();                                               // both regions are rewritten by the next tile
+  }
+}
+
+size_t unit_lds_bytes(int th, int tw, int stride, int c1, int c, int esz) {
+  const int positions = ((th - 1) * stride + 3) * ((tw - 1) * stride + 3);
+  return (size_t)unit_lds_a(positions, th * tw, c1, c, esz) + unit_lds_b(positions, c, esz);
+}
+
+template <typename T>
+static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
+  constexpr int ESZ = (int)sizeof(T), CE = Tr<T>::CE, BKE = Tr<T>::BKE;
+  const int s = a.dw_stride;
+  // what the kernel assumes, checked again on the host: a wrong shape would index outside the LDS block or the tensors
+  if (a.mode != M_FLAT || a.has_res || a.pool != POOL_NONE || a.ksplit >= 1 || a.kchunk || a.pair || a.fire || a.pwdw || !a.wfrag || !a.vec_out ||
+      a.R != 1 || a.S != 1 || a.stride != 1 || a.pad != 0 || a.C % CE != 0 || a.K % CE != 0 || a.C < CE || a.K < CE || a.C / CE > UN_NT ||
+      a.unit_C % CE != 0 || a.unit_C < CE || a.Kred_pad < (a.C + BKE - 1) / BKE * BKE || a.Kred_pad % BKE != 0 ||
+      a.unit_kred < (a.unit_C + BKE - 1) / BKE * BKE || a.unit_kred % BKE != 0 || a.dw_k != 3 || a.dw_pad != 1 || (s != 1 && s != 2) ||
+      !a.dw_w || !a.dw_scale || !a.dw_shift || !a.fire_w[0] || !a.fire_scale[0] || !a.fire_shift[0] ||
+      a.OH != (a.dw_H + 2 - 3) / s + 1 || a.OW != (a.dw_W + 2 - 3) / s + 1 || a.th < 1 || a.tw < 1 ||
+      a.tiles_y != (a.OH + a.th - 1) / a.th || a.tiles_x != (a.OW + a.tw - 1) / a.tw || a.tiles_n != 1 ||
+      a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m || a.grid < 1 || a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.unit_C ||
+      a.in_sN % CE != 0 || a.in_sH % CE != 0 || a.in_sW % CE != 0 || ((uintptr_t)a.in & 15) || ((uintptr_t)a.out & 15) || a.out_sP % CE != 0 || a.out_sN % CE != 0 ||
+      a.out_sP < (a.ileave ? 2 : 1) * a.K || (a.ileave && !a.res))
+    return (int)hipErrorInvalidValue;
+  const int lds = (int)unit_lds_bytes(a.th, a.tw, s, a.unit_C, a.C, ESZ);
+  if (lds > 160 * 1024) return (int)hipErrorInvalidValue;
+  static int raised = 0;
+  if (lds > raised) {
+    hipError_t e = hipFuncSetAttribute((const void*)unit_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return (int)e;
+    raised = lds;
+  }
+  hipLaunchKernelGGL((unit_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(UN_NT), lds, st, a);
+  return (int)hipGetLastError();
+}
+
+int launch_unit(const ConvArgs& a, int dtype, void* stream) {
+  return dtype == DT_BF16 ? launch_unit_t<bf16_t>(a, (hipStream_t)stream) : launch_unit_t<float>(a, (hipStream_t)stream);
+}
+
+}  // namespace xenos

@@ -465,6 +465,43 @@ def test_pointwise_depthwise_linked_on_chip(stride, h, w, c, k, n, tail, compute
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("stride,h,w,c,mid,k,n,tail", [(1, 33, 32, 16, 16, 24, 1, "conv"), (2, 65, 63, 24, 72, 40, 1, "conv"), (1, 7, 7, 64, 136, 200, 21, "conv"),
+                                                       (1, 14, 14, 88, 88, 88, 6, "shuffle"), (2, 19, 45, 40, 200, 136, 5, "conv"),
+                                                       (1, 28, 37, 8, 8, 8, 1, "out"), (1, 5, 206, 232, 40, 320, 1, "cat")])
+def test_pointwise_depthwise_pointwise_linked_on_chip(stride, h, w, c, mid, k, n, tail, compute):
+    # link level 3, pointwise -> depthwise -> pointwise as one chain, both intermediate tensors on chip.  At least 1024 output
+    # pixels (1040 and 1029 here: the smallest it takes), clipped blocks at every border and overhanging tiles, channel counts
+    # that are no whole 32-channel block and no whole 32-byte k-group (8, 24, 40, 72, 88, 136, 200, 232), reductions longer than
+    # the ring of weights in flight; tails: a dense 3x3, the store that finishes a two-group shuffle, the graph output, a concat slice.
+    b = wg.builder("unit", (n, c, h, w), 41, nonzero_bias=True)
+    x = b.cbr(0, c if tail != "shuffle" else 2 * c, 3, 1, 1, name="pre")
+    if tail == "shuffle":
+        lo, t = b.slice(x, 0, c), b.slice(x, c, c)
+    else:
+        t = x
+    t = b.cbr(t, mid, 1, name="pw")
+    t = b.cbr(t, mid, 3, stride, 1, groups=mid, name="dw", relu=False)
+    t = b.cbr(t, k, 1, name="pw2")
+    fmt = {}
+    if tail == "out":
+        fmt = dict(out_layout=1, out_dtype=compute)
+    elif tail == "shuffle":
+        t = b.cbr(b.shuffle(b.concat([lo, t]), 2), 16, 3, 1, 1, name="post")
+    else:
+        if tail == "cat":
+            t = b.concat([b.cbr(x, 16, 3, 1, 1, name="side"), t])
+        t = b.cbr(t, 80, 3, 1, 1, name="post")
+    g = b.finish(t)
+    y3, i3 = check(g, xo.forward(g), compute=compute, link=3, **fmt)
+    assert sum(1 for ch in i3["chains"] if ch.get("loader") == "unit") == 1
+    assert not any(ch["kind"] in ("dwconv", "elt") for ch in i3["chains"])
+    if not any(ch["kind"] == "splitk_finish" for ch in i3["chains"]):
+        y3s, _ = run_gpu(g, compute=compute, link=3, split=0, **fmt)
+        assert np.array_equal(y3, y3s)                        # one workgroup walking every tile, other tiles: same bits
+    check_chains(g, compute, link=3, **fmt)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("h,w,c,s,e1,e3,n,pool,tail", [(13, 13, 32, 16, 64, 64, 2, 0, "conv"), (27, 21, 64, 32, 128, 72, 1, 3, "conv"),
                                                        (9, 30, 24, 48, 40, 200, 3, 0, "conv"), (14, 14, 128, 64, 256, 256, 1, 2, "conv"),
                                                        (55, 55, 64, 16, 64, 64, 1, 3, "gap"), (5, 5, 16, 16, 8, 8, 2, 0, "out"),
