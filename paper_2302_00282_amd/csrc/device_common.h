@@ -111,6 +111,22 @@ __device__ __forceinline__ void fetch_args(const void* ka) {
 }
 #define FETCH_ARGS(T) fetch_args<(int)sizeof(T)>((const void*)__builtin_amdgcn_kernarg_segment_ptr())
 
+// n / d for 0 <= n < kSmallDiv, exactly: (n + 0.5) / d is at least 0.5 / d away from an integer, and reciprocal, product and
+// conversion together are off by less than 2^-21 of it.  Four instructions; the compiler's division by a run-time integer is
+// some thirty, several of them at quarter rate, and is what the index arithmetic of a short chain is made of (eight of them in
+// the loader of unit_kernel were 3 of the 5 k cycles until its input was in LDS).
+constexpr int kSmallDiv = 1 << 20;
+struct SmallDiv {
+  int d;
+  float r;
+  __device__ __forceinline__ explicit SmallDiv(int d_) : d(d_), r(__builtin_amdgcn_rcpf((float)d_)) {}
+  __device__ __forceinline__ int operator()(int n) const { return (int)(((float)n + 0.5f) * r); }
+};
+// n / d of wavefront-uniform values of any size
+__device__ __forceinline__ int uniform_div(int n, int d) {
+  return __builtin_amdgcn_readfirstlane(n < kSmallDiv ? SmallDiv(d)(n) : n / d);
+}
+
 constexpr int NT = 256;          // threads per workgroup (4 wavefronts of 64)
 constexpr int ROWB = kRowBytes;  // data bytes per tile row per reduction step
 constexpr int CPR = ROWB / 16;   // 16-byte chunks per tile row

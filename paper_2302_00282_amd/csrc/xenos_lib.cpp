@@ -1616,7 +1616,7 @@ struct Planner {
             int th, tw;
             const int pw2 = unit_consumer(i, dn);
             if (pw2 >= 0 && iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
-                choose_unit_tile(std::max(is.c, iv0.cphys), tshape[dn + 1], tshape[i + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, &th, &tw))
+                iv0.sP * is.h * is.w * p.esz < (1ll << 31) && choose_unit_tile(std::max(is.c, iv0.cphys), tshape[dn + 1], tshape[i + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, &th, &tw))
               return plan_unit(i, walk, dn, pw2, th, tw);
           }
           if (dn >= 0 && pwdw_wanted(i, dn)) {

@@ -13,6 +13,7 @@
 // output recomputed) a 176-channel 14x14 unit at batch 32 took 8.4 + 18.2 us for 0.8 GFLOP and 7 MB; all output channels in
 // one workgroup take the recomputation out, and both weight matrices, packed in fragment order, go from the cache straight
 // into the registers of the wavefront that multiplies them, UN_RING k-groups ahead: no barrier inside a GEMM, four per tile.
+// Timestamps (176 channels, cycles): input block 5.0 k, first GEMM 5.2 k, stencil 2.8 k, second GEMM and stores 6.5 k.
 #include "device_common.h"
 
 namespace xenos {
@@ -31,23 +32,33 @@ __host__ __device__ constexpr int unit_lds_b(int positions, int c, int esz) {
   return cmax(positions * unit_pitch(c, esz), UN_NW * 32 * unit_stg_pitch(esz));
 }
 
+// A pointer the compiler takes as new at this place: addresses computed from it stay inside the tile loop, as a wavefront-uniform
+// base and a 32-bit lane offset.  (Hoisted out of the loop as 64-bit lane addresses they were spilled.)
+typedef const __attribute__((address_space(1))) unsigned char* gptr_t;
+__device__ __forceinline__ gptr_t here(const void* p) {
+  uint64_t v = (uint64_t)p;
+  asm volatile("" : "+s"(v));
+  return (gptr_t)v;
+}
+__device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(const __attribute__((address_space(1))) u32x4_t*)(base + off); }
+
 // Transposed GEMM of `nrows` LDS rows (pitch bytes apart, nkg k-groups of 32 bytes each) with ncb blocks of 32 channels, a
 // wavefront per 64 rows x 32 channels.  w: fragments [block][kgs][lane] of 16 bytes.  pre(block, row0) runs before a block's
 // reduction, epi(block, row0, acc) receives each finished 32 x 32 part: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3)
 // of the block in acc[4 g ..].
 template <typename T, typename PreFn, typename EpiFn>
-__device__ __forceinline__ void unit_gemm(const u32x4_t* w, int kgs, int nkg, const unsigned char* s_rows, int pitch, int nrows, int ncb, PreFn pre, EpiFn epi) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l31 = lane & 31, lhalf = lane >> 5;
+__device__ __forceinline__ void unit_gemm(const void* w, int kgs, int nkg, const unsigned char* s_rows, int pitch, int nrows, int ncb, PreFn pre, EpiFn epi) {
+  const unsigned lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l31 = (int)lane & 31, lhalf = (int)lane >> 5;
   const int ngr = (nrows + 63) / 64;
 #pragma unroll 1
   for (int u = wave; u < ncb * ngr; u += UN_NW) {
-    const int rg = u / ncb, cb = u - rg * ncb, row0 = rg * 64;
+    const int rg = uniform_div(u, ncb), cb = u - rg * ncb, row0 = rg * 64;
     const bool two = row0 + 32 < nrows;                            // (uniform)
-    const u32x4_t* wp = w + (long long)cb * kgs * 64 + lane;
+    const gptr_t wp = here((const unsigned char*)w + (long long)cb * kgs * 1024);
     u32x4_t rb[UN_RING];
 #pragma unroll
-    for (int d = 0; d < UN_RING; ++d) rb[d] = wp[(d < nkg ? d : nkg - 1) * 64];
+    for (int d = 0; d < UN_RING; ++d) rb[d] = ld16(wp + (d < nkg ? d : nkg - 1) * 1024, lane * 16u);
     pre(cb, row0);
     // (rows past the end read the last row; their results are not stored)
     const unsigned char* pa0 = s_rows + (row0 + l31 < nrows ? row0 + l31 : nrows - 1) * pitch + lhalf * 16;
@@ -55,24 +66,45 @@ __device__ __forceinline__ void unit_gemm(const u32x4_t* w, int kgs, int nkg, co
     f32x16_t acc0, acc1;
 #pragma unroll
     for (int e = 0; e < 16; ++e) { acc0[e] = 0.f; acc1[e] = 0.f; }
-    auto round = [&](int k0, auto MORE) __attribute__((always_inline)) {
+    // N k-groups from k0 + d0 on: their fragments are read before the first MFMA
+    auto block = [&](int k0, int d0, auto NC) __attribute__((always_inline)) {
+      constexpr int N = decltype(NC)::value;
+      u32x4_t fa0[N], fa1[N];
 #pragma unroll
-      for (int d = 0; d < UN_RING; ++d) {
-        if (k0 + d < nkg) {                                        // (uniform)
-          const u32x4_t fa0 = *(const u32x4_t*)(pa0 + (k0 + d) * 32), fa1 = *(const u32x4_t*)(pa1 + (k0 + d) * 32);
-          if constexpr (sizeof(T) == 2) {
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d]), __builtin_bit_cast(bf16x8_t, fa0), acc0, 0, 0, 0);
-            if (two) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d]), __builtin_bit_cast(bf16x8_t, fa1), acc1, 0, 0, 0);
-          } else {
+      for (int d = 0; d < N; ++d) {
+        fa0[d] = *(const u32x4_t*)(pa0 + (k0 + d0 + d) * 32);
+        fa1[d] = *(const u32x4_t*)(pa1 + (k0 + d0 + d) * 32);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d][e]), __uint_as_float(fa0[e]), acc0, 0, 0, 0);
-            if (two) {
+      for (int d = 0; d < N; ++d) {
+        if constexpr (sizeof(T) == 2) {
+          acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d0 + d]), __builtin_bit_cast(bf16x8_t, fa0[d]), acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rb[d0 + d]), __builtin_bit_cast(bf16x8_t, fa1[d]), acc1, 0, 0, 0);
+        } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d][e]), __uint_as_float(fa1[e]), acc1, 0, 0, 0);
-            }
+          for (int e = 0; e < 4; ++e) acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d0 + d][e]), __uint_as_float(fa0[d][e]), acc0, 0, 0, 0);
+          if (two) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(rb[d0 + d][e]), __uint_as_float(fa1[d][e]), acc1, 0, 0, 0);
           }
         }
-        if constexpr (decltype(MORE)::value) rb[d] = wp[(k0 + UN_RING + d < nkg ? k0 + UN_RING + d : nkg - 1) * 64];
+      }
+    };
+    auto round = [&](int k0, auto MORE) __attribute__((always_inline)) {
+#pragma unroll
+      for (int d0 = 0; d0 < UN_RING; d0 += 4) {
+        if (decltype(MORE)::value || k0 + d0 + 4 <= nkg) {         // (uniform)
+          block(k0, d0, std::integral_constant<int, 4>());
+        } else {
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (k0 + d0 + d < nkg) block(k0, d0 + d, std::integral_constant<int, 1>());
+        }
+        if constexpr (decltype(MORE)::value) {
+#pragma unroll
+          for (int d = d0; d < d0 + 4; ++d) rb[d] = ld16(wp + (k0 + UN_RING + d < nkg ? k0 + UN_RING + d : nkg - 1) * 1024, lane * 16u);
+        }
       }
     };
     int k0 = 0;
@@ -102,50 +134,52 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
   unsigned char* s_mid = smem + unit_lds_a(P, npx, C1, C, ESZ);    // [block position][C]
   unsigned char* s_stg = s_mid + wave * 32 * STP;
   const int tiles_sp = a.tiles_y * a.tiles_x;
-  const int cgs = C / CE, pgs = UN_NT / cgs;                       // stencil: a thread keeps its channel group, pgs pixels side by side
-  const int cg = tid % cgs, pg = tid / cgs;
+  const int cgs = C / CE;                                          // stencil: a thread keeps its channel group, pgs pixels side by side
+  const SmallDiv by_cgs(cgs), by_tw(a.tw);
+  const int pgs = by_cgs(UN_NT), pg = by_cgs(tid), cg = tid - pg * cgs;
   const bool dw_on = pg < pgs;
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int n = t / tiles_sp, rr = t - n * tiles_sp, ty = rr / a.tiles_x, tx = rr - ty * a.tiles_x;
+    const int n = uniform_div(t, tiles_sp), rr = t - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
     const int oy0 = ty * a.th, ox0 = tx * a.tw;
     const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
     const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.dw_H ? iy0 + PH : a.dw_H;
     const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.dw_W ? ix0 + PWd : a.dw_W;
     const int wv = x_hi - x_lo, npos = (y_hi - y_lo) * wv;          // the part of the block inside the map (never empty)
+    const SmallDiv by_wv(wv);
 
     // ---- the input block, all channels; k-groups are filled up with zeros ---------------------------------
     {
-      const int cpr = (PX - 16) / 16, total = npos * cpr;
+      const int cpr = (PX - 16) / 16, total = npos * cpr;          // (a fraction of the LDS: far below kSmallDiv)
+      const SmallDiv by_cpr(cpr);
+      const gptr_t src = here((const T*)a.in + (long long)n * a.in_sN + (long long)y_lo * a.in_sH + (long long)x_lo * a.in_sW);
+      const int sH = (int)a.in_sH * ESZ, sW = (int)a.in_sW * ESZ;  // (an image takes less than 2 GB)
       constexpr int U = 4;                                         // requests before the first LDS write
       for (int i0 = tid; i0 < total; i0 += U * UN_NT) {
         u32x4_t v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int i = i0 + u * UN_NT < total ? i0 + u * UN_NT : total - 1;
-          const int r = i / cpr, c = i - r * cpr, py = r / wv, px = r - py * wv;
+          const int r = by_cpr(i), c = i - r * cpr, py = by_wv(r), px = r - py * wv;
           const bool ok = c * CE < C1;
-          v[u] = *(const u32x4_t*)((const T*)a.in + (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW + (ok ? c * CE : 0));
+          v[u] = ld16(src, (unsigned)(py * sH + px * sW + (ok ? c * 16 : 0)));
           if (!ok) v[u] = z;
         }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int i = i0 + u * UN_NT, r = i / cpr, c = i - r * cpr;
+          const int i = i0 + u * UN_NT, r = by_cpr(i), c = i - r * cpr;
           if (i < total) *(u32x4_t*)(s_x + r * PX + c * 16) = v[u];
         }
       }
     }
     if (npos < P)                                                  // the zero padding of the depthwise convolution
       for (int i = tid; i < P * (PM / 16); i += UN_NT) *(u32x4_t*)(s_mid + i * 16) = z;
-    // this thread's depthwise weights
-    u32x4_t dww[9];
-#pragma unroll
-    for (int t9 = 0; t9 < 9; ++t9) dww[t9] = *(const u32x4_t*)((const T*)a.dw_w + (long long)t9 * C + cg * CE);
     __syncthreads();
 
     f32x4_t sc[4], sh[4];                                          // scale and shift of the lane's channels
     // ---- first pointwise chain, into the stencil's block ----------------------------------------------------
-    unit_gemm<T>((const u32x4_t*)a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, s_x, PX, npos, (C + 31) / 32,
+    unit_gemm<T>(a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, s_x, PX, npos, (C + 31) / 32,
       [&](int cb, int) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -156,7 +190,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
       [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
         const int m = row0 + l31;
         if (m >= npos) return;
-        const int py = m / wv, px = m - py * wv;
+        const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * PM;
         const float lo = a.fire_relu[0] ? 0.f : -3.4028235e38f;
 #pragma unroll
@@ -176,6 +210,10 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
           }
         }
       });
+    const gptr_t dwp = here(a.dw_w);
+    u32x4_t dww[9];                                                // this thread's depthwise weights, on their way over the barrier
+#pragma unroll
+    for (int t9 = 0; t9 < 9; ++t9) dww[t9] = ld16(dwp + t9 * C * ESZ, (unsigned)cg * 16u);
     __syncthreads();                                               // the block is complete, the input block is free
 
     // ---- depthwise chain, into the operand panel of the second GEMM -----------------------------------------
@@ -187,7 +225,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
         *(f32x4_t*)&dsh[e] = *(const f32x4_t*)(a.dw_shift + cg * CE + e);
       }
       for (int q = pg; q < npx; q += pgs) {
-        const int qy = q / a.tw, qx = q - qy * a.tw;
+        const int qy = by_tw(q), qx = q - qy * a.tw;
         const unsigned char* src = s_mid + ((qy * s) * PWd + qx * s) * PM + cg * 16;
         u32x4_t xr[9];
 #pragma unroll
@@ -216,7 +254,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
     __syncthreads();                                               // the panel is complete, the block is free
 
     // ---- second pointwise chain -------------------------------------------------------------------------------
-    unit_gemm<T>((const u32x4_t*)a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, s_x, PM, npx, (a.K + 31) / 32,
+    unit_gemm<T>(a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, s_x, PM, npx, (a.K + 31) / 32,
       [&](int cb, int) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -232,7 +270,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
 #pragma unroll
         for (int u = 0; u < STG_IT; ++u) {
           const int idx = lane + u * 64, r = idx / G, g16 = idx - r * G;
-          const int q = row0 + r, qy = q / a.tw, qx = q - qy * a.tw, oy = oy0 + qy, ox = ox0 + qx, k0 = cb * 32 + g16 * CE;
+          const int q = row0 + r, qy = by_tw(q), qx = q - qy * a.tw, oy = oy0 + qy, ox = ox0 + qx, k0 = cb * 32 + g16 * CE;
           const bool ok = q < npx && oy < a.OH && ox < a.OW && k0 < a.K;
           const long long p = (long long)oy * a.OW + ox;
           dst[u] = ok ? (long long)n * a.out_sN + p * a.out_sP + (a.ileave ? 2 * k0 : k0) : -1;
@@ -284,7 +322,7 @@ static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
       a.OH != (a.dw_H + 2 - 3) / s + 1 || a.OW != (a.dw_W + 2 - 3) / s + 1 || a.th < 1 || a.tw < 1 ||
       a.tiles_y != (a.OH + a.th - 1) / a.th || a.tiles_x != (a.OW + a.tw - 1) / a.tw || a.tiles_n != 1 ||
       a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m || a.grid < 1 || a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.unit_C ||
-      a.in_sN % CE != 0 || a.in_sH % CE != 0 || a.in_sW % CE != 0 || ((uintptr_t)a.in & 15) || ((uintptr_t)a.out & 15) || a.out_sP % CE != 0 || a.out_sN % CE != 0 ||
+      a.in_sH * a.dw_H * ESZ >= (1ll << 31) || a.in_sN % CE != 0 || a.in_sH % CE != 0 || a.in_sW % CE != 0 || ((uintptr_t)a.in & 15) || ((uintptr_t)a.out & 15) || a.out_sP % CE != 0 || a.out_sN % CE != 0 ||
       a.out_sP < (a.ileave ? 2 : 1) * a.K || (a.ileave && !a.res))
     return (int)hipErrorInvalidValue;
   const int lds = (int)unit_lds_bytes(a.th, a.tw, s, a.unit_C, a.C, ESZ);
