@@ -196,15 +196,17 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
   unsigned char* s_op = smem + PH * PWd * MP;
   const int tiles_sp = a.tiles_y * a.tiles_x;
   const int cg = tid % CG;
+  const SmallDiv by_tw(a.tw);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int tile_n = t / a.tiles_m, tm = t - tile_n * a.tiles_m;  // neighbours share a weight slice
-    const int n = tm / tiles_sp, rr = tm - n * tiles_sp, ty = rr / a.tiles_x, tx = rr - ty * a.tiles_x;
+    const int tile_n = uniform_div(t, a.tiles_m), tm = t - tile_n * a.tiles_m;  // neighbours share a weight slice
+    const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
     const int oy0 = ty * a.th, ox0 = tx * a.tw;                    // first depthwise output pixel of the tile
     const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
     const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.H ? iy0 + PH : a.H;
     const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.W ? ix0 + PWd : a.W;
     const int hv = y_hi - y_lo, wv = x_hi - x_lo, npos = hv * wv;   // the part of the block inside the map (never empty)
+    const SmallDiv by_wv(wv);
 
     // this thread's depthwise weights and folded scale / shift: its channel group is the same for all its pixels
     const int k0 = tile_n * BN + cg * CE;
@@ -232,12 +234,12 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
     pw_gemm_phase<T>(a, tile_n * BN, s_op, (npos + BM - 1) / BM, [&](int mc, int row) -> long long {
       const int m = mc * BM + row;
       if (m >= npos) return -1;
-      const int py = m / wv, px = m - py * wv;
+      const int py = by_wv(m), px = m - py * wv;
       return (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * BM + wave_m * 32 + l31;
       if (m < npos) {
-        const int py = m / wv, px = m - py * wv;
+        const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * MP;
         const float lo = a.relu ? 0.f : -3.4028235e38f;
 #pragma unroll
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
         *(f32x4_t*)&dsh[e] = *(const f32x4_t*)(a.dw_shift + k0 + e);
       }
       for (int q = tid / CG; q < a.th * a.tw; q += NT / CG) {
-        const int qy = q / a.tw, qx = q - qy * a.tw;
+        const int qy = by_tw(q), qx = q - qy * a.tw;
         const int oy = oy0 + qy, ox = ox0 + qx;
         if (oy >= a.OH || ox >= a.OW) continue;
         const unsigned char* src = s_mid + ((qy * s) * PWd + qx * s) * MP + cg * 16;
@@ -396,16 +398,18 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   unsigned char* s_cb = s_free + 4 * 32 * STP;                     // POOL: [conv pixel][64 channels]
   const int tiles_sp = a.tiles_y * a.tiles_x;
   const int npix = CH * CW;
+  const SmallDiv by_cw(CW), by_ppw(POOL ? a.ppw : 1);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int gz = t / a.tiles_m, tm = t - gz * a.tiles_m;          // channel share, spatial tile
-    const int n = tm / tiles_sp, rr = tm - n * tiles_sp, ty = rr / a.tiles_x, tx = rr - ty * a.tiles_x;
+    const int gz = uniform_div(t, a.tiles_m), tm = t - gz * a.tiles_m;   // channel share, spatial tile
+    const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
     // first conv-output pixel of the tile
     const int oy0 = POOL ? ty * a.pph * a.ps - a.pp : ty * a.th, ox0 = POOL ? tx * a.ppw * a.ps - a.pp : tx * a.tw;
     const int iy0 = oy0 - ring, ix0 = ox0 - ring;                  // map position of block position (0, 0)
     const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.H ? iy0 + PH : a.H;
     const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.W ? ix0 + PWd : a.W;
     const int hv = y_hi - y_lo, wv = x_hi - x_lo, npos = hv * wv;   // the part of the block inside the map (never empty)
+    const SmallDiv by_wv(wv);
 
     if (hv < PH || wv < PWd) {
       const u32x4_t z = {0u, 0u, 0u, 0u};
@@ -438,12 +442,12 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     pw_gemm_phase<T, TAPS1>(a, 0, s_b, (npos + 63) / 64, [&](int mc, int row) -> long long {
       const int m = mc * 64 + row;
       if (m >= npos) return -1;
-      const int py = m / wv, px = m - py * wv;
+      const int py = by_wv(m), px = m - py * wv;
       return (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * 64 + wave_m * 32 + l31;
       if (m < npos) {
-        const int py = m / wv, px = m - py * wv;
+        const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_sq + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * SQP;
         const float lo = a.relu ? 0.f : -3.4028235e38f;
 #pragma unroll
@@ -467,7 +471,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       }
     }, [&](int mc, int row) -> int {
       const int m = mc * 64 + row, mm = m < npos ? m : 0;
-      const int py = mm / wv, px = mm - py * wv;
+      const int py = by_wv(mm), px = mm - py * wv;
       return ((y_lo + py) << 16) | (x_lo + px);
     });
     __syncthreads();                                               // the block is complete, the GEMM stages are free
@@ -507,7 +511,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
           v = *(const u32x4_t*)(s_stg + r * STP + cg * 16);
         }
         if (mr < npix && k0 < E) {
-          const int qy = mr / CW, qx = mr - qy * CW;
+          const int qy = by_cw(mr), qx = mr - qy * CW;
           if constexpr (POOL) {
             *(u32x4_t*)(s_cb + mr * CBP + (wave_n * 32 + cg * CE) * ESZ) = v;
           } else {
@@ -526,7 +530,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       constexpr int CG = 64 / CE;
       for (int idx = tid; idx < a.pph * a.ppw * CG; idx += NT) {
         const int q = idx / CG, cg = idx - q * CG, k0 = j * 64 + cg * CE;
-        const int qy = q / a.ppw, qx = q - qy * a.ppw;
+        const int qy = by_ppw(q), qx = q - qy * a.ppw;
         const int gy = ty * a.pph + qy, gx = tx * a.ppw + qx;
         if (gy >= a.PH || gx >= a.PW || k0 >= E) continue;
         float mx[CE];
@@ -570,7 +574,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     auto first_tap = [&](int which, int mc) __attribute__((always_inline)) -> const unsigned char* {
       const int m = mc * 64 + wave_m * 32 + l31;
       const int mm = m < npix ? m : 0;
-      const int py = mm / CW, px = mm - py * CW;
+      const int py = by_cw(mm), px = mm - py * CW;
       return s_sq + ((py + (which ? 0 : ring)) * PWd + px + (which ? 0 : ring)) * SQP + lhalf * 16;
     };
     if constexpr (KGS > 0) {
@@ -626,6 +630,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
         {   // the tile's weights: 64 channels x taps x S, contiguous in memory (rows beyond E are zero)
           const unsigned char* src = (const unsigned char*)a.fire_w[which] + (long long)j * 64 * wrow_b;
           const int cpr = wrow_b / 16, total = 64 * cpr;
+          const SmallDiv by_cpr(cpr);
           // six requests per thread before the first is written to LDS: as a loop of load-then-store the copy paid one
           // memory latency per 4 KB (timestamps inside the kernel: 3.2 us for the 72 KB of a 3x3 tile over 64 channels)
           constexpr int CB = 6;
@@ -638,7 +643,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < CB; ++u) {
-              const int idx = idx0 + u * NT, row = idx / cpr, c = idx - row * cpr;
+              const int idx = idx0 + u * NT, row = by_cpr(idx), c = idx - row * cpr;
               if (idx < total) *(u32x4_t*)(s_b + row * WP + c * 16) = wv[u];
             }
           }
