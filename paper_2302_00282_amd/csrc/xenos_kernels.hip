@@ -53,20 +53,21 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
   // tiles once per channel tile, so at any time the workgroups of one XCD share one weight slice in their L2 and
   // neighbouring pixel tiles share their input halo.  xm = 8 when there are many pixel tiles; problems with few
   // pixel tiles (batch 1, fully connected layers) spread the channel tiles over the XCDs instead.
-  const int xm = a.xcd_m, xn = NUM_XCD / xm;
+  const int xm = a.xcd_m, lxm = __builtin_ctz(xm), lxn = 3 - lxm, xn = 1 << lxn;   // (xm is 1, 2, 4 or 8)
   const int NZ = a.tiles_n * ksplit;
-  const int mchunk = (a.tiles_m + xm - 1) / xm, zchunk = (NZ + xn - 1) / xn;
+  const int mchunk = (a.tiles_m + xm - 1) >> lxm, zchunk = (NZ + xn - 1) >> lxn;
+  const AnyDiv by_ohw(OHW), by_ow(a.OW);
   const int slots = mchunk * zchunk * NUM_XCD;
 
   for (int t = blockIdx.x; t < slots; t += gridDim.x) {
     const int xcd = t % NUM_XCD, j = t / NUM_XCD;
-    const int xi = xcd % xm, xj = xcd / xm;
-    const int m0 = xi * a.tiles_m / xm, m1 = (xi + 1) * a.tiles_m / xm;
-    const int z0 = xj * NZ / xn, z1 = (xj + 1) * NZ / xn;
-    const int lm = j % mchunk, lz = j / mchunk;
+    const int xi = xcd & (xm - 1), xj = xcd >> lxm;
+    const int m0 = xi * a.tiles_m >> lxm, m1 = (xi + 1) * a.tiles_m >> lxm;
+    const int z0 = xj * NZ >> lxn, z1 = (xj + 1) * NZ >> lxn;
+    const int lz = uniform_div(j, mchunk), lm = j - lz * mchunk;
     if (lm >= m1 - m0 || lz >= z1 - z0) continue;                  // uniform per workgroup
     const int tile_m = m0 + lm;
-    const int tile_n = (z0 + lz) / ksplit, zsplit = (z0 + lz) % ksplit;
+    const int tile_n = uniform_div(z0 + lz, ksplit), zsplit = z0 + lz - tile_n * ksplit;
     // this workgroup's share of the reduction steps: [s_begin, s_begin + nsteps)
     const int s_begin = partial ? zsplit * a.steps_per_split : 0;
     const int nsteps = partial ? (nsteps_all - s_begin < a.steps_per_split ? nsteps_all - s_begin : a.steps_per_split) : nsteps_all;
@@ -75,9 +76,9 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
     int img = 0, oy0 = 0, ox0 = 0, py = 0, px = 0;
     if (MODE == M_PATCH) {
       const int pper = a.patches_y * a.patches_x;
-      img = tile_m / pper;
-      const int pr = tile_m % pper;
-      py = pr / a.patches_x; px = pr % a.patches_x;
+      img = uniform_div(tile_m, pper);
+      const int pr = tile_m - img * pper;
+      py = uniform_div(pr, a.patches_x); px = pr - py * a.patches_x;
       oy0 = py * a.pph * a.ps - a.pp;
       ox0 = px * a.ppw * a.ps - a.pp;
     } else if (MODE == M_GAP) {
@@ -99,21 +100,21 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         if (MODE == M_FLAT) {
           const int m = tile_m * BM + row;
           ok = ok && m < a.M_total;
-          n = m / OHW; const int p = m - n * OHW; oh = p / a.OW; ow = p - oh * a.OW;
+          n = by_ohw(m); const int p = m - n * OHW; oh = by_ow(p); ow = p - oh * a.OW;
         } else if (MODE == M_ZIGZAG) {
           const int m = tile_m * BM + row;
           ok = ok && m < a.M_total;
           const int wdx = m >> 2, j = m & 3, pw_ = a.PH * a.PW;
-          n = wdx / pw_; const int q = wdx - n * pw_; const int ph = q / a.PW;
+          n = AnyDiv(pw_)(wdx); const int q = wdx - n * pw_; const int ph = AnyDiv(a.PW)(q);
           oh = 2 * ph + (j >> 1); ow = 2 * (q - ph * a.PW) + (j & 1);
         } else if (MODE == M_PATCH) {
-          const int cy = row / a.patch_w, cx = row - cy * a.patch_w;
+          const int cy = SmallDiv(a.patch_w)(row), cx = row - cy * a.patch_w;
           n = img; oh = oy0 + cy; ow = ox0 + cx;
           ok = ok && cy < a.patch_h && oh >= 0 && oh < a.OH && ow >= 0 && ow < a.OW;
         } else {
           const int p = mc * BM + row;
           ok = ok && p < OHW;
-          n = img; oh = p / a.OW; ow = p - oh * a.OW;
+          n = img; oh = by_ow(p); ow = p - oh * a.OW;
         }
         ih0[it] = ok ? oh * a.stride - a.pad : -(1 << 28);
         iw0[it] = ow * a.stride - a.pad;
@@ -125,11 +126,12 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
       int kc, kr, ks;
       {
         if (a.kchunk) {
-          const int rs_n = a.R * a.S, cc = s_begin / rs_n, rs = s_begin - cc * rs_n;
-          kc = cc * BKE + ch * CE; kr = rs / a.S; ks = rs - kr * a.S;
+          const int rs_n = a.R * a.S, cc = uniform_div(s_begin, rs_n), rs = s_begin - cc * rs_n;
+          kc = cc * BKE + ch * CE; kr = uniform_div(rs, a.S); ks = rs - kr * a.S;
         } else {
           const int kk = s_begin * BKE + ch * CE;
-          kc = kk % a.C; const int rs = kk / a.C; ks = rs % a.S; kr = rs / a.S;
+          const int rs = AnyDiv(a.C)(kk);
+          kc = kk - rs * a.C; kr = AnyDiv(a.S)(rs); ks = rs - kr * a.S;
         }
       }
       const unsigned char* wrow[B_IT];
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           if (MODE == M_FLAT) {
             const int m = tile_m * BM + q;
             if (m >= a.M_total) continue;
-            const int n = m / OHW, p = m - n * OHW;
+            const int n = by_ohw(m), p = m - n * OHW;
             obase = (long long)n * a.out_sN + (long long)p * a.out_sP;
             rb_ = (long long)n * a.res_sN + (long long)p * a.res_sP;
             const float* sp = stg + q * SP + col0;
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
             const int wdx = ((tile_m * BM) >> 2) + q;
             if (wdx >= (a.M_total >> 2)) continue;
             const int PHW = a.PH * a.PW;
-            const int n = wdx / PHW, pq = wdx - n * PHW;
+            const int n = AnyDiv(PHW)(wdx), pq = wdx - n * PHW;
             obase = (long long)n * a.out_sN + (long long)pq * a.out_sP;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -427,7 +429,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
               for (int e = 0; e < CE; ++e) v[e] *= 0.25f;
             }
           } else {  // M_PATCH
-            const int qy = q / a.ppw, qx = q - qy * a.ppw;
+            const int qy = SmallDiv(a.ppw)(q), qx = q - qy * a.ppw;
             const int gy = py * a.pph + qy, gx = px * a.ppw + qx;
             if (gy >= a.PH || gx >= a.PW) continue;
             obase = (long long)img * a.out_sN + (long long)(gy * a.PW + gx) * a.out_sP;
@@ -2184,9 +2186,10 @@ __global__ __launch_bounds__(NT, 3) void dwpw_kernel(const ConvArgs a) {
   unsigned char* s_w = smem + BM * PP;
   const int OHW = a.OH * a.OW;
   const int Cpad = (a.C + BKE - 1) / BKE * BKE;                    // the packed weights are zero beyond C
+  const AnyDiv by_ohw(OHW), by_ow(a.OW);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int tile_m = t % a.tiles_m, tile_n = t / a.tiles_m;      // neighbours share a weight tile
+    const int tile_n = uniform_div(t, a.tiles_m), tile_m = t - tile_n * a.tiles_m;   // neighbours share a weight tile
     f32x16_t acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
@@ -2194,13 +2197,14 @@ __global__ __launch_bounds__(NT, 3) void dwpw_kernel(const ConvArgs a) {
     for (int p0 = 0; p0 < Cpad; p0 += CP) {
       const int cp = Cpad - p0 < CP ? Cpad - p0 : CP;              // channels of this panel (multiple of BKE)
       const int cpc = cp / CE;                                     // 16-byte chunks per pixel
+      const SmallDiv by_cpc(cpc);
       // ---- phase A: depthwise chain of 64 pixels x cp channels into the panel -------------------------
       for (int it = tid; it < BM * cpc; it += NT) {
-        const int px = it / cpc, c0 = p0 + (it - px * cpc) * CE;
+        const int px = by_cpc(it), c0 = p0 + (it - px * cpc) * CE;
         const int m = tile_m * BM + px;
         const bool valid = m < a.M_total && c0 < a.C;
         const int mm = m < a.M_total ? m : 0;
-        const int n = mm / OHW, q = mm - n * OHW, oh = q / a.OW, ow = q - oh * a.OW;
+        const int n = by_ohw(mm), q = mm - n * OHW, oh = by_ow(q), ow = q - oh * a.OW;
         const int ih0 = oh * a.dw_stride - a.dw_pad, iw0 = ow * a.dw_stride - a.dw_pad;
         const long long base = (long long)n * a.dw_sN;
         const int cc = c0 < a.C ? c0 : 0;
@@ -2358,7 +2362,7 @@ __global__ __launch_bounds__(NT, 3) void dwpw_kernel(const ConvArgs a) {
       const int r = idx / CG, cg = idx - r * CG;
       const int m = tile_m * BM + r, k0 = tile_n * BN + cg * CE;
       if (m >= a.M_total || k0 >= a.K) continue;
-      const int n = m / OHW, q = m - n * OHW;
+      const int n = by_ohw(m), q = m - n * OHW;
       const u32x4_t mine = *(const u32x4_t*)(stg + r * SPB + cg * 16);
       if (a.ileave)
         ileave_store<T>((T*)a.out + (long long)n * a.out_sN + (long long)q * a.out_sP + 2 * k0, mine,
@@ -2498,29 +2502,64 @@ size_t dwpw_lds_bytes(int panel_channels, int esz) { return (size_t)dwpw_lds(pan
 // ---------------------------------------------------------------------------------------------
 // Depthwise convolution chain: one thread = one 16-byte channel vector of one output pixel.
 // ---------------------------------------------------------------------------------------------
-// K3: the 3x3 kernel with its nine taps unrolled; IDX = int when the work items fit 31 bits (three 32-bit divisions per
-// item instead of three 64-bit ones, which cost more than the nine taps).
+// K3: the 3x3 kernel with its nine taps unrolled; IDX = int when the work items fit 31 bits (64-bit divisions, three per item,
+// cost more than the nine taps).
 template <typename T, bool K3, typename IDX>
 __global__ __launch_bounds__(NT) void dw_kernel(const DwArgs a) {
   FETCH_ARGS(DwArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE;
   const int cv = a.C / CE;
-  const int R = K3 ? 3 : a.R, S = K3 ? 3 : a.S;
+  [[maybe_unused]] const int R = a.R, S = a.S;
+  const AnyDiv by_cv(cv), by_ow(a.OW), by_oh(a.OH);
   for (IDX idx = (IDX)blockIdx.x * NT + threadIdx.x; idx < (IDX)a.total_vec; idx += (IDX)gridDim.x * NT) {
-    const int c0 = (int)(idx % cv) * CE;
-    IDX pix = idx / cv;
-    const int ow = (int)(pix % a.OW); pix /= a.OW;
-    const int oh = (int)(pix % a.OH);
-    const int n = (int)(pix / a.OH);
-    float acc[CE];
+    int c0, ow, oh, n;
+    if constexpr (sizeof(IDX) == 4) {
+      const int pix = by_cv(idx), row = by_ow(pix);
+      c0 = (idx - pix * cv) * CE;
+      ow = pix - row * a.OW;
+      n = by_oh(row);
+      oh = row - n * a.OH;
+    } else {
+      c0 = (int)(idx % cv) * CE;
+      IDX pix = idx / cv;
+      ow = (int)(pix % a.OW); pix /= a.OW;
+      oh = (int)(pix % a.OH);
+      n = (int)(pix / a.OH);
+    }
+    float acc[CE], sc[CE], sh[CE];
 #pragma unroll
     for (int e = 0; e < CE; ++e) acc[e] = 0.f;
 #pragma unroll
+    for (int e = 0; e < CE; e += 4) {
+      *(f32x4_t*)&sc[e] = *(const f32x4_t*)(a.scale + c0 + e);
+      *(f32x4_t*)&sh[e] = *(const f32x4_t*)(a.shift + c0 + e);
+    }
+    if constexpr (K3) {
+      // all loads before the first product (a tap outside the map reads the nearest pixel inside and counts as zero): with a
+      // branch around every tap the nine latencies followed each other
+      u32x4_t xr[9], wr[9];
+      const T* img = (const T*)a.in + (long long)n * a.in_sN + c0;
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) {
+        const int ih = oh * a.stride - a.pad + t9 / 3, iw = ow * a.stride - a.pad + t9 % 3;
+        const int ch = ih < 0 ? 0 : ih < a.H ? ih : a.H - 1, cw = iw < 0 ? 0 : iw < a.W ? iw : a.W - 1;
+        xr[t9] = *(const u32x4_t*)(img + ((long long)ch * a.W + cw) * a.in_sP);
+        wr[t9] = *(const u32x4_t*)((const T*)a.w + (long long)t9 * a.C + c0);
+        if (ch != ih || cw != iw) xr[t9] = u32x4_t{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) {
+        float x[CE], w[CE];
+        tr::unpack(xr[t9], x);
+        tr::unpack(wr[t9], w);
+#pragma unroll
+        for (int e = 0; e < CE; ++e) acc[e] = fmaf(x[e], w[e], acc[e]);
+      }
+    } else {
     for (int r = 0; r < R; ++r) {
       const int ih = oh * a.stride - a.pad + r;
       if ((unsigned)ih >= (unsigned)a.H) continue;
-#pragma unroll
       for (int s = 0; s < S; ++s) {
         const int iw = ow * a.stride - a.pad + s;
         if ((unsigned)iw >= (unsigned)a.W) continue;
@@ -2533,9 +2572,10 @@ __global__ __launch_bounds__(NT) void dw_kernel(const DwArgs a) {
         for (int e = 0; e < CE; ++e) acc[e] = fmaf(x[e], w[e], acc[e]);
       }
     }
+    }
 #pragma unroll
     for (int e = 0; e < CE; ++e) {
-      float v = acc[e] * a.scale[c0 + e] + a.shift[c0 + e];
+      float v = acc[e] * sc[e] + sh[e];
       acc[e] = a.relu ? fmx(v, 0.f) : v;
     }
     T* o = (T*)a.out + (long long)n * a.out_sN + ((long long)oh * a.OW + ow) * a.out_sP + c0;
@@ -2571,91 +2611,154 @@ int launch_dw(const DwArgs& a, int dtype, void* stream) {
 // ---------------------------------------------------------------------------------------------
 // Second half of a reduction-split chain: sum the shares in index order, then scale/shift, shortcut, ReLU, store.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
+// V = 4: a thread finishes four consecutive channels (16-byte loads of the shares, one store), index arithmetic in 32 bits; V = 1
+// for channel counts, strides and sizes that do not allow it.  Bound by latency at batch 1, where it ends every split chain.
+template <int V> struct Acc;
+template <> struct Acc<1> { typedef float type; };
+template <> struct Acc<4> { typedef f32x4_t type; };
+
+template <typename T, int V>
 __global__ __launch_bounds__(NT) void splitk_finish_kernel(const SplitKArgs a) {
   FETCH_ARGS(SplitKArgs);
   using tr = Tr<T>;
+  typedef typename Acc<V>::type acc_t;
   // the shares of one output element, added in index order.  Eight loads are requested before the first is added: a
   // loop of load-then-add pays one cache latency per share (32 shares: 5 us for the plain pass, 20 us for the averaging
   // one, measured), this pays one per eight.
-  auto sum_shares = [&](const float* p0) __attribute__((always_inline)) -> float {
+  auto sum_shares = [&](const float* p0) __attribute__((always_inline)) -> acc_t {
     const long long zs = (long long)a.M * a.part_ld;
-    float v = 0.f;
+    acc_t v = {};
     int z = 0;
     for (; z + 8 <= a.ksplit; z += 8) {
-      float t[8];
+      acc_t t[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = p0[(z + u) * zs];
+      for (int u = 0; u < 8; ++u) t[u] = *(const acc_t*)(p0 + (z + u) * zs);
 #pragma unroll
       for (int u = 0; u < 8; ++u) v += t[u];
     }
     if (z + 4 <= a.ksplit) {
-      float t[4];
+      acc_t t[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] = p0[(z + u) * zs];
+      for (int u = 0; u < 4; ++u) t[u] = *(const acc_t*)(p0 + (z + u) * zs);
 #pragma unroll
       for (int u = 0; u < 4; ++u) v += t[u];
       z += 4;
     }
-    for (; z < a.ksplit; ++z) v += p0[z * zs];
+    for (; z < a.ksplit; ++z) v += *(const acc_t*)(p0 + z * zs);
     return v;
   };
+  auto load_res = [&](long long o) __attribute__((always_inline)) -> acc_t {
+    if constexpr (V == 1) {
+      return tr::ld(a.res, o);
+    } else if constexpr (sizeof(T) == 2) {
+      const uint2 r = *(const uint2*)((const uint16_t*)a.res + o);
+      return acc_t{bf2f((uint16_t)r.x), __uint_as_float(r.x & 0xffff0000u), bf2f((uint16_t)r.y), __uint_as_float(r.y & 0xffff0000u)};
+    } else {
+      return *(const acc_t*)((const float*)a.res + o);
+    }
+  };
+  auto relu = [&](acc_t v) __attribute__((always_inline)) -> acc_t {
+    if constexpr (V == 1) {
+      return fmx(v, 0.f);
+    } else {
+      return acc_t{fmx(v[0], 0.f), fmx(v[1], 0.f), fmx(v[2], 0.f), fmx(v[3], 0.f)};
+    }
+  };
   if (a.gap) {
-    // linked global average (CBRA): a workgroup owns 16 channels of one image; 16 thread groups finish the pixels
-    // p = g, g + 16, ... and the 16 partial sums are added in group order
-    constexpr int CH = 16, PG = NT / CH;
-    __shared__ float s_sum[NT];
+    // linked global average (CBRA): a workgroup owns 16 channels of one image; PG thread groups finish the pixels
+    // p = g, g + PG, ..., their sums are added in two rounds of fixed order
+    constexpr int CH = 16, LN = CH / V, PG = NT / LN;               // V = 4: 64 pixels at a time, most maps in one round of loads
+    __shared__ __align__(16) float s_sum[PG * CH];
+    __shared__ float s_part[NT];
     const int kt = (a.K + CH - 1) / CH;
-    const int kk = threadIdx.x % CH, pg = threadIdx.x / CH;
+    const int kk = (threadIdx.x % LN) * V, pg = threadIdx.x / LN;
     for (int blk = blockIdx.x; blk < (a.M / a.OHW) * kt; blk += gridDim.x) {
       const long long n = blk / kt;
       const int k = (blk % kt) * CH + kk;
-      float s = 0.f;
+      acc_t s = {};
       if (k < a.K) {
-        const float sc = a.scale[k], sh = a.shift[k];
+        const acc_t sc = *(const acc_t*)(a.scale + k), sh = *(const acc_t*)(a.shift + k);
         for (int p = pg; p < a.OHW; p += PG) {
           const long long m = n * a.OHW + p;
-          float v = sum_shares(a.part + m * a.part_ld + k);
+          acc_t v = sum_shares(a.part + m * a.part_ld + k);
           v = v * sc + sh;
-          if (a.res) v += tr::ld(a.res, n * a.res_sN + p * a.res_sP + k);
-          if (a.relu) v = fmx(v, 0.f);
+          if (a.res) v += load_res(n * a.res_sN + p * a.res_sP + k);
+          if (a.relu) v = relu(v);
           s += v;
         }
       }
-      s_sum[threadIdx.x] = s;
+      *(acc_t*)&s_sum[pg * CH + kk] = s;
       __syncthreads();
-      if (pg == 0 && k < a.K) {
+      {
+        constexpr int W = PG / (NT / CH);                          // groups per thread of the first round
+        const int c = threadIdx.x % CH, g = threadIdx.x / CH;
         float t = 0.f;
-        for (int w = 0; w < PG; ++w) t += s_sum[w * CH + kk];
+#pragma unroll
+        for (int w = 0; w < W; ++w) t += s_sum[(g * W + w) * CH + c];
+        s_part[threadIdx.x] = t;
+      }
+      __syncthreads();
+      const int ko = (blk % kt) * CH + (int)threadIdx.x;
+      if (threadIdx.x < CH && ko < a.K) {
+        float t = 0.f;
+#pragma unroll
+        for (int g = 0; g < NT / CH; ++g) t += s_part[g * CH + threadIdx.x];
         t /= (float)a.OHW;
-        const long long o = n * a.out_sN + (long long)k * a.out_sK;
+        const long long o = n * a.out_sN + (long long)ko * a.out_sK;
         if (a.out_f32) ((float*)a.out)[o] = t; else tr::st(a.out, o, t);
       }
       __syncthreads();
     }
     return;
   }
-  const long long total = (long long)a.M * a.K;
-  for (long long idx = (long long)blockIdx.x * NT + threadIdx.x; idx < total; idx += (long long)gridDim.x * NT) {
-    const int k = (int)(idx % a.K);
-    const long long m = idx / a.K;
-    float v = sum_shares(a.part + m * a.part_ld + k);
-    v = v * a.scale[k] + a.shift[k];
-    const long long n = m / a.OHW, p = m - n * a.OHW;
-    if (a.res) v += tr::ld(a.res, n * a.res_sN + p * a.res_sP + k);
-    if (a.relu) v = fmx(v, 0.f);
-    const long long o = n * a.out_sN + p * a.out_sP + (long long)k * a.out_sK;
-    if (a.out_f32) ((float*)a.out)[o] = v; else tr::st(a.out, o, v);
+  if constexpr (V == 4) {
+    const int kv = a.K / 4, total = a.M * kv;
+    const AnyDiv by_kv(kv), by_ohw(a.OHW);
+    for (int idx = (int)blockIdx.x * NT + (int)threadIdx.x; idx < total; idx += (int)gridDim.x * NT) {
+      const int m = by_kv(idx), k = (idx - m * kv) * 4, n = by_ohw(m), p = m - n * a.OHW;
+      const acc_t sc = *(const acc_t*)(a.scale + k), sh = *(const acc_t*)(a.shift + k);
+      acc_t r = {};
+      if (a.res) r = load_res((long long)n * a.res_sN + (long long)p * a.res_sP + k);
+      acc_t v = sum_shares(a.part + (long long)m * a.part_ld + k);
+      v = v * sc + sh;
+      if (a.res) v += r;
+      if (a.relu) v = relu(v);
+      const long long o = (long long)n * a.out_sN + (long long)p * a.out_sP + k;
+      if (a.out_f32 || sizeof(T) == 4) *(acc_t*)((float*)a.out + o) = v;
+      else *(uint2*)((uint16_t*)a.out + o) = uint2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+    }
+  } else {
+    const long long total = (long long)a.M * a.K;
+    for (long long idx = (long long)blockIdx.x * NT + threadIdx.x; idx < total; idx += (long long)gridDim.x * NT) {
+      const int k = (int)(idx % a.K);
+      const long long m = idx / a.K;
+      float v = sum_shares(a.part + m * a.part_ld + k);
+      v = v * a.scale[k] + a.shift[k];
+      const long long n = m / a.OHW, p = m - n * a.OHW;
+      if (a.res) v += tr::ld(a.res, n * a.res_sN + p * a.res_sP + k);
+      if (a.relu) v = fmx(v, 0.f);
+      const long long o = n * a.out_sN + p * a.out_sP + (long long)k * a.out_sK;
+      if (a.out_f32) ((float*)a.out)[o] = v; else tr::st(a.out, o, v);
+    }
   }
 }
 
-int launch_splitk_finish(const SplitKArgs& a, int dtype, void* stream) {
-  hipStream_t st = (hipStream_t)stream;
-  if (a.ksplit < 1 || a.OHW < 1 || a.M % a.OHW != 0) return (int)hipErrorInvalidValue;
-  const int grid = a.gap ? grid_for((long long)(a.M / a.OHW) * ((a.K + 15) / 16), 1) : grid_for((long long)a.M * a.K, NT);
-  if (dtype == DT_BF16) hipLaunchKernelGGL(splitk_finish_kernel<bf16_t>, dim3(grid), dim3(NT), 0, st, a);
-  else hipLaunchKernelGGL(splitk_finish_kernel<float>, dim3(grid), dim3(NT), 0, st, a);
+template <typename T>
+static int launch_splitk_finish_t(const SplitKArgs& a, hipStream_t st) {
+  const size_t rb = 4 * sizeof(T), ob = a.out_f32 ? 16 : rb;
+  const bool vec = a.K % 4 == 0 && a.part_ld % 4 == 0 && ((uintptr_t)a.part & 15) == 0 && ((uintptr_t)a.scale & 15) == 0 && ((uintptr_t)a.shift & 15) == 0 &&
+                   (long long)a.M * a.K < (1ll << 30) &&
+                   (!a.res || ((uintptr_t)a.res % rb == 0 && a.res_sN % 4 == 0 && a.res_sP % 4 == 0)) &&
+                   (a.gap || (a.out_sK == 1 && (uintptr_t)a.out % ob == 0 && a.out_sN % 4 == 0 && a.out_sP % 4 == 0));
+  const int grid = a.gap ? grid_for((long long)(a.M / a.OHW) * ((a.K + 15) / 16), 1) : grid_for((long long)a.M * a.K / (vec ? 4 : 1), NT);
+  if (vec) hipLaunchKernelGGL((splitk_finish_kernel<T, 4>), dim3(grid), dim3(NT), 0, st, a);
+  else hipLaunchKernelGGL((splitk_finish_kernel<T, 1>), dim3(grid), dim3(NT), 0, st, a);
   return (int)hipGetLastError();
+}
+
+int launch_splitk_finish(const SplitKArgs& a, int dtype, void* stream) {
+  if (a.ksplit < 1 || a.OHW < 1 || a.M % a.OHW != 0) return (int)hipErrorInvalidValue;
+  return dtype == DT_BF16 ? launch_splitk_finish_t<bf16_t>(a, (hipStream_t)stream) : launch_splitk_finish_t<float>(a, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2684,14 +2787,20 @@ __global__ __launch_bounds__(NT) void elt_vec_kernel(const EltArgs a) {
   constexpr int CE = tr::CE;
   const int cv = a.C / CE;
   const long long total = a.pixels * cv;
+  const bool small = total < (1ll << 30);                          // (uniform: index arithmetic in 32 bits)
+  const AnyDiv by_cv(cv);
   for (long long idx = (long long)blockIdx.x * NT + threadIdx.x; idx < total; idx += (long long)gridDim.x * NT) {
-    const int c = (int)(idx % cv) * CE;
-    const long long p = idx / cv;
+    const long long p = small ? (long long)by_cv((int)idx) : idx / cv;
+    const int c = (int)(idx - p * cv) * CE;
     float v[CE];
     tr::unpack(*(const u32x4_t*)((const T*)a.a + p * a.a_sP + c), v);
     if (a.op == ELT_AFFINE) {
 #pragma unroll
-      for (int e = 0; e < CE; ++e) v[e] = v[e] * a.scale[c + e] + a.shift[c + e];
+      for (int e = 0; e < CE; e += 4) {
+        const f32x4_t sc = *(const f32x4_t*)(a.scale + c + e), sh = *(const f32x4_t*)(a.shift + c + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[e + u] = v[e + u] * sc[u] + sh[u];
+      }
     } else if (a.op == ELT_ADD) {
       float w[CE];
       tr::unpack(*(const u32x4_t*)((const T*)a.b + p * a.b_sP + c), w);
