@@ -26,7 +26,11 @@ __host__ __device__ constexpr int lds_conv_bytes() { return cmax(2 * (BM + BN) *
 // DWPRO: the A operand is not read from memory but produced on the fly by a linked depthwise 3x3 convolution
 // (+ scale/shift + ReLU) of the tensor `in`: the depthwise output never exists in HBM (Section 2.2: the depthwise
 // producer hands its result to the pointwise consumer in the consumer's channel-first order).
-template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE, bool DWPRO = false>
+// UNI: the tap of a reduction step is the same for the whole workgroup (1x1, or channel-chunk major order), so tap and offset advance
+// in scalar registers: some 30 instructions a step, against 100 with branches between for the general form, whose lanes may be
+// at different taps.  At batch 1 the loader was half of a step (timestamps, 64 x 64 tile: 1.08 k cycles a step with the general
+// form, 0.64 without any loads).
+template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE, bool DWPRO = false, bool UNI = false>
 __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
@@ -120,14 +124,18 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         iw0[it] = ow * a.stride - a.pad;
         // element offset of input pixel (ih0, iw0); only ever dereferenced together with an in-range tap
         rbase[it] = ok ? (long long)n * a.in_sN + (long long)ih0[it] * a.in_sH + (long long)iw0[it] * a.in_sW : 0;
+        if (UNI) rbase[it] += ch * CE;
         if (DWPRO) rbase[it] = ok ? (long long)n * a.dw_sN : 0;    // image base of the depthwise input; (ih0, iw0) = pointwise pixel
       }
       // reduction position (r, s, c) of this thread's 16-byte chunk
       int kc, kr, ks;
+      long long koff_u = 0;                                        // UNI: element offset of the step's tap and channel chunk
       {
-        if (a.kchunk) {
-          const int rs_n = a.R * a.S, cc = uniform_div(s_begin, rs_n), rs = s_begin - cc * rs_n;
-          kc = cc * BKE + ch * CE; kr = uniform_div(rs, a.S); ks = rs - kr * a.S;
+        if constexpr (UNI) {
+          const int rs_n = a.R * a.S, cc = rs_n > 1 ? uniform_div(s_begin, rs_n) : s_begin, rs = s_begin - cc * rs_n;
+          kr = a.S > 1 ? uniform_div(rs, a.S) : rs; ks = rs - kr * a.S;
+          kc = cc * BKE;                                           // (of the workgroup; a lane's channels are kc + ch * CE ..)
+          koff_u = (long long)kr * a.in_sH + (long long)ks * a.in_sW + kc;
         } else {
           const int kk = s_begin * BKE + ch * CE;
           const int rs = AnyDiv(a.C)(kk);
@@ -223,6 +231,20 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
             ra[it] = tr::pack(d);
           }
           kc += BKE;
+        } else if constexpr (UNI) {
+          const bool kok = kc + ch * CE < a.C;                     // (the padding of a 1x1 reduction; steps past the end are not requested)
+          okm = 0;
+#pragma unroll
+          for (int it = 0; it < A_IT; ++it) {
+            const bool ok = kok && (unsigned)(ih0[it] + kr) < (unsigned)a.H && (unsigned)(iw0[it] + ks) < (unsigned)a.W;
+            ra[it] = *(const u32x4_t*)((const T*)a.in + (ok ? rbase[it] + koff_u : 0));
+            okm |= (ok ? 1u : 0u) << it;
+          }
+          ++ks; koff_u += a.in_sW;
+          if (ks == a.S) {
+            ks = 0; ++kr; koff_u += a.in_sH - a.S * a.in_sW;
+            if (kr == a.R) { kr = 0; kc += BKE; koff_u += BKE - a.R * a.in_sH; }
+          }
         } else if constexpr (!SCALAR) {
           const bool kok = step < nsteps && kr < a.R && kc < a.C; // false for every step past the end of this share
           const long long koff = (long long)kr * a.in_sH + (long long)ks * a.in_sW + kc;
@@ -235,12 +257,9 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
             ra[it] = *(const u32x4_t*)((const T*)a.in + off);
             okm |= (ok ? 1u : 0u) << it;
           }
-          if (a.kchunk) {   // channel-chunk major: all taps of one chunk in consecutive steps (halo reuse in cache)
-            if (++ks == a.S) { ks = 0; if (++kr == a.R) { kr = 0; kc += BKE; } }
-          } else {          // tap major: (r, s) outer, channels inner
-            kc += BKE;
-            while (kc >= a.C) { kc -= a.C; if (++ks == a.S) { ks = 0; ++kr; } }
-          }
+          // tap major: (r, s) outer, channels inner (channel-chunk major order takes UNI)
+          kc += BKE;
+          while (kc >= a.C) { kc -= a.C; if (++ks == a.S) { ks = 0; ++kr; } }
         } else {
           okm = ~0u;
           float f[A_IT][CE];
@@ -280,32 +299,40 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           if (B_CH % NT == 0 || idx < B_CH) *(u32x4_t*)(sb + (idx / CPR) * LDS_ROW + (idx % CPR) * 16) = rb[it];
         }
       };
+      // (a wavefront with one 32 x 32 block reads all fragments of a step before its first MFMA)
+      constexpr int KB = UNI && TM * TN == 1 ? KG : 1;
       auto compute = [&](int stage) {
         const unsigned char* sa = smem + stage * (BM + BN) * LDS_ROW;
         const unsigned char* sb = sa + BM * LDS_ROW;
 #pragma unroll
-        for (int kg = 0; kg < KG; ++kg) {
-          u32x4_t fa[TM], fb[TN];
+        for (int k0 = 0; k0 < KG; k0 += KB) {
+          u32x4_t fa[KB][TM], fb[KB][TN];
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-            fa[i] = *(const u32x4_t*)(sa + (wave_m * WM + i * 32 + l31) * LDS_ROW + kg * 32 + lhalf * 16);
+          for (int kg = 0; kg < KB; ++kg) {
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            fb[j] = *(const u32x4_t*)(sb + (wave_n * WN + j * 32 + l31) * LDS_ROW + kg * 32 + lhalf * 16);
+            for (int i = 0; i < TM; ++i)
+              fa[kg][i] = *(const u32x4_t*)(sa + (wave_m * WM + i * 32 + l31) * LDS_ROW + (k0 + kg) * 32 + lhalf * 16);
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
+            for (int j = 0; j < TN; ++j)
+              fb[kg][j] = *(const u32x4_t*)(sb + (wave_n * WN + j * 32 + l31) * LDS_ROW + (k0 + kg) * 32 + lhalf * 16);
+          }
+          if constexpr (KB > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              if constexpr (sizeof(T) == 2) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
-                                                                    __builtin_bit_cast(bf16x8_t, fb[j]), acc[i][j], 0, 0, 0);
-              } else {
+          for (int kg = 0; kg < KB; ++kg)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[i][e]), __uint_as_float(fb[j][e]),
-                                                                   acc[i][j], 0, 0, 0);
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j) {
+                if constexpr (sizeof(T) == 2) {
+                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[kg][i]),
+                                                                      __builtin_bit_cast(bf16x8_t, fb[kg][j]), acc[i][j], 0, 0, 0);
+                } else {
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[kg][i][e]), __uint_as_float(fb[kg][j][e]),
+                                                                     acc[i][j], 0, 0, 0);
+                }
               }
-            }
         }
       };
 
@@ -2123,20 +2150,28 @@ static int launch_stem_lds(const ConvArgs& a, int dtype, hipStream_t st) {
 }
 
 
-template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE>
-static int launch_conv_inst(const ConvArgs& a, hipStream_t st) {
+template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE, bool UNI>
+static int launch_conv_uni(const ConvArgs& a, hipStream_t st) {
   constexpr int lds = lds_conv_bytes<BM, BN>();
   if (lds > 64 * 1024) {   // more than the default dynamic-LDS limit: raise it once per instantiation
     static bool raised = false;
     if (!raised) {
-      hipError_t e = hipFuncSetAttribute((const void*)conv_kernel<T, BM, BN, WM, WN, SCALAR, MODE>,
+      hipError_t e = hipFuncSetAttribute((const void*)conv_kernel<T, BM, BN, WM, WN, SCALAR, MODE, false, UNI>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       if (e != hipSuccess) return (int)e;
       raised = true;
     }
   }
-  hipLaunchKernelGGL((conv_kernel<T, BM, BN, WM, WN, SCALAR, MODE>), dim3(a.grid), dim3(NT), lds, st, a);
+  hipLaunchKernelGGL((conv_kernel<T, BM, BN, WM, WN, SCALAR, MODE, false, UNI>), dim3(a.grid), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
+}
+
+template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE>
+static int launch_conv_inst(const ConvArgs& a, hipStream_t st) {
+  if constexpr (!SCALAR)
+    if (a.kchunk || (a.R == 1 && a.S == 1)) return launch_conv_uni<T, BM, BN, WM, WN, SCALAR, MODE, true>(a, st);
+  if (a.kchunk) return (int)hipErrorInvalidValue;
+  return launch_conv_uni<T, BM, BN, WM, WN, SCALAR, MODE, false>(a, st);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, bool SCALAR>
