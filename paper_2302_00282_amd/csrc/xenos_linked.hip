@@ -215,6 +215,13 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
 #pragma unroll
     for (int t9 = 0; t9 < 9; ++t9) dww[t9] = *(const u32x4_t*)((const T*)a.dw_w + (long long)t9 * a.K + (kok ? k0 : 0));
 
+    float dsc[CE], dsh[CE];
+#pragma unroll
+    for (int e = 0; e < CE; e += 4) {
+      *(f32x4_t*)&dsc[e] = *(const f32x4_t*)(a.dw_scale + (kok ? k0 : 0) + e);
+      *(f32x4_t*)&dsh[e] = *(const f32x4_t*)(a.dw_shift + (kok ? k0 : 0) + e);
+    }
+
     if (hv < PH || wv < PWd) {
       // the block overhangs the map: those positions are the zero padding of the depthwise convolution
       const u32x4_t z = {0u, 0u, 0u, 0u};
@@ -264,24 +271,22 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
 
     // ---- depthwise chain out of the block: one thread = one 16-byte channel group of one output pixel --------
     if (kok) {
-      float dsc[CE], dsh[CE];
-#pragma unroll
-      for (int e = 0; e < CE; e += 4) {
-        *(f32x4_t*)&dsc[e] = *(const f32x4_t*)(a.dw_scale + k0 + e);
-        *(f32x4_t*)&dsh[e] = *(const f32x4_t*)(a.dw_shift + k0 + e);
-      }
       for (int q = tid / CG; q < a.th * a.tw; q += NT / CG) {
         const int qy = by_tw(q), qx = q - qy * a.tw;
         const int oy = oy0 + qy, ox = ox0 + qx;
         if (oy >= a.OH || ox >= a.OW) continue;
         const unsigned char* src = s_mid + ((qy * s) * PWd + qx * s) * MP + cg * 16;
+        u32x4_t xr[9];
+#pragma unroll
+        for (int t9 = 0; t9 < 9; ++t9) xr[t9] = *(const u32x4_t*)(src + ((t9 / 3) * PWd + t9 % 3) * MP);
+        __builtin_amdgcn_sched_barrier(0);
         float d[CE];
 #pragma unroll
         for (int e = 0; e < CE; ++e) d[e] = 0.f;
 #pragma unroll
         for (int t9 = 0; t9 < 9; ++t9) {
           float x[CE], w[CE];
-          tr::unpack(*(const u32x4_t*)(src + ((t9 / 3) * PWd + t9 % 3) * MP), x);
+          tr::unpack(xr[t9], x);
           tr::unpack(dww[t9], w);
 #pragma unroll
           for (int e = 0; e < CE; ++e) d[e] = fmaf(x[e], w[e], d[e]);
@@ -478,14 +483,22 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
 
     // ---- phase 2: this workgroup's expand tiles -----------------------------------------------------------
     // epilogue of a wavefront's 32 pixels x 32 channels of chunk mc of channel tile j
-    auto tile_epilogue = [&](int which, int j, int mc, const f32x16_t& acc) __attribute__((always_inline)) {
+    auto load_affine = [&](int which, int j, f32x4_t* esc, f32x4_t* esh) __attribute__((always_inline)) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int kk = j * 64 + wave_n * 32 + g * 8 + lhalf * 4;
+        esc[g] = *(const f32x4_t*)(a.fire_scale[which] + kk);
+        esh[g] = *(const f32x4_t*)(a.fire_shift[which] + kk);
+      }
+    };
+    auto tile_epilogue = [&](int which, int j, int mc, const f32x16_t& acc, const f32x4_t* esc, const f32x4_t* esh) __attribute__((always_inline)) {
       const int E = a.fire_E[which];
       const float lo = a.fire_relu[which] ? 0.f : -3.4028235e38f;
       // finished values change hands inside the wavefront only
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int c = g * 8 + lhalf * 4, kk = j * 64 + wave_n * 32 + c;
-        const f32x4_t sc = *(const f32x4_t*)(a.fire_scale[which] + kk), sh = *(const f32x4_t*)(a.fire_shift[which] + kk);
+        const int c = g * 8 + lhalf * 4;
+        const f32x4_t sc = esc[g], sh = esh[g];
         float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
@@ -586,6 +599,8 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
           if (j != gz) load_w(which, j, w);
 #pragma unroll 1
           for (int mc = 0; mc * 64 < npix; ++mc) {
+            f32x4_t esc[4], esh[4];
+            if constexpr (KGS < 4) load_affine(which, j, esc, esh);   // (before the MFMAs, which cover its latency, where the registers allow it)
             const unsigned char* pa = first_tap(which, mc);
             f32x16_t acc;
 #pragma unroll
@@ -610,7 +625,8 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w[g * GT * KGS + f]), __builtin_bit_cast(bf16x8_t, fa[g & 1][f]), acc, 0, 0, 0);
               __builtin_amdgcn_sched_barrier(0);
             }
-            tile_epilogue(which, j, mc, acc);
+            if constexpr (KGS == 4) load_affine(which, j, esc, esh);
+            tile_epilogue(which, j, mc, acc, esc, esh);
           }
           if constexpr (POOL) tile_pool(which, j);
         }
@@ -651,6 +667,8 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
         __syncthreads();
 #pragma unroll 1
         for (int mc = 0; mc * 64 < npix; ++mc) {
+          f32x4_t esc[4], esh[4];
+          load_affine(which, j, esc, esh);
           const unsigned char* pa = first_tap(which, mc);
           const unsigned char* pb = s_b + (wave_n * 32 + l31) * WP + lhalf * 16;
           f32x16_t acc;
@@ -667,7 +685,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[e]), __uint_as_float(fa[e]), acc, 0, 0, 0);
             }
           }
-          tile_epilogue(which, j, mc, acc);
+          tile_epilogue(which, j, mc, acc, esc, esh);
         }
         if constexpr (POOL) tile_pool(which, j);
         else __syncthreads();                                      // the weight tile is rewritten
