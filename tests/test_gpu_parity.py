@@ -465,6 +465,24 @@ def test_pointwise_depthwise_linked_on_chip(stride, h, w, c, k, n, tail, compute
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("n,c,h,w", [(1, 8, 1, 1), (3, 24, 5, 7), (2, 40, 33, 17), (1, 1032, 3, 3)])
+def test_elementwise_operators_share_a_pass(n, c, h, w, compute):
+    # BN, bias and ReLU behind a tensor no convolution produces are one element-wise pass, and so are an add and its ReLU;
+    # a tensor with a second reader ends the pass.  The ReLU commutes with the rounding of the stored tensor.
+    b = wg.builder("pre", (n, c, h, w), 43, nonzero_bias=True)
+    x = b.maxpool(0, 1, 1)
+    u = b.relu(b.bias(b.bn(x)))
+    v = b.bn(x)
+    t = b.relu(b.add(u, b.relu(v)))
+    t = b.add(t, v)
+    g = b.finish(b.cbr(t, 16, 1, name="post"))
+    y, info = check(g, xo.forward(g), compute=compute, link=2)
+    kinds = [[g.ops[o].kind for o in ch["ops"]] for ch in info["chains"] if ch["kind"] == "elt"]
+    assert sorted(kinds) == sorted([["bn", "bias", "relu"], ["bn"], ["relu"], ["add", "relu"], ["add"]]), kinds
+    check_chains(g, compute, link=2)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("stride,h,w,c,mid,k,n,tail", [(1, 33, 32, 16, 16, 24, 1, "conv"), (2, 65, 63, 24, 72, 40, 1, "conv"), (1, 7, 7, 64, 136, 200, 21, "conv"),
                                                        (1, 14, 14, 88, 88, 88, 6, "shuffle"), (2, 19, 45, 40, 200, 136, 5, "conv"),
                                                        (1, 28, 37, 8, 8, 8, 1, "out"), (1, 5, 206, 232, 40, 320, 1, "cat")])
