@@ -175,7 +175,9 @@ void write_plan_json(xenos_plan& p);
 // ---------------------------------------------------------------------------------------------
 // Planner
 // ---------------------------------------------------------------------------------------------
-// Fewest output pixels (all images) of a chain on unit_kernel
+// Fewest output pixels (all images) of a chain on unit_kernel: in fp32, where a tile per workgroup with all channels leaves most
+// units idle at the fp32 MFMA rate, the whole ShuffleNet graph takes 385 us at batch 2 with the rule and 463 with every unit
+// linked.  (In bf16 the link would gain below it too: batch 2 290 us with the rule, 228 with every unit linked.)
 constexpr long long kUnitMinPixels = 1024;
 
 struct Planner {
@@ -1137,7 +1139,7 @@ struct Planner {
   // The pointwise convolution behind depthwise node dn (= pwdw_consumer(i)) if all three can run as one chain: a plain 1x1
   // chain of its own (no shortcut, no pooling) that stores 16-byte channel groups, or finishes a two-group shuffle whose other
   // part exists already.  A pointwise convolution that hands on to the next depthwise one stays out (see pwdw_wanted), and so
-  // do few pixels, which are better spread over the units by channel tiles too, as two chains.  Returns the node or -1.
+  // do few pixels (kUnitMinPixels).  Returns the node or -1.
   int unit_consumer(int i, int dn) const {
     const Shape os = tshape[dn + 1];
     if ((long long)os.n * os.h * os.w < kUnitMinPixels) return -1;
@@ -1305,10 +1307,10 @@ struct Planner {
   }
 
   // Tile (output pixels, or pooling windows) and number of channel shares of a Fire-module chain.  A workgroup's time in
-  // microseconds, from timestamps taken inside the kernel at its phase boundaries (bf16, batch 1): 1.4 to start, the
-  // squeeze GEMM of its clipped block 1.0 + 0.35 per chunk of 64 positions and reduction step, and for every expand
-  // tile of its share the weight copy (0.7 + 0.15 per 4 KB), the GEMM (0.5 + 0.028 per tap and k-group, per chunk of 64
-  // pixels) and 0.9 for epilogue and stores (+ 1.5 with a linked pooling): at batch 1 these fixed latencies, not the
+  // microseconds, from timestamps taken inside the kernel at its phase boundaries (batch 1): 1.4 to start, the squeeze GEMM
+  // of its clipped block 1.0 + 0.35 per chunk of 64 positions and reduction step, and for every expand tile of its share the
+  // weights (bf16: 0.3, requested ahead into registers; fp32: a copy to LDS, 0.7 + 0.15 per 4 KB), the GEMM (0.5 + 0.016 or
+  // 0.11 per tap and k-group, per chunk of 64 pixels) and 0.4 or 0.9 for epilogue and stores (+ 1.5 with a linked pooling): at batch 1 these fixed latencies, not the
   // MFMA work, are the time of a module.  The longest workgroup decides, or the sum of all over the units' slots.
   bool choose_fire_tile(ConvArgs& c) const {
     const int num_cu = std::max(1, p.hw.num_cu);
