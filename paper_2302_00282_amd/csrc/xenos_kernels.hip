@@ -2571,8 +2571,9 @@ __global__ __launch_bounds__(NT) void dw_kernel(const DwArgs a) {
       *(f32x4_t*)&sh[e] = *(const f32x4_t*)(a.shift + c0 + e);
     }
     if constexpr (K3) {
-      // all loads before the first product (a tap outside the map reads the nearest pixel inside and counts as zero): with a
-      // branch around every tap the nine latencies followed each other
+      // all loads before the first product (a tap outside the map reads the nearest pixel inside; pixel and weight then count as
+      // zero, so that an infinite weight does not meet the padding): with a branch around every tap the nine latencies
+      // followed each other
       u32x4_t xr[9], wr[9];
       const T* img = (const T*)a.in + (long long)n * a.in_sN + c0;
 #pragma unroll
@@ -2581,7 +2582,7 @@ __global__ __launch_bounds__(NT) void dw_kernel(const DwArgs a) {
         const int ch = ih < 0 ? 0 : ih < a.H ? ih : a.H - 1, cw = iw < 0 ? 0 : iw < a.W ? iw : a.W - 1;
         xr[t9] = *(const u32x4_t*)(img + ((long long)ch * a.W + cw) * a.in_sP);
         wr[t9] = *(const u32x4_t*)((const T*)a.w + (long long)t9 * a.C + c0);
-        if (ch != ih || cw != iw) xr[t9] = u32x4_t{0u, 0u, 0u, 0u};
+        if (ch != ih || cw != iw) xr[t9] = wr[t9] = u32x4_t{0u, 0u, 0u, 0u};
       }
 #pragma unroll
       for (int t9 = 0; t9 < 9; ++t9) {

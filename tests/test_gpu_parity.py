@@ -465,6 +465,23 @@ def test_pointwise_depthwise_linked_on_chip(stride, h, w, c, k, n, tail, compute
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("stride,h,w", [(1, 1, 1), (1, 7, 9), (2, 8, 5)])
+def test_depthwise_padding_does_not_meet_infinite_weights(stride, h, w, compute):
+    # a tap outside the map adds nothing, whatever its weight is: with an infinite weight in a corner of the window the outputs
+    # whose corner lies in the padding are the finite sums of the other taps, the others are infinite
+    b = wg.builder("dwinf", (2, 16, h, w), 51, nonzero_bias=True)
+    g = b.finish(b.cbr(0, 16, 3, stride, 1, groups=16, name="dw", bn=False, relu=False))
+    g.ops[0].params["weight"][:, :, 0, 2] = np.inf
+    ref = xo.forward(g)
+    fin = np.isfinite(ref)
+    assert fin.any() and (fin.all() or h > 1)
+    y, info = run_gpu(g, compute=compute, link=2)
+    assert any(ch["kind"] == "dwconv" for ch in info["chains"])
+    assert np.array_equal(np.isfinite(y), fin) and np.array_equal(y[~fin], ref[~fin].astype(np.float32))
+    assert rel_err(y[fin], ref[fin]) <= TOL[compute]
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("n,c,h,w", [(1, 8, 1, 1), (3, 24, 5, 7), (2, 40, 33, 17), (1, 1032, 3, 3)])
 def test_elementwise_operators_share_a_pass(n, c, h, w, compute):
     # BN, bias and ReLU behind a tensor no convolution produces are one element-wise pass, and so are an add and its ReLU;
