@@ -44,6 +44,10 @@ __device__ __forceinline__ gptr_t here(const void* p) {
 }
 __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(const __attribute__((address_space(1))) u32x4_t*)(base + off); }
 
+// ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
+// replace -infinity)
+__device__ __forceinline__ float unit_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
+
 // Transposed GEMM of `nrows` LDS rows (pitch bytes apart, nkg k-groups of 32 bytes each) with ncb blocks of 32 channels, a
 // wavefront per 64 rows x 32 channels.  w: fragments [block][kgs][lane] of 16 bytes.  pre(block, row0) runs before a block's
 // reduction, epi(block, row0, acc) receives each finished 32 x 32 part: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3)
@@ -194,7 +198,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
         if (m >= npos) return;
         const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * PM;
-        const float lo = a.fire_relu[0] ? 0.f : -3.4028235e38f;
+        const float lo = unit_floor(a.fire_relu[0]);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = cb * 32 + g * 8 + lhalf * 4;
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
       },
       [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
         // finished values change hands inside the wavefront only (LDS serves its requests in order)
-        const float lo = a.relu ? 0.f : -3.4028235e38f;
+        const float lo = unit_floor(a.relu);
         u32x4_t oth[STG_IT];
         long long dst[STG_IT];
 #pragma unroll

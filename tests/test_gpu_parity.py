@@ -537,6 +537,35 @@ def test_pointwise_depthwise_pointwise_linked_on_chip(stride, h, w, c, mid, k, n
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("relu_pw,relu_out", [(False, False), (False, True), (True, False)])
+def test_pointwise_depthwise_pointwise_keeps_infinities(relu_pw, relu_out, compute):
+    # an infinite value of a stage without a ReLU reaches the next stage as it is, in the linked chain as operator by operator
+    b = wg.builder("unitinf", (1, 16, 33, 32), 61, nonzero_bias=True)
+    t = b.cbr(0, 16, 1, name="pre")
+    t = b.cbr(t, 24, 1, name="pw", bn=False, relu=relu_pw)
+    pw = len(b.g.ops) - (2 if relu_pw else 1)
+    t = b.cbr(t, 24, 3, 1, 1, groups=24, name="dw", bn=False, relu=False)
+    t = b.cbr(t, 16, 1, name="pw2", bn=False, relu=False)
+    last = len(b.g.ops) - 1
+    t = b.relu(t) if relu_out else t
+    g = b.finish(t)
+    g.ops[pw].params["bias"][5] = -np.inf                     # -inf behind the first convolution, or 0 with its ReLU
+    if relu_pw:
+        g.ops[last].params["bias"][3] = -np.inf               # an output channel of -inf
+    dw = next(o for o in g.ops if o.name == "dw" and o.kind == "conv")
+    dw.params["weight"] = (np.abs(dw.params["weight"]) * np.float32(1e-3)).astype(np.float32)
+    g.ops[last].params["weight"][:, 5] *= np.float32(1e-30)
+    ref = xo.forward(g)
+    fmt = dict(out_layout=1, out_dtype=compute)
+    y, info = run_gpu(g, compute=compute, link=3, **fmt)
+    assert sum(1 for ch in info["chains"] if ch.get("loader") == "unit") == 1
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(y), fin) and np.array_equal(y[~fin], ref[~fin].astype(np.float32))
+    if fin.any():
+        assert rel_err(y[fin], ref[fin]) <= TOL[compute]
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("h,w,c,s,e1,e3,n,pool,tail", [(13, 13, 32, 16, 64, 64, 2, 0, "conv"), (27, 21, 64, 32, 128, 72, 1, 3, "conv"),
                                                        (9, 30, 24, 48, 40, 200, 3, 0, "conv"), (14, 14, 128, 64, 256, 256, 1, 2, "conv"),
                                                        (55, 55, 64, 16, 64, 64, 1, 3, "gap"), (5, 5, 16, 16, 8, 8, 2, 0, "out"),
