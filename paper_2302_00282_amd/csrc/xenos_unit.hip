@@ -319,7 +319,8 @@ template <typename T>
 static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
   constexpr int ESZ = (int)sizeof(T), CE = Tr<T>::CE, BKE = Tr<T>::BKE;
   const int s = a.dw_stride;
-  // what the kernel assumes, checked again on the host: a wrong shape would index outside the LDS block or the tensors
+  // what the kernel assumes, checked again on the host: a wrong shape would index outside the LDS block or the tensors (the caller's
+  // output may lie at any element: the hardware takes 16-byte stores there)
   if (a.mode != M_FLAT || a.has_res || a.pool != POOL_NONE || a.ksplit >= 1 || a.kchunk || a.pair || a.fire || a.pwdw || !a.wfrag || !a.vec_out ||
       a.R != 1 || a.S != 1 || a.stride != 1 || a.pad != 0 || a.C % CE != 0 || a.K % CE != 0 || a.C < CE || a.K < CE || a.C / CE > UN_NT ||
       a.unit_C % CE != 0 || a.unit_C < CE || a.Kred_pad < (a.C + BKE - 1) / BKE * BKE || a.Kred_pad % BKE != 0 ||
@@ -328,7 +329,7 @@ static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
       a.OH != (a.dw_H + 2 - 3) / s + 1 || a.OW != (a.dw_W + 2 - 3) / s + 1 || a.th < 1 || a.tw < 1 ||
       a.tiles_y != (a.OH + a.th - 1) / a.th || a.tiles_x != (a.OW + a.tw - 1) / a.tw || a.tiles_n != 1 ||
       a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m || a.grid < 1 || a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.unit_C ||
-      a.in_sH * a.dw_H * ESZ >= (1ll << 31) || a.in_sN % CE != 0 || a.in_sH % CE != 0 || a.in_sW % CE != 0 || ((uintptr_t)a.in & 15) || ((uintptr_t)a.out & 15) || a.out_sP % CE != 0 || a.out_sN % CE != 0 ||
+      a.in_sH * a.dw_H * ESZ >= (1ll << 31) || a.in_sN % CE != 0 || a.in_sH % CE != 0 || a.in_sW % CE != 0 || ((uintptr_t)a.in & 15) || a.out_sP % CE != 0 || a.out_sN % CE != 0 ||
       a.out_sP < (a.ileave ? 2 : 1) * a.K || (a.ileave && !a.res))
     return (int)hipErrorInvalidValue;
   const int lds = (int)unit_lds_bytes(a.th, a.tw, s, a.unit_C, a.C, ESZ);

@@ -565,6 +565,31 @@ def test_pointwise_depthwise_pointwise_keeps_infinities(relu_pw, relu_out, compu
         assert rel_err(y[fin], ref[fin]) <= TOL[compute]
 
 
+@pytest.mark.parametrize("compute,off", [(0, 1), (0, 2), (1, 2), (1, 4)])
+def test_pointwise_depthwise_pointwise_takes_an_output_at_any_element(off, compute):
+    # the caller's output pointer needs no alignment beyond its element's (4 and 8 bytes past a 16-byte boundary here): same
+    # bits as at an aligned address, and nothing outside the output is written
+    X = _xenos()
+    b = wg.builder("unitoff", (2, 16, 33, 19), 67, nonzero_bias=True)
+    t = b.cbr(0, 24, 1, name="pre")
+    t = b.cbr(t, 40, 1, name="pw")
+    t = b.cbr(t, 40, 3, 1, 1, groups=40, name="dw", relu=False)
+    g = b.finish(b.cbr(t, 24, 1, name="pw2"))
+    s = X.Session(g, link=3, compute=compute, out_layout=1, out_dtype=compute)
+    try:
+        assert s.info["chains"][-1].get("loader") == "unit"
+        s.forward(g.x)
+        n, guard = s.y.numel(), 64
+        buf = s.torch.full((n + 2 * guard,), 7.0, dtype=s.y.dtype, device=s.device)
+        assert buf.data_ptr() % 16 == 0
+        X.xenos_run(s.plan, s.x.data_ptr(), buf[guard + off:].data_ptr(), s.stream())
+        s.torch.cuda.synchronize()
+        assert s.torch.equal(buf[guard + off:guard + off + n], s.y.view(-1))
+        assert (buf[:guard + off] == 7).all() and (buf[guard + off + n:] == 7).all()
+    finally:
+        s.close()
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("h,w,c,s,e1,e3,n,pool,tail", [(13, 13, 32, 16, 64, 64, 2, 0, "conv"), (27, 21, 64, 32, 128, 72, 1, 3, "conv"),
                                                        (9, 30, 24, 48, 40, 200, 3, 0, "conv"), (14, 14, 128, 64, 256, 256, 1, 2, "conv"),
