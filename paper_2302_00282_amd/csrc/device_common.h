@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
+#include "index_div.h"
 #include "kernels.h"
 
 namespace xenos {
@@ -111,29 +112,18 @@ __device__ __forceinline__ void fetch_args(const void* ka) {
 }
 #define FETCH_ARGS(T) fetch_args<(int)sizeof(T)>((const void*)__builtin_amdgcn_kernarg_segment_ptr())
 
-// n / d for 0 <= n < kSmallDiv, exactly: (n + 0.5) / d is at least 0.5 / d away from an integer, and reciprocal, product and
-// conversion together are off by less than 2^-21 of it.  Four instructions; the compiler's division by a run-time integer is
-// some thirty, several of them at quarter rate, and is what the index arithmetic of a short chain is made of (eight of them in
-// the loader of unit_kernel were 3 of the 5 k cycles until its input was in LDS).
-constexpr int kSmallDiv = 1 << 20;
+// division by a run-time integer that many indices share (index_div.h)
 struct SmallDiv {
   int d;
   float r;
   __device__ __forceinline__ explicit SmallDiv(int d_) : d(d_), r(__builtin_amdgcn_rcpf((float)d_)) {}
-  __device__ __forceinline__ int operator()(int n) const { return (int)(((float)n + 0.5f) * r); }
+  __device__ __forceinline__ int operator()(int n) const { return small_quotient(n, r); }
 };
-// n / d for any 0 <= n < 2^31: the product is off by at most 2^-21 of the quotient, a second one of the remainder leaves at
-// most one either way.  Some fifteen instructions.
 struct AnyDiv {
   int d;
   float r;
   __device__ __forceinline__ explicit AnyDiv(int d_) : d(d_), r(__builtin_amdgcn_rcpf((float)d_)) {}
-  __device__ __forceinline__ int operator()(int n) const {
-    int q = (int)((float)n * r);
-    q += (int)((float)(n - q * d) * r);
-    const int rem = n - q * d;
-    return rem < 0 ? q - 1 : rem >= d ? q + 1 : q;
-  }
+  __device__ __forceinline__ int operator()(int n) const { return any_quotient(n, d, r); }
 };
 // n / d of wavefront-uniform values of any size
 __device__ __forceinline__ int uniform_div(int n, int d) {

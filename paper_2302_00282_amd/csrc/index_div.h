@@ -1,0 +1,23 @@
+// Quotients of indices by a run-time integer d from r, an approximation of 1 / d within one unit in the last place (what the
+// hardware's reciprocal instruction gives).  Plain arithmetic, the same on the host: tests compile this file by itself.
+#pragma once
+
+namespace xenos {
+
+// n / d for 0 <= n < kSmallDiv, exactly: (n + 0.5) / d is at least 0.5 / d away from an integer, and reciprocal, product and
+// conversion together are off by less than 2^-21 of it.  Four instructions; the compiler's division by a run-time integer is
+// some thirty, several of them at quarter rate, and is what the index arithmetic of a short chain is made of (eight of them in
+// the loader of unit_kernel were 3 of the 5 k cycles until its input was in LDS).
+constexpr int kSmallDiv = 1 << 20;
+__attribute__((always_inline)) constexpr int small_quotient(int n, float r) { return (int)(((float)n + 0.5f) * r); }
+
+// n / d for any 0 <= n < 2^31: the product is off by at most 2^-21 of the quotient, a second one of the remainder leaves at
+// most one either way.  Some fifteen instructions.  (Unsigned: a first quotient above the true one times d may reach 2^31.)
+__attribute__((always_inline)) constexpr int any_quotient(int n, int d, float r) {
+  unsigned q = (unsigned)((float)n * r);
+  q += (unsigned)(int)((float)(int)((unsigned)n - q * (unsigned)d) * r);
+  const int rem = (int)((unsigned)n - q * (unsigned)d);
+  return (int)(rem < 0 ? q - 1 : rem >= d ? q + 1 : q);
+}
+
+}  // namespace xenos

@@ -1,0 +1,57 @@
+"""The quotients every kernel index is made of (csrc/index_div.h), on the host: the file itself compiled by the host compiler, with
+the reciprocal at its correctly rounded value and one unit in the last place to either side."""
+import os
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2302_00282_amd", "csrc")
+
+PROGRAM = r"""
+#include <initializer_list>
+#include <math.h>
+#include <stdint.h>
+#include <stdio.h>
+#include "index_div.h"
+using namespace xenos;
+
+static long long bad = 0, seen = 0;
+static void check(int64_t n, int d, bool small_only) {
+  if (n < 0 || n > INT32_MAX) return;
+  const float r0 = (float)(1.0 / d);
+  for (float r : {nextafterf(r0, 0.f), r0, nextafterf(r0, 2.f)}) {
+    const int want = (int)(n / d);
+    ++seen;
+    if (n < kSmallDiv && small_quotient((int)n, r) != want && ++bad < 9) printf("small %lld / %d\n", (long long)n, d);
+    if (!small_only && any_quotient((int)n, d, r) != want && ++bad < 9) printf("any %lld / %d\n", (long long)n, d);
+  }
+}
+
+int main() {
+  // every quotient boundary below kSmallDiv of every divisor up to 2048, and of larger ones in growing steps
+  for (int64_t d = 1; d < (1ll << 31); d += d < 2048 ? 1 : d / 97 + 1)
+    for (int64_t m = 0; m <= kSmallDiv + d; m += d) { check(m - 1, (int)d, true); check(m, (int)d, true); }
+  // boundaries over the whole range: around multiples k d with k spread over its octaves, and around the ends of the range
+  uint64_t s = 88172645463325252ull;
+  for (int64_t d = 1; d < (1ll << 31); d += d < 4096 ? 1 : d / 211 + 1) {
+    const int64_t kmax = INT32_MAX / d;
+    for (int i = 0; i < 96; ++i) {
+      s ^= s << 13; s ^= s >> 7; s ^= s << 17;
+      const int64_t k = i < 4 ? kmax - i : (int64_t)(s % (uint64_t)(kmax + 1)) >> (s >> 59);
+      for (int o = -1; o <= 1; ++o) check(k * d + o, (int)d, false);
+    }
+    for (int o = 0; o < 3; ++o) { check(o, (int)d, false); check((int64_t)INT32_MAX - o, (int)d, false); }
+  }
+  printf("%lld quotients, %lld wrong\n", seen, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_index_quotients_are_exact_over_their_ranges(tmp_path):
+    src, exe = tmp_path / "div.cpp", tmp_path / "div"
+    src.write_text(PROGRAM)
+    # (float arithmetic as written, signed overflow and conversions out of range are errors)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-fsanitize=signed-integer-overflow,float-cast-overflow",
+                    "-fno-sanitize-recover=all", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    print(r.stdout)
