@@ -175,9 +175,10 @@ void write_plan_json(xenos_plan& p);
 // ---------------------------------------------------------------------------------------------
 // Planner
 // ---------------------------------------------------------------------------------------------
-// Fewest output pixels (all images) of a chain on unit_kernel: in fp32, where a tile per workgroup with all channels leaves most
-// units idle at the fp32 MFMA rate, the whole ShuffleNet graph takes 385 us at batch 2 with the rule and 463 with every unit
-// linked.  (In bf16 the link would gain below it too: batch 2 290 us with the rule, 228 with every unit linked.)
+// Fewest output pixels (all images) of a chain on unit_kernel: the range Planner::unit_pays is measured over ends there.  In fp32
+// a tile per workgroup with all channels leaves most units idle below it: the whole ShuffleNet graph takes 385 us at batch 2 with
+// the line and 463 with every unit linked.  In bf16 the line is not where the link stops gaining (290 us with it, 228 with every
+// unit linked): units of few pixels run there as they did before the kernel was made.
 constexpr long long kUnitMinPixels = 1024;
 
 struct Planner {
@@ -1139,7 +1140,7 @@ struct Planner {
   // The pointwise convolution behind depthwise node dn (= pwdw_consumer(i)) if all three can run as one chain: a plain 1x1
   // chain of its own (no shortcut, no pooling) that stores 16-byte channel groups, or finishes a two-group shuffle whose other
   // part exists already.  A pointwise convolution that hands on to the next depthwise one stays out (see pwdw_wanted), and so
-  // do few pixels (kUnitMinPixels).  Returns the node or -1.
+  // do few pixels (kUnitMinPixels).  Whether the link pays is asked afterwards (unit_pays).  Returns the node or -1.
   int unit_consumer(int i, int dn) const {
     const Shape os = tshape[dn + 1];
     if ((long long)os.n * os.h * os.w < kUnitMinPixels) return -1;
@@ -1190,6 +1191,51 @@ struct Planner {
     return best < 1e300;
   }
 
+  // Is a unit faster as one chain of th x tw tiles than as the two chains it is otherwise?  unit_kernel keeps all channels in one
+  // workgroup: with wide layers its tiles are a few pixels (LDS), every tile reads both weight matrices, and in fp32 the MFMA
+  // work of a tile runs on one unit (fp32, 1024 channels, 32 x 32: 90 us as two chains, 307 as one; bf16 33 and 64).  Time models
+  // in microseconds, their terms fitted to 900 random shapes (8 to 1024 channels, 1024 to 60000 output pixels) measured both ways,
+  // nine tenths of them within 25 %; the fp32 one, which errs against small units, gives them 2 us.  Of 600 other shapes 126 lost
+  // more than 4 % when linked wherever a tile fits LDS, up to five times; by this rule 10 do, at most 19 %, and two that gain more
+  // than 4 % (5 and 10 %) stay apart.
+  bool unit_pays(int c1, const Shape& ms, const Shape& os, int s, int K, int th, int tw) const {
+    if (!p.opts.split) return true;
+    const bool b16 = p.dt == DT_BF16;
+    const int C = ms.c, num_cu = std::max(1, p.hw.num_cu);
+    auto over = [](long long a, long long b) { return (double)((a + b - 1) / b); };
+    const double kg1 = over((long long)c1 * p.esz, 32), kg2 = over((long long)C * p.esz, 32);   // 32-byte k-groups of the GEMMs
+    const long long mp = (long long)ms.n * ms.h * ms.w, px = (long long)os.n * os.h * os.w;
+
+    const int npx = th * tw, npos = std::min((th - 1) * s + 3, ms.h) * std::min((tw - 1) * s + 3, ms.w);
+    const double rounds = over((long long)((os.h + th - 1) / th) * ((os.w + tw - 1) / tw) * os.n, num_cu);
+    // k-groups of the busiest wavefront; MFMA k-groups of a SIMD; weights, staged input and stencil of a tile
+    const double serial = over((long long)over(npos, 64) * (long long)over(C, 32), 8) * kg1 + over((long long)over(npx, 64) * (long long)over(K, 32), 8) * kg2;
+    const double mfma = over((long long)over(npos, 32) * (long long)over(C, 32), 4) * kg1 + over((long long)over(npx, 32) * (long long)over(K, 32), 4) * kg2;
+    const double w_mb = ((double)c1 * C * over(npos, 64) + (double)C * K * over(npx, 64)) * p.esz * 1e-6;
+    const double in_rd = (double)npos * (c1 / p.ce) / 2048, st_rd = (double)npx * (C / p.ce) / 512;
+    const double io = ((double)mp * c1 + (double)px * K) * p.esz * 1e-6, mid = (double)C * p.esz * 1e-6;
+    const double linked = b16 ? rounds * (5.5 + 0.069 * serial + 0.81 * st_rd + 3.5 * in_rd + 3.9 * w_mb) + 0.37 * io
+                              : rounds * (5.0 + 0.062 * serial + 0.118 * mfma + 5.7 * in_rd) + 0.35 * io;
+
+    // apart: 64 x 64 tiles over 128-byte steps, two workgroups to a unit (fp32: the MFMA work of the two follows one another)
+    const double st1 = over((long long)c1 * p.esz, kRowBytes), st2 = over((long long)C * p.esz, kRowBytes);
+    auto waves = [&](double tiles) { return b16 ? std::max(1.0, tiles / (2.0 * num_cu)) : std::ceil(tiles / num_cu); };
+    const double w2 = waves(over(px, 64) * over(K, 64));
+    double apart;
+    if (C / p.ce <= 32) {                                          // convolution, then depthwise -> pointwise
+      const double w1 = waves(over(mp, 64) * over(C, 64)), mb = io + 2.0 * mp * mid;
+      apart = b16 ? 4.5 + 1.03 * st1 * w1 + (1.97 * st2 + 1.7) * w2 + 0.62 * mb : 7.0 + 2.06 * st1 * w1 + 1.8 * st2 * w2 + 0.23 * mb;
+    } else {                                                       // pointwise -> depthwise, then convolution
+      ConvArgs t{};
+      t.N = ms.n; t.H = ms.h; t.W = ms.w; t.OH = os.h; t.OW = os.w; t.K = C; t.dw_stride = s;
+      double longest = 0, all = 0;
+      if (!choose_pwdw_tile(t, &longest, &all)) return true;
+      const double w1 = std::max(longest, all / ((b16 ? 2.0 : 1.0) * num_cu)), mb = io + 2.0 * px * mid;
+      apart = b16 ? (0.95 * st1 + 1.63) * w1 + (0.22 * st2 + 2.1) * w2 + 0.58 * mb : 1.9 + (1.12 * st1 + 0.52) * w1 + (0.30 * st2 + 3.3) * w2 + 0.47 * mb;
+    }
+    return linked <= apart + (b16 ? 0.0 : 2.0);
+  }
+
   // Hands the pointwise and the depthwise chain to the pointwise chain behind them (planned as the step of all three).
   xenos_status plan_unit(int i, const ChainWalk& w1, int dn, int pw2, int th, int tw) {
     const Shape is = tshape[nodes[i].in[0]], ms = tshape[i + 1], os = tshape[dn + 1];
@@ -1224,7 +1270,8 @@ struct Planner {
   // Tile of depthwise output pixels for a pointwise -> depthwise chain: the GEMM runs over the block positions inside
   // the map in chunks of 64, so the cost of a tile is its chunk count (+ a fixed part); the longest workgroup queue
   // decides.  Two workgroups share a compute unit.
-  bool choose_pwdw_tile(ConvArgs& c) const {
+  // (longest_chunks, all_chunks: what the chosen tiling costs in chunks, the longest tile and all tiles of the launch)
+  bool choose_pwdw_tile(ConvArgs& c, double* longest_chunks = nullptr, double* all_chunks = nullptr) const {
     const int s = c.dw_stride, num_cu = std::max(1, p.hw.num_cu);
     const size_t lds_cap = std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
     double best = 1e300;
@@ -1248,7 +1295,11 @@ struct Planner {
         // tilings that fit one round it prefers the one with the least recomputation)
         const double all = total * c.N * tiles_n;
         const double t = p.opts.split ? std::max(all / (2.0 * num_cu), longest) + all / (8.0 * num_cu) : total;
-        if (t < best - 1e-9) { best = t; c.th = th; c.tw = tw; c.tiles_y = ty; c.tiles_x = tx; }
+        if (t < best - 1e-9) {
+          best = t; c.th = th; c.tw = tw; c.tiles_y = ty; c.tiles_x = tx;
+          if (longest_chunks) *longest_chunks = longest;
+          if (all_chunks) *all_chunks = all;
+        }
       }
     return best < 1e300;
   }
@@ -1618,7 +1669,8 @@ struct Planner {
             int th, tw;
             const int pw2 = unit_consumer(i, dn);
             if (pw2 >= 0 && iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
-                iv0.sP * is.h * is.w * p.esz < (1ll << 31) && choose_unit_tile(std::max(is.c, iv0.cphys), tshape[dn + 1], tshape[i + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, &th, &tw))
+                iv0.sP * is.h * is.w * p.esz < (1ll << 31) && choose_unit_tile(std::max(is.c, iv0.cphys), tshape[dn + 1], tshape[i + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, &th, &tw) &&
+                unit_pays(std::max(is.c, iv0.cphys), tshape[i + 1], tshape[dn + 1], desc(nodes[dn]).stride_h, desc(nodes[pw2]).out_c, th, tw))
               return plan_unit(i, walk, dn, pw2, th, tw);
           }
           if (dn >= 0 && pwdw_wanted(i, dn)) {

@@ -368,6 +368,26 @@ def test_pattern_pointwise_to_depthwise_on_chip():
     assert all(c.get("loader") != "pwdw" for c in l2["chains"])
 
 
+@pytest.mark.parametrize("compute,n,hw,c,mid,k,linked", [
+    # linked: the widths of the ShuffleNet graph, narrow units at any size, a narrow middle between wide ends
+    (1, 32, 28, 88, 88, 88, 1), (1, 32, 14, 176, 176, 176, 1), (1, 32, 7, 352, 352, 352, 1), (0, 32, 14, 88, 88, 88, 1),
+    (0, 1, 32, 24, 24, 24, 1), (1, 1, 56, 24, 144, 24, 1), (1, 8, 28, 1024, 128, 1024, 1), (1, 8, 28, 512, 512, 512, 1),
+    # apart: wide units, whose tiles of a few pixels read all weights each (measured 1.2 to 5 times the time of the two chains)
+    (0, 1, 38, 728, 728, 728, 0), (0, 1, 32, 1024, 1024, 1024, 0), (0, 8, 28, 512, 512, 512, 0), (0, 32, 7, 256, 256, 256, 0),
+    (0, 8, 14, 96, 576, 96, 0), (1, 8, 14, 512, 512, 512, 0), (1, 1, 32, 728, 728, 728, 0), (1, 8, 28, 1024, 1024, 1024, 0)])
+def test_unit_is_one_chain_only_where_that_is_faster(compute, n, hw, c, mid, k, linked):
+    b = wg._Builder("unit", (n, 8, hw, hw), 1, False, False)
+    t = b.cbr(0, c, 1, name="pre")
+    t = b.cbr(t, mid, 1, name="pw")
+    t = b.cbr(t, mid, 3, 1, 1, groups=mid, name="dw", relu=False)
+    t = b.cbr(t, k, 1, name="pw2")
+    g = b.finish(b.cbr(t, 8, 3, 1, 1, name="post"))
+    info = plan_json(g, link=3, compute=compute)["plan"]
+    assert sum(ch.get("loader") == "unit" for ch in info["chains"]) == linked, [(ch["kind"], ch.get("loader")) for ch in info["chains"]]
+    ran = [o for ch in info["chains"] if ch["kind"] != "splitk_finish" for o in ch["ops"]]
+    assert sorted(ran) == list(range(len(g.ops)))
+
+
 def test_pattern_depthwise_to_pointwise_on_chip():
     # a depthwise convolution whose pointwise consumer ends the cascade keeps the older link: its result is the
     # operand panel of the pointwise GEMM (ShuffleNet units of the first two stages; the third, 352 channels, is too
