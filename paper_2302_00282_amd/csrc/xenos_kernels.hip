@@ -163,8 +163,10 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
       // latency (0.46 us, against 0.06 us of MFMA work) with two sets, at batch 1 and at batch 32 alike.  The vector
       // loader is branch-free (out-of-range taps load a dummy address and are zeroed when published), so the number of
       // loads in flight is known statically and only the oldest set is waited for.  (The 128 x 128 tile keeps two sets:
-      // its accumulators leave no room for more.)
-      constexpr int D = (BM * BN >= 128 * 128) ? 2 : 4;
+      // its accumulators leave no room for more.  So does the form behind a linked depthwise producer, whose pixel operand is
+      // computed and not in flight: with four sets its form with a global average spilled 29 registers in bf16 and 36 in fp32;
+      // with two it spills none, 64 -> 256 channels, 14 x 14, batch 128: 35.3 -> 30.0 us in bf16, 51.3 -> 40.6 in fp32.)
+      constexpr int D = (BM * BN >= 128 * 128 || DWPRO) ? 2 : 4;
       u32x4_t ra[D][A_IT], rb[D][B_IT];
       unsigned okm_[D];
 
