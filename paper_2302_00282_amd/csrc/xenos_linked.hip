@@ -375,8 +375,12 @@ __host__ __device__ constexpr int fire_lds(int positions, int S, int esz, int po
 // first 1x1 tile's are requested before phase 1 and the first 3x3 tile's behind it, so their latency passes under the GEMMs,
 // phase 2 has no barrier (unpooled) and reads only pixel fragments from LDS.  Staged through LDS, a 3x3 tile over 64 channels
 // cost a copy of 3.2 us before its first MFMA and twice the fragment reads (SqueezeNet bf16 batch 1 121 -> 94 us, batch 32
-// 242 -> 203 us).  The fragments must not be undefined on any path: their registers are then kept over the whole kernel.  0 (fp32, whose fragments do not fit the registers):
-// the weights of a tile are copied to LDS.
+// 242 -> 203 us).  The fragments must not be undefined on any path: their registers are then kept over the whole kernel.  With 64
+// squeeze channels a 3x3 tile is 144 registers of the 256: the last four of its nine taps are requested behind the 1x1 tiles, whose
+// registers they take (the first five cover their latency), and nothing of the lane's addresses is kept from tile to tile.
+// Requested all at once, 23 to 36 registers were spilled (modules of 64 squeeze channels 4 to 28 % slower, ones of a pair that
+// ends in a 1x1 convolution slower than through LDS).  KGS = 0 (fp32, whose fragments do not fit the registers): the weights of a
+// tile are copied to LDS.
 template <typename T, bool POOL, int TAPS1, int KGS>
 __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
@@ -385,9 +389,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   constexpr int STP = fire_stg_pitch(ESZ), CBP = fire_cb_pitch(ESZ);
   constexpr int G = 32 * ESZ / 16;                                 // 16-byte channel groups of a wavefront's 32 channels
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wave_m = wave >> 1, wave_n = wave & 1;
-  const int l31 = lane & 31, lhalf = lane >> 5;
+  const int wave = (int)threadIdx.x >> 6, wave_m = wave >> 1, wave_n = wave & 1;
 
   const int S = a.K;                                               // squeeze channels
   const int SQP = fire_sq_pitch(S, ESZ);
@@ -408,6 +410,11 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   const SmallDiv by_cw(CW), by_ppw(POOL ? a.ppw : 1);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    // (64 squeeze channels: what follows from the lane's number is worked out per tile and not kept over all tiles, for whose
+    // registers the expand weights have no room)
+    int tid = (int)threadIdx.x;
+    if constexpr (KGS == 4) asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, l31 = lane & 31, lhalf = lane >> 5;
     const int gz = uniform_div(t, a.tiles_m), tm = t - gz * a.tiles_m;   // channel share, spatial tile
     const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
     // first conv-output pixel of the tile
@@ -424,18 +431,22 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     }
     // KGS > 0: this wavefront's weight fragments of the first tile of each part
     u32x4_t w0[KGS > 0 ? KGS : 1];
-    auto load_w = [&](int which, int j, auto& w) __attribute__((always_inline)) {
+    auto load_w = [&](int which, int j, auto& w, auto F0, auto F1) __attribute__((always_inline)) {   // fragments F0 .. F1
       constexpr int NF = sizeof(w) / sizeof(u32x4_t);
       if (a.fire_E[which] > 0) {
         const u32x4_t* src = (const u32x4_t*)a.fire_w[which] + (j * 64 < a.fire_E[which] ? j * 2 + wave_n : 0) * NF * 64 + lane;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) w[f] = src[f * 64];
+        for (int f = F0(); f < F1(); ++f) w[f] = src[f * 64];
       } else {                                                     // (not left undefined: the registers would be kept over the whole kernel)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) w[f] = u32x4_t{0u, 0u, 0u, 0u};
+        for (int f = F0(); f < F1(); ++f) w[f] = u32x4_t{0u, 0u, 0u, 0u};
       }
     };
-    if constexpr (KGS > 0) load_w(0, gz, w0);
+    constexpr std::integral_constant<int, 0> f_begin;
+    constexpr std::integral_constant<int, KGS> f_end1;
+    constexpr std::integral_constant<int, 9 * KGS> f_end9;
+    constexpr std::integral_constant<int, (KGS == 4 ? 5 : 9) * KGS> f_ahead9;   // of a 3x3 tile: requested before the 1x1 tiles
+    if constexpr (KGS > 0) load_w(0, gz, w0, f_begin, f_end1);
 
     // ---- phase 1: the squeeze chain of the block, into LDS -------------------------------------------------
     // (scale and shift of this lane's channels are the same for every chunk: requested once)
@@ -596,9 +607,9 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       // the tiles gz, gz + tiles_n, ... of one part; w holds the fragments of the first
       auto tiles = [&](int which, auto& w) __attribute__((always_inline)) {
         constexpr int TAPS = sizeof(w) / sizeof(u32x4_t) / KGS;
+        if (gz * 64 >= a.fire_E[which]) return;
 #pragma unroll 1
-        for (int j = gz; j * 64 < a.fire_E[which]; j += a.tiles_n) {
-          if (j != gz) load_w(which, j, w);
+        for (int j = gz;;) {
 #pragma unroll 1
           for (int mc = 0; mc * 64 < npix; ++mc) {
             f32x4_t esc[4], esh[4];
@@ -631,11 +642,15 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
             tile_epilogue(which, j, mc, acc, esc, esh);
           }
           if constexpr (POOL) tile_pool(which, j);
+          j += a.tiles_n;
+          if (j * 64 >= a.fire_E[which]) break;
+          load_w(which, j, w, f_begin, std::integral_constant<int, TAPS * KGS>());   // (here and not at the top, which would keep w over the pooling)
         }
       };
       u32x4_t w1[9 * KGS];
-      load_w(1, gz, w1);
+      load_w(1, gz, w1, f_begin, f_ahead9);
       tiles(0, w0);
+      load_w(1, gz, w1, f_ahead9, f_end9);
       tiles(1, w1);
       __syncthreads();                                             // the squeeze block and the stages are rewritten
     } else {
