@@ -45,7 +45,7 @@ __device__ __forceinline__ gptr_t here(const void* p) {
 __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(const __attribute__((address_space(1))) u32x4_t*)(base + off); }
 
 // ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
-// replace -infinity)
+// replace -infinity).  For fmx_raw: of fmaxf the compiler makes a maximum and a selection per value.
 __device__ __forceinline__ float unit_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
 
 // Transposed GEMM of `nrows` LDS rows (pitch bytes apart, nkg k-groups of 32 bytes each) with ncb blocks of 32 channels, a
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
           if (c >= C) continue;
           float y[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
+          for (int e = 0; e < 4; ++e) y[e] = fmx_raw(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
           if constexpr (sizeof(T) == 2) {
             uint2 o;
             o.x = f2bf2(y[0], y[1]);
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
           const int c = g * 8 + lhalf * 4;
           float y[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
+          for (int e = 0; e < 4; ++e) y[e] = fmx_raw(acc[4 * g + e] * sc[g][e] + sh[g][e], lo);
           if constexpr (sizeof(T) == 2) {
             uint2 o;
             o.x = f2bf2(y[0], y[1]);
