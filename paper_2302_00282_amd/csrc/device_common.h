@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 #include <type_traits>
 #include "index_div.h"
 #include "kernels.h"
@@ -128,6 +129,17 @@ struct AnyDiv {
 // n / d of wavefront-uniform values of any size
 __device__ __forceinline__ int uniform_div(int n, int d) {
   return __builtin_amdgcn_readfirstlane(n < kSmallDiv ? SmallDiv(d)(n) : n / d);
+}
+
+// Dynamic LDS of a kernel whose launches differ in their need: its limit is raised once, to all of a unit's memory.  (Raised to what
+// the launch at hand needs, two threads' first launches could leave the smaller limit behind.)
+constexpr int kLdsPerUnit = 160 * 1024;
+template <typename F>
+inline hipError_t raise_lds_limit(F* kernel, std::atomic<bool>& raised) {
+  if (raised.load(std::memory_order_acquire)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerUnit);
+  if (e == hipSuccess) raised.store(true, std::memory_order_release);
+  return e;
 }
 
 constexpr int NT = 256;          // threads per workgroup (4 wavefronts of 64)

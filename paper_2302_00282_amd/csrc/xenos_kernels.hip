@@ -2422,12 +2422,9 @@ static int launch_dwpw_t(const ConvArgs& a, hipStream_t st) {
       a.tiles_m != (a.M_total + 63) / 64 || a.tiles_n != (a.K + 63) / 64 || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
       a.Kred_pad < (a.C + BKE - 1) / BKE * BKE || !a.dw_w || !a.dw_scale || !a.dw_shift || !a.zeros || ((uintptr_t)a.zeros & 15))
     return (int)hipErrorInvalidValue;
-  static int raised = 0;
-  if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)dwpw_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return (int)e;
-    raised = lds;
-  }
+  static std::atomic<bool> raised{false};
+  const hipError_t e = raise_lds_limit(dwpw_kernel<T>, raised);
+  if (e != hipSuccess) return (int)e;
   hipLaunchKernelGGL((dwpw_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
 }

@@ -320,12 +320,9 @@ static int launch_pwdw_t(const ConvArgs& a, hipStream_t st) {
   const int positions = ((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3);
   const int lds = pwdw_lds(positions, ESZ);
   if (positions > kPwDwMaxPositions || lds > 160 * 1024) return (int)hipErrorInvalidValue;
-  static int raised = 0;
-  if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)pwdw_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return (int)e;
-    raised = lds;
-  }
+  static std::atomic<bool> raised{false};
+  const hipError_t e = raise_lds_limit(pwdw_kernel<T>, raised);
+  if (e != hipSuccess) return (int)e;
   hipLaunchKernelGGL((pwdw_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
 }
@@ -714,12 +711,9 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
 
 template <typename T, bool POOL, int TAPS1, int KGS>
 static int launch_fire_kgs(const ConvArgs& a, int lds, hipStream_t st) {
-  static int raised = 0;
-  if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)fire_kernel<T, POOL, TAPS1, KGS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return (int)e;
-    raised = lds;
-  }
+  static std::atomic<bool> raised{false};
+  const hipError_t e = raise_lds_limit(fire_kernel<T, POOL, TAPS1, KGS>, raised);
+  if (e != hipSuccess) return (int)e;
   hipLaunchKernelGGL((fire_kernel<T, POOL, TAPS1, KGS>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
 }

@@ -334,12 +334,9 @@ static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
     return (int)hipErrorInvalidValue;
   const int lds = (int)unit_lds_bytes(a.th, a.tw, s, a.unit_C, a.C, ESZ);
   if (lds > 160 * 1024) return (int)hipErrorInvalidValue;
-  static int raised = 0;
-  if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)unit_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return (int)e;
-    raised = lds;
-  }
+  static std::atomic<bool> raised{false};
+  const hipError_t e = raise_lds_limit(unit_kernel<T>, raised);
+  if (e != hipSuccess) return (int)e;
   hipLaunchKernelGGL((unit_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(UN_NT), lds, st, a);
   return (int)hipGetLastError();
 }

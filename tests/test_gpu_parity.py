@@ -590,6 +590,44 @@ def test_pointwise_depthwise_pointwise_takes_an_output_at_any_element(off, compu
         s.close()
 
 
+def test_linked_kernels_launched_by_several_threads():
+    # plans whose units and modules need different amounts of private memory, first launched by several threads at a time, each on
+    # its own stream: every pass gives the bits of a pass alone
+    import threading
+    X = _xenos()
+    import torch
+    graphs = []
+    for c in (16, 48, 88, 176):
+        b = wg.builder("thr", (1, 16, 33, 32), 71 + c, nonzero_bias=True)
+        t = b.cbr(0, c, 1, name="pre")
+        t = b.cbr(t, c, 1, name="pw")
+        t = b.cbr(t, c, 3, 1, 1, groups=c, name="dw", relu=False)
+        t = b.cbr(t, 64, 1, name="pw2")
+        q = b.cbr(t, 16 + 16 * (c > 48), 1, name="sq")
+        graphs.append(b.finish(b.concat([b.cbr(q, c, 1, name="e1"), b.cbr(q, c, 3, 1, 1, name="e3")])))
+    sessions = [X.Session(g, link=3, compute=1) for g in graphs]
+    for s in sessions:
+        assert {"unit", "fire"} <= {ch.get("loader") for ch in s.info["chains"]}
+    got, start = [None] * len(sessions), threading.Barrier(len(sessions))
+
+    def work(i):
+        s = sessions[i]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            s.set_input(graphs[i].x)
+            start.wait()
+            for _ in range(3):
+                s.run()
+            torch.cuda.current_stream().synchronize()
+            got[i] = s._y_numpy()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(sessions))]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    for s, g, y in zip(sessions, graphs, got):
+        assert y is not None and np.array_equal(y, s.forward(g.x))
+        s.close()
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("h,w,c,s,e1,e3,n,pool,tail", [(13, 13, 32, 16, 64, 64, 2, 0, "conv"), (27, 21, 64, 32, 128, 72, 1, 3, "conv"),
                                                        (9, 30, 24, 48, 40, 200, 3, 0, "conv"), (14, 14, 128, 64, 256, 256, 1, 2, "conv"),
