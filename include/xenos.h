@@ -105,7 +105,8 @@ typedef struct {
  *        1 = fused CBR only; pooling / add / concat stay separate passes (the "HO baseline")
  *        2 = operator linking on (Section 4.1): CBR + pool, shortcut add, concat-by-offset
  *        3 = 2 plus the chains whose intermediate tensor stays on chip (Table 1, ConvX -> ConvY): depthwise -> pointwise
- *            and pointwise -> depthwise (Section 2.2 example), from 1024 output pixels on pointwise -> depthwise -> pointwise,
+ *            and pointwise -> depthwise (Section 2.2 example), from 1024 output pixels on pointwise -> depthwise -> pointwise where
+ *            the planner expects one chain to be faster than two,
  *            a 1x1 squeeze convolution -> its 1x1 and 3x3 expand
  *            convolutions -> concat (-> max-pool), and, on the bf16 path, a first-layer 3x3 -> 3x3 convolution pair
  * split: 0 = every chain runs on ONE compute unit (no operator split; for tests)
