@@ -1362,7 +1362,9 @@ struct Planner {
   // of its clipped block 1.0 + 0.35 per chunk of 64 positions and reduction step, and for every expand tile of its share the
   // weights (bf16: 0.3, requested ahead into registers; fp32: a copy to LDS, 0.7 + 0.15 per 4 KB), the GEMM (0.5 + 0.016 or
   // 0.11 per tap and k-group, per chunk of 64 pixels) and 0.4 or 0.9 for epilogue and stores (+ 1.5 with a linked pooling): at batch 1 these fixed latencies, not the
-  // MFMA work, are the time of a module.  The longest workgroup decides, or the sum of all over the units' slots.
+  // MFMA work, are the time of a module.  The longest workgroup decides, or the queue of a unit, counted
+  // in whole workgroups (two side by side where LDS allows): a few more workgroups than fit the units' slots cost a round of their own
+  // (4 x 128 x 150 x 150 -> 32 -> 40 pooled, 608 workgroups 100 us, 440 of larger tiles 78; SqueezeNet bf16 batch 32 185.3 -> 172.8 us).
   bool choose_fire_tile(ConvArgs& c) const {
     const int num_cu = std::max(1, p.hw.num_cu);
     const size_t lds_cap = std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
@@ -1407,7 +1409,8 @@ struct Planner {
           const double wgs = (double)shares * ty * tx * c.N;
           const double all = ((double)shares * sq_total + (double)ty * tx * ex_total) * c.N + 1.4 * wgs;
           const double longest = 1.4 + sq_longest + ex_longest;
-          const double t = p.opts.split ? std::max(all / ((double)occ * num_cu), longest) + all / (8.0 * num_cu) : all;
+          const double rounds = std::ceil(wgs / num_cu) / occ;
+          const double t = p.opts.split ? std::max(std::max(rounds, 1.0) * all / wgs, longest) + all / (8.0 * num_cu) : all;
           if (t < best - 1e-9) {
             best = t;
             if (pool) { c.pph = th; c.ppw = tw; c.th = CH; c.tw = CW; } else { c.th = th; c.tw = tw; }

@@ -388,6 +388,21 @@ def test_unit_is_one_chain_only_where_that_is_faster(compute, n, hw, c, mid, k, 
     assert sorted(ran) == list(range(len(g.ops)))
 
 
+@pytest.mark.parametrize("n,c,hw,mid,k,r1,pool", [(32, 64, 27, 48, 128, 3, 1), (12, 192, 61, 32, 96, 1, 1), (8, 128, 110, 48, 128, 3, 0),
+                                                  (4, 128, 150, 32, 40, 3, 1), (32, 256, 55, 48, 192, 3, 0)])
+def test_fire_tiles_leave_no_nearly_empty_round(n, c, hw, mid, k, r1, pool):
+    # two workgroups to a unit, 512 at a time: a tile size that gives a few more than that costs a round for those few
+    b = wg._Builder("pair", (n, 8, hw, hw), 1, False, False)
+    t = b.cbr(0, c, 1, name="pre")
+    t = b.cbr(t, mid, r1, 1, r1 // 2, name="first")
+    t = b.cbr(t, k, 1, name="second")
+    t = b.maxpool(t, 3, 2, 0, ceil=1) if pool else t
+    g = b.finish(b.cbr(t, 8, 1, name="post"))
+    fire, = [ch for ch in plan_json(g, link=3, compute=1)["plan"]["chains"] if ch.get("loader") == "fire"]
+    tiles = fire["tiles_m"] * fire["tiles_n"]
+    assert tiles <= 512 or tiles >= 0.8 * 256 * -(-tiles // 256), tiles
+
+
 def test_pattern_depthwise_to_pointwise_on_chip():
     # a depthwise convolution whose pointwise consumer ends the cascade keeps the older link: its result is the
     # operand panel of the pointwise GEMM (ShuffleNet units of the first two stages; the third, 352 channels, is too
