@@ -63,6 +63,26 @@ template <> struct Tr<bf16_t> {
   }
 };
 
+// 16-byte loads through a buffer descriptor: a 32-bit byte offset from a wavefront-uniform base; an offset beyond the window's `bytes`
+// (kNoLoad, or any with bytes = 0) reads zeros and no memory.  A masked element costs neither a branch nor a selection, and a loop can
+// issue the same loads on every turn: behind a branch around them the compiler has to assume the path with the fewest loads in flight
+// and waits for all of them.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr unsigned kNoLoad = 0xffffffffu;
+__device__ __forceinline__ rsrc_t make_window(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
+}
+// (soff is not part of what is compared with the window: 0, or inside it together with off)
+__device__ __forceinline__ u32x4_t load_window(rsrc_t w, unsigned off, unsigned soff = 0) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(w, (int)off, __builtin_amdgcn_readfirstlane((int)soff), 0));
+}
+// off or nothing.  (Without the barrier the compiler makes a branch of the selection, with a load on either side.)
+__device__ __forceinline__ u32x4_t load_window_if(rsrc_t w, bool ok, unsigned off) {
+  unsigned o = ok ? off : kNoLoad;
+  asm volatile("" : "+v"(o));
+  return load_window(w, o);
+}
+
 // max(a, b).  `fmaxf` must quiet signalling NaNs, which costs an extra `v_max x, x, x` per operand whose origin the compiler
 // cannot see: values moved between lanes by DPP or unpacked from bf16 with bit operations, i.e. every operand of the
 // pooling reductions (two thirds of their instructions).  fmx_raw is the bare instruction for those places; NaN inputs are

@@ -207,6 +207,7 @@ int launch_pool(const PoolArgs& a, int dtype, void* stream);
 int launch_cvt(const CvtArgs& a, int dtype, void* stream);
 int launch_splitk_finish(const SplitKArgs& a, int dtype, void* stream);
 size_t conv_lds_bytes(int cfg, int mode);
+bool conv_window_fits(const ConvArgs& a, int esz);   // the uniform-tap loader addresses the tensors of a tile with 32 bits
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

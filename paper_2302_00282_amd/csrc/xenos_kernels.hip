@@ -34,7 +34,7 @@ template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE, boo
 __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
-  constexpr int CE = tr::CE, BKE = tr::BKE;
+  constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
   constexpr int WAVES_N = BN / WN;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int A_CH = BM * CPR, B_CH = BN * CPR;                      // 16-byte chunks per step
@@ -95,7 +95,9 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
       // ---- decode the rows this thread loads ---------------------------------------------------
       int ih0[A_IT], iw0[A_IT];
       long long rbase[A_IT];
+      unsigned roff[A_IT];                                            // UNI: byte offset of pixel (ih0, iw0), this thread's chunk, from the tile's first image
       const int ch = tid % CPR;
+      const int n_first = MODE == M_FLAT ? uniform_div(tile_m * BM, OHW) : MODE == M_ZIGZAG ? uniform_div(tile_m * (BM / 4), a.PH * a.PW) : img;
 #pragma unroll
       for (int it = 0; it < A_IT; ++it) {
         const int row = (tid + it * NT) / CPR;
@@ -124,28 +126,36 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         iw0[it] = ow * a.stride - a.pad;
         // element offset of input pixel (ih0, iw0); only ever dereferenced together with an in-range tap
         rbase[it] = ok ? (long long)n * a.in_sN + (long long)ih0[it] * a.in_sH + (long long)iw0[it] * a.in_sW : 0;
-        if (UNI) rbase[it] += ch * CE;
+        if constexpr (UNI) roff[it] = ((unsigned)(n - n_first) * (unsigned)a.in_sN + (unsigned)ih0[it] * (unsigned)a.in_sH + (unsigned)iw0[it] * (unsigned)a.in_sW + ch * CE) * ESZ;
         if (DWPRO) rbase[it] = ok ? (long long)n * a.dw_sN : 0;    // image base of the depthwise input; (ih0, iw0) = pointwise pixel
       }
       // reduction position (r, s, c) of this thread's 16-byte chunk
       int kc, kr, ks;
-      long long koff_u = 0;                                        // UNI: element offset of the step's tap and channel chunk
+      unsigned koff_u = 0;                                         // UNI: byte offset of the step's tap and channel chunk
       {
         if constexpr (UNI) {
           const int rs_n = a.R * a.S, cc = rs_n > 1 ? uniform_div(s_begin, rs_n) : s_begin, rs = s_begin - cc * rs_n;
           kr = a.S > 1 ? uniform_div(rs, a.S) : rs; ks = rs - kr * a.S;
           kc = cc * BKE;                                           // (of the workgroup; a lane's channels are kc + ch * CE ..)
-          koff_u = (long long)kr * a.in_sH + (long long)ks * a.in_sW + kc;
+          koff_u = ((unsigned)kr * (unsigned)a.in_sH + (unsigned)ks * (unsigned)a.in_sW + kc) * ESZ;
         } else {
           const int kk = s_begin * BKE + ch * CE;
           const int rs = AnyDiv(a.C)(kk);
           kc = kk - rs * a.C; kr = AnyDiv(a.S)(rs); ks = rs - kr * a.S;
         }
       }
+      // UNI: what the tile reads lies in windows of less than 4 GB (checked by the host)
+      const int m_last = min(tile_m * BM + BM, a.M_total) - 1;
+      const int n_last = MODE == M_FLAT ? uniform_div(m_last, OHW) : MODE == M_ZIGZAG ? uniform_div(m_last >> 2, a.PH * a.PW) : img;
+      const unsigned in_bytes = (unsigned)(((n_last - n_first) * a.in_sN + (a.H - 1) * a.in_sH + (a.W - 1) * a.in_sW + a.C) * ESZ);
+      const unsigned w_bytes = (unsigned)BN * (unsigned)a.Kred_pad * ESZ;
+      const unsigned char* wbase = (const unsigned char*)a.w + (long long)tile_n * BN * a.Kred_pad * ESZ;
+      unsigned woff[B_IT];
       const unsigned char* wrow[B_IT];
 #pragma unroll
       for (int it = 0; it < B_IT; ++it) {
         const int row = (tid + it * NT) / CPR;
+        woff[it] = ((unsigned)(row < BN ? row : 0) * (unsigned)a.Kred_pad + ch * CE) * ESZ;
         wrow[it] = (const unsigned char*)a.w +
                    ((long long)(tile_n * BN + (row < BN ? row : 0)) * a.Kred_pad + ch * CE) * (long long)sizeof(T);
       }
@@ -234,19 +244,22 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           }
           kc += BKE;
         } else if constexpr (UNI) {
-          const bool kok = kc + ch * CE < a.C;                     // (the padding of a 1x1 reduction; steps past the end are not requested)
-          okm = 0;
+          const bool kok = kc + ch * CE < a.C;                     // (the padding of a 1x1 reduction)
+          const rsrc_t wa = make_window((const T*)a.in + (long long)n_first * a.in_sN, step < nsteps ? in_bytes : 0);
 #pragma unroll
           for (int it = 0; it < A_IT; ++it) {
-            const bool ok = kok && (unsigned)(ih0[it] + kr) < (unsigned)a.H && (unsigned)(iw0[it] + ks) < (unsigned)a.W;
-            ra[it] = *(const u32x4_t*)((const T*)a.in + (ok ? rbase[it] + koff_u : 0));
-            okm |= (ok ? 1u : 0u) << it;
+            const bool ok = kok & ((unsigned)(ih0[it] + kr) < (unsigned)a.H) & ((unsigned)(iw0[it] + ks) < (unsigned)a.W);
+            ra[it] = load_window_if(wa, ok, roff[it] + koff_u);
           }
-          ++ks; koff_u += a.in_sW;
+          ++ks; koff_u += (unsigned)a.in_sW * ESZ;
           if (ks == a.S) {
-            ks = 0; ++kr; koff_u += a.in_sH - a.S * a.in_sW;
-            if (kr == a.R) { kr = 0; kc += BKE; koff_u += BKE - a.R * a.in_sH; }
+            ks = 0; ++kr; koff_u += ((unsigned)a.in_sH - a.S * (unsigned)a.in_sW) * ESZ;
+            if (kr == a.R) { kr = 0; kc += BKE; koff_u += (BKE - a.R * (unsigned)a.in_sH) * ESZ; }
           }
+          const rsrc_t wb = make_window(wbase, step < nsteps ? w_bytes : 0);
+#pragma unroll
+          for (int it = 0; it < B_IT; ++it) rb[it] = load_window(wb, woff[it], step < nsteps ? bstep * ROWB : 0);
+          return;
         } else if constexpr (!SCALAR) {
           const bool kok = step < nsteps && kr < a.R && kc < a.C; // false for every step past the end of this share
           const long long koff = (long long)kr * a.in_sH + (long long)ks * a.in_sW + kc;
@@ -293,7 +306,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           const int idx = tid + it * NT;
           const u32x4_t z = {0u, 0u, 0u, 0u};
           if (A_CH % NT == 0 || idx < A_CH)
-            *(u32x4_t*)(sa + (idx / CPR) * LDS_ROW + (idx % CPR) * 16) = ((okm >> it) & 1u) ? ra[it] : z;
+            *(u32x4_t*)(sa + (idx / CPR) * LDS_ROW + (idx % CPR) * 16) = UNI || ((okm >> it) & 1u) ? ra[it] : z;
         }
 #pragma unroll
         for (int it = 0; it < B_IT; ++it) {
@@ -338,24 +351,49 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         }
       };
 
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        okm_[d] = 0;
-        if (d < nsteps) load_global(d, ra[d], rb[d], okm_[d]);     // (uniform; the loader's position advances step by step)
-      }
-      for (int step0 = 0; step0 < nsteps; step0 += D) {
+      auto multiply = [&](int d) __attribute__((always_inline)) {
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);        // keep the requests ahead of the MFMA block
+        compute(d & 1);
+      };
+      // (stage d % 2 was last read by step - 2, which every wavefront finished before the barrier of step - 1)
+      if constexpr (!UNI) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          const int step = step0 + d;
-          if (step < nsteps) {                                     // (uniform)
-            // stage d % 2 was last read by step - 2, which every wavefront finished before the barrier of step - 1
-            store_lds(d & 1, ra[d], rb[d], okm_[d]);
-            if (step + D < nsteps) load_global(step + D, ra[d], rb[d], okm_[d]);
-            __syncthreads();
-            __builtin_amdgcn_sched_barrier(0);    // keep the requests ahead of the MFMA block
-            compute(d & 1);
+          okm_[d] = 0;
+          if (d < nsteps) load_global(d, ra[d], rb[d], okm_[d]);   // (uniform; the loader's position advances step by step)
+        }
+        for (int step0 = 0; step0 < nsteps; step0 += D) {
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            if (step0 + d < nsteps) {                              // (uniform)
+              store_lds(d & 1, ra[d], rb[d], okm_[d]);
+              if (step0 + d + D < nsteps) load_global(step0 + d + D, ra[d], rb[d], okm_[d]);
+              multiply(d);
+            }
           }
         }
+      } else {
+#pragma unroll
+        for (int d = 0; d < D; ++d) load_global(d, ra[d], rb[d], okm_[d]);
+        // No branch around the loads, which would make every D-th step wait for all of them (past the end they read nothing); the last
+        // round requests nothing, since the epilogue's loads queue up behind.  ResNet-18 batch 1 172.5 -> 168.9 us, SqueezeNet fp32 batch 32
+        // 677 -> 667; with requests in the last round too 179.6 and 690.
+        int step0 = 0;
+        for (; step0 + D < nsteps; step0 += D) {
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            store_lds(d & 1, ra[d], rb[d], okm_[d]);
+            load_global(step0 + d + D, ra[d], rb[d], okm_[d]);
+            multiply(d);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+          if (d == 0 || step0 + d < nsteps) {                      // (uniform)
+            store_lds(d & 1, ra[d], rb[d], okm_[d]);
+            multiply(d);
+          }
       }
       __syncthreads();                            // the epilogue's staging aliases the operand stages
 
@@ -2168,10 +2206,19 @@ static int launch_conv_uni(const ConvArgs& a, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
+// Do the images and the weight rows of a tile fit the 4 GB windows of the uniform-tap loader (with room for an offset's rounding)?
+bool conv_window_fits(const ConvArgs& a, int esz) {
+  const long long per = a.mode == M_ZIGZAG ? 4ll * a.PH * a.PW : (long long)a.OH * a.OW, lim = 0xffffff00ll;
+  const long long images = a.mode == M_FLAT || a.mode == M_ZIGZAG ? std::min<long long>(a.N, (128 - 1) / std::max(per, 1ll) + 2) : 1;
+  if (a.in_sN < 0 || a.in_sH < 0 || a.in_sW < 0 || a.in_sN > lim || a.in_sH > lim || a.in_sW > lim) return false;
+  const long double bytes = ((long double)(images - 1) * a.in_sN + (long double)a.H * a.in_sH + (long double)a.W * a.in_sW + a.C) * esz;
+  return bytes < (long double)lim && 128.0L * a.Kred_pad * esz < (long double)lim;
+}
+
 template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE>
 static int launch_conv_inst(const ConvArgs& a, hipStream_t st) {
   if constexpr (!SCALAR)
-    if (a.kchunk || (a.R == 1 && a.S == 1)) return launch_conv_uni<T, BM, BN, WM, WN, SCALAR, MODE, true>(a, st);
+    if ((a.kchunk || (a.R == 1 && a.S == 1)) && conv_window_fits(a, (int)sizeof(T))) return launch_conv_uni<T, BM, BN, WM, WN, SCALAR, MODE, true>(a, st);
   if (a.kchunk) return (int)hipErrorInvalidValue;
   return launch_conv_uni<T, BM, BN, WM, WN, SCALAR, MODE, false>(a, st);
 }

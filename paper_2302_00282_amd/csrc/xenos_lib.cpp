@@ -794,7 +794,8 @@ struct Planner {
     // source [K][C][R][S] -> destination [K][reduction index]; the reduction index is (r*S+s)*C + c, or, when
     // the channels divide into whole steps, ((c/step)*R*S + r*S + s)*step + c%step so that the R*S taps of
     // one channel chunk are consecutive steps and re-read the same input pixels while they are still cached
-    const bool kchunk = C % bke == 0 && R * S > 1 && !st.scalar && !st.fc_stream;
+    // (tensors beyond the 32-bit addresses of the loader for that order keep the plain one)
+    const bool kchunk = C % bke == 0 && R * S > 1 && !st.scalar && !st.fc_stream && conv_window_fits(st.conv, p.esz);
     st.conv.kchunk = kchunk ? 1 : 0;
     // channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
     // folded shuffle of g groups (tensor channel j * m + i is the operator's channel i * g + j), its shuffled position
@@ -1663,7 +1664,8 @@ struct Planner {
           FireMatch fm;
           if (fire_consumers(i, &fm)) {
             const View& iv0 = p.views[tview[nd.in[0]]];
-            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0)
+            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
+                iv0.sP * is.h * is.w * p.esz < (1ll << 31))
               return plan_fire(i, walk, fm);
           }
           const int dn = pwdw_consumer(i);
@@ -1678,7 +1680,8 @@ struct Planner {
           }
           if (dn >= 0 && pwdw_wanted(i, dn)) {
             const View& iv0 = p.views[tview[nd.in[0]]];
-            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0)
+            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
+                iv0.sP * is.h * is.w * p.esz < (1ll << 31))
               return plan_pwdw(i, walk, dn);
           }
         }

@@ -24,8 +24,12 @@ constexpr int PG_STAGES_BYTES = 2 * (PG_BM + PG_BN) * LDS_ROW;
 // batch 32; timestamps inside the kernels showed it exposed once per chunk, 1.4 us per chunk of a 64-channel layer of
 // which 0.3 are work) passes behind the steps before it, across chunk boundaries too.  A ring of PG_DEPTH register sets
 // holds the requests in flight, two LDS stages hold the step being multiplied and the next one, one barrier per step.
-// pixel(chunk, row) gives the element offset of a row's input pixel (-1 = no pixel); epilogue(chunk, acc) receives
+// pixel(chunk, row) gives the element offset of a row's input pixel in the image at `in` (-1 = no pixel); epilogue(chunk, acc) receives
 // the finished accumulators of a chunk (lane = row wave_m * 32 + l31, channels wave_n * 32 + 8 g + 4 lhalf + 0..3).
+// Requests go through buffer windows and are issued on every turn, past the end too (they then read nothing); with a branch around
+// them every fourth step waited for all loads in flight, a memory round trip of about 1 us: MobileNet batch 1 102.0 -> 90.1 us, fp32
+// 182.2 -> 156.7 (a step of a 512-channel 14x14 layer 0.41 -> 0.28 us, MFMA work 0.06).  Requests past the end are not free in the
+// last round, whose loads the caller's next ones queue up behind: 95.2 and 162.1 us with them.
 // Ends without a barrier: the caller's next barrier frees the stages.
 // TAPS = 9: the convolution is 3x3 / stride 1 / pad 1 instead of 1x1, its weights packed with all taps of a chunk of BKE
 // channels in consecutive steps (a.C a multiple of BKE): step s is tap s % 9 of chunk s / 9, the input element of a row
@@ -35,8 +39,8 @@ constexpr int PG_DEPTH = 4;
 struct NoCoord { __device__ __forceinline__ int operator()(int, int) const { return 0; } };
 
 template <typename T, int TAPS = 1, typename PixelFn, typename EpiFn, typename CoordFn = NoCoord>
-__device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, int k_row0, unsigned char* s_op, int nchunks, PixelFn pixel, EpiFn epilogue,
-                                              CoordFn coord = CoordFn()) {
+__device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, const T* in, int k_row0, unsigned char* s_op, int nchunks, PixelFn pixel,
+                                              EpiFn epilogue, CoordFn coord = CoordFn()) {
   static_assert(TAPS == 1 || TAPS == 9, "1x1 or 3x3 / pad 1");
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
@@ -48,64 +52,59 @@ __device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, int k_row0, uns
   const int l31 = lane & 31, lhalf = lane >> 5;
   const int nsteps = a.Kred_pad / BKE, G = nchunks * nsteps;
   const int ch = tid % CPR;
-  const unsigned char* wrow[B_IT];
+  // (an image takes less than 2 GB and 64 rows of weights less than 4: checked by the host.  kFar is beyond any such window, and stays so
+  // with a step's offset added)
+  constexpr unsigned kFar = 1u << 31;
+  const unsigned w_bytes = (unsigned)BN * (unsigned)a.Kred_pad * ESZ, in_bytes = (unsigned)((a.H - 1) * (int)a.in_sH + (a.W - 1) * (int)a.in_sW + a.C) * ESZ;
+  const unsigned char* wbase = (const unsigned char*)a.w + (long long)k_row0 * a.Kred_pad * ESZ;
+  unsigned woff[B_IT];
 #pragma unroll
   for (int it = 0; it < B_IT; ++it) {
     const int idx = tid + it * NT;
-    wrow[it] = (const unsigned char*)a.w + ((long long)(k_row0 + idx / CPR) * a.Kred_pad + (idx % CPR) * CE) * (long long)ESZ;
+    woff[it] = ((unsigned)(idx / CPR) * (unsigned)a.Kred_pad + (idx % CPR) * CE) * ESZ;
   }
   // the chunk and step the next request belongs to, and this thread's input rows of that chunk
   int ld_chunk = -1, ld_step = nsteps - 1;
-  long long abase[A_IT];
+  unsigned aoff[A_IT];
   int ayx[TAPS == 9 ? A_IT : 1];                                   // TAPS = 9: (y << 16) | x of this thread's rows
-  unsigned arow = 0;
   u32x4_t ra[D][A_IT], rb[D][B_IT];
-  unsigned okm[D];                                                 // which of a set's input chunks are real (the others are zero)
   auto request = [&](int q, int d) __attribute__((always_inline)) {
-    if (q >= G) return;                                            // (uniform)
-    if (++ld_step == nsteps) {
+    const bool more = q < G;                                       // (uniform; the same loads are issued past the end, from empty windows)
+    if (more && ++ld_step == nsteps) {
       ld_step = 0;
       ++ld_chunk;
-      arow = 0;
 #pragma unroll
       for (int it = 0; it < A_IT; ++it) {
-        const long long off = pixel(ld_chunk, (tid + it * NT) / CPR);
-        arow |= (off >= 0 ? 1u : 0u) << it;
-        abase[it] = (off >= 0 ? off : 0) + ch * CE;
+        const int off = pixel(ld_chunk, (tid + it * NT) / CPR);
+        aoff[it] = off >= 0 ? (unsigned)(off + ch * CE) * ESZ : kFar;
         if constexpr (TAPS == 9) ayx[it] = coord(ld_chunk, (tid + it * NT) / CPR);
       }
     }
+    const rsrc_t wa = make_window(in, more ? in_bytes : 0), wb = make_window(wbase, more ? w_bytes : 0);
     if constexpr (TAPS == 9) {
       const int cch = ld_step / 9, tap = ld_step - cch * 9, dy = tap / 3 - 1, dx = tap - (tap / 3) * 3 - 1;
-      const long long toff = (long long)dy * a.in_sH + (long long)dx * a.in_sW + (long long)cch * BKE;
-      unsigned ok = 0;
+      const int toff = (dy * (int)a.in_sH + dx * (int)a.in_sW + cch * BKE) * ESZ;
 #pragma unroll
       for (int it = 0; it < A_IT; ++it) {
         const int y = (ayx[it] >> 16) + dy, x = (ayx[it] & 0xffff) + dx;
-        ok |= (((arow >> it) & 1u) && (unsigned)y < (unsigned)a.H && (unsigned)x < (unsigned)a.W ? 1u : 0u) << it;
+        const bool ok = (aoff[it] < kFar) & ((unsigned)y < (unsigned)a.H) & ((unsigned)x < (unsigned)a.W);
+        ra[d][it] = load_window_if(wa, ok, aoff[it] + toff);
       }
-      okm[d] = ok;
-#pragma unroll
-      for (int it = 0; it < A_IT; ++it)
-        ra[d][it] = *(const u32x4_t*)((const T*)a.in + (((ok >> it) & 1u) ? abase[it] + toff : 0));
     } else {
-      const int kc = ld_step * BKE + ch * CE;
-      okm[d] = kc < a.C ? arow : 0u;                               // channels beyond C are the padding of the reduction
+      const bool kok = ld_step * BKE + ch * CE < a.C;              // channels beyond C are the padding of the reduction
 #pragma unroll
-      for (int it = 0; it < A_IT; ++it)
-        ra[d][it] = *(const u32x4_t*)((const T*)a.in + (((okm[d] >> it) & 1u) ? abase[it] + ld_step * BKE : 0));
+      for (int it = 0; it < A_IT; ++it) ra[d][it] = load_window_if(wa, kok, aoff[it] + ld_step * ROWB);
     }
 #pragma unroll
-    for (int it = 0; it < B_IT; ++it) rb[d][it] = *(const u32x4_t*)(wrow[it] + (long long)ld_step * ROWB);
+    for (int it = 0; it < B_IT; ++it) rb[d][it] = load_window(wb, woff[it], more ? ld_step * ROWB : 0);
   };
   auto store = [&](int stage, int d) __attribute__((always_inline)) {
     unsigned char* sa = s_op + stage * (BM + BN) * LDS_ROW;
     unsigned char* sb = sa + BM * LDS_ROW;
-    const u32x4_t z = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int it = 0; it < A_IT; ++it) {
       const int idx = tid + it * NT;
-      *(u32x4_t*)(sa + (idx / CPR) * LDS_ROW + (idx % CPR) * 16) = ((okm[d] >> it) & 1u) ? ra[d][it] : z;
+      *(u32x4_t*)(sa + (idx / CPR) * LDS_ROW + (idx % CPR) * 16) = ra[d][it];
     }
 #pragma unroll
     for (int it = 0; it < B_IT; ++it) {
@@ -134,26 +133,34 @@ __device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, int k_row0, uns
 #pragma unroll
   for (int d = 0; d < D; ++d) request(d, d);
   int c_chunk = 0, c_step = 0;
-  for (int g0 = 0; g0 < G; g0 += D) {
+  auto multiply = [&](int d) __attribute__((always_inline)) {
+    __syncthreads();                                               // the step (and whatever the caller wrote before the phase) is visible
+    compute(d & 1);
+    if (++c_step == nsteps) {
+      epilogue(c_chunk, acc);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+      c_step = 0;
+      ++c_chunk;
+    }
+  };
+  // (no branch around the loads, which would make the next step wait for all of them; the last round requests nothing)
+  int g0 = 0;
+  for (; g0 + D < G; g0 += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      const int g = g0 + d;
-      if (g < G) {                                                 // (uniform)
-        // stage d % 2 was last read by step g - 2, which every wavefront finished before the barrier of step g - 1
-        store(d & 1, d);
-        request(g + D, d);
-        __syncthreads();                                           // step g (and whatever the caller wrote before the phase) is visible
-        compute(d & 1);
-        if (++c_step == nsteps) {
-          epilogue(c_chunk, acc);
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-          c_step = 0;
-          ++c_chunk;
-        }
-      }
+      // stage d % 2 was last read by step g - 2, which every wavefront finished before the barrier of step g - 1
+      store(d & 1, d);
+      request(g0 + d + D, d);
+      multiply(d);
     }
   }
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d == 0 || g0 + d < G) {                                    // (uniform)
+      store(d & 1, d);
+      multiply(d);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -177,7 +184,7 @@ __host__ __device__ constexpr int pwdw_mid_pitch(int esz) { return PD_BN * esz +
 __host__ __device__ constexpr int pwdw_lds(int positions, int esz) { return positions * pwdw_mid_pitch(esz) + 2 * (PD_BM + PD_BN) * LDS_ROW; }
 
 template <typename T>
-__global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
+__global__ __launch_bounds__(NT, 2) void pwdw_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
@@ -238,11 +245,11 @@ __global__ __launch_bounds__(NT) void pwdw_kernel(const ConvArgs a) {
     }
     // ---- pointwise GEMM of the block, 64 positions x 64 channels per chunk over all input channels, and the pointwise
     // chain's epilogue into the LDS block: lane = position wave_m*32 + l31, channels wave_n*32 + 8*g + 4*lhalf + (0..3)
-    pw_gemm_phase<T>(a, tile_n * BN, s_op, (npos + BM - 1) / BM, [&](int mc, int row) -> long long {
+    pw_gemm_phase<T>(a, (const T*)a.in + (long long)n * a.in_sN, tile_n * BN, s_op, (npos + BM - 1) / BM, [&](int mc, int row) -> int {
       const int m = mc * BM + row;
       if (m >= npos) return -1;
       const int py = by_wv(m), px = m - py * wv;
-      return (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW;
+      return (y_lo + py) * (int)a.in_sH + (x_lo + px) * (int)a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * BM + wave_m * 32 + l31;
       if (m < npos) {
@@ -315,7 +322,7 @@ static int launch_pwdw_t(const ConvArgs& a, hipStream_t st) {
       a.OH != (a.H + 2 - 3) / s + 1 || a.OW != (a.W + 2 - 3) / s + 1 || a.th < 1 || a.tw < 1 ||
       a.tiles_y != (a.OH + a.th - 1) / a.th || a.tiles_x != (a.OW + a.tw - 1) / a.tw || a.tiles_m != a.N * a.tiles_y * a.tiles_x ||
       a.tiles_n != (a.K + PD_BN - 1) / PD_BN || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
-      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || a.out_sP < a.K)
+      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || a.in_sH * a.H * ESZ >= (1ll << 31) || 64ll * a.Kred_pad * ESZ >= (1ll << 32) - 256 || a.out_sP < a.K)
     return (int)hipErrorInvalidValue;
   const int positions = ((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3);
   const int lds = pwdw_lds(positions, ESZ);
@@ -407,10 +414,10 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
   const SmallDiv by_cw(CW), by_ppw(POOL ? a.ppw : 1);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    // (64 squeeze channels: what follows from the lane's number is worked out per tile and not kept over all tiles, for whose
+    // (64 squeeze channels, or 48 with a pooling: what follows from the lane's number is worked out per tile and not kept over all tiles, for whose
     // registers the expand weights have no room)
     int tid = (int)threadIdx.x;
-    if constexpr (KGS == 4) asm volatile("" : "+v"(tid));
+    if constexpr (KGS == 4 || (KGS == 3 && POOL)) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, l31 = lane & 31, lhalf = lane >> 5;
     const int gz = uniform_div(t, a.tiles_m), tm = t - gz * a.tiles_m;   // channel share, spatial tile
     const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
@@ -454,11 +461,11 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       qsc[g] = *(const f32x4_t*)(a.scale + (c < S ? c : 0));
       qsh[g] = *(const f32x4_t*)(a.shift + (c < S ? c : 0));
     }
-    pw_gemm_phase<T, TAPS1>(a, 0, s_b, (npos + 63) / 64, [&](int mc, int row) -> long long {
+    pw_gemm_phase<T, TAPS1>(a, (const T*)a.in + (long long)n * a.in_sN, 0, s_b, (npos + 63) / 64, [&](int mc, int row) -> int {
       const int m = mc * 64 + row;
       if (m >= npos) return -1;
       const int py = by_wv(m), px = m - py * wv;
-      return (long long)n * a.in_sN + (long long)(y_lo + py) * a.in_sH + (long long)(x_lo + px) * a.in_sW;
+      return (y_lo + py) * (int)a.in_sH + (x_lo + px) * (int)a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * 64 + wave_m * 32 + l31;
       if (m < npos) {
@@ -747,7 +754,7 @@ static int launch_fire_t(const ConvArgs& a, hipStream_t st) {
       a.K < 1 || a.K > 64 || (a.K * ESZ) % 32 != 0 || a.OH != a.H || a.OW != a.W ||
       (a.fire_E[0] < 1 && a.fire_E[1] < 1) ||
       a.tiles_n < 1 || a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
-      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C)
+      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || a.in_sH * a.H * ESZ >= (1ll << 31) || 64ll * a.Kred_pad * ESZ >= (1ll << 32) - 256)
     return (int)hipErrorInvalidValue;
   for (int e = 0; e < 2; ++e) {   // a part with no channels does not exist (a ConvX -> ConvY pair instead of a module)
     if (a.fire_E[e] == 0) continue;

@@ -465,6 +465,39 @@ def test_pointwise_depthwise_linked_on_chip(stride, h, w, c, k, n, tail, compute
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("c", [16, 56, 64, 120, 192, 256, 264, 520])
+def test_reductions_of_every_length(c, compute):
+    # one to seventeen steps: shorter than, as long as and longer than the ring of operand sets, with and without a ragged last step; as a
+    # plain 1x1, a 3x3 in channel-chunk order (c a multiple of a step), the 1x1 of a pointwise -> depthwise pair (three chunks of
+    # positions) and the squeeze of a Fire module; the input tensor is also read at addresses that are no multiple of 16 bytes
+    X = _xenos()
+    b = wg.builder("steps", (2, c, 13, 11), 71, nonzero_bias=True)
+    x = b.cbr(0, c, 1, name="pre")
+    p = b.cbr(b.cbr(x, 72, 1, name="pw"), 72, 3, 1, 1, groups=72, name="dw")
+    q = b.cbr(x, 32, 1, name="sq")
+    q = b.concat([b.cbr(q, 24, 1, name="e1"), b.cbr(q, 32, 3, 1, 1, name="e3")])
+    r = b.cbr(0, 40, 3, 1, 1, name="conv3")
+    g = b.finish(b.cbr(b.concat([p, q, r, b.cbr(0, 24, 1, name="conv1")]), 16, 1, name="out"))
+    ref = xo.forward(g)
+    for link in (2, 3):
+        for tile in ((0,) if link == 3 else (0, 1, 2, 3, 4)):
+            check(g, ref, compute=compute, link=link, tile=tile)
+    s = X.Session(g, link=3, compute=compute, in_layout=1, in_dtype=compute)
+    try:
+        y = s.forward(g.x).copy()
+        n = s.x.numel()
+        buf = s.torch.full((n + 64,), float("nan"), dtype=s.x.dtype, device=s.device)
+        for off in (1, 6):
+            buf[off:off + n] = s.x.reshape(-1)
+            buf[:off] = float("nan")
+            X.xenos_run(s.plan, buf[off:].data_ptr(), s.y.data_ptr(), s.stream())
+            s.torch.cuda.synchronize()
+            assert np.array_equal(s.y.float().cpu().numpy(), y)
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("stride,h,w", [(1, 1, 1), (1, 7, 9), (2, 8, 5)])
 def test_depthwise_padding_does_not_meet_infinite_weights(stride, h, w, compute):
     # a tap outside the map adds nothing, whatever its weight is: with an infinite weight in a corner of the window the outputs
