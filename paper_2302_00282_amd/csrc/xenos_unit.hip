@@ -14,8 +14,11 @@
 // one workgroup take the recomputation out, and both weight matrices, packed in fragment order, go from the cache straight
 // into the registers of the wavefront that multiplies them, UN_RING k-groups ahead: no barrier inside a GEMM, four per tile.
 // A network of such units (ShuffleNet graph, batch 32, bf16): 509 -> 319 us.  Timestamps of the first version (176 channels,
-// cycles): input block 5.0 k, first GEMM 5.2 k, stencil 2.8 k, second GEMM and stores 6.5 k; requesting all weights and the
-// depthwise weights at the start as well was slower (the registers it takes are spilled: 371 against 352 us).
+// cycles): input block 5.0 k, first GEMM 5.2 k, stencil 2.8 k, second GEMM and stores 6.5 k.  So the weights travel a phase ahead: the
+// first GEMM's ring is requested behind the input block's first loads, the second one's as the first one's is used up (it arrives
+// behind the stencil), and the other half of a shuffled concat ahead of the reduction it waits for: 314.3 -> 308.0 us.  The rest of that
+// latency is all workgroups reading the same 60 to 250 KB of weights.  Kept for 12 k-groups only, and what depends on the thread's index
+// computed per tile: requesting all weights and the depthwise weights at the start was slower (spilled: 371 against 352 us).
 #include "device_common.h"
 
 namespace xenos {
@@ -42,29 +45,51 @@ __device__ __forceinline__ gptr_t here(const void* p) {
   asm volatile("" : "+s"(v));
   return (gptr_t)v;
 }
+// The thread's index, taken as new likewise
+__device__ __forceinline__ int thread_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(const __attribute__((address_space(1))) u32x4_t*)(base + off); }
 
 // ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
 // replace -infinity).  For fmx_raw: of fmaxf the compiler makes a maximum and a selection per value.
 __device__ __forceinline__ float unit_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
 
-// Transposed GEMM of `nrows` LDS rows (pitch bytes apart, nkg k-groups of 32 bytes each) with ncb blocks of 32 channels, a
-// wavefront per 64 rows x 32 channels.  w: fragments [block][kgs][lane] of 16 bytes.  pre(block, row0) runs before a block's
-// reduction, epi(block, row0, acc) receives each finished 32 x 32 part: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3)
-// of the block in acc[4 g ..].
+// The weight fragments of a unit_gemm: w as [block of 32 channels][kgs][lane] of 16 bytes, nkg of the kgs k-groups in use.  Part u is 64
+// rows x 32 channels and works with block u % ncb; a k-group past the end, and every one of a part past the end, reads no memory.
+struct UnitWeights {
+  const void* w;
+  int kgs, nkg, ncb, parts;
+  __device__ __forceinline__ UnitWeights(const void* w_, int kgs_, int nkg_, int ncb_, int nrows) : w(w_), kgs(kgs_), nkg(nkg_), ncb(ncb_), parts(ncb_ * ((nrows + 63) / 64)) {}
+  __device__ __forceinline__ rsrc_t window(int u) const {
+    const int cb = u - uniform_div(u, ncb) * ncb;
+    return make_window((const unsigned char*)w + (long long)cb * kgs * 1024, u < parts ? nkg * 1024u : 0u);
+  }
+};
+// k-groups 0 .. UN_RING - 1 of a part
+__device__ __forceinline__ void unit_request(rsrc_t wp, u32x4_t (&rb)[UN_RING]) {
+  const unsigned off = (thread_here() & 63) * 16u;
+#pragma unroll
+  for (int d = 0; d < UN_RING; ++d) rb[d] = load_window(wp, off + d * 1024u);
+}
+
+// Transposed GEMM of `nrows` LDS rows (pitch bytes apart) with the blocks of `w`, a wavefront per part.  rb holds the requested
+// fragments of the wavefront's first part; as a part's last ones are used up, those of its next part are requested, behind the last
+// part those of `next`.  pre(block, row0) runs before a part's reduction, epi(block, row0, half, acc) receives each finished 32 x 32
+// half of it: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3) of the block in acc[4 g ..].
 template <typename T, typename PreFn, typename EpiFn>
-__device__ __forceinline__ void unit_gemm(const void* w, int kgs, int nkg, const unsigned char* s_rows, int pitch, int nrows, int ncb, PreFn pre, EpiFn epi) {
-  const unsigned lane = threadIdx.x & 63;
+__device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN_RING], rsrc_t next, const unsigned char* s_rows, int pitch, int nrows, PreFn pre, EpiFn epi) {
+  const unsigned lane = thread_here() & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l31 = (int)lane & 31, lhalf = (int)lane >> 5;
-  const int ngr = (nrows + 63) / 64;
+  const int nkg = w.nkg, ncb = w.ncb;
+  if (wave >= w.parts) unit_request(next, rb);
 #pragma unroll 1
-  for (int u = wave; u < ncb * ngr; u += UN_NW) {
+  for (int u = wave; u < w.parts; u += UN_NW) {
     const int rg = uniform_div(u, ncb), cb = u - rg * ncb, row0 = rg * 64;
     const bool two = row0 + 32 < nrows;                            // (uniform)
-    const gptr_t wp = here((const unsigned char*)w + (long long)cb * kgs * 1024);
-    u32x4_t rb[UN_RING];
-#pragma unroll
-    for (int d = 0; d < UN_RING; ++d) rb[d] = ld16(wp + (d < nkg ? d : nkg - 1) * 1024, lane * 16u);
+    const rsrc_t wp = w.window(u), wn = u + UN_NW < w.parts ? w.window(u + UN_NW) : next;
     pre(cb, row0);
     // (rows past the end read the last row; their results are not stored)
     const unsigned char* pa0 = s_rows + (row0 + l31 < nrows ? row0 + l31 : nrows - 1) * pitch + lhalf * 16;
@@ -107,18 +132,17 @@ __device__ __forceinline__ void unit_gemm(const void* w, int kgs, int nkg, const
           for (int d = 0; d < 3; ++d)
             if (k0 + d0 + d < nkg) block(k0, d0 + d, std::integral_constant<int, 1>());
         }
-        if constexpr (decltype(MORE)::value) {
 #pragma unroll
-          for (int d = d0; d < d0 + 4; ++d) rb[d] = ld16(wp + (k0 + UN_RING + d < nkg ? k0 + UN_RING + d : nkg - 1) * 1024, lane * 16u);
-        }
+        for (int d = d0; d < d0 + 4; ++d)
+          rb[d] = decltype(MORE)::value ? load_window(wp, lane * 16u + (unsigned)(k0 + UN_RING + d) * 1024u) : load_window(wn, lane * 16u + d * 1024u);
       }
     };
     int k0 = 0;
 #pragma unroll 1
     for (; k0 + UN_RING < nkg; k0 += UN_RING) round(k0, std::true_type());
     round(k0, std::false_type());
-    epi(cb, row0, acc0);
-    if (two) epi(cb, row0 + 32, acc1);
+    epi(cb, row0, 0, acc0);
+    if (two) epi(cb, row0 + 32, 1, acc1);
   }
 }
 
@@ -129,8 +153,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
   constexpr int CE = tr::CE, ESZ = (int)sizeof(T);
   constexpr int STP = unit_stg_pitch(ESZ), G = 32 * ESZ / 16, STG_IT = 32 * G / 64;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l31 = lane & 31, lhalf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const u32x4_t z = {0u, 0u, 0u, 0u};
 
   const int s = a.dw_stride, C = a.C, C1 = a.unit_C;
@@ -142,10 +165,13 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
   const int tiles_sp = a.tiles_y * a.tiles_x;
   const int cgs = C / CE;                                          // stencil: a thread keeps its channel group, pgs pixels side by side
   const SmallDiv by_cgs(cgs), by_tw(a.tw);
-  const int pgs = by_cgs(UN_NT), pg = by_cgs(tid), cg = tid - pg * cgs;
-  const bool dw_on = pg < pgs;
+  const int pgs = by_cgs(UN_NT);
+  u32x4_t rb[UN_RING];                                             // weight fragments in flight
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    const int tid = thread_here(), lane = tid & 63, l31 = lane & 31, lhalf = lane >> 5;
+    const int pg = by_cgs(tid), cg = tid - pg * cgs;
+    const bool dw_on = pg < pgs;
     const int n = uniform_div(t, tiles_sp), rr = t - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
     const int oy0 = ty * a.th, ox0 = tx * a.tw;
     const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
@@ -153,6 +179,8 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
     const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.dw_W ? ix0 + PWd : a.dw_W;
     const int wv = x_hi - x_lo, npos = (y_hi - y_lo) * wv;          // the part of the block inside the map (never empty)
     const SmallDiv by_wv(wv);
+    const UnitWeights w1(a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, (C + 31) / 32, npos);
+    const UnitWeights w2(a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, (a.K + 31) / 32, npx);
 
     // ---- the input block, all channels; k-groups are filled up with zeros ---------------------------------
     {
@@ -161,8 +189,8 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
       const gptr_t src = here((const T*)a.in + (long long)n * a.in_sN + (long long)y_lo * a.in_sH + (long long)x_lo * a.in_sW);
       const int sH = (int)a.in_sH * ESZ, sW = (int)a.in_sW * ESZ;  // (an image takes less than 2 GB)
       constexpr int U = 4;                                         // requests before the first LDS write
-      for (int i0 = tid; i0 < total; i0 += U * UN_NT) {
-        u32x4_t v[U];
+      u32x4_t v[U];
+      auto request = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int i = i0 + u * UN_NT < total ? i0 + u * UN_NT : total - 1;
@@ -172,11 +200,21 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
           if (!ok) v[u] = z;
         }
         __builtin_amdgcn_sched_barrier(0);
+      };
+      auto store = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int i = i0 + u * UN_NT, r = by_cpr(i), c = i - r * cpr;
           if (i < total) *(u32x4_t*)(s_x + r * PX + c * 16) = v[u];
         }
+      };
+      request(tid);
+      unit_request(w1.window(wave), rb);                           // on their way while the block is written
+      __builtin_amdgcn_sched_barrier(0);
+      store(tid);
+      for (int i0 = tid + U * UN_NT; i0 < total; i0 += U * UN_NT) {
+        request(i0);
+        store(i0);
       }
     }
     if (npos < P)                                                  // the zero padding of the depthwise convolution
@@ -185,7 +223,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
 
     f32x4_t sc[4], sh[4];                                          // scale and shift of the lane's channels
     // ---- first pointwise chain, into the stencil's block ----------------------------------------------------
-    unit_gemm<T>(a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, s_x, PX, npos, (C + 31) / 32,
+    unit_gemm<T>(w1, rb, w2.window(wave), s_x, PX, npos,
       [&](int cb, int) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -193,7 +231,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
           sh[g] = *(const f32x4_t*)(a.fire_shift[0] + cb * 32 + g * 8 + lhalf * 4);
         }
       },
-      [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
+      [&](int cb, int row0, int, const f32x16_t& acc) __attribute__((always_inline)) {
         const int m = row0 + l31;
         if (m >= npos) return;
         const int py = by_wv(m), px = m - py * wv;
@@ -260,28 +298,38 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
     __syncthreads();                                               // the panel is complete, the block is free
 
     // ---- second pointwise chain -------------------------------------------------------------------------------
-    unit_gemm<T>(a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, s_x, PM, npx, (a.K + 31) / 32,
-      [&](int cb, int) __attribute__((always_inline)) {
+    u32x4_t oth[2][STG_IT];                                        // the other half of the concat, requested ahead of the reduction
+    // the output pixel of which the lane stores 16 bytes in round u of a half; false: none
+    auto pixel = [&](int ln, int cb, int row, int u, long long& p) __attribute__((always_inline)) {
+      const int idx = ln + u * 64, r = idx / G, g16 = idx - r * G;
+      const int q = row + r, qy = by_tw(q), qx = q - qy * a.tw, oy = oy0 + qy, ox = ox0 + qx;
+      p = (long long)oy * a.OW + ox;
+      return q < npx && oy < a.OH && ox < a.OW && cb * 32 + g16 * CE < a.K;
+    };
+    auto other = [&](int cb, int row, int h) __attribute__((always_inline)) {
+      const int ln = thread_here() & 63;
+#pragma unroll
+      for (int u = 0; u < STG_IT; ++u) {
+        const int k0 = cb * 32 + (ln + u * 64) % G * CE;
+        long long p;
+        const bool ok = pixel(ln, cb, row, u, p);
+        oth[h][u] = a.ileave && ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
+      }
+    };
+    unit_gemm<T>(w2, rb, make_window(a.w, 0), s_x, PM, npx,
+      [&](int cb, int row0) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           sc[g] = *(const f32x4_t*)(a.scale + cb * 32 + g * 8 + lhalf * 4);
           sh[g] = *(const f32x4_t*)(a.shift + cb * 32 + g * 8 + lhalf * 4);
         }
+        if constexpr (sizeof(T) == 2) other(cb, row0, 0), other(cb, row0 + 32, 1);
       },
-      [&](int cb, int row0, const f32x16_t& acc) __attribute__((always_inline)) {
+      [&](int cb, int row0, int h, const f32x16_t& acc) __attribute__((always_inline)) {
         // finished values change hands inside the wavefront only (LDS serves its requests in order)
         const float lo = unit_floor(a.relu);
-        u32x4_t oth[STG_IT];
-        long long dst[STG_IT];
-#pragma unroll
-        for (int u = 0; u < STG_IT; ++u) {
-          const int idx = lane + u * 64, r = idx / G, g16 = idx - r * G;
-          const int q = row0 + r, qy = by_tw(q), qx = q - qy * a.tw, oy = oy0 + qy, ox = ox0 + qx, k0 = cb * 32 + g16 * CE;
-          const bool ok = q < npx && oy < a.OH && ox < a.OW && k0 < a.K;
-          const long long p = (long long)oy * a.OW + ox;
-          dst[u] = ok ? (long long)n * a.out_sN + p * a.out_sP + (a.ileave ? 2 * k0 : k0) : -1;
-          oth[u] = a.ileave && ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
-        }
+        const int ln = thread_here() & 63, l31 = ln & 31, lhalf = ln >> 5;
+        if constexpr (sizeof(T) != 2) other(cb, row0, h);          // (32 registers of both halves would be spilled)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = g * 8 + lhalf * 4;
@@ -299,11 +347,14 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < STG_IT; ++u) {
-          const int idx = lane + u * 64, r = idx / G, g16 = idx - r * G;
+          const int idx = ln + u * 64, r = idx / G, g16 = idx - r * G;
           const u32x4_t mine = *(const u32x4_t*)(s_stg + r * STP + g16 * 16);
-          if (dst[u] < 0) continue;
-          if (a.ileave) ileave_store<T>((T*)a.out + dst[u], mine, oth[u], a.ileave == 1);
-          else *(u32x4_t*)((T*)a.out + dst[u]) = mine;
+          const int k0 = cb * 32 + g16 * CE;
+          long long p;
+          if (!pixel(ln, cb, row0, u, p)) continue;
+          T* dst = (T*)a.out + (long long)n * a.out_sN + p * a.out_sP + (a.ileave ? 2 * k0 : k0);
+          if (a.ileave) ileave_store<T>(dst, mine, oth[h][u], a.ileave == 1);
+          else *(u32x4_t*)dst = mine;
         }
       });
     __syncthreads();                                               // both regions are rewritten by the next tile
