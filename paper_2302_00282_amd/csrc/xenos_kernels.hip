@@ -1969,23 +1969,90 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
   constexpr int K = KB * 32;
   constexpr int SPITCH = K * 2 + 16;                               // staging row pitch (odd number of 16-byte slots)
   constexpr int CPP = K * 2 / 16, PPI = 64 / CPP;                  // 16-byte chunks per output pixel, pixels per store instruction
-  __shared__ __align__(16) unsigned char s_xin[SL_INMAX * 8];
+  constexpr int NP = (sl_inpos(NSTEP) + SL_NT - 1) / SL_NT;        // positions of the block a thread stages
+  constexpr int BLOCK = NP * SL_NT * 8;
+  __shared__ __align__(16) unsigned char s_xin[2 * BLOCK];         // this tile's block and the next one's
   __shared__ __align__(16) unsigned char s_stage[SL_NW * 32 * SPITCH];
   __shared__ __align__(16) float s_aff[2 * K];
-  __shared__ int2 s_tap[NSTEP][2];                                 // per step and lane half: LDS byte offsets of its two taps (-1 = none)
+  __shared__ int2 s_tap[NSTEP][2];                                 // per step and lane half: LDS byte offsets of its two taps
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, lhalf = lane >> 5;
   const int st = a.stride;
   // convolution pixels of a tile: TH x TW, or, with a linked max-pooling, the CH x CW block that the tile's pph x ppw
   // pooling windows cover (window overlap recomputed per tile; at most 128 pixels = one per lane of the 4 wavefronts)
   const int CH = POOL ? (a.pph - 1) * a.ps + a.pk : SL_TH, CW = POOL ? (a.ppw - 1) * a.ps + a.pk : SL_TW;
-  const int IH = (CH - 1) * st + a.R, IW = (CW - 1) * st + a.S, npos = IH * IW, nin = a.pair_C * npos;
+  const int IH = (CH - 1) * st + a.R, IW = (CW - 1) * st + a.S, npos = IH * IW;
   const int ntaps = a.R * a.S;
 
-  for (int i = tid; i < SL_INMAX * 2; i += SL_NT) ((uint32_t*)s_xin)[i] = 0u;   // channel slots beyond pair_C stay zero
+  // ---- the input block of a tile: consecutive threads along W, all channels of a position by one thread, which writes them with
+  // one instruction; what does not depend on the tile (position in the block, offset from its first one) is worked out once ------
+  int xe[NP], xg[NP];
+  {
+    const SmallDiv by_iw(IW);
+#pragma unroll
+    for (int it = 0; it < NP; ++it) {
+      const int e = tid + it * SL_NT, ir = by_iw(e), ic = e - ir * IW;
+      xe[it] = e < npos ? (ir << 12) | ic : -1;
+      xg[it] = (int)(ir * a.pair_sH + ic);
+    }
+  }
+  const unsigned c01 = a.pair_C > 1 ? 0xffffffffu : 0xffffu, c23 = a.pair_C > 3 ? 0xffffffffu : a.pair_C == 3 ? 0xffffu : 0u;
+  float xr[NP][4];
+  unsigned okm = 0;
+  const int tiles_img = a.tiles_y * a.tiles_x;
+  // first convolution pixel of a tile (may lie outside the map when the pooling is padded)
+  auto tile_origin = [&](int tile, int& n, int& tyi, int& txi, int& cy0, int& cx0) __attribute__((always_inline)) {
+    n = uniform_div(tile, tiles_img);
+    const int tr = tile - n * tiles_img;
+    tyi = uniform_div(tr, a.tiles_x); txi = tr - tyi * a.tiles_x;
+    cy0 = POOL ? tyi * a.pph * a.ps - a.pp : tyi * SL_TH;
+    cx0 = POOL ? txi * a.ppw * a.ps - a.pp : txi * SL_TW;
+  };
+  auto load_block = [&](int tile) __attribute__((always_inline)) {
+    int n, tyi, txi, cy0, cx0;
+    tile_origin(tile, n, tyi, txi, cy0, cx0);
+    const int iy0 = cy0 * st - a.pad, ix0 = cx0 * st - a.pad;
+    // (may point before the tensor: only elements inside the image are read, the others read the tensor's first element)
+    const float* src = (const float*)a.in + ((long long)n * a.pair_sN + (long long)iy0 * a.pair_sH + ix0);
+    okm = 0;
+    const float* p[NP];
+#pragma unroll
+    for (int it = 0; it < NP; ++it) {
+      const int ir = (xe[it] >> 12) & 0xfff, ic = xe[it] & 0xfff;
+      const bool ok = xe[it] >= 0 && (unsigned)(iy0 + ir) < (unsigned)a.H && (unsigned)(ix0 + ic) < (unsigned)a.W;
+      p[it] = ok ? src + xg[it] : (const float*)a.in;
+      okm |= (ok ? 1u : 0u) << it;
+    }
+    // (channels that do not exist read channel 0 and are masked; a fourth one is rare enough for a branch)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int it = 0; it < NP; ++it) xr[it][c] = p[it][c < a.pair_C ? c * a.pair_sC : 0];
+    if (a.pair_C > 3) {                                            // (uniform)
+#pragma unroll
+      for (int it = 0; it < NP; ++it) xr[it][3] = p[it][3 * a.pair_sC];
+    }
+  };
+  auto store_block = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int it = 0; it < NP; ++it) {
+      const bool ok = (okm >> it) & 1u;
+      uint2 o;
+      o.x = ok ? f2bf2(xr[it][0], xr[it][1]) & c01 : 0u;
+      o.y = ok ? f2bf2(xr[it][2], xr[it][3]) & c23 : 0u;
+      *(uint2*)(s_xin + buf * BLOCK + (tid + it * SL_NT) * 8) = o;
+    }
+  };
+#pragma unroll
+  for (int it = 0; it < NP; ++it) xr[it][3] = 0.f;
+  int tile = blockIdx.x;
+  if (tile < a.tiles_m) load_block(tile);
+
   if (tid < 2 * K) s_aff[tid] = tid < K ? a.scale[tid] : a.shift[tid - K];
   if (tid < NSTEP * 2) {
-    const int j = tid >> 1, hh = tid & 1, t0 = 4 * j + 2 * hh, t1 = t0 + 1;
-    s_tap[j][hh] = make_int2(t0 < ntaps ? ((t0 / a.S) * IW + t0 % a.S) * 8 : -1, t1 < ntaps ? ((t1 / a.S) * IW + t1 % a.S) * 8 : -1);
+    // (slots beyond the last tap read position 0 of the window: their weights are zero and the block holds finite values)
+    const SmallDiv by_s(a.S);
+    const int j = tid >> 1, hh = tid & 1, t0 = 4 * j + 2 * hh, t1 = t0 + 1, r0 = by_s(t0), r1 = by_s(t1);
+    s_tap[j][hh] = make_int2(t0 < ntaps ? (r0 * IW + t0 - r0 * a.S) * 8 : 0, t1 < ntaps ? (r1 * IW + t1 - r1 * a.S) * 8 : 0);
   }
   // resident weights: rows = channels 32 * b + l31, [K][NSTEP * 16] with slot = tap * 4 + channel
   u32x4_t w[NSTEP][KB];
@@ -1997,69 +2064,25 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
   // this lane's convolution pixel of the tile and where its window starts in the staged block
   const int q = wave * 32 + l31;
   const bool qok = q < CH * CW;
-  const int ty = qok ? q / CW : 0, tx = qok ? q - ty * CW : 0;
+  const int ty = qok ? SmallDiv(CW)(q) : 0, tx = qok ? q - ty * CW : 0;
   const int xbase = ((ty * st) * IW + tx * st) * 8;
   const float lo = a.relu ? 0.f : -3.4028235e38f;
   unsigned char* stg = s_stage + wave * (32 * SPITCH);
-  const int tiles_img = a.tiles_y * a.tiles_x;
-
-  // ---- the input block of a tile: element e = (channel, block row, block column), consecutive threads along W; what does
-  // not depend on the tile (position in the block, offset from the block's first element) is worked out once ----------
-  constexpr int NI = (sl_inpos(NSTEP) * 4 + SL_NT - 1) / SL_NT;
-  int xe[NI], xg[NI];
-#pragma unroll
-  for (int it = 0; it < NI; ++it) {
-    const int e = tid + it * SL_NT;
-    const int c = e / npos, rem = e - c * npos, ir = rem / IW, ic = rem - ir * IW;
-    xe[it] = e < nin ? (c << 24) | (ir << 12) | ic : -1;
-    xg[it] = (int)(c * a.pair_sC + ir * a.pair_sH + ic);
-  }
-  float xr[NI];
-  // first convolution pixel of a tile (may lie outside the map when the pooling is padded)
-  auto tile_origin = [&](int tile, int& n, int& cy0, int& cx0) __attribute__((always_inline)) {
-    n = tile / tiles_img;
-    const int tr = tile - n * tiles_img, tyi = tr / a.tiles_x, txi = tr - tyi * a.tiles_x;
-    cy0 = POOL ? tyi * a.pph * a.ps - a.pp : tyi * SL_TH;
-    cx0 = POOL ? txi * a.ppw * a.ps - a.pp : txi * SL_TW;
-  };
-  auto load_block = [&](int tile) __attribute__((always_inline)) {
-    int n, cy0, cx0;
-    tile_origin(tile, n, cy0, cx0);
-    const int iy0 = cy0 * st - a.pad, ix0 = cx0 * st - a.pad;
-    // (may point before the tensor: only elements inside the image are read, the others read the tensor's first element)
-    const float* src = (const float*)a.in + ((long long)n * a.pair_sN + (long long)iy0 * a.pair_sH + ix0);
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      const int ir = (xe[it] >> 12) & 0xfff, ic = xe[it] & 0xfff;
-      const bool ok = xe[it] >= 0 && (unsigned)(iy0 + ir) < (unsigned)a.H && (unsigned)(ix0 + ic) < (unsigned)a.W;
-      const float* ptr = ok ? src + xg[it] : (const float*)a.in;
-      const float v = *ptr;
-      xr[it] = ok ? v : 0.f;
-    }
-  };
-  auto store_block = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int it = 0; it < NI; ++it) {
-      if (xe[it] >= 0) {
-        const int c = xe[it] >> 24, ir = (xe[it] >> 12) & 0xfff, ic = xe[it] & 0xfff;
-        *(uint16_t*)(s_xin + (ir * IW + ic) * 8 + c * 2) = f2bf(xr[it]);
-      }
-    }
-  };
 
   // pooling stage: the window and 16-byte channel group this thread finishes in the first round
-  const int pl_wi = tid / CPP, pl_ch = tid - pl_wi * CPP, pl_wy = POOL ? pl_wi / a.ppw : 0, pl_wx = POOL ? pl_wi - pl_wy * a.ppw : 0;
+  const int pl_wi = tid / CPP, pl_ch = tid - pl_wi * CPP, pl_wy = POOL ? SmallDiv(a.ppw)(pl_wi) : 0, pl_wx = POOL ? pl_wi - pl_wy * a.ppw : 0;
 
-  int tile = blockIdx.x;
-  if (tile < a.tiles_m) load_block(tile);
-  while (tile < a.tiles_m) {
-    int n, cy0, cx0;
-    tile_origin(tile, n, cy0, cx0);
-    __syncthreads();                                               // the previous tile's reads of the block and of the staging are done
-    store_block();
-    __syncthreads();
+  if (tile < a.tiles_m) store_block(0);
+  if (tile + (int)gridDim.x < a.tiles_m) load_block(tile + gridDim.x);
+  __syncthreads();                                                 // the block, the taps and the scales are there
+  int tap[NSTEP][2];
+#pragma unroll
+  for (int j = 0; j < NSTEP; ++j) { const int2 t = s_tap[j][lhalf]; tap[j][0] = xbase + t.x; tap[j][1] = xbase + t.y; }
+  for (int buf = 0; tile < a.tiles_m; buf ^= 1) {
+    int n, tyi, txi, cy0, cx0;
+    tile_origin(tile, n, tyi, txi, cy0, cx0);
     const int next = tile + gridDim.x;
-    if (next < a.tiles_m) load_block(next);                        // in flight during this tile's convolution and stores
+    const unsigned char* xin = s_xin + buf * BLOCK;
     // ---- the convolution of this wavefront's 32 pixels ----------------------------------------------------------
     f32x16_t acc[KB];
 #pragma unroll
@@ -2068,10 +2091,8 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
       for (int e = 0; e < 16; ++e) acc[b][e] = 0.f;
 #pragma unroll
     for (int j = 0; j < NSTEP; ++j) {
-      const int2 t = s_tap[j][lhalf];
-      // (slots beyond the last tap read position 0 of the window: their weights are zero and the block holds finite values)
-      const uint2 t0 = *(const uint2*)(s_xin + xbase + (t.x >= 0 ? t.x : 0));
-      const uint2 t1 = *(const uint2*)(s_xin + xbase + (t.y >= 0 ? t.y : 0));
+      const uint2 t0 = *(const uint2*)(xin + tap[j][0]);
+      const uint2 t1 = *(const uint2*)(xin + tap[j][1]);
       const u32x4_t fa = {t0.x, t0.y, t1.x, t1.y};
 #pragma unroll
       for (int b = 0; b < KB; ++b)
@@ -2096,10 +2117,12 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
         if (POOL && !inmap) o = uint2{0xff80ff80u, 0xff80ff80u};
         *(uint2*)(stg + l31 * SPITCH + c0 * 2) = o;
       }
+    // the next tile's block, whose buffer was last read a tile ago; requests of the one after it go ahead of this tile's stores
+    if (next < a.tiles_m) store_block(buf ^ 1);
+    if (next + (int)gridDim.x < a.tiles_m) load_block(next + gridDim.x);
     if constexpr (POOL) {
       // ---- linked max-pooling: one thread = one 16-byte channel group of one pooling window of the tile -------------
       __syncthreads();
-      const int tr = tile - n * tiles_img, tyi = tr / a.tiles_x, txi = tr - tyi * a.tiles_x;
       for (int idx = tid; idx < a.pph * a.ppw * CPP; idx += SL_NT) {
         // (the first round's window and channel group are the same for every tile: worked out once, before the tile loop)
         int wi = pl_wi, ch = pl_ch, wy = pl_wy, wx = pl_wx;
@@ -2143,9 +2166,9 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
         if (oy < a.OH && ox < a.OW)
           *(u32x4_t*)((unsigned char*)a.out + ((long long)n * a.out_sN + (long long)(oy * a.OW + ox) * a.out_sP) * 2 + ch * 16) = o;
       }
-      __builtin_amdgcn_wave_barrier();
     }
     tile = next;
+    __syncthreads();                                               // the next block is complete, this tile's reads of the staging are done
   }
 }
 

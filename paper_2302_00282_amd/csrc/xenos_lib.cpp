@@ -643,7 +643,9 @@ struct Planner {
         c.tiles_y = (c.PH + c.pph - 1) / c.pph; c.tiles_x = (c.PW + c.ppw - 1) / c.ppw;
       }
       c.tiles_m = c.N * c.tiles_y * c.tiles_x; c.tiles_n = 1; c.ntiles = c.tiles_m; c.xcd_m = 8;
-      c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, 4 * num_cu)) : 1;
+      // as many workgroups as are resident (stem_lds_kernel's launch bounds), so that none starts, with its weights and tables, behind another
+      const int resident = c.R * c.S > 12 ? 2 : c.K > 32 ? 3 : 4;
+      c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, resident * num_cu)) : 1;
       st.cfg = kStemLdsCfg;
       st.lds = conv_lds_bytes(kStemLdsCfg, c.mode);
       return XENOS_OK;
