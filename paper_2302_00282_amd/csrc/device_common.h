@@ -94,6 +94,10 @@ __device__ __forceinline__ float fmx_raw(float a, float b) {
   return r;
 }
 
+// ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
+// replace -infinity).  For fmx_raw: of fmaxf the compiler makes a maximum and a selection per value.
+__device__ __forceinline__ float relu_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
+
 // Two-group channel shuffle done by a store: CE finished channels of a pixel (`mine`) and the same channels of the other
 // part of the concat (`oth`) alternate in the output, `first` = mine at the even positions.  Two 16-byte stores.
 template <typename T>

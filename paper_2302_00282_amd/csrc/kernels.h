@@ -48,13 +48,14 @@ static const int kPairCfg = 6;
 // workgroup, reduction shared out over workgroups; always followed by the summing pass)
 static const int kFcCfg = 7;
 static const int kFcChannels = 128;
-// Configuration index of the first-layer kernel that stages its input block in LDS (bf16 path, fp32 NCHW graph input with at most 4
+// Configuration index of the first-layer kernel that stages its input block in LDS (bf16 path, or fp32 with a pooling; fp32 NCHW graph input with at most 4
 // channels, square kernel up to 7x7, stride 1 or 2): tiles of kStemLdsTh x kStemLdsTw output pixels of one image
 static const int kStemLdsCfg = 8;
 static const int kStemLdsPph = 3, kStemLdsPpw = 8;   // pooling windows per tile when a max-pooling is linked
 static const int kStemLdsTh = 8, kStemLdsTw = 16, kStemLdsInMax = 784;   // (7 * 2 + 7) x (15 * 2 + 7) = 777 positions at most
 // (per kernel size class the kernel is instantiated for, by taps: up to 3x3 at stride 2 a block is at most 17 x 33 or 15 x 35
 // positions, up to 5x5 19 x 35)
+static const int kStemLdsF32Rounds = 3;   // fp32 path: positions of the block per thread of 256 (16 bytes each, two blocks and the staging in 64 KB)
 static inline int stem_lds_in_positions(int taps) { return taps <= 12 ? 576 : taps <= 28 ? 672 : kStemLdsInMax; }
 // Configuration index of the kernel that links a pointwise (1x1) convolution chain with the depthwise 3x3 chain that consumes
 // it: a TH x TW block of depthwise output pixels x kPwDwChannels channels per workgroup, the pointwise output of the block

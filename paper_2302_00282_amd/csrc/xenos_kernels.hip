@@ -1940,7 +1940,7 @@ static int launch_stem_t(const ConvArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// First-layer chain with the input block staged on chip (bf16 path; at most 4 input channels read from the caller's
+// First-layer chain with the input block staged on chip (bf16 path, and fp32 with a linked pooling; at most 4 input channels read from the caller's
 // fp32 NCHW tensor, square kernel up to 7x7, stride 1 or 2, K = 32 or 64).  stem_kernel gathers every element of every
 // window from memory (up to 80 single loads per pixel for a 7x7 kernel: bound by address processing, not by bytes);
 // here a workgroup owns a TH x TW block of output pixels of one image, reads the input block those windows cover ONCE
@@ -1959,18 +1959,28 @@ static_assert(SL_TH * SL_TW == 32 * SL_NW && SL_TW == 16, "one wavefront = two t
 constexpr int sl_inpos(int nstep) { return nstep <= 3 ? 576 : nstep <= 7 ? 672 : SL_INMAX; }
 static_assert(sl_inpos(3) == 576 && sl_inpos(7) == 672, "the same limits as stem_lds_in_positions(), which the host checks");
 
+// fp32 (kernels up to 5x5 behind which a max-pooling is linked): positions of 16 bytes, a lane half per tap, an MFMA per channel; it takes
+// out the convolution's result, written and read again by a pooling pass of its own before (101 MB each way on a 3x3 / 2 layer of 64
+// channels at batch 32): SqueezeNet batch 32 fp32 665.6 -> 630.8 us.
+//
 // (the small kernels keep three or six weight fragments per lane, so four or three workgroups share a compute unit instead of
 // two: a tile is a chain of short dependent phases, and what hides their latencies is other tiles in flight.  Measured at
 // batch 32 on the 3x3 / 2 first layers with a linked pooling: 64 channels 33.7 -> 30.3 us with three workgroups (30.8 with four,
 // which spills), 24 channels padded to 32: 28.3 -> 23.5 us with four)
-template <int KB, int NSTEP, bool POOL>
-__global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void stem_lds_kernel(const ConvArgs a) {
+// The block is double-buffered: the next one is written behind this tile's products, so two barriers a tile and no wait for the
+// output stores, which queue up behind its loads; one thread converts all channels of a position and writes them at once (four
+// 2-byte LDS writes before), tap offsets lie in registers; as many workgroups as are resident (7x7 / 2 with four per unit: the last half
+// began behind the first, weights and all, 4 us).  Networks at batch 32: SqueezeNet 169.5 -> 159.9 us, ShuffleNet graph 308.0 -> 301.9,
+// ResNet-18 379.2 -> 362.8.
+template <typename T, int KB, int NSTEP, bool POOL>
+__global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void stem_lds_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
-  constexpr int K = KB * 32;
-  constexpr int SPITCH = K * 2 + 16;                               // staging row pitch (odd number of 16-byte slots)
-  constexpr int CPP = K * 2 / 16, PPI = 64 / CPP;                  // 16-byte chunks per output pixel, pixels per store instruction
-  constexpr int NP = (sl_inpos(NSTEP) + SL_NT - 1) / SL_NT;        // positions of the block a thread stages
-  constexpr int BLOCK = NP * SL_NT * 8;
+  constexpr bool F32 = sizeof(T) == 4;
+  constexpr int K = KB * 32, ESZ = (int)sizeof(T), CE = 16 / ESZ;
+  constexpr int SPITCH = K * ESZ + 16;                             // staging row pitch (odd number of 16-byte slots)
+  constexpr int CPP = K * ESZ / 16, PPI = 64 / CPP;                // 16-byte chunks per output pixel, pixels per store instruction
+  constexpr int NP = F32 ? kStemLdsF32Rounds : (sl_inpos(NSTEP) + SL_NT - 1) / SL_NT;   // positions of the block a thread stages
+  constexpr int PB = 4 * ESZ, BLOCK = NP * SL_NT * PB;             // (more positions than a block has: the last one is zeros)
   __shared__ __align__(16) unsigned char s_xin[2 * BLOCK];         // this tile's block and the next one's
   __shared__ __align__(16) unsigned char s_stage[SL_NW * 32 * SPITCH];
   __shared__ __align__(16) float s_aff[2 * K];
@@ -2036,10 +2046,15 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
 #pragma unroll
     for (int it = 0; it < NP; ++it) {
       const bool ok = (okm >> it) & 1u;
-      uint2 o;
-      o.x = ok ? f2bf2(xr[it][0], xr[it][1]) & c01 : 0u;
-      o.y = ok ? f2bf2(xr[it][2], xr[it][3]) & c23 : 0u;
-      *(uint2*)(s_xin + buf * BLOCK + (tid + it * SL_NT) * 8) = o;
+      unsigned char* dst = s_xin + buf * BLOCK + (tid + it * SL_NT) * PB;
+      if constexpr (F32) {
+        *(f32x4_t*)dst = f32x4_t{ok ? xr[it][0] : 0.f, ok && a.pair_C > 1 ? xr[it][1] : 0.f, ok && a.pair_C > 2 ? xr[it][2] : 0.f, 0.f};
+      } else {
+        uint2 o;
+        o.x = ok ? f2bf2(xr[it][0], xr[it][1]) & c01 : 0u;
+        o.y = ok ? f2bf2(xr[it][2], xr[it][3]) & c23 : 0u;
+        *(uint2*)dst = o;
+      }
     }
   };
 #pragma unroll
@@ -2049,24 +2064,37 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
 
   if (tid < 2 * K) s_aff[tid] = tid < K ? a.scale[tid] : a.shift[tid - K];
   if (tid < NSTEP * 2) {
-    // (slots beyond the last tap read position 0 of the window: their weights are zero and the block holds finite values)
+    // (slots beyond the last tap: the block's last position, which is zeros, as their weights are)
     const SmallDiv by_s(a.S);
-    const int j = tid >> 1, hh = tid & 1, t0 = 4 * j + 2 * hh, t1 = t0 + 1, r0 = by_s(t0), r1 = by_s(t1);
-    s_tap[j][hh] = make_int2(t0 < ntaps ? (r0 * IW + t0 - r0 * a.S) * 8 : 0, t1 < ntaps ? (r1 * IW + t1 - r1 * a.S) * 8 : 0);
+    const int j = tid >> 1, hh = tid & 1, t0 = F32 ? 4 * j + hh : 4 * j + 2 * hh, t1 = F32 ? t0 + 2 : t0 + 1, r0 = by_s(t0), r1 = by_s(t1);
+    s_tap[j][hh] = make_int2(t0 < ntaps ? (r0 * IW + t0 - r0 * a.S) * PB : -1, t1 < ntaps ? (r1 * IW + t1 - r1 * a.S) * PB : -1);
   }
   // resident weights: rows = channels 32 * b + l31, [K][NSTEP * 16] with slot = tap * 4 + channel
-  u32x4_t w[NSTEP][KB];
+  // bf16: a step of the MFMA is four taps, two per lane half; fp32: two taps, one per half, and one MFMA per channel
+  u32x4_t w[F32 ? 1 : NSTEP][KB];
+  float wf[F32 ? 2 * NSTEP : 1][KB][3];
+  if constexpr (F32) {
 #pragma unroll
-  for (int j = 0; j < NSTEP; ++j)
+    for (int j = 0; j < 2 * NSTEP; ++j)
 #pragma unroll
-    for (int b = 0; b < KB; ++b)
-      w[j][b] = *(const u32x4_t*)((const unsigned char*)a.dw_w + ((32 * b + l31) * (NSTEP * 16) + j * 16 + lhalf * 8) * 2);
+      for (int b = 0; b < KB; ++b) {
+        const f32x4_t v = *(const f32x4_t*)((const float*)a.dw_w + (32 * b + l31) * (NSTEP * 16) + (2 * j + lhalf) * 4);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) wf[j][b][c] = v[c];
+      }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NSTEP; ++j)
+#pragma unroll
+      for (int b = 0; b < KB; ++b)
+        w[j][b] = *(const u32x4_t*)((const unsigned char*)a.dw_w + ((32 * b + l31) * (NSTEP * 16) + j * 16 + lhalf * 8) * 2);
+  }
   // this lane's convolution pixel of the tile and where its window starts in the staged block
   const int q = wave * 32 + l31;
   const bool qok = q < CH * CW;
   const int ty = qok ? SmallDiv(CW)(q) : 0, tx = qok ? q - ty * CW : 0;
-  const int xbase = ((ty * st) * IW + tx * st) * 8;
-  const float lo = a.relu ? 0.f : -3.4028235e38f;
+  const int xbase = ((ty * st) * IW + tx * st) * PB;
+  const float lo = relu_floor(a.relu);
   unsigned char* stg = s_stage + wave * (32 * SPITCH);
 
   // pooling stage: the window and 16-byte channel group this thread finishes in the first round
@@ -2077,7 +2105,7 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
   __syncthreads();                                                 // the block, the taps and the scales are there
   int tap[NSTEP][2];
 #pragma unroll
-  for (int j = 0; j < NSTEP; ++j) { const int2 t = s_tap[j][lhalf]; tap[j][0] = xbase + t.x; tap[j][1] = xbase + t.y; }
+  for (int j = 0; j < NSTEP; ++j) { const int2 t = s_tap[j][lhalf]; tap[j][0] = t.x >= 0 ? xbase + t.x : BLOCK - PB; tap[j][1] = t.y >= 0 ? xbase + t.y : BLOCK - PB; }
   for (int buf = 0; tile < a.tiles_m; buf ^= 1) {
     int n, tyi, txi, cy0, cx0;
     tile_origin(tile, n, tyi, txi, cy0, cx0);
@@ -2091,12 +2119,24 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
       for (int e = 0; e < 16; ++e) acc[b][e] = 0.f;
 #pragma unroll
     for (int j = 0; j < NSTEP; ++j) {
+      if constexpr (F32) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (4 * j + 2 * i >= ntaps) continue;                    // (uniform)
+          const f32x4_t v = *(const f32x4_t*)(xin + tap[j][i]);
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[2 * j + i][b][c], v[c], acc[b], 0, 0, 0);
+        }
+        continue;
+      }
       const uint2 t0 = *(const uint2*)(xin + tap[j][0]);
       const uint2 t1 = *(const uint2*)(xin + tap[j][1]);
       const u32x4_t fa = {t0.x, t0.y, t1.x, t1.y};
 #pragma unroll
       for (int b = 0; b < KB; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w[j][b]), __builtin_bit_cast(bf16x8_t, fa), acc[b], 0, 0, 0);
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w[F32 ? 0 : j][b]), __builtin_bit_cast(bf16x8_t, fa), acc[b], 0, 0, 0);
     }
     // ---- epilogue: lane = pixel l31, channels 32*b + 8*g + 4*lhalf + (0..3); transposed through this wavefront's LDS
     // slice so that every store instruction writes whole pixels.  With a linked pooling, pixels outside the map are
@@ -2110,12 +2150,19 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
         const f32x4_t sc = *(const f32x4_t*)&s_aff[c0], sh = *(const f32x4_t*)&s_aff[K + c0];
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = fmx(acc[b][4 * g + e] * sc[e] + sh[e], lo);
-        uint2 o;
-        o.x = f2bf2(y[0], y[1]);
-        o.y = f2bf2(y[2], y[3]);
-        if (POOL && !inmap) o = uint2{0xff80ff80u, 0xff80ff80u};
-        *(uint2*)(stg + l31 * SPITCH + c0 * 2) = o;
+        for (int e = 0; e < 4; ++e) y[e] = fmx_raw(acc[b][4 * g + e] * sc[e] + sh[e], lo);
+        if constexpr (F32) {
+          f32x4_t o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = POOL && !inmap ? -INFINITY : y[e];
+          *(f32x4_t*)(stg + l31 * SPITCH + c0 * 4) = o;
+        } else {
+          uint2 o;
+          o.x = f2bf2(y[0], y[1]);
+          o.y = f2bf2(y[2], y[3]);
+          if (POOL && !inmap) o = uint2{0xff80ff80u, 0xff80ff80u};
+          *(uint2*)(stg + l31 * SPITCH + c0 * 2) = o;
+        }
       }
     // the next tile's block, whose buffer was last read a tile ago; requests of the one after it go ahead of this tile's stores
     if (next < a.tiles_m) store_block(buf ^ 1);
@@ -2129,9 +2176,9 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
         if (idx != tid) { wi = idx / CPP; ch = idx - wi * CPP; wy = wi / a.ppw; wx = wi - wy * a.ppw; }
         const int py = tyi * a.pph + wy, px = txi * a.ppw + wx;
         if (py >= a.PH || px >= a.PW) continue;
-        float m[8];
+        float m[CE];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m[e] = -INFINITY;
+        for (int e = 0; e < CE; ++e) m[e] = -INFINITY;
         if (a.pk == 3) {
           // (all nine reads of the window before the first maximum: one LDS latency, not nine)
           u32x4_t wv9[9];
@@ -2140,21 +2187,21 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
             wv9[t9] = *(const u32x4_t*)(s_stage + ((wy * a.ps + t9 / 3) * CW + wx * a.ps + t9 % 3) * SPITCH + ch * 16);
 #pragma unroll
           for (int t9 = 0; t9 < 9; ++t9) {
-            float v[8];
-            Tr<bf16_t>::unpack(wv9[t9], v);
+            float v[CE];
+            Tr<T>::unpack(wv9[t9], v);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m[e] = fmx_raw(m[e], v[e]);
+            for (int e = 0; e < CE; ++e) m[e] = fmx_raw(m[e], v[e]);
           }
         } else {
           for (int i = 0; i < a.pk; ++i)
             for (int j = 0; j < a.pk; ++j) {
-              float v[8];
-              Tr<bf16_t>::unpack(*(const u32x4_t*)(s_stage + ((wy * a.ps + i) * CW + wx * a.ps + j) * SPITCH + ch * 16), v);
+              float v[CE];
+              Tr<T>::unpack(*(const u32x4_t*)(s_stage + ((wy * a.ps + i) * CW + wx * a.ps + j) * SPITCH + ch * 16), v);
 #pragma unroll
-              for (int e = 0; e < 8; ++e) m[e] = fmx_raw(m[e], v[e]);
+              for (int e = 0; e < CE; ++e) m[e] = fmx_raw(m[e], v[e]);
             }
         }
-        *(u32x4_t*)((unsigned char*)a.out + ((long long)n * a.out_sN + (long long)(py * a.PW + px) * a.out_sP) * 2 + ch * 16) = Tr<bf16_t>::pack(m);
+        *(u32x4_t*)((unsigned char*)a.out + ((long long)n * a.out_sN + (long long)(py * a.PW + px) * a.out_sP) * ESZ + ch * 16) = Tr<T>::pack(m);
       }
     } else {
       __builtin_amdgcn_wave_barrier();
@@ -2164,7 +2211,7 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
         const u32x4_t o = *(const u32x4_t*)(stg + px * SPITCH + ch * 16);
         const int oy = cy0 + 2 * wave + (px >> 4), ox = cx0 + (px & 15);
         if (oy < a.OH && ox < a.OW)
-          *(u32x4_t*)((unsigned char*)a.out + ((long long)n * a.out_sN + (long long)(oy * a.OW + ox) * a.out_sP) * 2 + ch * 16) = o;
+          *(u32x4_t*)((unsigned char*)a.out + ((long long)n * a.out_sN + (long long)(oy * a.OW + ox) * a.out_sP) * ESZ + ch * 16) = o;
       }
     }
     tile = next;
@@ -2172,12 +2219,13 @@ __global__ __launch_bounds__(SL_NT, NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void ste
   }
 }
 
-template <int KB, bool POOL>
+template <typename T, int KB, bool POOL>
 static int launch_stem_lds_kb(const ConvArgs& a, hipStream_t st) {
   const int taps = a.R * a.S;
-  if (taps <= 12) hipLaunchKernelGGL((stem_lds_kernel<KB, 3, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
-  else if (taps <= 28) hipLaunchKernelGGL((stem_lds_kernel<KB, 7, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
-  else if (taps <= 52) hipLaunchKernelGGL((stem_lds_kernel<KB, 13, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+  if (taps <= 12) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 3, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+  else if (taps <= 28) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 7, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+  else if constexpr (sizeof(T) == 4) return (int)hipErrorInvalidValue;   // (7x7, 64 channels: thirty registers of the weights are spilled)
+  else if (taps <= 52) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 13, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
   else return (int)hipErrorInvalidValue;
   return (int)hipGetLastError();
 }
@@ -2187,9 +2235,10 @@ static int launch_stem_lds(const ConvArgs& a, int dtype, hipStream_t st) {
   const bool pool = a.pool != POOL_NONE;
   const int CH = pool ? (a.pph - 1) * a.ps + a.pk : SL_TH, CW = pool ? (a.ppw - 1) * a.ps + a.pk : SL_TW;
   const int IH = (CH - 1) * a.stride + a.R, IW = (CW - 1) * a.stride + a.S;
-  if (dtype != DT_BF16 || a.pair_C < 1 || a.pair_C > 4 || a.C != a.pair_C || a.R != a.S || a.R < 1 || a.R > 7 || (a.stride != 1 && a.stride != 2) ||
+  const int esz = dtype == DT_BF16 ? 2 : 4;
+  if (a.pair_C < 1 || a.pair_C > (esz == 2 ? 4 : 3) || (esz == 4 && (!pool || IH * IW >= kStemLdsF32Rounds * SL_NT)) || a.C != a.pair_C || a.R != a.S || a.R < 1 || a.R > 7 || (a.stride != 1 && a.stride != 2) ||
       a.pad < 0 || a.pad > a.R || IH * IW > stem_lds_in_positions(a.R * a.S) || IH >= 4096 || IW >= 4096 || !a.dw_w || a.has_res || a.ksplit >= 1 ||
-      a.out_sK != 1 || a.out_f32 || (a.out_sP * 2) % 16 != 0 || (a.out_sN * 2) % 16 != 0 || ((uintptr_t)a.out & 15) || ((uintptr_t)a.dw_w & 15) ||
+      a.out_sK != 1 || (a.out_f32 && esz != 4) || (a.out_sP * esz) % 16 != 0 || (a.out_sN * esz) % 16 != 0 || ((uintptr_t)a.out & 15) || ((uintptr_t)a.dw_w & 15) ||
       a.pair_sN < 0 || a.pair_sC < 0 || a.pair_sH < 0 || (long long)4 * a.pair_sC + (long long)(a.H + 64) * a.pair_sH >= (1ll << 31) ||
       a.OH != (a.H + 2 * a.pad - a.R) / a.stride + 1 || a.OW != (a.W + 2 * a.pad - a.S) / a.stride + 1)
     return (int)hipErrorInvalidValue;
@@ -2200,15 +2249,15 @@ static int launch_stem_lds(const ConvArgs& a, int dtype, hipStream_t st) {
         a.PH < 1 || a.PW < 1 || (a.PH - 1) * a.ps - a.pp >= a.OH || (a.PW - 1) * a.ps - a.pp >= a.OW ||
         a.tiles_y != (a.PH + a.pph - 1) / a.pph || a.tiles_x != (a.PW + a.ppw - 1) / a.ppw || a.tiles_m != a.N * a.tiles_y * a.tiles_x)
       return (int)hipErrorInvalidValue;
-    if (a.K == 32) return launch_stem_lds_kb<1, true>(a, st);
-    if (a.K == 64) return launch_stem_lds_kb<2, true>(a, st);
+    if (a.K == 32) return esz == 2 ? launch_stem_lds_kb<bf16_t, 1, true>(a, st) : launch_stem_lds_kb<float, 1, true>(a, st);
+    if (a.K == 64) return esz == 2 ? launch_stem_lds_kb<bf16_t, 2, true>(a, st) : launch_stem_lds_kb<float, 2, true>(a, st);
     return (int)hipErrorInvalidValue;
   }
   if (a.mode != M_FLAT || a.th != SL_TH || a.tw != SL_TW || a.tiles_y != (a.OH + SL_TH - 1) / SL_TH || a.tiles_x != (a.OW + SL_TW - 1) / SL_TW ||
       a.tiles_m != a.N * a.tiles_y * a.tiles_x)
     return (int)hipErrorInvalidValue;
-  if (a.K == 32) return launch_stem_lds_kb<1, false>(a, st);
-  if (a.K == 64) return launch_stem_lds_kb<2, false>(a, st);
+  if (a.K == 32) return launch_stem_lds_kb<bf16_t, 1, false>(a, st);
+  if (a.K == 64) return launch_stem_lds_kb<bf16_t, 2, false>(a, st);
   return (int)hipErrorInvalidValue;
 }
 

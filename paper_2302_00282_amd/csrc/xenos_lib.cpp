@@ -644,7 +644,7 @@ struct Planner {
       }
       c.tiles_m = c.N * c.tiles_y * c.tiles_x; c.tiles_n = 1; c.ntiles = c.tiles_m; c.xcd_m = 8;
       // as many workgroups as are resident (stem_lds_kernel's launch bounds), so that none starts, with its weights and tables, behind another
-      const int resident = c.R * c.S > 12 ? 2 : c.K > 32 ? 3 : 4;
+      const int resident = c.R * c.S > 12 || p.dt == DT_F32 ? 2 : c.K > 32 ? 3 : 4;
       c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, resident * num_cu)) : 1;
       st.cfg = kStemLdsCfg;
       st.lds = conv_lds_bytes(kStemLdsCfg, c.mode);
@@ -1558,7 +1558,9 @@ struct Planner {
         // takes a linked max-pooling of 2 or 3 wide windows at stride 2: 3 x 8 windows per tile, their convolution block
         // recomputed per tile.
         const View& gv = p.views[tview[0]];
-        stem_lds = p.dt == DT_BF16 && p.opts.tile == 0 && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
+        // On the fp32 path it is for kernels up to 5x5 with such a pooling, at link level 3 (at level 2 the pooling stays a pass of its own).
+        const bool f32 = p.dt == DT_F32;
+        stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5 && p.hw.lds_bytes_per_cu >= 64 * 1024)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
                    (d.stride_h == 1 || d.stride_h == 2) && d.pad_h == d.pad_w && d.pad_h <= d.kh && gv.f32 && gv.sP == 1 &&
                    ((kStemLdsTh - 1) * d.stride_h + d.kh) * ((kStemLdsTw - 1) * d.stride_h + d.kw) <= stem_lds_in_positions(d.kh * d.kw);
         bool keep_pool = false;
@@ -1569,6 +1571,7 @@ struct Planner {
                       pd.pad_h == pd.pad_w && pd.pad_h >= 0 && pd.pad_h <= 1 && chh * cww <= kStemLdsTh * kStemLdsTw &&
                       ((chh - 1) * d.stride_h + d.kh) * ((cww - 1) * d.stride_h + d.kw) <= stem_lds_in_positions(d.kh * d.kw);
         }
+        if (f32 && !keep_pool) stem_lds = false;
         // (a 3x3 layer takes the LDS-staged form only for its linked pooling: one launch for two, the same time at batch 32;
         // without pooling the gather form is faster)
         if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;
@@ -1737,11 +1740,16 @@ struct Planner {
         if (st.stem_lds) {
           // weights [K][steps * 16] with reduction slot = tap * 4 + channel (4 taps per MFMA step of 16)
           const int taps = d.kh * d.kw, nstep = taps <= 12 ? 3 : taps <= 28 ? 7 : 13;
-          std::vector<uint16_t> ws((size_t)Kk * nstep * 16, 0);
+          std::vector<uint16_t> ws(p.dt == DT_BF16 ? (size_t)Kk * nstep * 16 : 0, 0);
+          std::vector<float> wf(p.dt == DT_BF16 ? 0 : (size_t)Kk * nstep * 16, 0.f);
           for (int k = 0; k < K; ++k)
             for (int c = 0; c < is.c; ++c)
-              for (int t = 0; t < taps; ++t) ws[(size_t)k * nstep * 16 + t * 4 + c] = f2bf_host(go.weight[((size_t)k * is.c + c) * taps + t]);
-          st.dw_w_off = (long long)wpush(ws.data(), ws.size() * 2);
+              for (int t = 0; t < taps; ++t) {
+                const float v = go.weight[((size_t)k * is.c + c) * taps + t];
+                if (p.dt == DT_BF16) ws[(size_t)k * nstep * 16 + t * 4 + c] = f2bf_host(v);
+                else wf[(size_t)k * nstep * 16 + t * 4 + c] = v;
+              }
+          st.dw_w_off = (long long)(p.dt == DT_BF16 ? wpush(ws.data(), ws.size() * 2) : wpush(wf.data(), wf.size() * 4));
           a.pair_C = is.c; a.pair_sN = iv.sN; a.pair_sC = iv.sK; a.pair_sH = iv.sP * is.w;
         }
         if (from_pair) {

@@ -53,10 +53,6 @@ __device__ __forceinline__ int thread_here() {
 }
 __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(const __attribute__((address_space(1))) u32x4_t*)(base + off); }
 
-// ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
-// replace -infinity).  For fmx_raw: of fmaxf the compiler makes a maximum and a selection per value.
-__device__ __forceinline__ float unit_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
-
 // The weight fragments of a unit_gemm: w as [block of 32 channels][kgs][lane] of 16 bytes, nkg of the kgs k-groups in use.  Part u is 64
 // rows x 32 channels and works with block u % ncb; a k-group past the end, and every one of a part past the end, reads no memory.
 struct UnitWeights {
@@ -236,7 +232,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
         if (m >= npos) return;
         const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * PM;
-        const float lo = unit_floor(a.fire_relu[0]);
+        const float lo = relu_floor(a.fire_relu[0]);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = cb * 32 + g * 8 + lhalf * 4;
@@ -327,7 +323,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
       },
       [&](int cb, int row0, int h, const f32x16_t& acc) __attribute__((always_inline)) {
         // finished values change hands inside the wavefront only (LDS serves its requests in order)
-        const float lo = unit_floor(a.relu);
+        const float lo = relu_floor(a.relu);
         const int ln = thread_here() & 63, l31 = ln & 31, lhalf = ln >> 5;
         if constexpr (sizeof(T) != 2) other(cb, row0, h);          // (32 registers of both halves would be spilled)
 #pragma unroll

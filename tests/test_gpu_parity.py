@@ -281,6 +281,23 @@ def test_first_layer_reads_the_graph_input_in_place(k, ksz, stride, pad, hw, c, 
         assert rel_err(y, ys.astype(np.float64)) <= TOL[compute]
 
 
+@pytest.mark.parametrize("k,ksz,stride,pad,h,w,c,pool", [(64, 3, 2, 0, 41, 55, 3, (3, 0, 1)), (32, 3, 1, 1, 9, 23, 1, (2, 0, 0)), (24, 3, 2, 1, 45, 33, 3, (3, 1, 0)),
+                                                          (64, 5, 2, 2, 37, 70, 2, (3, 1, 0)), (32, 5, 1, 2, 8, 17, 3, (3, 0, 1)), (48, 4, 2, 1, 64, 31, 3, (2, 0, 1)),
+                                                          (64, 5, 2, 0, 7, 9, 3, (2, 1, 0))])
+def test_fp32_first_layer_with_its_pooling_in_one_launch(k, ksz, stride, pad, h, w, c, pool):
+    # link level 3, fp32: input block and pooling staged on chip; odd tap counts end in half a step, ragged tiles of 3 x 8 windows on
+    # every side, maps smaller than a tile, persistent workgroups (one walking all tiles gives the same bits); the route of level 2 agrees
+    b = wg.builder("stem_f32", (3, c, h, w), 29, nonzero_bias=True)
+    t = b.maxpool(b.cbr(0, k, ksz, stride, pad, name="c0", relu=k != 48), pool[0], 2, pool[1], ceil=pool[2])
+    g = b.finish(b.cbr(t, 24, 1, name="c1"))
+    ref = xo.forward(g)
+    y, info = check(g, ref, compute=0, link=3)
+    assert info["chains"][0]["loader"] == "stem" and info["chains"][0]["pool"] != 0 and not any(ch["kind"] == "pool" for ch in info["chains"])
+    ys, _ = run_gpu(g, compute=0, link=3, split=0)
+    assert rel_err(y, ys.astype(np.float64)) <= TOL[0]
+    check(g, ref, compute=0, link=2)
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("pool", [0, 1])
 def test_padded_first_layer_feeds_a_linked_depthwise_pair(pool, compute):
