@@ -129,11 +129,12 @@ def test_every_operator_runs_exactly_once(cfg, batch):
             assert len(non_cat) == len(set(non_cat))
 
 
+@pytest.mark.parametrize("compute", [X.XENOS_F32, X.XENOS_BF16])
 @pytest.mark.parametrize("hw,rows", [(13, 64), (14, 128), (7, 64), (8, 64), (11, 128), (17, 64)])
-def test_fp32_global_average_takes_the_tile_that_pads_less(hw, rows):
+def test_global_average_takes_the_tile_that_pads_less(hw, rows, compute):
     b = wg.builder("gap", (32, 64, hw, hw), 3)
     g = b.finish(b.gap(b.cbr(b.cbr(0, 64, 1, name="a"), 1000, 1, name="c")))
-    chain = [c for c in plan_json(g, link=2, compute=X.XENOS_F32)["plan"]["chains"] if c.get("mode") == "gap"]
+    chain = [c for c in plan_json(g, link=2, compute=compute)["plan"]["chains"] if c.get("mode") == "gap"]
     assert len(chain) == 1 and chain[0]["bm"] == rows and chain[0]["bn"] == 64
 
 
