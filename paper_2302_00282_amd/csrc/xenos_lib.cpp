@@ -1564,8 +1564,9 @@ struct Planner {
         const View& gv = p.views[tview[0]];
         // On the fp32 path it is for kernels up to 5x5 with such a pooling, at link level 3 (at level 2 the pooling stays a pass of its own).
         const bool f32 = p.dt == DT_F32;
-        stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5 && 4 * gv.sK + (is.h + 64ll) * is.w < (1ll << 31) && p.hw.lds_bytes_per_cu >= 64 * 1024)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
+        stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5 && p.hw.lds_bytes_per_cu >= 64 * 1024)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
                    (d.stride_h == 1 || d.stride_h == 2) && d.pad_h == d.pad_w && d.pad_h <= d.kh && gv.f32 && gv.sP == 1 &&
+                   4 * gv.sK + (is.h + 64ll) * is.w < (1ll << 31) &&   // (its offsets inside an image are 32 bits)
                    ((kStemLdsTh - 1) * d.stride_h + d.kh) * ((kStemLdsTw - 1) * d.stride_h + d.kw) <= stem_lds_in_positions(d.kh * d.kw);
         bool keep_pool = false;
         if (stem_lds && pool_node >= 0 && !placed.count(cur) && cur != out_tid) {

@@ -428,6 +428,28 @@ def test_pattern_depthwise_to_pointwise_on_chip():
         assert c["K"] == 352 and _kinds(g, c).count("conv") == 2
 
 
+def undrawn(shape):
+    """A builder whose tensors are shapes only (the input has no array): for plans of graphs too large to draw."""
+    b = wg._Builder("undrawn", (1, 1, 1, 1), 1, False, False)
+    b.g.input_shape, b.g.x, b._shapes = tuple(shape), None, [tuple(shape)]
+    return b
+
+
+@pytest.mark.parametrize("compute", [X.XENOS_F32, X.XENOS_BF16])
+@pytest.mark.parametrize("ksz,pool", [(3, 1), (7, 0), (7, 1)])
+def test_first_layer_of_an_image_beyond_32_bit_offsets_is_gathered(ksz, pool, compute):
+    # stem_lds_kernel's offsets inside an image are 32 bits, 4 channels + 64 rows of it: 104 w elements here
+    def first(w):
+        b = undrawn((1, 3, 8, w))
+        t = b.cbr(0, 64, ksz, 2, ksz // 2, name="a")
+        t = b.maxpool(t, 3, 2, 1) if pool else t
+        return plan_json(b.finish(b.cbr(t, 8, 1, name="b")), link=3, compute=compute)["plan"]["chains"][0]
+    fits, beyond = first((1 << 31) // 104 - 2), first((1 << 31) // 104 + 2)
+    if compute == X.XENOS_BF16 or (ksz == 3 and pool):
+        assert fits["loader"] == "stem" and fits["bm"] == 128
+    assert beyond["loader"] == "stem" and beyond["bm"] == 32 and beyond["pool"] == 0
+
+
 def test_pattern_first_layer_pair_on_chip():
     g = wg.build(3, 2, draw=False)
     l3 = plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]
