@@ -1582,7 +1582,10 @@ struct Planner {
         if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;
         // (a padded channel count only where the chain stays as linked as the general kernel would have it)
         const bool padded = K != 32 && K != 64;
-        if ((stem_lds || is.c * d.kh * d.kw <= kStemRed) && (keep_pool || (c2 != out_tid && !placed.count(c2) && !(padded && pool_node >= 0)))) {
+        // (the gather's offsets inside a window are 32 bits: a larger image is imported)
+        const bool gathers = is.c * d.kh * d.kw <= kStemRed &&
+                             (is.c - 1) * gv.sK + ((d.kh - 1ll) * is.w + d.kw - 1) * gv.sP < (1ll << 31);
+        if ((stem_lds || gathers) && (keep_pool || (c2 != out_tid && !placed.count(c2) && !(padded && pool_node >= 0)))) {
           stem = true;
           if (pool_node >= 0 && !keep_pool) { absorbed.pop_back(); pool_node = -1; cur = c2; last = l2; }
         } else {

@@ -450,6 +450,16 @@ def test_first_layer_of_an_image_beyond_32_bit_offsets_is_gathered(ksz, pool, co
     assert beyond["loader"] == "stem" and beyond["bm"] == 32 and beyond["pool"] == 0
 
 
+@pytest.mark.parametrize("compute", [X.XENOS_F32, X.XENOS_BF16])
+def test_first_layer_whose_windows_pass_32_bits_is_imported(compute):
+    # the gather's table holds 32-bit offsets inside a window, here 2 channels + 2 rows + 2: 18 w + 2 elements
+    def first(w):
+        b = undrawn((1, 3, 8, w))
+        return plan_json(b.finish(b.cbr(b.cbr(0, 64, 3, 2, 1, name="a"), 8, 1, name="b")), link=3, compute=compute)["plan"]["chains"][0]
+    w = ((1 << 31) - 3) // 18
+    assert first(w)["loader"] == "stem" and first(w + 1)["kind"] == "cvt"
+
+
 def test_pattern_first_layer_pair_on_chip():
     g = wg.build(3, 2, draw=False)
     l3 = plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]
