@@ -703,6 +703,7 @@ struct Planner {
       if (conv_lds_bytes(cfg, c.mode) > p.hw.lds_bytes_per_cu) continue;   // parameter split must fit private memory
       if (st.scalar && !conv_cfg_has_scalar_loader(cfg)) continue;
       if (c.dw_w && !conv_cfg_has_dw_prologue(cfg, c.mode)) continue;
+      if (c.kchunk && !conv_window_fits(c, p.esz)) continue;       // its loader for that order has 32-bit addresses (the halo kernel has not)
       ConvArgs t = c;
       if (c.mode == M_FLAT || c.mode == M_ZIGZAG) {
         t.tiles_m = (c.M_total + tc.bm - 1) / tc.bm;
@@ -777,6 +778,11 @@ struct Planner {
         }
       }
     }
+    if (best < 0 && c.kchunk) {                                    // no kernel takes the chain in this order
+      c.kchunk = 0;
+      st.cands.clear();
+      return split_conv(st);
+    }
     if (best < 0) return fail(XENOS_EUNSUPPORTED, "%s: no tile configuration fits %zu bytes of LDS (or the forced one does not apply)",
                               st.name.c_str(), p.hw.lds_bytes_per_cu);
     c = best_args;
@@ -786,24 +792,28 @@ struct Planner {
     return XENOS_OK;
   }
 
-  // ---- pack weights of a dense conv / fc in operand order -------------------------------------
+  // Length and order of a dense chain's reduction.  The reduction index is (r*S+s)*C + c, or, when the channels divide into
+  // whole steps, ((c/step)*R*S + r*S + s)*step + c%step so that the R*S taps of one channel chunk are consecutive steps
+  // and re-read the same input pixels while they are still cached.  (split_conv goes back to the first where it must)
+  void set_reduction(Step& st, int C, int R, int S) const {
+    const int bke = kRowBytes / p.esz;
+    st.conv.Kred = R * S * C;
+    st.conv.Kred_pad = (st.conv.Kred + bke - 1) / bke * bke;
+    st.conv.kchunk = C % bke == 0 && R * S > 1 && !st.scalar && !st.fc_stream;
+  }
+
+  // ---- pack weights of a dense conv / fc in operand order (set_reduction's) -------------------------------------
   // Csrc = channels of the operator's weights, C = channels the kernel reduces over (>= Csrc, extra ones zero)
   void pack_dense(Step& st, const GOp& o, int Csrc, int C, int R, int S, int K) {
     const int bke = kRowBytes / p.esz;
-    const int kred = R * S * C, kred_pad = (kred + bke - 1) / bke * bke;
+    const int kred_pad = st.conv.Kred_pad;
+    const bool kchunk = st.conv.kchunk;
     const int kout_pad = (K + 127) / 128 * 128;
-    st.conv.Kred = kred; st.conv.Kred_pad = kred_pad;
     const size_t bytes = (size_t)kout_pad * kred_pad * p.esz;
     st.w_off = (long long)wpush(nullptr, bytes);
     unsigned char* base = p.wimage.data() + st.w_off;
     memset(base, 0, bytes);
-    // source [K][C][R][S] -> destination [K][reduction index]; the reduction index is (r*S+s)*C + c, or, when
-    // the channels divide into whole steps, ((c/step)*R*S + r*S + s)*step + c%step so that the R*S taps of
-    // one channel chunk are consecutive steps and re-read the same input pixels while they are still cached
-    // (tensors beyond the 32-bit addresses of the loader for that order keep the plain one)
-    const bool kchunk = C % bke == 0 && R * S > 1 && !st.scalar && !st.fc_stream && conv_window_fits(st.conv, p.esz);
-    st.conv.kchunk = kchunk ? 1 : 0;
-    // channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
+    // source [K][C][R][S] -> destination [K][reduction index]; channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
     // folded shuffle of g groups (tensor channel j * m + i is the operator's channel i * g + j), its shuffled position
     const int shg = pack_shuffle_groups, shm = shg ? Csrc / shg : 1;
     auto wch = [&](int c) -> size_t { return shg ? (size_t)(c % shm) * shg + c / shm : (size_t)c; };
@@ -1258,6 +1268,7 @@ struct Planner {
     Step first;
     first.conv.wfrag = 1;
     dwpro.pw_C = std::max(is.c, p.views[dwpro.v_in].cphys);        // (padding channels multiply zero weights)
+    set_reduction(first, dwpro.pw_C, 1, 1);
     pack_dense(first, g.ops[nodes[i].src], is.c, dwpro.pw_C, 1, 1, ms.c);
     dwpro.pw_w_off = first.w_off; dwpro.pw_kred = first.conv.Kred_pad; dwpro.pw_relu = w1.relu;
     push_affine(w1.af, (ms.c + 127) / 128 * 128, &dwpro.pw_scale_off, &dwpro.pw_shift_off);
@@ -1446,6 +1457,7 @@ struct Planner {
     a.R = R1; a.S = R1; a.stride = 1; a.pad = R1 / 2; a.OH = is.h; a.OW = is.w; a.PH = is.h; a.PW = is.w;
     a.in_sN = iv.sN; a.in_sH = iv.sP * is.w; a.in_sW = iv.sP;
     a.relu = w.relu; a.mode = M_FLAT; a.pool = POOL_NONE; a.fire = 1;
+    set_reduction(st, a.C, R1, R1);
     pack_dense(st, go, is.c, a.C, R1, R1, S);
     if (R1 == 3 && !a.kchunk) return fail(XENOS_EUNSUPPORTED, "%s: 3x3 weights of a linked pair are not packed by channel chunk", st.name.c_str());
     push_affine(w.af, (S + 127) / 128 * 128, &st.scale_off, &st.shift_off);
@@ -1827,12 +1839,13 @@ struct Planner {
                        a.OH == 1 && a.OW == 1 && a.R == is.h && a.S == is.w && a.pad == 0 && is.n <= 32 && !st.scalar && a.C == is.c &&
                        ((long long)a.R * a.S * a.C) % 64 == 0 && (long long)a.R * a.S * a.C >= 512 && (long long)a.R * a.S * a.C < (1ll << 30) &&
                        iv.sN % p.ce == 0 && iv.sN >= (long long)a.R * a.S * a.C && (a.R * a.S == 1 || (iv.sP == a.C && iv.sN == (long long)a.R * a.S * a.C));
-        {
+        set_reduction(st, a.C, a.R, a.S);
+        auto pack_weights = [&]() {
           const int src_node = nd.in[0] - 1;
           pack_shuffle_groups = !is_fc && src_node >= 0 && nodes[src_node].kind == XENOS_OP_SHUFFLE && fold_shuffle[src_node] ? desc(nodes[src_node]).groups : 0;
-        }
-        pack_dense(st, go, is_fc ? is.c : is.c, a.C, a.R, a.S, K);
-        pack_shuffle_groups = 0;
+          pack_dense(st, go, is.c, a.C, a.R, a.S, K);
+          pack_shuffle_groups = 0;
+        };
         push_affine(af, (K + 127) / 128 * 128, &st.scale_off, &st.shift_off);
         if (st.scalar) {
           std::vector<int32_t> tab((size_t)2 * a.Kred_pad);
@@ -1861,6 +1874,7 @@ struct Planner {
         }
         if (a.unit) {
           if (!a.vec_out || a.mode != M_FLAT || has_res) return fail(XENOS_EUNSUPPORTED, "%s: output of the unit's chain is not aligned", st.name.c_str());
+          pack_weights();
           a.th = pro.th; a.tw = pro.tw;
           a.tiles_y = (a.OH + a.th - 1) / a.th; a.tiles_x = (a.OW + a.tw - 1) / a.tw;
           a.tiles_m = a.ntiles = a.N * a.tiles_y * a.tiles_x;
@@ -1888,6 +1902,8 @@ struct Planner {
         }
         xenos_status rc = split_conv(st);
         if (rc != XENOS_OK) return rc;
+        if (hsplit.ks >= 2) a.kchunk = 1;                          // (the order of the halo kernel, which runs the chain whatever split_conv chose)
+        pack_weights();
         if (a.dw_panel > 0) st.lds = dwpw_lds_bytes(a.dw_panel, p.esz);
         st.flops = 2.0 * a.N * a.OH * a.OW * (double)K * a.R * a.S * is.c + (from_dw ? pro.flops : 0.0) + (from_pair ? ppro.flops : 0.0);
         if (from_dw) st.bytes_w += pro.bytes_w;
@@ -2012,6 +2028,7 @@ struct Planner {
     a.relu = w1.relu; a.mode = M_FLAT; a.pool = POOL_NONE;
     a.pwdw = 1; a.dw_k = 3; a.dw_stride = dd.stride_h; a.dw_pad = 1; a.dw_relu = w2.relu; a.dw_H = is.h; a.dw_W = is.w;
     a.M_total = a.N * a.OH * a.OW;
+    set_reduction(st, a.C, 1, 1);
     pack_dense(st, go, is.c, a.C, 1, 1, K);
     push_affine(w1.af, (K + 127) / 128 * 128, &st.scale_off, &st.shift_off);
     st.dw_w_off = pack_depthwise(g.ops[dnode.src], K, 9);

@@ -460,6 +460,24 @@ def test_first_layer_whose_windows_pass_32_bits_is_imported(compute):
     assert first(w)["loader"] == "stem" and first(w + 1)["kind"] == "cvt"
 
 
+def test_large_tensors_keep_the_halo_kernel():
+    # the channel-chunk order is conv3x3_kernel's too, which has no 32-bit windows: two fp32 images of 2.2 GB stay on it, a layer that it
+    # does not take (stride 2) is planned as before, and so is a forced tile of the general kernel
+    def second(stride, **kw):
+        b = undrawn((2, 8, 2950, 2950))
+        t = b.cbr(b.cbr(0, 64, 1, name="a"), 128, 3, stride, 1, name="b")
+        return plan_json(b.finish(b.cbr(t, 8, 1, name="c")), link=2, compute=X.XENOS_F32, **kw)["plan"]["chains"][-2]
+    assert second(1)["halo"] and not second(2)["halo"] and not second(1, tile=3)["halo"]
+
+
+def test_linked_3x3_pair_of_images_just_below_the_limit():
+    # two images of 32 KB less than 2 GB: the weights of the first convolution are in channel-chunk order whatever conv_kernel could address
+    b = undrawn((2, 8, 257, 65280))
+    t = b.cbr(b.cbr(b.cbr(0, 64, 1, name="a"), 32, 3, 1, 1, name="b"), 64, 1, name="c")
+    chains = plan_json(b.finish(b.cbr(t, 8, 1, name="d")), link=3, compute=X.XENOS_BF16)["plan"]["chains"]
+    assert [c.get("loader") for c in chains].count("fire") == 1
+
+
 def test_pattern_first_layer_pair_on_chip():
     g = wg.build(3, 2, draw=False)
     l3 = plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]
