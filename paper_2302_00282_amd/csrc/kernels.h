@@ -55,8 +55,14 @@ static const int kStemLdsPph = 3, kStemLdsPpw = 8;   // pooling windows per tile
 static const int kStemLdsTh = 8, kStemLdsTw = 16, kStemLdsInMax = 784;   // (7 * 2 + 7) x (15 * 2 + 7) = 777 positions at most
 // (per kernel size class the kernel is instantiated for, by taps: up to 3x3 at stride 2 a block is at most 17 x 33 or 15 x 35
 // positions, up to 5x5 19 x 35)
-static const int kStemLdsF32Rounds = 3;   // fp32 path: positions of the block per thread of 256 (16 bytes each, two blocks and the staging in 64 KB)
-static inline int stem_lds_in_positions(int taps) { return taps <= 12 ? 576 : taps <= 28 ? 672 : kStemLdsInMax; }
+constexpr int stem_lds_in_positions(int taps) { return taps <= 12 ? 576 : taps <= 28 ? 672 : kStemLdsInMax; }
+constexpr int stem_lds_steps(int taps) { return taps <= 12 ? 3 : taps <= 28 ? 7 : 13; }          // steps of four taps
+constexpr int stem_lds_rounds(int taps) { return (stem_lds_in_positions(taps) + 255) / 256; }    // positions of the block per thread of 256
+// LDS of the kernel for 32 or 64 output channels: two input blocks of four-channel positions, the staging slices of four wavefronts (32
+// pixels, pitch an odd number of 16-byte slots), scale and shift, the tap offsets of either lane half.  The kernel asserts the same
+constexpr size_t stem_lds_bytes(int taps, int channels, int esz) {
+  return (size_t)2 * stem_lds_rounds(taps) * 256 * 4 * esz + 4 * 32 * (channels * esz + 16) + 2 * channels * 4 + stem_lds_steps(taps) * 2 * 8;
+}
 // Configuration index of the kernel that links a pointwise (1x1) convolution chain with the depthwise 3x3 chain that consumes
 // it: a TH x TW block of depthwise output pixels x kPwDwChannels channels per workgroup, the pointwise output of the block
 // (+ halo) staged in LDS, at most kPwDwMaxPositions positions

@@ -1951,13 +1951,7 @@ static int launch_stem_t(const ConvArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------------
 constexpr int SL_NW = 4, SL_NT = 64 * SL_NW;
 constexpr int SL_TH = kStemLdsTh, SL_TW = kStemLdsTw;             // output pixels of a tile: 8 x 16 = 4 wavefronts x 32
-constexpr int SL_INMAX = kStemLdsInMax;                            // positions of the staged input block
 static_assert(SL_TH * SL_TW == 32 * SL_NW && SL_TW == 16, "one wavefront = two tile rows of 16 pixels");
-
-// positions of the staged input block by kernel size class (NSTEP MFMA steps of four taps): up to 3x3 at stride 2 a block is
-// at most 17 x 33 or 15 x 35 positions, up to 5x5 19 x 35; the host checks the launch against these
-constexpr int sl_inpos(int nstep) { return nstep <= 3 ? 576 : nstep <= 7 ? 672 : SL_INMAX; }
-static_assert(sl_inpos(3) == 576 && sl_inpos(7) == 672, "the same limits as stem_lds_in_positions(), which the host checks");
 
 // fp32 (kernels up to 5x5 behind which a max-pooling is linked): positions of 16 bytes, a lane half per tap, an MFMA per channel; it takes
 // out the convolution's result, written and read again by a pooling pass of its own before (101 MB each way on a 3x3 / 2 layer of 64
@@ -1979,12 +1973,14 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
   constexpr int K = KB * 32, ESZ = (int)sizeof(T), CE = 16 / ESZ;
   constexpr int SPITCH = K * ESZ + 16;                             // staging row pitch (odd number of 16-byte slots)
   constexpr int CPP = K * ESZ / 16, PPI = 64 / CPP;                // 16-byte chunks per output pixel, pixels per store instruction
-  constexpr int NP = F32 ? kStemLdsF32Rounds : (sl_inpos(NSTEP) + SL_NT - 1) / SL_NT;   // positions of the block a thread stages
-  constexpr int PB = 4 * ESZ, BLOCK = NP * SL_NT * PB;             // (more positions than a block has: the last one is zeros)
+  constexpr int NP = stem_lds_rounds(4 * NSTEP);                   // positions of the block a thread stages
+  constexpr int PB = 4 * ESZ, BLOCK = NP * SL_NT * PB;
+  static_assert(NP * SL_NT > stem_lds_in_positions(4 * NSTEP), "the last position of the buffer is beyond the block: zeros");
   __shared__ __align__(16) unsigned char s_xin[2 * BLOCK];         // this tile's block and the next one's
   __shared__ __align__(16) unsigned char s_stage[SL_NW * 32 * SPITCH];
   __shared__ __align__(16) float s_aff[2 * K];
   __shared__ int2 s_tap[NSTEP][2];                                 // per step and lane half: LDS byte offsets of its two taps
+  static_assert(sizeof(s_xin) + sizeof(s_stage) + sizeof(s_aff) + sizeof(s_tap) == stem_lds_bytes(4 * NSTEP, K, ESZ), "what the planner counts");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, lhalf = lane >> 5;
   const int st = a.stride;
   // convolution pixels of a tile: TH x TW, or, with a linked max-pooling, the CH x CW block that the tile's pph x ppw
@@ -2236,7 +2232,7 @@ static int launch_stem_lds(const ConvArgs& a, int dtype, hipStream_t st) {
   const int CH = pool ? (a.pph - 1) * a.ps + a.pk : SL_TH, CW = pool ? (a.ppw - 1) * a.ps + a.pk : SL_TW;
   const int IH = (CH - 1) * a.stride + a.R, IW = (CW - 1) * a.stride + a.S;
   const int esz = dtype == DT_BF16 ? 2 : 4;
-  if (a.pair_C < 1 || a.pair_C > (esz == 2 ? 4 : 3) || (esz == 4 && (!pool || IH * IW >= kStemLdsF32Rounds * SL_NT)) || a.C != a.pair_C || a.R != a.S || a.R < 1 || a.R > 7 || (a.stride != 1 && a.stride != 2) ||
+  if (a.pair_C < 1 || a.pair_C > (esz == 2 ? 4 : 3) || (esz == 4 && !pool) || a.C != a.pair_C || a.R != a.S || a.R < 1 || a.R > 7 || (a.stride != 1 && a.stride != 2) ||
       a.pad < 0 || a.pad > a.R || IH * IW > stem_lds_in_positions(a.R * a.S) || IH >= 4096 || IW >= 4096 || !a.dw_w || a.has_res || a.ksplit >= 1 ||
       a.out_sK != 1 || (a.out_f32 && esz != 4) || (a.out_sP * esz) % 16 != 0 || (a.out_sN * esz) % 16 != 0 || ((uintptr_t)a.out & 15) || ((uintptr_t)a.dw_w & 15) ||
       a.pair_sN < 0 || a.pair_sC < 0 || a.pair_sH < 0 || (long long)4 * a.pair_sC + (long long)(a.H + 64) * a.pair_sH >= (1ll << 31) ||
@@ -2640,7 +2636,6 @@ size_t conv_lds_bytes(int cfg, int /*mode*/) {
   if (cfg == kHaloCfg) return v2_lds_total(128);
   if (cfg == kPairCfg) return PR_LDS;
   if (cfg == kFcCfg) return 0;
-  if (cfg == kStemLdsCfg) return 32 * 1024;   // static: input block, staging slices, tables
   if (cfg == kStemCfg) return 40 * 1024;   // static: staging slices (at most 4 x 32 x 272 bytes) + tables
   const TileCfg& c = kTileCfgs[cfg];
   const size_t main_b = (size_t)2 * (c.bm + c.bn) * LDS_ROW;

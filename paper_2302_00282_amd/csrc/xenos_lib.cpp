@@ -647,7 +647,7 @@ struct Planner {
       const int resident = c.R * c.S > 12 || p.dt == DT_F32 ? 2 : c.K > 32 ? 3 : 4;
       c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, resident * num_cu)) : 1;
       st.cfg = kStemLdsCfg;
-      st.lds = conv_lds_bytes(kStemLdsCfg, c.mode);
+      st.lds = stem_lds_bytes(c.R * c.S, c.K, p.esz);
       return XENOS_OK;
     }
     if (st.stem) {   // one wavefront = 32 pixels x all channels; workgroups of 4 wavefronts stride over the pixel blocks
@@ -1563,8 +1563,7 @@ struct Planner {
       // (the gather form takes reductions up to kStemRed elements, the LDS-staged form up to 4 channels x 7 x 7 taps)
       if (!dw && !is_fc && nd.in[0] == 0 && in_lazy && link >= 2 && !has_res && (is.c * d.kh * d.kw <= kStemRed || (is.c <= 4 && d.kh <= 7 && d.kw <= 7)) &&
           // (32 or 64 output channels, or up to a quarter fewer: the kernels compute the padded count)
-          K <= 64 && K % p.ce == 0 && 4 * ((K <= 32 ? 32 : 64) - K) <= (K <= 32 ? 32 : 64) && is.h <= 8192 &&
-          conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu && (p.opts.tile == 0 || p.opts.tile == kStemCfg + 1)) {
+          K <= 64 && K % p.ce == 0 && 4 * ((K <= 32 ? 32 : 64) - K) <= (K <= 32 ? 32 : 64) && is.h <= 8192 && (p.opts.tile == 0 || p.opts.tile == kStemCfg + 1)) {
         // l2 = last node of the chain without its pooling, c2 = that node's output tensor
         const int l2 = pool_node < 0 ? last : absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
         const int c2 = l2 + 1;
@@ -1576,8 +1575,9 @@ struct Planner {
         const View& gv = p.views[tview[0]];
         // On the fp32 path it is for kernels up to 5x5 with such a pooling, at link level 3 (at level 2 the pooling stays a pass of its own).
         const bool f32 = p.dt == DT_F32;
-        stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5 && p.hw.lds_bytes_per_cu >= 64 * 1024)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
+        stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
                    (d.stride_h == 1 || d.stride_h == 2) && d.pad_h == d.pad_w && d.pad_h <= d.kh && gv.f32 && gv.sP == 1 &&
+                   stem_lds_bytes(d.kh * d.kw, K <= 32 ? 32 : 64, p.esz) <= p.hw.lds_bytes_per_cu &&
                    4 * gv.sK + (is.h + 64ll) * is.w < (1ll << 31) &&   // (its offsets inside an image are 32 bits)
                    ((kStemLdsTh - 1) * d.stride_h + d.kh) * ((kStemLdsTw - 1) * d.stride_h + d.kw) <= stem_lds_in_positions(d.kh * d.kw);
         bool keep_pool = false;
@@ -1595,7 +1595,7 @@ struct Planner {
         // (a padded channel count only where the chain stays as linked as the general kernel would have it)
         const bool padded = K != 32 && K != 64;
         // (the gather's offsets inside a window are 32 bits: a larger image is imported)
-        const bool gathers = is.c * d.kh * d.kw <= kStemRed &&
+        const bool gathers = is.c * d.kh * d.kw <= kStemRed && conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu &&
                              (is.c - 1) * gv.sK + ((d.kh - 1ll) * is.w + d.kw - 1) * gv.sP < (1ll << 31);
         if ((stem_lds || gathers) && (keep_pool || (c2 != out_tid && !placed.count(c2) && !(padded && pool_node >= 0)))) {
           stem = true;
@@ -1759,7 +1759,7 @@ struct Planner {
         }
         if (st.stem_lds) {
           // weights [K][steps * 16] with reduction slot = tap * 4 + channel (4 taps per MFMA step of 16)
-          const int taps = d.kh * d.kw, nstep = taps <= 12 ? 3 : taps <= 28 ? 7 : 13;
+          const int taps = d.kh * d.kw, nstep = stem_lds_steps(taps);
           std::vector<uint16_t> ws(p.dt == DT_BF16 ? (size_t)Kk * nstep * 16 : 0, 0);
           std::vector<float> wf(p.dt == DT_BF16 ? 0 : (size_t)Kk * nstep * 16, 0.f);
           for (int k = 0; k < K; ++k)
