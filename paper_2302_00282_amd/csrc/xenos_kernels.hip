@@ -373,6 +373,26 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
             }
           }
         }
+      } else if (nsteps < D) {
+        // (uniform) A reduction shorter than the ring requests its own steps only: an empty request passes through the same data path
+        // as a real one, 0.13 us a set, and the epilogue's loads queue up behind it
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d) {
+          if (d < nsteps) {
+            load_global(d, ra[d], rb[d], okm_[d]);
+          } else {                                                 // (or the sets are live from one tile to the next: 50 registers)
+#pragma unroll
+            for (int it = 0; it < A_IT; ++it) ra[d][it] = u32x4_t{};
+#pragma unroll
+            for (int it = 0; it < B_IT; ++it) rb[d][it] = u32x4_t{};
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+          if (d < nsteps) {
+            store_lds(d & 1, ra[d], rb[d], okm_[d]);
+            multiply(d);
+          }
       } else {
 #pragma unroll
         for (int d = 0; d < D; ++d) load_global(d, ra[d], rb[d], okm_[d]);
