@@ -68,7 +68,7 @@ template <> struct Tr<bf16_t> {
 // issue the same loads on every turn: behind a branch around them the compiler has to assume the path with the fewest loads in flight
 // and waits for all of them.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr unsigned kNoLoad = 0xffffffffu;
+constexpr unsigned kNoLoad = 0xffffffffu, kWindow = 0xffffff00u;     // (kWindow: the largest, for offsets that the host has bounded)
 __device__ __forceinline__ rsrc_t make_window(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000);
 }

@@ -4,6 +4,8 @@
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
+#include <algorithm>
+#include <cmath>
 
 namespace xenos {
 
@@ -214,7 +216,26 @@ int launch_pool(const PoolArgs& a, int dtype, void* stream);
 int launch_cvt(const CvtArgs& a, int dtype, void* stream);
 int launch_splitk_finish(const SplitKArgs& a, int dtype, void* stream);
 size_t conv_lds_bytes(int cfg, int mode);
-bool conv_window_fits(const ConvArgs& a, int esz);   // the uniform-tap loader addresses the tensors of a tile with 32 bits
+
+// Bytes from the first input row that a tile of conv_kernel's (at most 128 of the chain's pixels, row by row, or a patch) touches to the
+// end of what it reads, at most.  With pixels of two images the tile ends `rows` output rows into the second at most and began as many
+// before the end of the first.
+inline double conv_tile_span(const ConvArgs& a, int esz) {
+  const bool flat = a.mode == M_FLAT, zig = a.mode == M_ZIGZAG;
+  const double per = zig ? 4.0 * a.PH * a.PW : (double)a.OH * a.OW, line = zig ? 2.0 * a.PW : (double)a.OW;
+  const double images = flat || zig ? std::min<double>(a.N, std::floor(127 / per) + 2) : 1;
+  const double rows = a.mode == M_PATCH ? 128 : zig ? 2 * (std::floor(64 / line) + 2) : std::floor(127 / line) + 2;
+  const double sN = (double)a.in_sN, sH = (double)a.in_sH;
+  double span = (images - 1) * sN + a.H * sH;
+  if (images == 1) span = std::min(span, (rows * a.stride + a.R) * sH);
+  if (images == 2) span = std::min(span, std::max(0.0, sN - std::min((zig ? 2 * a.PH : a.OH) * a.stride, a.H) * sH) + (2 * rows * a.stride + a.R + a.pad) * sH);
+  return (span + (double)a.W * (double)a.in_sW + a.C) * esz;
+}
+// Can the loader for reductions whose tap is uniform address them, and a tile's weight rows, with 32-bit offsets?
+inline bool conv_window_fits(const ConvArgs& a, int esz) {
+  const double lim = 0xffffff00ll;
+  return a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && conv_tile_span(a, esz) < lim && 128.0 * a.Kred_pad * esz < lim;
+}
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

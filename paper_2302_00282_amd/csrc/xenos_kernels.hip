@@ -95,9 +95,11 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
       // ---- decode the rows this thread loads ---------------------------------------------------
       int ih0[A_IT], iw0[A_IT];
       long long rbase[A_IT];
-      unsigned roff[A_IT];                                            // UNI: byte offset of pixel (ih0, iw0), this thread's chunk, from the tile's first image
+      // UNI: byte offset of pixel (ih0, iw0), this thread's chunk, from the first input row that this wavefront's rows touch, which
+      // is its first row's (none begins above it).  What follows lies within 4 GB (conv_window_fits)
+      unsigned roff[A_IT];
+      [[maybe_unused]] int n_first = 0, ih_first = 0;
       const int ch = tid % CPR;
-      const int n_first = MODE == M_FLAT ? uniform_div(tile_m * BM, OHW) : MODE == M_ZIGZAG ? uniform_div(tile_m * (BM / 4), a.PH * a.PW) : img;
 #pragma unroll
       for (int it = 0; it < A_IT; ++it) {
         const int row = (tid + it * NT) / CPR;
@@ -124,9 +126,13 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         }
         ih0[it] = ok ? oh * a.stride - a.pad : -(1 << 28);
         iw0[it] = ow * a.stride - a.pad;
+        if (UNI && it == 0) {
+          n_first = __builtin_amdgcn_readfirstlane(n);
+          ih_first = min(max(__builtin_amdgcn_readfirstlane(oh) * a.stride - a.pad, 0), a.H);
+        }
         // element offset of input pixel (ih0, iw0); only ever dereferenced together with an in-range tap
         rbase[it] = ok ? (long long)n * a.in_sN + (long long)ih0[it] * a.in_sH + (long long)iw0[it] * a.in_sW : 0;
-        if constexpr (UNI) roff[it] = ((unsigned)(n - n_first) * (unsigned)a.in_sN + (unsigned)ih0[it] * (unsigned)a.in_sH + (unsigned)iw0[it] * (unsigned)a.in_sW + ch * CE) * ESZ;
+        if constexpr (UNI) roff[it] = ((unsigned)(n - n_first) * (unsigned)a.in_sN + (unsigned)(ih0[it] - ih_first) * (unsigned)a.in_sH + (unsigned)iw0[it] * (unsigned)a.in_sW + ch * CE) * ESZ;
         if (DWPRO) rbase[it] = ok ? (long long)n * a.dw_sN : 0;    // image base of the depthwise input; (ih0, iw0) = pointwise pixel
       }
       // reduction position (r, s, c) of this thread's 16-byte chunk
@@ -144,11 +150,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           kc = kk - rs * a.C; kr = AnyDiv(a.S)(rs); ks = rs - kr * a.S;
         }
       }
-      // UNI: what the tile reads lies in windows of less than 4 GB (checked by the host)
-      const int m_last = min(tile_m * BM + BM, a.M_total) - 1;
-      const int n_last = MODE == M_FLAT ? uniform_div(m_last, OHW) : MODE == M_ZIGZAG ? uniform_div(m_last >> 2, a.PH * a.PW) : img;
-      const unsigned in_bytes = (unsigned)(((n_last - n_first) * a.in_sN + (a.H - 1) * a.in_sH + (a.W - 1) * a.in_sW + a.C) * ESZ);
-      const unsigned w_bytes = (unsigned)BN * (unsigned)a.Kred_pad * ESZ;
+      [[maybe_unused]] const T* abase = (const T*)a.in + ((long long)n_first * a.in_sN + (long long)ih_first * a.in_sH);
       const unsigned char* wbase = (const unsigned char*)a.w + (long long)tile_n * BN * a.Kred_pad * ESZ;
       unsigned woff[B_IT];
       const unsigned char* wrow[B_IT];
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
           kc += BKE;
         } else if constexpr (UNI) {
           const bool kok = kc + ch * CE < a.C;                     // (the padding of a 1x1 reduction)
-          const rsrc_t wa = make_window((const T*)a.in + (long long)n_first * a.in_sN, step < nsteps ? in_bytes : 0);
+          const rsrc_t wa = make_window(abase, step < nsteps ? kWindow : 0);
 #pragma unroll
           for (int it = 0; it < A_IT; ++it) {
             const bool ok = kok & ((unsigned)(ih0[it] + kr) < (unsigned)a.H) & ((unsigned)(iw0[it] + ks) < (unsigned)a.W);
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
             ks = 0; ++kr; koff_u += ((unsigned)a.in_sH - a.S * (unsigned)a.in_sW) * ESZ;
             if (kr == a.R) { kr = 0; kc += BKE; koff_u += (BKE - a.R * (unsigned)a.in_sH) * ESZ; }
           }
-          const rsrc_t wb = make_window(wbase, step < nsteps ? w_bytes : 0);
+          const rsrc_t wb = make_window(wbase, step < nsteps ? kWindow : 0);
 #pragma unroll
           for (int it = 0; it < B_IT; ++it) rb[it] = load_window(wb, woff[it], step < nsteps ? bstep * ROWB : 0);
           return;
@@ -380,11 +382,11 @@ __global__ __launch_bounds__(NT, 2) void conv_kernel(const ConvArgs a) {
         for (int d = 0; d < D - 1; ++d) {
           if (d < nsteps) {
             load_global(d, ra[d], rb[d], okm_[d]);
-          } else {                                                 // (or the sets are live from one tile to the next: 50 registers)
+          } else {             // (defined, without an instruction: or the sets are live from one tile to the next, 50 registers)
 #pragma unroll
-            for (int it = 0; it < A_IT; ++it) ra[d][it] = u32x4_t{};
+            for (int it = 0; it < A_IT; ++it) asm("" : "=v"(ra[d][it]));
 #pragma unroll
-            for (int it = 0; it < B_IT; ++it) rb[d][it] = u32x4_t{};
+            for (int it = 0; it < B_IT; ++it) asm("" : "=v"(rb[d][it]));
           }
         }
 #pragma unroll
@@ -2292,15 +2294,6 @@ static int launch_conv_uni(const ConvArgs& a, hipStream_t st) {
   }
   hipLaunchKernelGGL((conv_kernel<T, BM, BN, WM, WN, SCALAR, MODE, false, UNI>), dim3(a.grid), dim3(NT), lds, st, a);
   return (int)hipGetLastError();
-}
-
-// Do the images and the weight rows of a tile fit the 4 GB windows of the uniform-tap loader (with room for an offset's rounding)?
-bool conv_window_fits(const ConvArgs& a, int esz) {
-  const long long per = a.mode == M_ZIGZAG ? 4ll * a.PH * a.PW : (long long)a.OH * a.OW, lim = 0xffffff00ll;
-  const long long images = a.mode == M_FLAT || a.mode == M_ZIGZAG ? std::min<long long>(a.N, (128 - 1) / std::max(per, 1ll) + 2) : 1;
-  if (a.in_sN < 0 || a.in_sH < 0 || a.in_sW < 0 || a.in_sN > lim || a.in_sH > lim || a.in_sW > lim) return false;
-  const long double bytes = ((long double)(images - 1) * a.in_sN + (long double)a.H * a.in_sH + (long double)a.W * a.in_sW + a.C) * esz;
-  return bytes < (long double)lim && 128.0L * a.Kred_pad * esz < (long double)lim;
 }
 
 template <typename T, int BM, int BN, int WM, int WN, bool SCALAR, int MODE>

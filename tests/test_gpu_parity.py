@@ -515,6 +515,37 @@ def test_reductions_of_every_length(c, compute):
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("ksz", [1, 3])
+def test_tiles_of_images_beyond_4_gb(ksz, compute):
+    # two images of 2.2 GB each: 1x1, and 3x3 / 2 in channel-chunk order, address them from a tile's first row.  The rows on either side
+    # of the border between the images are what the same layers make of those rows alone
+    X = _xenos()
+    c, h, w, rows = (16 if compute else 8), 3000, 5800, 40
+
+    def session(n, h):
+        b = wg._Builder("large", (1, 1, 1, 1), 73, True, True)
+        b.g.input_shape, b.g.x, b._shapes = (n, c, h, w), None, [(n, c, h, w)]
+        t = b.cbr(0, 64 if compute else 32, 1, name="wide")
+        g = b.finish(b.cbr(t, 32, ksz, ksz // 2 + 1, ksz // 2, name="tested"))
+        return X.Session(g, link=2, compute=compute, in_dtype=compute, in_layout=1, out_dtype=compute, out_layout=1)
+
+    big, part = session(2, h), session(1, rows)
+    try:
+        big.x.uniform_(-1, 1)
+        big.run()
+        s = ksz // 2 + 1
+        for x, y, skip in ((big.x[:1, -rows:], big.y[:1, -(rows // s):], ksz // 2), (big.x[1:, :rows], big.y[1:, :rows // s], 0)):
+            part.x.copy_(x)
+            part.run()
+            got, ref = y[:, skip:].double(), part.y[:, skip:].double()   # (the cut leaves out the row above the first)
+            assert float((got - ref).abs().max()) <= TOL[compute] * float(ref.abs().max()) and float(ref.abs().max()) > 0.1
+        big.torch.cuda.synchronize()
+    finally:
+        big.close()
+        part.close()
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("stride,h,w", [(1, 1, 1), (1, 7, 9), (2, 8, 5)])
 def test_depthwise_padding_does_not_meet_infinite_weights(stride, h, w, compute):
     # a tap outside the map adds nothing, whatever its weight is: with an infinite weight in a corner of the window the outputs
