@@ -236,6 +236,11 @@ inline bool conv_window_fits(const ConvArgs& a, int esz) {
   const double lim = 0xffffff00ll;
   return a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && conv_tile_span(a, esz) < lim && 128.0 * a.Kred_pad * esz < lim;
 }
+// Do `rows` rows of an image, from where a block of positions begins, and 64 rows of weights fit the windows of pw_gemm_phase?
+constexpr unsigned kBlockWindow = 1u << 31;
+inline bool block_window_fits(const ConvArgs& a, int rows, int esz) {
+  return (double)a.in_sH * std::min(rows, a.H) * esz < kBlockWindow && 64.0 * a.Kred_pad * esz < 0xffffff00ll;
+}
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

@@ -1296,7 +1296,7 @@ struct Planner {
     for (int th = 1; th <= c.OH; ++th)
       for (int tw = 1; tw <= c.OW; ++tw) {
         const int PH = (th - 1) * s + 3, PWd = (tw - 1) * s + 3;
-        if (PH * PWd > kPwDwMaxPositions) break;
+        if (PH * PWd > kPwDwMaxPositions || !block_window_fits(c, PH, p.esz)) break;
         if (pwdw_lds_bytes(th, tw, s, p.esz) > lds_cap) break;
         const int ty = (c.OH + th - 1) / th, tx = (c.OW + tw - 1) / tw;
         double total = 0, longest = 0;
@@ -1395,7 +1395,7 @@ struct Planner {
     for (int th = 1; th <= YH; ++th)
       for (int tw = 1; tw <= XW; ++tw) {
         const int CH = pool ? (th - 1) * c.ps + c.pk : th, CW = pool ? (tw - 1) * c.ps + c.pk : tw;
-        if ((CH + 2 * ring) * (CW + 2 * ring) > kFireMaxPositions) break;
+        if ((CH + 2 * ring) * (CW + 2 * ring) > kFireMaxPositions || !block_window_fits(c, CH + 2 * ring + c.R - 1, p.esz)) break;
         const size_t lds = fire_lds_bytes(CH, CW, S, p.esz, pool ? 1 : 0, ring);
         if (lds > lds_cap) break;
         const int occ = 2 * lds <= lds_cap ? 2 : 1;
@@ -1686,11 +1686,12 @@ struct Planner {
         st.bytes_in = view_bytes(st.v_in); st.bytes_w = (long long)bytes; st.bytes_out = view_bytes(st.v_out);
       } else {
         if (!dwpro.active && !pairpro.active && !is_fc && !stem) {
+          // (the smallest blocks of the two kernels read up to seven rows; larger ones are chosen among those that fit their windows)
+          auto small_rows = [&](const View& v) { return v.sP * is.w * std::min(is.h, 7) * p.esz < (long long)kBlockWindow; };
           FireMatch fm;
           if (fire_consumers(i, &fm)) {
             const View& iv0 = p.views[tview[nd.in[0]]];
-            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
-                iv0.sP * is.h * is.w * p.esz < (1ll << 31))
+            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 && small_rows(iv0))
               return plan_fire(i, walk, fm);
           }
           const int dn = pwdw_consumer(i);
@@ -1705,8 +1706,7 @@ struct Planner {
           }
           if (dn >= 0 && pwdw_wanted(i, dn)) {
             const View& iv0 = p.views[tview[nd.in[0]]];
-            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 &&
-                iv0.sP * is.h * is.w * p.esz < (1ll << 31))
+            if (iv0.internal_nhwc() && !iv0.f32 && iv0.esz == p.esz && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && iv0.sN % p.ce == 0 && small_rows(iv0))
               return plan_pwdw(i, walk, dn);
           }
         }

@@ -24,7 +24,8 @@ constexpr int PG_STAGES_BYTES = 2 * (PG_BM + PG_BN) * LDS_ROW;
 // batch 32; timestamps inside the kernels showed it exposed once per chunk, 1.4 us per chunk of a 64-channel layer of
 // which 0.3 are work) passes behind the steps before it, across chunk boundaries too.  A ring of PG_DEPTH register sets
 // holds the requests in flight, two LDS stages hold the step being multiplied and the next one, one barrier per step.
-// pixel(chunk, row) gives the element offset of a row's input pixel in the image at `in` (-1 = no pixel); epilogue(chunk, acc) receives
+// `in` is the first pixel that the block reads; pixel(chunk, row) gives the element offset of a row's input pixel from there (-1 = no
+// pixel; with nine taps the block's first row and column are the neighbours' where the map has them); epilogue(chunk, acc) receives
 // the finished accumulators of a chunk (lane = row wave_m * 32 + l31, channels wave_n * 32 + 8 g + 4 lhalf + 0..3).
 // Requests go through buffer windows and are issued on every turn, past the end too (they then read nothing); with a branch around
 // them every fourth step waited for all loads in flight, a memory round trip of about 1 us: MobileNet batch 1 102.0 -> 90.1 us, fp32
@@ -52,10 +53,9 @@ __device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, const T* in, in
   const int l31 = lane & 31, lhalf = lane >> 5;
   const int nsteps = a.Kred_pad / BKE, G = nchunks * nsteps;
   const int ch = tid % CPR;
-  // (an image takes less than 2 GB and 64 rows of weights less than 4: checked by the host.  kFar is beyond any such window, and stays so
-  // with a step's offset added)
-  constexpr unsigned kFar = 1u << 31;
-  const unsigned w_bytes = (unsigned)BN * (unsigned)a.Kred_pad * ESZ, in_bytes = (unsigned)((a.H - 1) * (int)a.in_sH + (a.W - 1) * (int)a.in_sW + a.C) * ESZ;
+  // (what the block reads takes less than 2 GB and 64 rows of weights less than 4: checked by the host.  kFar is beyond the window, and
+  // stays so with a step's offset added)
+  constexpr unsigned kFar = kBlockWindow;
   const unsigned char* wbase = (const unsigned char*)a.w + (long long)k_row0 * a.Kred_pad * ESZ;
   unsigned woff[B_IT];
 #pragma unroll
@@ -80,7 +80,7 @@ __device__ __forceinline__ void pw_gemm_phase(const ConvArgs& a, const T* in, in
         if constexpr (TAPS == 9) ayx[it] = coord(ld_chunk, (tid + it * NT) / CPR);
       }
     }
-    const rsrc_t wa = make_window(in, more ? in_bytes : 0), wb = make_window(wbase, more ? w_bytes : 0);
+    const rsrc_t wa = make_window(in, more ? kFar : 0), wb = make_window(wbase, more ? kWindow : 0);
     if constexpr (TAPS == 9) {
       const int cch = ld_step / 9, tap = ld_step - cch * 9, dy = tap / 3 - 1, dx = tap - (tap / 3) * 3 - 1;
       const int toff = (dy * (int)a.in_sH + dx * (int)a.in_sW + cch * BKE) * ESZ;
@@ -196,7 +196,7 @@ template <typename T>
 __global__ __launch_bounds__(NT, 2) void pwdw_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   using tr = Tr<T>;
-  constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
+  constexpr int CE = tr::CE, ESZ = (int)sizeof(T);
   constexpr int BM = PD_BM, BN = PD_BN;
   constexpr int MP = pwdw_mid_pitch(ESZ);
   constexpr int CG = BN / CE;                                      // 16-byte channel groups of a position
@@ -254,11 +254,12 @@ __global__ __launch_bounds__(NT, 2) void pwdw_kernel(const ConvArgs a) {
     }
     // ---- pointwise GEMM of the block, 64 positions x 64 channels per chunk over all input channels, and the pointwise
     // chain's epilogue into the LDS block: lane = position wave_m*32 + l31, channels wave_n*32 + 8*g + 4*lhalf + (0..3)
-    pw_gemm_phase<T>(a, (const T*)a.in + (long long)n * a.in_sN, tile_n * BN, s_op, (npos + BM - 1) / BM, [&](int mc, int row) -> int {
+    const T* first = (const T*)a.in + (long long)n * a.in_sN + (long long)y_lo * a.in_sH + (long long)x_lo * a.in_sW;
+    pw_gemm_phase<T>(a, first, tile_n * BN, s_op, (npos + BM - 1) / BM, [&](int mc, int row) -> int {
       const int m = mc * BM + row;
       if (m >= npos) return -1;
       const int py = by_wv(m), px = m - py * wv;
-      return (y_lo + py) * (int)a.in_sH + (x_lo + px) * (int)a.in_sW;
+      return py * (int)a.in_sH + px * (int)a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * BM + wave_m * 32 + l31;
       if (m < npos) {
@@ -331,7 +332,7 @@ static int launch_pwdw_t(const ConvArgs& a, hipStream_t st) {
       a.OH != (a.H + 2 - 3) / s + 1 || a.OW != (a.W + 2 - 3) / s + 1 || a.th < 1 || a.tw < 1 ||
       a.tiles_y != (a.OH + a.th - 1) / a.th || a.tiles_x != (a.OW + a.tw - 1) / a.tw || a.tiles_m != a.N * a.tiles_y * a.tiles_x ||
       a.tiles_n != (a.K + PD_BN - 1) / PD_BN || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
-      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || a.in_sH * a.H * ESZ >= (1ll << 31) || 64ll * a.Kred_pad * ESZ >= (1ll << 32) - 256 || a.out_sP < a.K)
+      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || !block_window_fits(a, (a.th - 1) * s + 3, ESZ) || a.out_sP < a.K)
     return (int)hipErrorInvalidValue;
   const int positions = ((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3);
   const int lds = pwdw_lds(positions, ESZ);
@@ -470,11 +471,13 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       qsc[g] = *(const f32x4_t*)(a.scale + (c < S ? c : 0));
       qsh[g] = *(const f32x4_t*)(a.shift + (c < S ? c : 0));
     }
-    pw_gemm_phase<T, TAPS1>(a, (const T*)a.in + (long long)n * a.in_sN, 0, s_b, (npos + 63) / 64, [&](int mc, int row) -> int {
+    const int yb = TAPS1 == 9 && y_lo > 0 ? 1 : 0, xb = TAPS1 == 9 && x_lo > 0 ? 1 : 0;   // rows and columns read before the block's
+    const T* first = (const T*)a.in + (long long)n * a.in_sN + (long long)(y_lo - yb) * a.in_sH + (long long)(x_lo - xb) * a.in_sW;
+    pw_gemm_phase<T, TAPS1>(a, first, 0, s_b, (npos + 63) / 64, [&](int mc, int row) -> int {
       const int m = mc * 64 + row;
       if (m >= npos) return -1;
       const int py = by_wv(m), px = m - py * wv;
-      return (y_lo + py) * (int)a.in_sH + (x_lo + px) * (int)a.in_sW;
+      return (yb + py) * (int)a.in_sH + (xb + px) * (int)a.in_sW;
     }, [&](int mc, const f32x16_t& acc) {
       const int m = mc * 64 + wave_m * 32 + l31;
       if (m < npos) {
@@ -763,7 +766,7 @@ static int launch_fire_t(const ConvArgs& a, hipStream_t st) {
       a.K < 1 || a.K > 64 || (a.K * ESZ) % 32 != 0 || a.OH != a.H || a.OW != a.W ||
       (a.fire_E[0] < 1 && a.fire_E[1] < 1) ||
       a.tiles_n < 1 || a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
-      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C || a.in_sH * a.H * ESZ >= (1ll << 31) || 64ll * a.Kred_pad * ESZ >= (1ll << 32) - 256)
+      a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C)
     return (int)hipErrorInvalidValue;
   for (int e = 0; e < 2; ++e) {   // a part with no channels does not exist (a ConvX -> ConvY pair instead of a module)
     if (a.fire_E[e] == 0) continue;
@@ -787,7 +790,7 @@ static int launch_fire_t(const ConvArgs& a, hipStream_t st) {
   const int ring = a.fire_E[1] > 0 ? 1 : 0;
   const int positions = (ch + 2 * ring) * (cw + 2 * ring);
   const int lds = fire_lds(positions, a.K, ESZ, pool_pos);
-  if (positions > kFireMaxPositions || lds > 160 * 1024) return (int)hipErrorInvalidValue;
+  if (positions > kFireMaxPositions || lds > 160 * 1024 || !block_window_fits(a, ch + 2 * ring + a.R - 1, ESZ)) return (int)hipErrorInvalidValue;
   if (first3) return pool ? launch_fire_inst<T, true, 9>(a, lds, st) : launch_fire_inst<T, false, 9>(a, lds, st);
   return pool ? launch_fire_inst<T, true, 1>(a, lds, st) : launch_fire_inst<T, false, 1>(a, lds, st);
 }

@@ -478,6 +478,20 @@ def test_linked_3x3_pair_of_images_just_below_the_limit():
     assert [c.get("loader") for c in chains].count("fire") == 1
 
 
+@pytest.mark.parametrize("pattern,compute", [("pwdw", X.XENOS_F32), ("pwdw", X.XENOS_BF16), ("fire", X.XENOS_BF16), ("fire3", X.XENOS_BF16)])
+def test_images_beyond_2_gb_stay_linked(pattern, compute):
+    # the windows of pw_gemm_phase cover the rows of a block, not an image (2.2 GB here)
+    b = undrawn((1, 8, 2950, 2950))
+    t = b.cbr(0, 128 if compute else 64, 1, name="a")
+    if pattern == "pwdw":
+        t = b.cbr(b.cbr(t, 16, 1, name="pw"), 16, 3, 2, 1, groups=16, name="dw")
+    else:
+        t = b.cbr(t, 32, 3 if pattern == "fire3" else 1, 1, int(pattern == "fire3"), name="sq")
+        t = b.concat([b.cbr(t, 16, 1, name="e1"), b.cbr(t, 16, 3, 1, 1, name="e3")]) if pattern == "fire" else b.cbr(t, 16, 1, name="e1")
+    chains = plan_json(b.finish(b.cbr(t, 8, 3, 1, 1, name="z")), link=3, compute=compute)["plan"]["chains"]
+    assert [c.get("loader") for c in chains].count(pattern[:4]) == 1
+
+
 def test_pattern_first_layer_pair_on_chip():
     g = wg.build(3, 2, draw=False)
     l3 = plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]

@@ -545,6 +545,40 @@ def test_tiles_of_images_beyond_4_gb(ksz, compute):
         part.close()
 
 
+@pytest.mark.parametrize("pattern,compute", [("pwdw", 0), ("pwdw", 1), ("fire", 1), ("fire3", 1)])
+def test_linked_chains_of_images_beyond_2_gb(pattern, compute):
+    # the last rows of a 2.2 GB image are what the same chains make of those rows alone (but for the rows next to the cut)
+    X = _xenos()
+    side, rows = 2950, 48
+
+    def session(h):
+        b = wg._Builder("large", (1, 1, 1, 1), 79, True, True)
+        b.g.input_shape, b.g.x, b._shapes = (1, 8, h, side), None, [(1, 8, h, side)]
+        t = b.cbr(0, 128 if compute else 64, 1, name="a")
+        if pattern == "pwdw":
+            t = b.cbr(b.cbr(t, 16, 1, name="pw"), 16, 3, 2, 1, groups=16, name="dw")
+        else:
+            t = b.cbr(t, 32, 3 if pattern == "fire3" else 1, 1, int(pattern == "fire3"), name="sq")
+            t = b.concat([b.cbr(t, 16, 1, name="e1"), b.cbr(t, 16, 3, 1, 1, name="e3")]) if pattern == "fire" else b.cbr(t, 16, 1, name="e1")
+        g = b.finish(b.cbr(t, 8, 3, 1, 1, name="z"))
+        return X.Session(g, link=3, compute=compute, in_dtype=compute, in_layout=1, out_dtype=compute, out_layout=1)
+
+    big, part = session(side), session(rows)
+    try:
+        for s in (big, part):
+            assert [c.get("loader") for c in s.info["chains"]].count(pattern[:4]) == 1
+        big.x.uniform_(-1, 1)
+        part.x.copy_(big.x[:, -rows:])
+        big.run()
+        part.run()
+        n = part.y.shape[1] - 4
+        got, ref = big.y[:, -n:].double(), part.y[:, -n:].double()
+        assert float((got - ref).abs().max()) <= TOL[compute] * float(ref.abs().max()) and float(ref.abs().max()) > 0.1
+    finally:
+        big.close()
+        part.close()
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("stride,h,w", [(1, 1, 1), (1, 7, 9), (2, 8, 5)])
 def test_depthwise_padding_does_not_meet_infinite_weights(stride, h, w, compute):
