@@ -97,6 +97,12 @@ __device__ __forceinline__ float fmx_raw(float a, float b) {
 // ReLU as a maximum, or nothing: max(y, NaN) is y for every y, infinite ones too (the lowest finite number as a floor would
 // replace -infinity).  For fmx_raw: of fmaxf the compiler makes a maximum and a selection per value.
 __device__ __forceinline__ float relu_floor(int relu) { return relu ? 0.f : __builtin_nanf(""); }
+// the same maximum with the floor in a scalar register
+__device__ __forceinline__ float fmx_floor(float y, float lo) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "s"(lo), "v"(y));
+  return r;
+}
 
 // Two-group channel shuffle done by a store: CE finished channels of a pixel (`mine`) and the same channels of the other
 // part of the concat (`oth`) alternate in the output, `first` = mine at the even positions.  Two 16-byte stores.

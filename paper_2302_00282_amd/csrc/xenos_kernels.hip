@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(V2_NT) void conv3x3_kernel(const ConvArgs a) {
         rbase[i] = ok ? (long long)n * a.res_sN + (long long)(oh * a.OW + ow) * a.res_sP : 0;
       }
     }
-    const float lo = a.relu ? 0.f : -3.4028235e38f;                // ReLU as a clamp: no branch per value
+    const float lo = relu_floor(a.relu);                           // ReLU as a clamp: no branch per value
     // (the tile's scale / shift and the output offsets of its rows were put into LDS by epilogue_tables() after the first
     // tap of the tile's last chunk: eight barriers ago)
     const float* s_aff = (const float*)(smem + v2_lds(BN));
@@ -1134,7 +1134,7 @@ __global__ __launch_bounds__(V2_NT) void conv3x3_kernel(const ConvArgs a) {
                 }
               }
 #pragma unroll
-              for (int e = 0; e < 4; ++e) y[e] = fmx(y[e], lo);
+              for (int e = 0; e < 4; ++e) y[e] = fmx_floor(y[e], lo);
               bool mine = true;                                    // does this lane hold the finished value?
               if (MODE == M_ZIGZAG) {
                 // the window's four pixels are lanes 4w .. 4w+3: butterfly over the quad, lane j keeps group g == j

@@ -743,6 +743,71 @@ def test_linked_kernels_launched_by_several_threads():
         s.close()
 
 
+def _without_relu(kernel, compute):
+    """A graph whose convolutions have no ReLU, one of them on `kernel`, with infinite values on its way; and how to plan it."""
+    b = wg.builder("inf_" + kernel, (2, 3 if kernel in ("stem_lds", "pair") else 16, 24, 22), 67, nonzero_bias=True)
+    conv = lambda t, k, r, s=1, groups=1: b.cbr(t, k, r, s, r // 2, groups=groups, bn=False, relu=False)
+    op = lambda t: b.g.ops[t - 1].params
+    kw = dict(link=3, out_layout=1, out_dtype=compute)
+    loader = kernel
+    if kernel == "stem_lds":
+        t = conv(0, 64, 3 if compute == 0 else 7, 2)
+        op(t)["bias"][5] = -np.inf
+        t = b.avgpool(b.maxpool(t, 3, 2, 1), 2, 2)
+        loader = "stem"
+    elif kernel == "conv3x3":
+        t = conv(b.cbr(0, 64, 1, name="pre"), 72, 3)
+        op(t)["bias"][5] = -np.inf
+        kw.update(link=2, tile=7)
+        loader = "vector"
+    elif kernel == "dwpw":
+        t = conv(conv(b.cbr(0, 64, 1, name="pre"), 64, 3, groups=64), 40, 1)
+        op(t)["bias"][5] = -np.inf
+        loader = "vector"
+    elif kernel == "pwdw":
+        t = conv(b.cbr(0, 16, 1, name="pre"), 24, 1)
+        op(t)["bias"][5] = -np.inf
+        t = conv(t, 24, 3, groups=24)
+        op(t)["weight"][5] = np.abs(op(t)["weight"][5])
+        t = conv(t, 16, 3)
+        op(t)["weight"][:, 5] = 1e-20
+    elif kernel in ("fire squeeze", "fire expand"):
+        t = conv(b.cbr(0, 32, 1, name="pre"), 16, 1)
+        if kernel == "fire squeeze":
+            op(t)["bias"][5] = -np.inf
+        e1, e3 = conv(t, 24, 1), conv(t, 24, 3)
+        for e in (e1, e3):
+            if kernel == "fire squeeze":
+                op(e)["weight"][:, 5] = 1e-20
+            else:
+                op(e)["bias"][3] = -np.inf
+        t = conv(b.concat([e1, e3]), 16, 1)
+        op(t)["weight"][:] = np.abs(op(t)["weight"]) * np.float32(1e-20)
+        loader = "fire"
+    elif kernel == "pair":
+        # -infinity at one pixel and weights above zero: averages of windows that are infinite in part
+        t = conv(conv(0, 64, 3), 64, 3)
+        for o in b.g.ops:
+            o.params["weight"][:] = np.abs(o.params["weight"]) if "weight" in o.params else 0
+        t = b.maxpool(b.avgpool(t, 2, 2), 2, 2)
+        b.g.x[1, 1, 9, 8] = -np.inf
+    return b.finish(t), loader, kw
+
+
+@pytest.mark.parametrize("kernel,compute", [(k, c) for k in ("stem_lds", "conv3x3") for c in (0, 1)])
+def test_infinite_values_pass_where_there_is_no_relu(kernel, compute):
+    g, loader, kw = _without_relu(kernel, compute)
+    ref = xo.forward(g)
+    y, info = run_gpu(g, compute=compute, **kw)
+    chains = [c for c in info["chains"] if c.get("loader") == loader]
+    assert chains and (kernel != "conv3x3" or any(c["halo"] for c in chains)) and (kernel != "dwpw" or any(c["dw_linked"] for c in chains))
+    fin = np.isfinite(ref)
+    assert not fin.all() and not np.isnan(ref).any()
+    assert np.array_equal(np.isfinite(y), fin) and np.array_equal(y[~fin], ref[~fin].astype(np.float32))
+    if fin.any():
+        assert rel_err(y[fin], ref[fin]) <= TOL[compute]
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("h,w,c,s,e1,e3,n,pool,tail", [(13, 13, 32, 16, 64, 64, 2, 0, "conv"), (27, 21, 64, 32, 128, 72, 1, 3, "conv"),
                                                        (9, 30, 24, 48, 40, 200, 3, 0, "conv"), (14, 14, 128, 64, 256, 256, 1, 2, "conv"),
