@@ -2503,14 +2503,14 @@ __global__ __launch_bounds__(NT, 3) void dwpw_kernel(const ConvArgs a) {
     }
     constexpr int SPB = BN * ESZ + 16;
     unsigned char* stg = s_panel;                                  // 64 rows x SPB bytes, inside the operand buffers
-    const float lo = a.relu ? 0.f : -3.4028235e38f;
+    const float lo = relu_floor(a.relu);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int c = wave_n * 32 + g * 8 + lhalf * 4, k0 = tile_n * BN + c;
       const f32x4_t sc = *(const f32x4_t*)(a.scale + k0), sh = *(const f32x4_t*)(a.shift + k0);
       float y[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
+      for (int e = 0; e < 4; ++e) y[e] = fmx_floor(acc[4 * g + e] * sc[e] + sh[e], lo);
       const int srow = wave_m * 32 + l31;
       if constexpr (sizeof(T) == 2) {
         uint2 o;
