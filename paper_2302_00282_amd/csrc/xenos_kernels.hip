@@ -1494,7 +1494,7 @@ __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
     abase[i] = ((ty < a.th && tx < a.tw) ? ty * PR_PW + tx : 0) * LDS_ROW + lhalf * 16;
   }
   const int nunits = (PP + 31) / 32;
-  const float lo1 = a.dw_relu ? 0.f : -3.4028235e38f, lo2 = a.relu ? 0.f : -3.4028235e38f;
+  const float lo1 = relu_floor(a.dw_relu), lo2 = relu_floor(a.relu);
   __syncthreads();
 
   for (;;) {
@@ -1534,7 +1534,7 @@ __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
           const f32x4_t sc = *(const f32x4_t*)(s_aff + c), sh = *(const f32x4_t*)(s_aff + PR_C + c);
           float y[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = fmx(c1[4 * g + e] * sc[e] + sh[e], lo1);
+          for (int e = 0; e < 4; ++e) y[e] = fmx_floor(c1[4 * g + e] * sc[e] + sh[e], lo1);
           uint2 o;
           o.x = inside ? f2bf2(y[0], y[1]) : 0u;                   // positions outside the image: padding of the second convolution
           o.y = inside ? f2bf2(y[2], y[3]) : 0u;
@@ -1602,7 +1602,7 @@ __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
         const f32x4_t sc = *(const f32x4_t*)(s_aff + 2 * PR_C + c), sh = *(const f32x4_t*)(s_aff + 3 * PR_C + c);
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = fmx(acc[i][4 * g + e] * sc[e] + sh[e], lo2);
+        for (int e = 0; e < 4; ++e) y[e] = fmx_floor(acc[i][4 * g + e] * sc[e] + sh[e], lo2);
         bool mine = true;
         if (MODE == M_ZIGZAG) {
           // the window's four pixels are lanes 4w .. 4w+3: butterfly over the quad, lane i keeps group g == i
