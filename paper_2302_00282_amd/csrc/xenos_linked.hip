@@ -265,14 +265,14 @@ __global__ __launch_bounds__(NT, 2) void pwdw_kernel(const ConvArgs a) {
       if (m < npos) {
         const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * MP;
-        const float lo = a.relu ? 0.f : -3.4028235e38f;
+        const float lo = relu_floor(a.relu);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = wave_n * 32 + g * 8 + lhalf * 4;
           const f32x4_t sc = psc[g], sh = psh[g];
           float y[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
+          for (int e = 0; e < 4; ++e) y[e] = fmx_floor(acc[4 * g + e] * sc[e] + sh[e], lo);
           if constexpr (sizeof(T) == 2) {
             uint2 o;
             o.x = f2bf2(y[0], y[1]);
