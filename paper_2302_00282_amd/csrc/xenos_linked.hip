@@ -483,7 +483,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       if (m < npos) {
         const int py = by_wv(m), px = m - py * wv;
         unsigned char* dst = s_sq + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * SQP;
-        const float lo = a.relu ? 0.f : -3.4028235e38f;
+        const float lo = relu_floor(a.relu);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int c = wave_n * 32 + g * 8 + lhalf * 4;
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
             const f32x4_t sc = qsc[g], sh = qsh[g];
             float y[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
+            for (int e = 0; e < 4; ++e) y[e] = fmx_floor(acc[4 * g + e] * sc[e] + sh[e], lo);
             if constexpr (sizeof(T) == 2) {
               uint2 o;
               o.x = f2bf2(y[0], y[1]);
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     };
     auto tile_epilogue = [&](int which, int j, int mc, const f32x16_t& acc, const f32x4_t* esc, const f32x4_t* esh) __attribute__((always_inline)) {
       const int E = a.fire_E[which];
-      const float lo = a.fire_relu[which] ? 0.f : -3.4028235e38f;
+      const float lo = relu_floor(a.fire_relu[which]);
       // finished values change hands inside the wavefront only
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
         const f32x4_t sc = esc[g], sh = esh[g];
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = fmx(acc[4 * g + e] * sc[e] + sh[e], lo);
+        for (int e = 0; e < 4; ++e) y[e] = fmx_floor(acc[4 * g + e] * sc[e] + sh[e], lo);
         if constexpr (sizeof(T) == 2) {
           uint2 o;
           o.x = f2bf2(y[0], y[1]);

@@ -794,7 +794,7 @@ def _without_relu(kernel, compute):
     return b.finish(t), loader, kw
 
 
-@pytest.mark.parametrize("kernel,compute", [(k, c) for k in ("stem_lds", "conv3x3", "dwpw", "pwdw") for c in (0, 1)] + [("pair", 1)])
+@pytest.mark.parametrize("kernel,compute", [(k, c) for k in ("stem_lds", "conv3x3", "dwpw", "pwdw", "fire squeeze", "fire expand") for c in (0, 1)] + [("pair", 1)])
 def test_infinite_values_pass_where_there_is_no_relu(kernel, compute):
     g, loader, kw = _without_relu(kernel, compute)
     ref = xo.forward(g)
