@@ -1332,7 +1332,7 @@ constexpr int PR_K1 = kPairRed;               // reduction slots of the first co
 constexpr int PR_INMAX = kPairInMax;          // positions of the staged input block, (TH+4) x (TW+4)
 constexpr int PR_PBYTES = PR_PPMAX * LDS_ROW;
 constexpr int PR_OFF_XIN = PR_PBYTES;
-constexpr int PR_OFF_AFF = PR_OFF_XIN + PR_INMAX * 8;
+constexpr int PR_OFF_AFF = PR_OFF_XIN + PR_INMAX * 8 + 16;   // (and a position of zeros)
 constexpr int PR_OFF_ROWPOS = PR_OFF_AFF + 4 * PR_C * 4;
 constexpr int PR_OFF_ROWOFF = PR_OFF_ROWPOS + PR_BM * 4;
 constexpr int PR_SPW = 32 * 2 + 8;              // staging row pitch: a wavefront's 32 channels + 8 bytes (18 dwords: the 32 rows of a store pass hit 32 bank pairs)
@@ -1456,7 +1456,7 @@ __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
   };
 
   // ---- set-up: scale / shift, row table, zeroed input block ---------------------------------------------------
-  for (int i = tid; i < PR_INMAX * 2; i += NTH) ((uint32_t*)s_xin)[i] = 0u;   // channel slots beyond pair_C stay zero
+  for (int i = tid; i < PR_INMAX * 2 + 4; i += NTH) ((uint32_t*)s_xin)[i] = 0u;   // channel slots beyond pair_C stay zero
   {
     const int w = tid / PR_C, c = tid - w * PR_C;                  // NTH == 4 * PR_C
     static_assert(NTH == 4 * PR_C, "one thread per folded scale / shift value");
@@ -1516,10 +1516,10 @@ __global__ __launch_bounds__(PR_NT, 2) void conv_pair_kernel(const ConvArgs a) {
       for (int e = 0; e < 16; ++e) c1[e] = 0.f;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        // (taps beyond the ninth read position 0 of the window: their weight slots are zero and the block holds finite values)
+        // (taps beyond the ninth read the zeros behind the block, as their weights are: an infinite value times zero is none)
         const int o0 = tap_off(j, 0), o1 = tap_off(j, 1);
-        const uint2 t0 = *(const uint2*)(xb + (o0 >= 0 ? o0 : 0));
-        const uint2 t1 = *(const uint2*)(xb + (o1 >= 0 ? o1 : 0));
+        const uint2 t0 = *(const uint2*)(o0 >= 0 ? xb + o0 : s_xin + PR_INMAX * 8);
+        const uint2 t1 = *(const uint2*)(o1 >= 0 ? xb + o1 : s_xin + PR_INMAX * 8);
         const u32x4_t fa = {t0.x, t0.y, t1.x, t1.y};
         c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w1[j]), __builtin_bit_cast(bf16x8_t, fa), c1, 0, 0, 0);
       }
