@@ -73,14 +73,14 @@ __device__ __forceinline__ void unit_request(rsrc_t wp, u32x4_t (&rb)[UN_RING]) 
 
 // Transposed GEMM of `nrows` LDS rows (pitch bytes apart) with the blocks of `w`, a wavefront per part.  rb holds the requested
 // fragments of the wavefront's first part; as a part's last ones are used up, those of its next part are requested, behind the last
-// part those of `next`.  pre(block, row0) runs before a part's reduction, epi(block, row0, half, acc) receives each finished 32 x 32
+// part those of `next` (NEXT; otherwise none: empty requests pass through the data path behind real ones, up to 0.7 us a tile).  pre(block, row0) runs before a part's reduction, epi(block, row0, half, acc) receives each finished 32 x 32
 // half of it: lane = row row0 + l31, channels 8 g + 4 lhalf + (0..3) of the block in acc[4 g ..].
-template <typename T, typename PreFn, typename EpiFn>
+template <typename T, bool NEXT, typename PreFn, typename EpiFn>
 __device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN_RING], rsrc_t next, const unsigned char* s_rows, int pitch, int nrows, PreFn pre, EpiFn epi) {
   const unsigned lane = thread_here() & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l31 = (int)lane & 31, lhalf = (int)lane >> 5;
   const int nkg = w.nkg, ncb = w.ncb;
-  if (wave >= w.parts) unit_request(next, rb);
+  if (NEXT && wave >= w.parts) unit_request(next, rb);
 #pragma unroll 1
   for (int u = wave; u < w.parts; u += UN_NW) {
     const int rg = uniform_div(u, ncb), cb = u - rg * ncb, row0 = rg * 64;
@@ -118,6 +118,7 @@ __device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN
         }
       }
     };
+    const bool more = NEXT || u + UN_NW < w.parts;                 // (uniform)
     auto round = [&](int k0, auto MORE) __attribute__((always_inline)) {
 #pragma unroll
       for (int d0 = 0; d0 < UN_RING; d0 += 4) {
@@ -128,9 +129,11 @@ __device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN
           for (int d = 0; d < 3; ++d)
             if (k0 + d0 + d < nkg) block(k0, d0 + d, std::integral_constant<int, 1>());
         }
+        if (decltype(MORE)::value || more) {
 #pragma unroll
-        for (int d = d0; d < d0 + 4; ++d)
-          rb[d] = decltype(MORE)::value ? load_window(wp, lane * 16u + (unsigned)(k0 + UN_RING + d) * 1024u) : load_window(wn, lane * 16u + d * 1024u);
+          for (int d = d0; d < d0 + 4; ++d)
+            rb[d] = decltype(MORE)::value ? load_window(wp, lane * 16u + (unsigned)(k0 + UN_RING + d) * 1024u) : load_window(wn, lane * 16u + d * 1024u);
+        }
       }
     };
     int k0 = 0;
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
 
     f32x4_t sc[4], sh[4];                                          // scale and shift of the lane's channels
     // ---- first pointwise chain, into the stencil's block ----------------------------------------------------
-    unit_gemm<T>(w1, rb, w2.window(wave), s_x, PX, npos,
+    unit_gemm<T, true>(w1, rb, w2.window(wave), s_x, PX, npos,
       [&](int cb, int) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
         oth[h][u] = a.ileave && ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
       }
     };
-    unit_gemm<T>(w2, rb, make_window(a.w, 0), s_x, PM, npx,
+    unit_gemm<T, false>(w2, rb, make_window(a.w, 0), s_x, PM, npx,
       [&](int cb, int row0) __attribute__((always_inline)) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
