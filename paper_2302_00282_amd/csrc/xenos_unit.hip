@@ -306,13 +306,18 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
       return q < npx && oy < a.OH && ox < a.OW && cb * 32 + g16 * CE < a.K;
     };
     auto other = [&](int cb, int row, int h) __attribute__((always_inline)) {
+      if (!a.ileave) {                                             // (uniform: no shuffle, no addresses to work out)
+#pragma unroll
+        for (int u = 0; u < STG_IT; ++u) asm("" : "=v"(oth[h][u]));
+        return;
+      }
       const int ln = thread_here() & 63;
 #pragma unroll
       for (int u = 0; u < STG_IT; ++u) {
         const int k0 = cb * 32 + (ln + u * 64) % G * CE;
         long long p;
         const bool ok = pixel(ln, cb, row, u, p);
-        oth[h][u] = a.ileave && ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
+        oth[h][u] = ok ? *(const u32x4_t*)((const T*)a.res + (long long)n * a.res_sN + p * a.res_sP + k0) : z;
       }
     };
     unit_gemm<T, false>(w2, rb, make_window(a.w, 0), s_x, PM, npx,
