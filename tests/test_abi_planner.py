@@ -138,6 +138,15 @@ def test_global_average_takes_the_tile_that_pads_less(hw, rows, compute):
     assert len(chain) == 1 and chain[0]["bm"] == rows and chain[0]["bn"] == 64
 
 
+@pytest.mark.parametrize("compute,rows", [(X.XENOS_F32, 64), (X.XENOS_BF16, 128)])
+def test_global_average_at_seven_eighths_of_the_rows(compute, rows):
+    # 20x20: 448 rows against 512, which pays in fp32 only
+    b = undrawn((32, 64, 20, 20))
+    g = b.finish(b.gap(b.cbr(b.cbr(0, 64, 1, name="a"), 1000, 1, name="c")))
+    chain, = [c for c in plan_json(g, link=2, compute=compute)["plan"]["chains"] if c.get("mode") == "gap"]
+    assert chain["bm"] == rows and chain["bn"] == 64
+
+
 def test_linking_patterns_of_the_workloads():
     g2 = wg.build(2, 1, draw=False)
     res = plan_json(g2, link=2, compute=X.XENOS_BF16)["plan"]
