@@ -2143,9 +2143,11 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
           if (4 * j + 2 * i >= ntaps) continue;                    // (uniform)
           const f32x4_t v = *(const f32x4_t*)(xin + tap[j][i]);
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
+          for (int c = 0; c < 3; ++c) {
+            if (c >= a.pair_C) break;                              // (uniform)
 #pragma unroll
             for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[2 * j + i][b][c], v[c], acc[b], 0, 0, 0);
+          }
         }
         continue;
       }
