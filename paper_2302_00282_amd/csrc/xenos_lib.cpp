@@ -643,9 +643,7 @@ struct Planner {
         c.tiles_y = (c.PH + c.pph - 1) / c.pph; c.tiles_x = (c.PW + c.ppw - 1) / c.ppw;
       }
       c.tiles_m = c.N * c.tiles_y * c.tiles_x; c.tiles_n = 1; c.ntiles = c.tiles_m; c.xcd_m = 8;
-      // as many workgroups as are resident (stem_lds_kernel's launch bounds), so that none starts, with its weights and tables, behind another
-      const int resident = c.R * c.S > 12 || p.dt == DT_F32 ? 2 : c.K > 32 ? 3 : 4;
-      c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, resident * num_cu)) : 1;
+      c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, stem_lds_resident(c.R * c.S, c.K, p.esz, c.pool != POOL_NONE) * num_cu)) : 1;
       st.cfg = kStemLdsCfg;
       st.lds = stem_lds_bytes(c.R * c.S, c.K, p.esz);
       return XENOS_OK;

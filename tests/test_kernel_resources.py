@@ -92,3 +92,11 @@ def test_first_layer_plans_count_the_lds_they_take(kernels, compute, k, ksz, poo
         assert small.get("lds", 0) < lds and (small.get("loader") != "stem" or small["bm"] != 128)
     except X.XenosError as e:                                      # (nor does any other kernel fit that)
         assert e.status == X.XENOS_EUNSUPPORTED and compute == 1
+
+
+@pytest.mark.parametrize("compute,k,ksz,pool", FIRST_LAYERS)
+def test_first_layer_plans_launch_what_a_unit_holds(kernels, compute, k, ksz, pool):
+    # 512 registers per lane and SIMD in granules of 8 (a workgroup has one wavefront on each of the four), 160 KB of LDS in granules of 1280
+    chain, meta = first_layer(kernels, compute, k, ksz, pool)
+    fit = min(512 // (-(-meta["vgpr_count"] // 8) * 8), 160 * 1024 // (-(-meta["group_segment_fixed_size"] // 1280) * 1280))
+    assert chain["grid"] == min(chain["tiles_m"], fit * X.MI355X["num_cu"]) and chain["tiles_m"] > chain["grid"]
