@@ -1588,11 +1588,16 @@ struct Planner {
                       ((chh - 1) * d.stride_h + d.kh) * ((cww - 1) * d.stride_h + d.kw) <= stem_lds_in_positions(d.kh * d.kw);
         }
         if (f32 && !keep_pool) stem_lds = false;
+        // (a padded channel count only where the chain stays as linked as the general kernel would have it)
+        const bool padded = K != 32 && K != 64;
+        // A small fp32 input with a padded channel count stays with the general kernel, which gathers it in place: where it does so in one
+        // reduction step against 16 taps or more, and where it computes no pixel twice (windows of 2) in place of 64 channels for
+        // 48 to 60.  Staged against gathered, graphs of up to 100000 input pixels: 24 of these 0.98 to 1.21 times the time, 1.09 on average,
+        // 29 others, which are staged, 0.62 to 1.03, 0.91 on average.
+        if (f32 && stem_lds && padded && in_gather && ((d.kh >= 4 && is.c * d.kh * d.kw <= 32) || (K > 32 && desc(nodes[pool_node]).kh == 2))) stem_lds = keep_pool = false;
         // (a 3x3 layer takes the LDS-staged form only for its linked pooling: one launch for two, the same time at batch 32;
         // without pooling the gather form is faster)
         if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;
-        // (a padded channel count only where the chain stays as linked as the general kernel would have it)
-        const bool padded = K != 32 && K != 64;
         // (the gather's offsets inside a window are 32 bits: a larger image is imported)
         const bool gathers = is.c * d.kh * d.kw <= kStemRed && conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu &&
                              (is.c - 1) * gv.sK + ((d.kh - 1ll) * is.w + d.kw - 1) * gv.sP < (1ll << 31);
