@@ -1616,7 +1616,9 @@ struct Planner {
           d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 1 && d.pad_w == 1 && pool_node < 0 && !placed.count(cur) && cur != out_tid) {
         const View& gv = p.views[tview[0]];
         const int nx = single_consumer(cur);
-        if (gv.f32 && gv.sP == 1 && nx >= 0 && pair_consumer_ok(nx)) {
+        // (its offsets in the graph input are 32 bits)
+        const bool offsets = is.n * gv.sN + 4 * gv.sK < (1ll << 31) && is.n * (is.h + 2ll) + kPairRows + 4 < (1ll << 31);
+        if (offsets && gv.f32 && gv.sP == 1 && nx >= 0 && pair_consumer_ok(nx)) {
           std::vector<uint16_t> w1((size_t)kPairChannels * kPairRed, 0);
           for (int k = 0; k < K; ++k)
             for (int c = 0; c < is.c; ++c)

@@ -521,6 +521,16 @@ def test_pattern_first_layer_pair_on_chip():
     assert plan_json(g, link=3, compute=X.XENOS_F32)["plan"]["chains"][0]["loader"] == "stem"   # the pair kernel is bf16 only
 
 
+def test_first_layer_pair_of_a_batch_beyond_32_bit_offsets_stays_apart():
+    # conv_pair_kernel's offsets in the graph input are 32 bits: n + 4 / 3 images of 3 x 512 x 512
+    def first(n):
+        b = undrawn((n, 3, 512, 512))
+        t = b.cbr(b.cbr(0, 64, 3, 1, 1, name="a"), 64, 3, 1, 1, name="b")
+        return plan_json(b.finish(b.cbr(b.maxpool(t, 2, 2), 8, 1, name="c")), link=3, compute=X.XENOS_BF16)["plan"]["chains"][0]["loader"]
+    n = ((1 << 31) - 1) // (3 << 18) - 2
+    assert first(n) == "pair" and first(n + 2) == "stem"
+
+
 def test_plan_metadata_names_the_graph_tensor_of_every_view():
     # per-chain checks rely on it: every chain's input / output view says which graph tensor (and channel range) it holds
     for cfg in (1, 2, 4, 5):
