@@ -1979,16 +1979,16 @@ static_assert(SL_TH * SL_TW == 32 * SL_NW && SL_TW == 16, "one wavefront = two t
 // out the convolution's result, written and read again by a pooling pass of its own before (101 MB each way on a 3x3 / 2 layer of 64
 // channels at batch 32): SqueezeNet batch 32 fp32 665.6 -> 630.8 us.
 //
-// (the small kernels keep three or six weight fragments per lane, so four or three workgroups share a compute unit instead of
-// two: a tile is a chain of short dependent phases, and what hides their latencies is other tiles in flight.  Measured at
-// batch 32 on the 3x3 / 2 first layers with a linked pooling: 64 channels 33.7 -> 30.3 us with three workgroups (30.8 with four,
-// which spills), 24 channels padded to 32: 28.3 -> 23.5 us with four)
+// (a tile is a chain of short dependent phases, and what hides their latencies is other tiles in flight: the small kernels keep
+// three or six weight fragments per lane, and the launch bounds see to it that three or four workgroups share a compute unit instead of
+// two; how many fit by the registers they then take says stem_lds_resident)
 // The block is double-buffered: the next one is written behind this tile's products, so two barriers a tile and no wait for the
 // output stores, which queue up behind its loads; one thread converts all channels of a position and writes them at once (four
-// 2-byte LDS writes before), tap offsets lie in registers; as many workgroups as are resident (7x7 / 2 with four per unit: the last half
+// 2-byte LDS writes before), tap offsets lie in registers; as many workgroups are launched as are resident (7x7 / 2 with four per unit: the last half
 // began behind the first, weights and all, 4 us).  Networks at batch 32: SqueezeNet 169.5 -> 159.9 us, ShuffleNet graph 308.0 -> 301.9,
 // ResNet-18 379.2 -> 362.8.
-template <typename T, int KB, int NSTEP, bool POOL>
+// (NC: fp32, the channels that a tap multiplies: those of the image)
+template <typename T, int KB, int NSTEP, bool POOL, int NC>
 __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 : 3) : 2) void stem_lds_kernel(const ConvArgs a) {
   FETCH_ARGS(ConvArgs);
   constexpr bool F32 = sizeof(T) == 4;
@@ -2090,7 +2090,7 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
   // resident weights: rows = channels 32 * b + l31, [K][NSTEP * 16] with slot = tap * 4 + channel
   // bf16: a step of the MFMA is four taps, two per lane half; fp32: two taps, one per half, and one MFMA per channel
   u32x4_t w[F32 ? 1 : NSTEP][KB];
-  float wf[F32 ? 2 * NSTEP : 1][KB][3];
+  float wf[F32 ? 2 * NSTEP : 1][KB][NC];
   if constexpr (F32) {
 #pragma unroll
     for (int j = 0; j < 2 * NSTEP; ++j)
@@ -2098,7 +2098,7 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
       for (int b = 0; b < KB; ++b) {
         const f32x4_t v = *(const f32x4_t*)((const float*)a.dw_w + (32 * b + l31) * (NSTEP * 16) + (2 * j + lhalf) * 4);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) wf[j][b][c] = v[c];
+        for (int c = 0; c < NC; ++c) wf[j][b][c] = v[c];
       }
   } else {
 #pragma unroll
@@ -2143,11 +2143,9 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
           if (4 * j + 2 * i >= ntaps) continue;                    // (uniform)
           const f32x4_t v = *(const f32x4_t*)(xin + tap[j][i]);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            if (c >= a.pair_C) break;                              // (uniform)
+          for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[2 * j + i][b][c], v[c], acc[b], 0, 0, 0);
-          }
         }
         continue;
       }
@@ -2239,15 +2237,20 @@ __global__ __launch_bounds__(SL_NT, sizeof(T) == 2 && NSTEP <= 3 ? (KB == 1 ? 4 
   }
 }
 
-template <typename T, int KB, bool POOL>
+template <typename T, int KB, bool POOL, int NC = 4>
 static int launch_stem_lds_kb(const ConvArgs& a, hipStream_t st) {
-  const int taps = a.R * a.S;
-  if (taps <= 12) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 3, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
-  else if (taps <= 28) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 7, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
-  else if constexpr (sizeof(T) == 4) return (int)hipErrorInvalidValue;   // (7x7, 64 channels: thirty registers of the weights are spilled)
-  else if (taps <= 52) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 13, POOL>), dim3(a.grid), dim3(SL_NT), 0, st, a);
-  else return (int)hipErrorInvalidValue;
-  return (int)hipGetLastError();
+  if constexpr (sizeof(T) == 4 && NC == 4) {
+    return a.pair_C == 1 ? launch_stem_lds_kb<T, KB, POOL, 1>(a, st) : a.pair_C == 2 ? launch_stem_lds_kb<T, KB, POOL, 2>(a, st) :
+           launch_stem_lds_kb<T, KB, POOL, 3>(a, st);
+  } else {
+    const int taps = a.R * a.S;
+    if (taps <= 12) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 3, POOL, NC>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+    else if (taps <= 28) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 7, POOL, NC>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+    else if constexpr (sizeof(T) == 4) return (int)hipErrorInvalidValue;   // (7x7, 64 channels: thirty registers of the weights are spilled)
+    else if (taps <= 52) hipLaunchKernelGGL((stem_lds_kernel<T, KB, 13, POOL, NC>), dim3(a.grid), dim3(SL_NT), 0, st, a);
+    else return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
+  }
 }
 
 static int launch_stem_lds(const ConvArgs& a, int dtype, hipStream_t st) {

@@ -76,7 +76,7 @@ def first_layer(kernels, compute, k, ksz, pool, **hw):
     chain = X.xenos_plan_query(P)["plan"]["chains"][0]
     X.xenos_destroy(P)
     steps = 3 if ksz < 4 else 7 if ksz < 6 else 13
-    name = "stem_lds_kernelI%sLi%dELi%dELb%dE" % ("NS_6bf16_tE" if compute else "f", 1 if k <= 32 else 2, steps, pool)
+    name = "stem_lds_kernelI%sLi%dELi%dELb%dELi%dE" % ("NS_6bf16_tE" if compute else "f", 1 if k <= 32 else 2, steps, pool, 4 if compute else 3)
     meta, = [v for n, v in kernels.items() if name in n]
     return chain, meta
 
