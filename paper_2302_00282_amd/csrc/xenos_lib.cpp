@@ -1213,7 +1213,7 @@ struct Planner {
   // in microseconds, their terms fitted to 900 random shapes (8 to 1024 channels, 1024 to 60000 output pixels) measured both ways,
   // nine tenths of them within 25 %; the fp32 one, which errs against small units, gives them 2 us.  Of 600 other shapes 126 lost
   // more than 4 % when linked wherever a tile fits LDS, up to five times; by this rule 10 do, at most 19 %, and two that gain more
-  // than 4 % (5 and 10 %) stay apart.
+  // than 4 % (5 and 10 %) stay apart.  (Fitted before the GEMM loops of both forms requested through windows, and not again.)
   bool unit_pays(int c1, const Shape& ms, const Shape& os, int s, int K, int th, int tw) const {
     if (!p.opts.split) return true;
     const bool b16 = p.dt == DT_BF16;
@@ -1342,7 +1342,8 @@ struct Planner {
     // (a 3x3 first convolution reads the taps of a chunk of input channels in consecutive steps: whole chunks only)
     if (first3 && (std::max(is.c, p.views[tview[nd.in[0]]].cphys) % (kRowBytes / p.esz) != 0 || is.h > 0xffff || is.w > 0xffff)) return false;
     // (fp32 at large batch: the module as three chains on the big GEMM tiles is faster than one chain whose squeeze halo is
-    // recomputed at the fp32 MFMA rate; measured on the SqueezeNet graph at batch 32, 0.67 against 0.74 ms)
+    // recomputed at the fp32 MFMA rate; measured on the SqueezeNet graph at batch 32, 0.67 against 0.74 ms, before the GEMM loops of
+    // either form requested through windows)
     if (p.dt == DT_F32 && (long long)is.n * is.h * is.w > 4096) return false;
     const ChainWalk w = walk_chain(i);
     if (w.has_res || w.pool_node >= 0 || w.cur == out_tid || placed.count(w.cur) || fin.count(w.cur) || (consumers[w.cur].size() != 2 && consumers[w.cur].size() != 1)) return false;
@@ -1382,6 +1383,7 @@ struct Planner {
   // MFMA work, are the time of a module.  The longest workgroup decides, or the queue of a unit, counted
   // in whole workgroups (two side by side where LDS allows): a few more workgroups than fit the units' slots cost a round of their own
   // (4 x 128 x 150 x 150 -> 32 -> 40 pooled, 608 workgroups 100 us, 440 of larger tiles 78; SqueezeNet bf16 batch 32 185.3 -> 172.8 us).
+  // (0.35 is a step that waited for all its requests every fourth time; they go through windows now, and a step takes about 0.28.)
   bool choose_fire_tile(ConvArgs& c) const {
     const int num_cu = std::max(1, p.hw.num_cu);
     const size_t lds_cap = std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
@@ -1566,13 +1568,14 @@ struct Planner {
         // l2 = last node of the chain without its pooling, c2 = that node's output tensor
         const int l2 = pool_node < 0 ? last : absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
         const int c2 = l2 + 1;
-        // The kernel that stages the input block in LDS (bf16 path, fp32 NCHW input with unit stride along W, at most 4
-        // channels, square kernel of 4x4 to 7x7, stride 1 or 2; measured at batch 32: 7x7 / 2 on 224x224 0.043 ms against
-        // 0.077 ms for the gather form, while 3x3 kernels, 9 gathers per pixel and channel, are faster on the gather form)
+        // The kernel that stages the input block in LDS (fp32 NCHW input with unit stride along W, square kernel, stride 1 or 2; bf16 path:
+        // at most 4 channels, 4x4 to 7x7, 3x3 with a pooling; measured at batch 32: 7x7 / 2 on 224x224 0.043 ms against 0.077 ms for
+        // the gather form, while 3x3 kernels without a pooling, 9 gathers per pixel and channel, were faster on the gather form)
         // takes a linked max-pooling of 2 or 3 wide windows at stride 2: 3 x 8 windows per tile, their convolution block
         // recomputed per tile.
         const View& gv = p.views[tview[0]];
-        // On the fp32 path it is for kernels up to 5x5 with such a pooling, at link level 3 (at level 2 the pooling stays a pass of its own).
+        // On the fp32 path it is for at most 3 channels and kernels of 3x3 to 5x5 with such a pooling, at link level 3 (at level 2 the pooling
+        // stays a pass of its own).
         const bool f32 = p.dt == DT_F32;
         stem_lds = p.opts.tile == 0 && (!f32 || (link >= 3 && is.c <= 3 && d.kh <= 5)) && is.c <= 4 && d.kh == d.kw && d.kh >= 3 && d.kh <= 7 && d.stride_h == d.stride_w &&
                    (d.stride_h == 1 || d.stride_h == 2) && d.pad_h == d.pad_w && d.pad_h <= d.kh && gv.f32 && gv.sP == 1 &&
@@ -1595,8 +1598,8 @@ struct Planner {
         // 48 to 60.  Staged against gathered, graphs of up to 100000 input pixels: 24 of these 0.98 to 1.21 times the time, 1.09 on average,
         // 29 others, which are staged, 0.62 to 1.03, 0.91 on average.
         if (f32 && stem_lds && padded && in_gather && ((d.kh >= 4 && is.c * d.kh * d.kw <= 32) || (K > 32 && desc(nodes[pool_node]).kh == 2))) stem_lds = keep_pool = false;
-        // (a 3x3 layer takes the LDS-staged form only for its linked pooling: one launch for two, the same time at batch 32;
-        // without pooling the gather form is faster)
+        // (a 3x3 layer takes the LDS-staged form only for its linked pooling, one launch for two; without pooling the gather form was faster
+        // than that kernel with a single buffer, and has not been compared with the present one)
         if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;
         // (the gather's offsets inside a window are 32 bits: a larger image is imported)
         const bool gathers = is.c * d.kh * d.kw <= kStemRed && conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu &&
