@@ -1593,11 +1593,11 @@ struct Planner {
         if (f32 && !keep_pool) stem_lds = false;
         // (a padded channel count only where the chain stays as linked as the general kernel would have it)
         const bool padded = K != 32 && K != 64;
-        // A small fp32 input with a padded channel count stays with the general kernel, which gathers it in place: where it does so in one
-        // reduction step against 16 taps or more, and where it computes no pixel twice (windows of 2) in place of 64 channels for
-        // 48 to 60.  Staged against gathered, graphs of up to 100000 input pixels: 24 of these 0.98 to 1.21 times the time, 1.09 on average,
-        // 29 others, which are staged, 0.62 to 1.03, 0.91 on average.
-        if (f32 && stem_lds && padded && in_gather && ((d.kh >= 4 && is.c * d.kh * d.kw <= 32) || (K > 32 && desc(nodes[pool_node]).kh == 2))) stem_lds = keep_pool = false;
+        // A small fp32 input with 48 to 60 channels stays with the general kernel, which gathers it in place, where that computes no pixel twice
+        // (windows of 2) or takes one reduction step against 16 taps or more; staged, 64 channels are computed.  Staged against gathered,
+        // inputs of up to 100000 pixels: 68 such graphs 0.94 to 1.27 times the time, 1.09 on average; 92 others, which are staged, 0.60 to
+        // 1.08, 0.93 on average.
+        if (f32 && stem_lds && padded && in_gather && K > 32 && (desc(nodes[pool_node]).kh == 2 || (d.kh >= 4 && is.c * d.kh * d.kw <= 32))) stem_lds = keep_pool = false;
         // (a 3x3 layer takes the LDS-staged form only for its linked pooling, one launch for two; without pooling the gather form was faster
         // than that kernel with a single buffer, and has not been compared with the present one)
         if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;

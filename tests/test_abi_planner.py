@@ -501,12 +501,12 @@ def test_images_beyond_2_gb_stay_linked(pattern, compute):
     assert [c.get("loader") for c in chains].count(pattern[:4]) == 1
 
 
-@pytest.mark.parametrize("c,k,ksz,pool,n,hw,staged", [(1, 24, 5, 2, 1, 64, 0), (1, 24, 5, 3, 1, 64, 0), (2, 24, 5, 2, 1, 64, 1), (1, 24, 3, 2, 1, 64, 1),
+@pytest.mark.parametrize("c,k,ksz,pool,n,hw,staged", [(1, 48, 5, 2, 1, 64, 0), (1, 48, 5, 3, 1, 64, 0), (2, 48, 5, 3, 1, 64, 1), (1, 24, 5, 2, 1, 64, 1),
                                                        (3, 48, 3, 2, 1, 64, 0), (3, 48, 3, 3, 1, 64, 1), (3, 32, 3, 2, 1, 64, 1), (1, 64, 5, 2, 1, 64, 1),
-                                                       (3, 48, 3, 2, 2, 224, 1), (1, 24, 5, 2, 2, 224, 1)])
+                                                       (3, 48, 3, 2, 2, 224, 1), (1, 48, 5, 3, 2, 224, 1)])
 def test_small_fp32_first_layers_with_padded_channels(c, k, ksz, pool, n, hw, staged):
-    # the general kernel gathers a small input in place: it keeps such a layer where that is one reduction step of 16 or more taps, or
-    # windows of 2 over more than 32 channels; other layers, and inputs from 100000 pixels on, are staged on chip
+    # the general kernel gathers a small input in place: it keeps such a layer of more than 32 channels where that is one reduction step
+    # of 16 or more taps, or windows of 2; other layers, and inputs from 100000 pixels on, are staged on chip
     b = undrawn((n, c, hw, hw))
     t = b.maxpool(b.cbr(0, k, ksz, 1, ksz // 2, name="a"), pool, 2, ceil=1)
     chain = plan_json(b.finish(b.cbr(t, 8, 1, name="b")), link=3, compute=X.XENOS_F32)["plan"]["chains"][0]
