@@ -718,10 +718,12 @@ struct Planner {
       t.tiles_n = (c.K + tc.bn - 1) / tc.bn;
       t.ntiles = t.tiles_m * t.tiles_n;
       // (global average: one workgroup walks an image, and the 64-row tile is nearly nine tenths as good as the 128-row one: it is taken
-      // where it pads an image to less than 0.88 of the other's rows, in bf16 0.87.  Maps of 5x5 to 20x20, 64 to 640 -> 384 to 1024 channels,
-      // batch 16 to 128, the rule against the 128-row tile: fp32 0.92 times the time on average, up to 0.98 at 7 of 8 the rows (20x20); bf16 0.95,
-      // and 1.00 to 1.04 there, which is why it stops short of them)
-      const double e = c.mode == M_GAP && tc.bm == 64 && tc.bn == 64 ? (p.dt == DT_F32 ? 0.75 : 0.74) : eff[cfg];
+      // where it pads an image to less than 0.88 of the other's rows; in bf16 0.87 of a 1x1 layer's, 0.80 of a wider kernel's, whose weights
+      // are read again for every 64 rows.  Against the 128-row tile, batch 16 to 128: 1x1 layers of 5x5 to 20x20, fp32 0.92 times the time on
+      // average, up to 0.98 at 7 of 8 the rows (20x20), bf16 0.95, and 1.00 to 1.04 there; 3x3 and 5x5 layers, fp32 0.93 up to 7 of 8, bf16
+      // 0.89 at 3 of 4 (13x13), and 1.05 to 1.12 for eleven of fifteen at 5 of 6 (17x17), which is why it stops before these)
+      const double gap = p.dt == DT_F32 ? 0.75 : c.R * c.S == 1 ? 0.74 : 0.68;
+      const double e = c.mode == M_GAP && tc.bm == 64 && tc.bn == 64 ? gap : eff[cfg];
       double per_tile = (double)tc.bm * tc.bn / e;
       if (c.mode == M_GAP) per_tile *= (double)((c.OH * c.OW + tc.bm - 1) / tc.bm);
       // two workgroups fit on a compute unit; below that, a smaller tile only shortens the critical path

@@ -138,11 +138,12 @@ def test_global_average_takes_the_tile_that_pads_less(hw, rows, compute):
     assert len(chain) == 1 and chain[0]["bm"] == rows and chain[0]["bn"] == 64
 
 
-@pytest.mark.parametrize("compute,rows", [(X.XENOS_F32, 64), (X.XENOS_BF16, 128)])
-def test_global_average_at_seven_eighths_of_the_rows(compute, rows):
-    # 20x20: 448 rows against 512, which pays in fp32 only
-    b = undrawn((32, 64, 20, 20))
-    g = b.finish(b.gap(b.cbr(b.cbr(0, 64, 1, name="a"), 1000, 1, name="c")))
+@pytest.mark.parametrize("hw,ksz,compute,rows", [(20, 1, X.XENOS_F32, 64), (20, 1, X.XENOS_BF16, 128), (17, 3, X.XENOS_F32, 64), (17, 3, X.XENOS_BF16, 128),
+                                                  (17, 1, X.XENOS_BF16, 64), (13, 3, X.XENOS_BF16, 64), (20, 3, X.XENOS_F32, 64)])
+def test_global_average_near_the_rows_of_the_larger_tile(hw, ksz, compute, rows):
+    # 20x20: 448 rows against 512, which pays in fp32 only; 17x17: 320 against 384, which in bf16 pays for 1x1 layers only
+    b = undrawn((32, 64, hw, hw))
+    g = b.finish(b.gap(b.cbr(b.cbr(0, 64, 1, name="a"), 1000, ksz, 1, ksz // 2, name="c")))
     chain, = [c for c in plan_json(g, link=2, compute=compute)["plan"]["chains"] if c.get("mode") == "gap"]
     assert chain["bm"] == rows and chain["bn"] == 64
 
