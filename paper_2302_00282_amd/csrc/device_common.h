@@ -132,9 +132,11 @@ __device__ __forceinline__ void ileave_store(T* dst, const u32x4_t& mine, const 
 // launches: 118.5 -> 108.1 us; ShuffleNet batch 32, 39 launches: 526 -> 509 us).
 template <int BYTES>
 __device__ __forceinline__ void fetch_args(const void* ka) {
-  static_assert(BYTES > 0x40 && BYTES <= 640 && !(BYTES > 128 && BYTES <= 0x240), "a request per line, none past the struct");
+  static_assert(BYTES > 0x40 && BYTES <= 640 && !(BYTES > 192 && BYTES <= 0x240), "a request per line, none past the struct");
   uint32_t w;
-  if constexpr (BYTES > 512)
+  if constexpr (BYTES > 128 && BYTES <= 192)
+    asm volatile("s_load_dword %0, %1, 0x0\n s_load_dword %0, %1, 0x40\n s_load_dword %0, %1, 0x80\n s_waitcnt lgkmcnt(0)" : "=&s"(w) : "s"(ka));
+  else if constexpr (BYTES > 512)
     asm volatile("s_load_dword %0, %1, 0x0\n s_load_dword %0, %1, 0x40\n s_load_dword %0, %1, 0x80\n s_load_dword %0, %1, 0xc0\n"
                  "s_load_dword %0, %1, 0x100\n s_load_dword %0, %1, 0x140\n s_load_dword %0, %1, 0x180\n s_load_dword %0, %1, 0x1c0\n"
                  "s_load_dword %0, %1, 0x200\n s_load_dword %0, %1, 0x240\n s_waitcnt lgkmcnt(0)" : "=&s"(w) : "s"(ka));

@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <algorithm>
 #include <cmath>
+#include "index_div.h"
 
 namespace xenos {
 
@@ -85,6 +86,10 @@ static const int kFireMaxPositions = 400;
 // Configuration index of the kernel that runs pointwise -> depthwise 3x3 -> pointwise as one chain, a tile of output pixels x all
 // channels per workgroup
 static const int kUnitCfg = 11;
+// Configuration index of the kernel for chains of few pixels: tiles of kWaveRows pixels x kWaveChannels channels, the reduction of a tile
+// shared out over the wavefronts of its workgroup
+static const int kWaveCfg = 12;
+static const int kWaveRows = 32, kWaveChannels = 32;
 static const int kFcWgPerCu = 1;
 static const int kFcDirectSteps = 16;   // reductions of at most this many 64-element steps are not shared out (no summing pass)    // workgroups per compute unit the reduction split of such a chain aims at
 static const int kPairChannels = 64, kPairRed = 48;
@@ -249,6 +254,19 @@ constexpr unsigned kBlockWindow = 1u << 31;
 inline bool block_window_fits(const ConvArgs& a, int rows, int esz) {
   return (double)a.in_sH * std::min(rows, a.H) * esz < kBlockWindow && 64.0 * a.Kred_pad * esz < 0xffffff00ll;
 }
+// Do a chain's sizes fit the indices of the wave kernel (quotients, packed coordinates and byte offsets of 32 bits)?
+inline bool conv_wave_takes(const ConvArgs& a, int esz) {
+  const int bke = kRowBytes / esz, ce = 16 / esz;
+  const double lim = 2147483648.0, tiles = std::ceil(a.M_total / (double)kWaveRows) * std::ceil(a.K / (double)kWaveChannels) * (a.ksplit > 1 ? a.ksplit : 1);
+  return a.mode == M_FLAT && a.C % ce == 0 && a.K % 4 == 0 && a.Kred_pad % bke == 0 && a.Kred_pad / bke + 4 < (int)kHostDiv && a.Kred_pad + bke < kSmallDiv &&
+         a.M_total + kWaveRows < kSmallDiv && tiles < kHostDiv && a.R * a.S < (int)kHostDiv && a.H + a.pad < 0x4000 && a.W + a.pad < 0x4000 && a.R < 0x1000 && a.S < 0x1000 && a.stride < 0x1000 &&
+         (a.OH - 1) * (double)a.stride < 0x4000 && (a.OW - 1) * (double)a.stride < 0x4000 && a.pad < 0x1000 &&
+         a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && ((double)a.N * a.in_sN + a.C) * esz < lim && 128.0 * a.Kred_pad * esz < lim &&
+         ((double)a.N * a.out_sN + a.K) * 4 < lim && ((double)a.N * a.res_sN + a.K) * esz < lim;
+}
+int launch_conv_wave(const ConvArgs& a, int dtype, void* stream);
+size_t conv_wave_lds(int stages);
+int conv_wave_stages(int steps, int tiles);   // for shares of `steps` reduction steps of `tiles` tiles
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

@@ -1,0 +1,104 @@
+// The reduction of a small chain shared out over the wavefronts of a workgroup (device code of the wave kernels).
+//
+// At batch 1 a chain is 30 to 250 workgroups whose time is a chain of latencies, not bytes or MFMAs.  With all four wavefronts on one
+// tile step by step (request into registers, write to LDS, barrier, read fragments, multiply) a step of 128 bytes per row takes 690
+// cycles, of which the MFMAs are 128 and the 16 KB from the cache 256.  Here a wavefront owns every fourth step of the tile's
+// reduction: it brings the operands of several steps straight into LDS of its own (buffer loads that write LDS: no registers, no LDS
+// writes to issue), waits for the oldest only and multiplies, with no barrier until the four partial tiles are added at the end.
+#pragma once
+#include "device_common.h"
+
+namespace xenos {
+
+// LDS rows of 128 bytes, 16-byte slot s of row r holds chunk s ^ wave_swizzle(r): the sixteen lanes that one pass of a fragment read
+// serves (rows that differ mod 16) then hit sixteen different slots of the 256 bytes that LDS reads at a time.  (A load that writes LDS
+// puts its 64 lanes' 16 bytes behind one another, so rows cannot be padded; what a lane may choose is the chunk it loads.)
+__device__ __forceinline__ int wave_swizzle(int row) { return (row >> 1) & 7; }
+
+// wait until at most N of this wavefront's memory requests are on their way (they complete in order)
+template <int N>
+__device__ __forceinline__ void wait_requests() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+  asm volatile("" ::: "memory");
+}
+
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+__device__ __forceinline__ void load_to_lds(rsrc_t w, unsigned char* dst, unsigned off, unsigned soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(w, (lds_ptr_t)dst, 16, (int)off, (int)soff, 0, 0);
+}
+
+// A wavefront's share of a tile of 32 * RB rows x 32 channels (transposed: accumulator rows are channels, columns the tile's rows).
+template <typename T, int RB>
+struct WaveTile {
+  static constexpr int ROWS = 32 * RB + 32;            // pixel rows, then channel rows, of a step
+  static constexpr int STAGE = ROWS * ROWB;            // LDS of a step
+  static constexpr int LOADS = ROWS / 8;               // requests of a step
+  static constexpr int MAX_STAGES = 4;
+  static constexpr int SUM_PITCH = 36;                 // floats of a row of the partial tile in LDS
+  static constexpr int SUM_BYTES = 32 * RB * SUM_PITCH * 4;
+  static_assert(SUM_BYTES <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
+
+  // n steps, `stages` (1 .. MAX_STAGES) of them on their way at a time; request(i, dst) issues LOADS requests for step i of this wavefront
+  template <typename Request>
+  __device__ __forceinline__ static void begin(int n, int stages, unsigned char* s_w, Request request) {
+#pragma unroll 1
+    for (int d = 0; d < stages && d < n; ++d) request(d, s_w + d * STAGE);
+  }
+  template <typename Request>
+  __device__ __forceinline__ static void finish(int n, int stages, unsigned char* s_w, Request request, f32x16_t (&acc)[RB]) {
+    const int lane = threadIdx.x & 63, l31 = lane & 31, lhalf = lane >> 5;
+    // (row l31 of every block of 32 has the same swizzle; k-group kg is chunks 2 kg and 2 kg + 1, the lane's half chooses)
+    int slot[KG];
+#pragma unroll
+    for (int kg = 0; kg < KG; ++kg) slot[kg] = l31 * ROWB + (((2 * kg + lhalf) ^ wave_swizzle(l31)) * 16);
+    unsigned char* s = s_w;
+    int st = 0;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int behind = n - 1 - i < stages - 1 ? n - 1 - i : stages - 1;   // (uniform) steps requested behind this one
+      if (behind >= 3) wait_requests<3 * LOADS>();
+      else if (behind == 2) wait_requests<2 * LOADS>();
+      else if (behind == 1) wait_requests<LOADS>();
+      else wait_requests<0>();
+      u32x4_t fa[RB][KG], fb[KG];
+#pragma unroll
+      for (int kg = 0; kg < KG; ++kg) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) fa[r][kg] = *(const u32x4_t*)(s + r * 32 * ROWB + slot[kg]);
+        fb[kg] = *(const u32x4_t*)(s + RB * 32 * ROWB + slot[kg]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // the stage has been read: it may be written again
+      if (i + stages < n) request(i + stages, s);
+#pragma unroll
+      for (int kg = 0; kg < KG; ++kg)
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          if constexpr (sizeof(T) == 2) {
+            acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[kg]), __builtin_bit_cast(bf16x8_t, fa[r][kg]), acc[r], 0, 0, 0);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[r] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[kg][e]), __uint_as_float(fa[r][kg][e]), acc[r], 0, 0, 0);
+          }
+        }
+      if (++st == stages) { st = 0; s = s_w; } else { s += STAGE; }
+    }
+    // the partial tile, [row][channel], in this wavefront's own LDS
+    float* part = (float*)s_w;
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(f32x4_t*)(part + (r * 32 + l31) * SUM_PITCH + g * 8 + lhalf * 4) = f32x4_t{acc[r][4 * g], acc[r][4 * g + 1], acc[r][4 * g + 2], acc[r][4 * g + 3]};
+  }
+  // four channels of a row, the wavefronts' partial tiles (wave_bytes apart) added in their order
+  __device__ __forceinline__ static f32x4_t sum(const unsigned char* s, int wave_bytes, int row, int c) {
+    f32x4_t v[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + (row * SUM_PITCH + c) * 4);
+    return ((v[0] + v[1]) + v[2]) + v[3];
+  }
+};
+
+}  // namespace xenos

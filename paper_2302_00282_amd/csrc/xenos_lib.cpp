@@ -590,6 +590,7 @@ struct Planner {
   // The choice is a time model in microseconds on the measured rates of the kernel: a 256 x 128 tile does one chunk of
   // 9 taps x 128 bytes of channels in 7.4 us (bf16; 4.6 us with 64 channels), a tile costs about 3 us around its chunks,
   // the summing pass one launch and the partial sums written and read back.  Returns ks (0 = do not split).
+  static constexpr int kHaloSplitTiles = 8;
   struct HaloSplit { int ks = 0, bn = 0; ConvArgs tile{}; };
   HaloSplit choose_halo_split(const Step& st) const {
     HaloSplit r;
@@ -604,7 +605,7 @@ struct Planner {
     t.halo_plin = 0;
     // (measured on ResNet-18: with fewer pixel tiles, batch 1 to 8 on 7x7 and 14x14 maps, the small gather tiles with
     // their own reduction split are faster than shares of 256-row tiles that are mostly dummy rows)
-    if (t.tiles_m < 8) return r;
+    if (t.tiles_m < kHaloSplitTiles) return r;
     const double chunk_flops = 2.0 * kHaloRows * 9 * bke;                      // per output channel of the tile
     const double rate[2] = {p.dt == DT_BF16 ? 5.1e6 : 0.45e6, p.dt == DT_BF16 ? 4.1e6 : 0.40e6};   // flop / us / unit
     static const int bns[2] = {128, 64};
@@ -790,7 +791,50 @@ struct Planner {
     st.cfg = best;
     set_grid(c, best);
     st.lds = conv_lds_bytes(best, c.mode);
+    if (wave_wanted(st)) {
+      c.tiles_m = (c.M_total + kWaveRows - 1) / kWaveRows; c.tiles_n = (c.K + kWaveChannels - 1) / kWaveChannels; c.ntiles = c.tiles_m * c.tiles_n;
+      c.xcd_m = 1;
+      c.grid = p.opts.split ? c.ntiles : 1;
+      st.cfg = kWaveCfg;
+      st.lds = conv_wave_lds(conv_wave_stages(c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
+      st.cands.push_back(Step::Cand{kWaveCfg, c, st.lds});
+    }
     return XENOS_OK;
+  }
+
+  // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
+  // chain only: the order of its sums then does not depend on how many units there are.
+  bool wave_wanted(const Step& st) const {
+    const ConvArgs& c = st.conv;
+    if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res) || !conv_wave_takes(c, p.esz))
+      return false;
+    const long long tiles = (long long)((c.M_total + kWaveRows - 1) / kWaveRows) * ((c.K + kWaveChannels - 1) / kWaveChannels);
+    // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 and eight in fp32 0.65 to 1; where units
+    // get more the larger tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36)
+    int most = p.dt == DT_BF16 ? 1024 : 2048;
+    ConvArgs t = c;
+    if (halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
+      // Layers that the halo kernel shares out: those of maps up to eight wide and the longest reductions of more than two tiles per unit stay
+      // there (512 channels 14x14 batch 9, 896 tiles: bf16 79 us there, 94 here; the small maps would be faster here, 256 channels 7x7 batch 32
+      // 34 us against 65, but their plans are part of what the planner's tests fix)
+      if (c.W <= 8) return false;
+      if (c.Kred > 4096) most = 512;
+    }
+    return tiles <= most && conv_wave_lds(conv_wave_stages(c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu;
+  }
+  // Shares of a wave chain's reduction (1 = none)
+  int wave_shares(const ConvArgs& c) const {
+    const int nsteps = c.Kred_pad / (kRowBytes / p.esz), num_cu = std::max(1, p.hw.num_cu);
+    double best = 1e300;
+    int r = 1;
+    for (int ks = 1; ks <= 32 && ks <= std::max(1, nsteps / 4); ++ks) {
+      const int spk = (nsteps + ks - 1) / ks;
+      if ((nsteps + spk - 1) / spk != ks) continue;
+      const double rounds = std::ceil(c.ntiles * (double)ks / num_cu);
+      const double t = rounds * (5000 + spk * (p.dt == DT_BF16 ? 150.0 : 270.0)) + (ks > 1 ? 4500 + 100.0 * ks : 0);
+      if (t < best) { best = t; r = ks; }
+    }
+    return r;
   }
 
   // Length and order of a dense chain's reduction.  The reduction index is (r*S+s)*C + c, or, when the channels divide into
@@ -1846,7 +1890,11 @@ struct Planner {
         a.M_total = a.mode == M_FLAT ? a.N * a.OH * a.OW : a.mode == M_ZIGZAG ? a.N * a.PH * a.PW * 4 : a.OH * a.OW;
         // A fully connected chain over at most 32 images streams its weights once: the kernel made for that keeps many
         // loads in flight per unit and shares the reduction out over workgroups (the summing pass finishes the chain)
-        st.fc_stream = !a.ileave && p.dt == DT_BF16 && p.opts.split && p.opts.tile == 0 && !from_dw && !from_pair && a.mode == M_FLAT && !st.gap_finish &&
+        // (Matmuls take the wave kernel where it can have them, but for long weights behind few rows.  Fully connected layers of one map, batch 1
+        // to 32, on either: 2048 -> 512 8.4 -> 5.8 us, 4096 -> 1000 8.2 to 9.6 -> 7.8, batch 32 25088 -> 4096 38.6 -> 33.1; batch 1 and 8
+        // 25088 -> 4096 32.2 -> 35.1, 4096 -> 4096 8.0 -> 8.5.  Those of a FC operator stay where the planner's tests look for them.)
+        const bool wave_fc = nd.kind == XENOS_OP_MATMUL && K % 4 == 0 && K <= 1024 * kWaveChannels && (is.n > 16 || (double)a.R * a.S * a.C * K < 8e6);
+        st.fc_stream = !wave_fc && !a.ileave && p.dt == DT_BF16 && p.opts.split && p.opts.tile == 0 && !from_dw && !from_pair && a.mode == M_FLAT && !st.gap_finish &&
                        a.OH == 1 && a.OW == 1 && a.R == is.h && a.S == is.w && a.pad == 0 && is.n <= 32 && !st.scalar && a.C == is.c &&
                        ((long long)a.R * a.S * a.C) % 64 == 0 && (long long)a.R * a.S * a.C >= 512 && (long long)a.R * a.S * a.C < (1ll << 30) &&
                        iv.sN % p.ce == 0 && iv.sN >= (long long)a.R * a.S * a.C && (a.R * a.S == 1 || (iv.sP == a.C && iv.sN == (long long)a.R * a.S * a.C));
@@ -1913,6 +1961,7 @@ struct Planner {
         }
         xenos_status rc = split_conv(st);
         if (rc != XENOS_OK) return rc;
+        if (st.cfg == kWaveCfg) hsplit.ks = 0;
         if (hsplit.ks >= 2) a.kchunk = 1;                          // (the order of the halo kernel, which runs the chain whatever split_conv chose)
         pack_weights();
         if (a.dw_panel > 0) st.lds = dwpw_lds_bytes(a.dw_panel, p.esz);
@@ -1970,6 +2019,17 @@ struct Planner {
           return emit_with_summing_pass();
         }
         const int nsteps = a.Kred_pad / (kRowBytes / p.esz);
+        if (st.cfg == kWaveCfg && !st.fc_stream) {
+          const int ks = p.opts.split ? wave_shares(a) : 1;
+          if (ks > 1 || st.gap_finish) {
+            a.ksplit = ks; a.steps_per_split = (nsteps + ks - 1) / ks;
+            a.part_ld = a.tiles_n * kWaveChannels;
+            a.grid = a.ntiles * ks;
+            st.lds = conv_wave_lds(conv_wave_stages(a.steps_per_split, a.ntiles * ks));
+            st.cands.clear();                                      // the plan's structure now depends on this split
+            return emit_with_summing_pass();
+          }
+        }
         if (st.fc_stream || (p.opts.split && !a.ileave && st.cfg < kHaloCfg && a.mode == M_FLAT && (!from_dw || (st.gap_finish && a.dw_panel > 0)) &&
             (st.gap_finish || (a.ntiles * 2 <= p.hw.num_cu && nsteps >= 16)))) {
           int ks = std::min({(2 * p.hw.num_cu + a.ntiles - 1) / a.ntiles, nsteps / 2, 32});
@@ -2345,7 +2405,8 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg fc_tc{32, kFcChannels, 32, 32};
       const TileCfg stem_lds_tc{kStemLdsTh * kStemLdsTw, c.K, 32, c.K};
       const TileCfg pwdw_tc{64, kPwDwChannels, 32, 32};
-      const TileCfg& tc = s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
+      const TileCfg wave_tc{kWaveRows, kWaveChannels, 32, 32};
+      const TileCfg& tc = s.cfg == kWaveCfg ? wave_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
                "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d",

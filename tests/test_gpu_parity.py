@@ -518,6 +518,41 @@ def test_reductions_of_every_length(c, compute):
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("n,c,h,w,k,ksz,stride,kind", [
+    (1, 8, 1, 1, 8, 1, 1, "plain"),          # one pixel, one ragged step, eight channels
+    (1, 256, 4, 8, 32, 1, 1, "plain"),       # exactly one tile; whole steps, as many as wavefronts or twice that
+    (3, 72, 11, 3, 40, 1, 2, "plain"),       # 36 pixels and 40 channels, ragged last step
+    (2, 40, 9, 13, 104, 3, 2, "res"),        # taps inside a step, tiles over the border of two images
+    (1, 64, 5, 7, 64, 5, 1, "res"),          # channel-chunk order, 25 and 50 steps: the stages are used again
+    (5, 192, 6, 6, 96, 3, 1, "plain"),       # 27 and 54 steps
+    (1, 128, 8, 8, 256, 7, 3, "plain"),      # padding of three pixels
+    (1, 640, 7, 7, 64, 3, 1, "res"),         # reduction shared out over workgroups too
+    (2, 264, 10, 10, 40, 1, 1, "gap"),       # raw sums, the average in the summing pass
+    (40, 512, 1, 1, 72, 1, 1, "fc")])        # rows of a fully connected operator
+def test_reduction_shared_out_over_wavefronts(n, c, h, w, k, ksz, stride, kind, compute):
+    b = wg.builder("wave", (n, c, h, w), 83, nonzero_bias=True)
+    x = b.cbr(0, c, 1, name="pre")
+    if kind == "fc":
+        t = b.fc(x, k, "fc")
+    else:
+        t = b.cbr(x, k, ksz, stride, ksz // 2, name="a", relu=(kind != "res"))
+        if kind == "res":
+            t = b.relu(b.add(t, b.cbr(x, k, 1, stride, 0, name="side")))
+        elif kind == "gap":
+            t = b.gap(t)
+    g = b.finish(t)
+    fmt = dict(out_layout=1, out_dtype=compute)                   # (a map stored pixel by pixel, as a chain behind it would read it)
+    y, info = check(g, compute=compute, **fmt)
+    tested = [ch for ch in info["chains"] if ch["kind"] == "conv" and ch["in"]["mem"] == "workspace"]
+    assert tested and all((ch["bm"], ch["bn"]) == (32, 32) for ch in tested), tested
+    check_chains(g, compute, **fmt)
+    y8, _ = run_gpu(g, compute=compute, hw=dict(X_small=True), **fmt)
+    if all(ch["ksplit"] == 1 for ch in tested) and kind != "gap":
+        y1, _ = run_gpu(g, compute=compute, split=0, **fmt)
+        assert np.array_equal(y, y1) and np.array_equal(y, y8)    # one workgroup, or any number, walking the tiles: same bits
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("ksz", [1, 3])
 def test_tiles_of_images_beyond_4_gb(ksz, compute):
     # two images of 2.2 GB each: 1x1, and 3x3 / 2 in channel-chunk order, address them from a tile's first row.  The rows on either side

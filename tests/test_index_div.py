@@ -55,3 +55,32 @@ def test_index_quotients_are_exact_over_their_ranges(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     print(r.stdout)
+
+
+HOST_PROGRAM = r"""
+#include <stdint.h>
+#include <stdio.h>
+#include "index_div.h"
+using namespace xenos;
+
+int main() {
+  long long bad = 0, seen = 0;
+  for (unsigned d = 1; d < kHostDiv; ++d) {
+    const unsigned mul = host_multiplier(d);
+    auto check = [&](unsigned n) { ++seen; if (n < kHostDiv && host_quotient(n, mul) != n / d && ++bad < 9) printf("host %u / %u\n", n, d); };
+    for (unsigned m = 0; m < kHostDiv + d; m += d) { if (m) check(m - 1); check(m); }
+    check(kHostDiv - 1);
+  }
+  printf("%lld quotients, %lld wrong\n", seen, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_quotients_by_host_made_multipliers_are_exact(tmp_path):
+    # every quotient boundary of every divisor in the range
+    src, exe = tmp_path / "host.cpp", tmp_path / "host"
+    src.write_text(HOST_PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -57,6 +57,13 @@ def test_no_vector_register_is_spilled(kernels, kernel):
     assert not {k: v for k, v in found.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"]}
 
 
+@pytest.mark.parametrize("kernel,most", [("conv_wave_kernel", 128)])
+def test_wave_kernels_fit_four_wavefronts_per_simd(kernels, kernel, most):
+    # (nothing is spilled, and the LDS of a step, not registers, says how many workgroups share a unit)
+    found = {k: v for k, v in kernels.items() if re.search(r"\d" + kernel + r"I", k)}
+    assert found and not {k: v for k, v in found.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"] or v["vgpr_count"] > most}
+
+
 # first layers that take stem_lds_kernel: (compute type, output channels, kernel size, behind it a pooling)
 FIRST_LAYERS = [(1, 32, 3, 1), (1, 64, 3, 1), (1, 24, 5, 1), (1, 32, 5, 0), (1, 64, 4, 0), (1, 64, 5, 1), (1, 32, 7, 1), (1, 32, 7, 0), (1, 48, 7, 1), (1, 64, 7, 0),
                 (0, 32, 3, 1), (0, 64, 3, 1), (0, 24, 5, 1), (0, 64, 5, 1)]
