@@ -141,7 +141,8 @@ struct ConvArgs {
   int dw_panel;          // > 0: the depthwise result of a whole panel of this many channels is staged in LDS (dwpw_kernel)
   // linked depthwise CONSUMER (pwdw_kernel): this 1x1 / stride 1 chain's output tile stays in LDS and a depthwise 3x3 chain
   // (dw_w [9][K], dw_scale / dw_shift [K], dw_stride, dw_pad = 1, dw_relu) runs out of it; H x W is the pointwise map,
-  // OH x OW the depthwise output, th x tw the tile of depthwise output pixels, tiles_y x tiles_x the tile grid per image
+  // OH x OW the depthwise output, th x tw the tile of depthwise output pixels, tiles_y x tiles_x the tile grid per image.
+  // 2: maps of few pixels, on pwdw_wave_kernel (a workgroup takes 32 of a tile's 64 channels)
   int pwdw;
   // linked Fire module (fire_kernel): this 1x1 / stride 1 chain is the squeeze (K <= 64 channels); its output tile (+ halo)
   // stays in LDS and two expand chains read it there: [0] 1x1, [1] 3x3 / pad 1.  fire_w: [E padded to 64][taps][K] in the
@@ -264,6 +265,24 @@ inline bool conv_wave_takes(const ConvArgs& a, int esz) {
          a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && ((double)a.N * a.in_sN + a.C) * esz < lim && 128.0 * a.Kred_pad * esz < lim &&
          ((double)a.N * a.out_sN + a.K) * 4 < lim && ((double)a.N * a.res_sN + a.K) * esz < lim;
 }
+// Pixels of the map that the windows of a tile of th x tw depthwise outputs cover, at most
+inline int wave_block_positions(const ConvArgs& a, int th, int tw) {
+  auto most = [&](int out, int t, int in) {
+    int r = 0;
+    for (int i = 0; i < out; i += t) r = std::max(r, std::min(i * a.dw_stride + (t - 1) * a.dw_stride + 2, in) - std::max(i * a.dw_stride - 1, 0));
+    return r;
+  };
+  return most(a.OH, th, a.H) * most(a.OW, tw, a.W);
+}
+// Do a pointwise -> depthwise chain's sizes fit the indices of its wave kernel?
+inline bool pwdw_wave_takes(const ConvArgs& a, int esz) {
+  const double lim = 2147483648.0, outs = (double)a.N * a.OH * a.OW * std::ceil(a.K / 32.0);   // (a tile is at least one output pixel)
+  return a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && ((double)a.N * a.in_sN + a.C) * esz < lim && ((double)a.N * a.out_sN + a.K) * esz < lim &&
+         128.0 * a.Kred_pad * esz < lim && outs < kHostDiv && a.Kred_pad * esz / kRowBytes + 4 < (int)kHostDiv;
+}
+int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream);
+size_t pwdw_wave_lds(const ConvArgs& a, int esz);
+constexpr int wave_mid_pitch(int esz) { return 32 * esz + 16; }
 int launch_conv_wave(const ConvArgs& a, int dtype, void* stream);
 size_t conv_wave_lds(int stages);
 int conv_wave_stages(int steps, int tiles);   // for shares of `steps` reduction steps of `tiles` tiles

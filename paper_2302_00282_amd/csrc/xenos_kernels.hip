@@ -2635,6 +2635,7 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
   }
   if (cfg == kPwDwCfg || a.pwdw) {
     if (cfg != kPwDwCfg || !a.pwdw || scalar_loader) return (int)hipErrorInvalidValue;
+    if (a.pwdw == 2) return launch_pwdw_wave(a, dtype, st);
     return launch_pwdw(a, dtype, st);
   }
   if (a.dw_w) {

@@ -1367,6 +1367,31 @@ struct Planner {
     return best < 1e300;
   }
 
+  // Tile of pwdw_wave_kernel, or false where the chain stays with pwdw_kernel: reductions of one step, which leave three wavefronts idle, and more
+  // than two workgroups per unit (MobileNet, bf16 / fp32, pwdw_kernel, two and four per unit: batch 2 95.4 / 168, 92.4 / 137, 95.6 / 140 us, batch
+  // 4 109.1 / 195.7, 108.8 / 190.9, 125.8 / 207).  Cycles of a workgroup: what it waits for, the bytes it loads or its MFMAs, the sum, the stencil.
+  // (Sizes of the chain only: the order of the pointwise sums must not depend on how many units there are; 256 stands for them.)
+  bool choose_pwdw_wave_tile(ConvArgs& c) const {
+    const int nsteps = c.Kred_pad * p.esz / kRowBytes, nh = (c.K + kWaveChannels - 1) / kWaveChannels, cg = kWaveChannels * p.esz / 16;
+    if (nsteps < 2 || !pwdw_wave_takes(c, p.esz)) return false;
+    double best = 1e300;
+    ConvArgs t = c, b = c;
+    for (t.th = 1; t.th <= c.OH; ++t.th)
+      for (t.tw = 1; t.tw <= c.OW; ++t.tw) {
+        if (wave_block_positions(c, t.th, t.tw) > kWaveRows) break;
+        t.tiles_y = (c.OH + t.th - 1) / t.th; t.tiles_x = (c.OW + t.tw - 1) / t.tw; t.tiles_m = c.N * t.tiles_y * t.tiles_x;
+        if (pwdw_wave_lds(t, p.esz) > std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024)) continue;
+        const double gemm = std::max(nsteps * 128.0, (nsteps + 3) / 4 * (p.esz == 2 ? 128.0 : 1024.0));
+        const double per = 1300 + gemm + std::ceil(t.th * t.tw * cg / 256.0) * (p.esz == 2 ? 1300 : 700);
+        const int wgs = t.tiles_m * nh;
+        const double cost = std::ceil(wgs / 256.0) * per + wgs;
+        if (cost < best) { best = cost; b = t; }
+      }
+    if (best >= 1e300 || b.tiles_m * nh > 512) return false;
+    c.th = b.th; c.tw = b.tw; c.tiles_y = b.tiles_y; c.tiles_x = b.tiles_x;
+    return true;
+  }
+
   // ---- link level 3, Fire module (Table 1, Conv1x1 -> Conv3x3; Section 4.1 last paragraph) -----------------------
   // squeeze = conv 1x1 / stride 1 / pad 0 (or, over whole reduction steps of input channels, 3x3 / stride 1 / pad 1: Table 1,
   // Conv3x3 -> Conv1x1 and Conv3x3 -> Conv3x3) with at most 64 output channels whose chain output is read by dense convolutions
@@ -2110,13 +2135,14 @@ struct Planner {
     a.vec_out = ov.sK == 1 && !ov.f32 && ov.esz == p.esz && ov.off % p.ce == 0 && ov.sP % p.ce == 0 && ov.sN % p.ce == 0;
     if (!a.vec_out) return fail(XENOS_EUNSUPPORTED, "%s: output of the pointwise -> depthwise chain is not aligned", st.name.c_str());
     if (!choose_pwdw_tile(a)) return fail(XENOS_EUNSUPPORTED, "%s: no tile of the pointwise -> depthwise kernel fits", st.name.c_str());
+    if (choose_pwdw_wave_tile(a)) a.pwdw = 2;
     a.tiles_m = a.N * a.tiles_y * a.tiles_x;
     a.tiles_n = (K + kPwDwChannels - 1) / kPwDwChannels;
     a.ntiles = a.tiles_m * a.tiles_n;
     a.xcd_m = 8;
-    a.grid = p.opts.split ? std::max(1, std::min(a.ntiles, 4 * std::max(1, p.hw.num_cu))) : 1;
+    a.grid = !p.opts.split ? 1 : a.pwdw == 2 ? 2 * a.ntiles : std::max(1, std::min(a.ntiles, 4 * std::max(1, p.hw.num_cu)));
     st.cfg = kPwDwCfg;
-    st.lds = pwdw_lds_bytes(a.th, a.tw, a.dw_stride, p.esz);
+    st.lds = a.pwdw == 2 ? pwdw_wave_lds(a, p.esz) : pwdw_lds_bytes(a.th, a.tw, a.dw_stride, p.esz);
     st.flops = 2.0 * is.n * is.h * is.w * (double)K * is.c + 2.0 * os.n * os.h * os.w * (double)K * 9;
     st.bytes_w += (long long)9 * K * p.esz;
     st.bytes_in = view_bytes(st.v_in); st.bytes_out = view_bytes(st.v_out);

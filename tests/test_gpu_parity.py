@@ -553,6 +553,30 @@ def test_reduction_shared_out_over_wavefronts(n, c, h, w, k, ksz, stride, kind, 
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("n,c,h,w,k,stride", [
+    (1, 136, 1, 1, 8, 1),        # one pixel, eight channels
+    (2, 72, 5, 4, 40, 1),        # a ragged last step and a ragged second channel part; a whole image in a tile
+    (1, 512, 14, 14, 96, 1),     # tiles clipped at every border
+    (3, 264, 9, 13, 64, 2),      # odd maps at stride 2, tiles of one and two outputs a row
+    (1, 1032, 7, 7, 32, 2),      # more steps than stages
+    (1, 128, 2, 40, 72, 1)])     # two rows
+def test_pointwise_depthwise_of_few_pixels(n, c, h, w, k, stride, compute):
+    b = wg.builder("pwdwave", (n, c, h, w), 89, nonzero_bias=True)
+    x = b.cbr(0, c, 1, name="pre")
+    t = b.cbr(x, k, 1, name="pw", relu=(stride == 1))
+    g = b.finish(b.cbr(t, k, 3, stride, 1, groups=k, name="dw", relu=(c != 72)))
+    fmt = dict(out_layout=1, out_dtype=compute)
+    y, info = check(g, compute=compute, link=3, **fmt)
+    tested, = [ch for ch in info["chains"] if ch.get("loader") == "pwdw"]
+    assert tested["grid"] == 2 * tested["tiles_m"] * tested["tiles_n"], tested      # (a workgroup takes 32 channels)
+    check_chains(g, compute, link=3, **fmt)
+    y1, _ = run_gpu(g, compute=compute, link=3, split=0, **fmt)
+    y8, _ = run_gpu(g, compute=compute, link=3, hw=dict(X_small=True), **fmt)
+    if all(ch.get("ksplit", 1) == 1 for ch in info["chains"]):    # (or the chain before it sums in another order)
+        assert np.array_equal(y, y1) and np.array_equal(y, y8)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("ksz", [1, 3])
 def test_tiles_of_images_beyond_4_gb(ksz, compute):
     # two images of 2.2 GB each: 1x1, and 3x3 / 2 in channel-chunk order, address them from a tile's first row.  The rows on either side

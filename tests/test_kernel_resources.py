@@ -57,9 +57,9 @@ def test_no_vector_register_is_spilled(kernels, kernel):
     assert not {k: v for k, v in found.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"]}
 
 
-@pytest.mark.parametrize("kernel,most", [("conv_wave_kernel", 128)])
-def test_wave_kernels_fit_four_wavefronts_per_simd(kernels, kernel, most):
-    # (nothing is spilled, and the LDS of a step, not registers, says how many workgroups share a unit)
+@pytest.mark.parametrize("kernel,most", [("conv_wave_kernel", 128), ("pwdw_wave_kernel", 256)])
+def test_wave_kernels_keep_everything_in_registers(kernels, kernel, most):
+    # (and leave room for four workgroups per unit, or two)
     found = {k: v for k, v in kernels.items() if re.search(r"\d" + kernel + r"I", k)}
     assert found and not {k: v for k, v in found.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"] or v["vgpr_count"] > most}
 
