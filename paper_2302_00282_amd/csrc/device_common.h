@@ -163,6 +163,14 @@ __device__ __forceinline__ int uniform_div(int n, int d) {
   return __builtin_amdgcn_readfirstlane(n < kSmallDiv ? SmallDiv(d)(n) : n / d);
 }
 
+// n / d of wavefront-uniform values by the host's multiplier, one scalar multiplication (the reciprocal on the vector unit, its conversions and
+// the way back were some 90 cycles each, three of them in a row before a tile's first request); mul = 0: by division
+__device__ __forceinline__ int tile_div(int n, int d, unsigned mul) {
+  if (mul) return (int)host_quotient((unsigned)n, mul);
+  asm volatile("" : "+s"(d));                          // (nothing of the division is worked out ahead, for calls that need none)
+  return n / d;
+}
+
 // Dynamic LDS of a kernel whose launches differ in their need: its limit is raised once, to all of a unit's memory.  (Raised to what
 // the launch at hand needs, two threads' first launches could leave the smaller limit behind.)
 constexpr int kLdsPerUnit = 160 * 1024;

@@ -215,8 +215,8 @@ __global__ __launch_bounds__(NT, 2) void pwdw_kernel(const ConvArgs a) {
   const SmallDiv by_tw(a.tw);
 
   for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
-    const int tile_n = uniform_div(t, a.tiles_m), tm = t - tile_n * a.tiles_m;  // neighbours share a weight slice
-    const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
+    const int tile_n = tile_div(t, a.tiles_m, a.q_tm), tm = t - tile_n * a.tiles_m;  // neighbours share a weight slice
+    const int n = tile_div(tm, tiles_sp, a.q_sp), rr = tm - n * tiles_sp, ty = tile_div(rr, a.tiles_x, a.q_tx), tx = rr - ty * a.tiles_x;
     const int oy0 = ty * a.th, ox0 = tx * a.tw;                    // first depthwise output pixel of the tile
     const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
     const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.H ? iy0 + PH : a.H;
@@ -340,7 +340,9 @@ static int launch_pwdw_t(const ConvArgs& a, hipStream_t st) {
   static std::atomic<bool> raised{false};
   const hipError_t e = raise_lds_limit(pwdw_kernel<T>, raised);
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL((pwdw_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
+  ConvArgs b = a;
+  b.set_quotients();
+  hipLaunchKernelGGL((pwdw_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, b);
   return (int)hipGetLastError();
 }
 
@@ -429,8 +431,8 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     int tid = (int)threadIdx.x;
     if constexpr (KGS == 4 || (KGS == 3 && POOL)) asm volatile("" : "+v"(tid));
     const int lane = tid & 63, l31 = lane & 31, lhalf = lane >> 5;
-    const int gz = uniform_div(t, a.tiles_m), tm = t - gz * a.tiles_m;   // channel share, spatial tile
-    const int n = uniform_div(tm, tiles_sp), rr = tm - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
+    const int gz = tile_div(t, a.tiles_m, a.q_tm), tm = t - gz * a.tiles_m;   // channel share, spatial tile
+    const int n = tile_div(tm, tiles_sp, a.q_sp), rr = tm - n * tiles_sp, ty = tile_div(rr, a.tiles_x, a.q_tx), tx = rr - ty * a.tiles_x;
     // first conv-output pixel of the tile
     const int oy0 = POOL ? ty * a.pph * a.ps - a.pp : ty * a.th, ox0 = POOL ? tx * a.ppw * a.ps - a.pp : tx * a.tw;
     const int iy0 = oy0 - ring, ix0 = ox0 - ring;                  // map position of block position (0, 0)
@@ -733,7 +735,9 @@ static int launch_fire_kgs(const ConvArgs& a, int lds, hipStream_t st) {
   static std::atomic<bool> raised{false};
   const hipError_t e = raise_lds_limit(fire_kernel<T, POOL, TAPS1, KGS>, raised);
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL((fire_kernel<T, POOL, TAPS1, KGS>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, a);
+  ConvArgs b = a;
+  b.set_quotients();
+  hipLaunchKernelGGL((fire_kernel<T, POOL, TAPS1, KGS>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(NT), lds, st, b);
   return (int)hipGetLastError();
 }
 

@@ -58,9 +58,11 @@ __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(co
 struct UnitWeights {
   const void* w;
   int kgs, nkg, ncb, parts;
-  __device__ __forceinline__ UnitWeights(const void* w_, int kgs_, int nkg_, int ncb_, int nrows) : w(w_), kgs(kgs_), nkg(nkg_), ncb(ncb_), parts(ncb_ * ((nrows + 63) / 64)) {}
+  unsigned mul;                                        // multiplier of quotients by ncb (0: division)
+  __device__ __forceinline__ UnitWeights(const void* w_, int kgs_, int nkg_, int ncb_, unsigned mul_, int nrows)
+      : w(w_), kgs(kgs_), nkg(nkg_), ncb(ncb_), parts(ncb_ * ((nrows + 63) / 64)), mul(mul_) {}
   __device__ __forceinline__ rsrc_t window(int u) const {
-    const int cb = u - uniform_div(u, ncb) * ncb;
+    const int cb = u - tile_div(u, ncb, mul) * ncb;
     return make_window((const unsigned char*)w + (long long)cb * kgs * 1024, u < parts ? nkg * 1024u : 0u);
   }
 };
@@ -83,7 +85,7 @@ __device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN
   if (NEXT && wave >= w.parts) unit_request(next, rb);
 #pragma unroll 1
   for (int u = wave; u < w.parts; u += UN_NW) {
-    const int rg = uniform_div(u, ncb), cb = u - rg * ncb, row0 = rg * 64;
+    const int rg = tile_div(u, ncb, w.mul), cb = u - rg * ncb, row0 = rg * 64;
     const bool two = row0 + 32 < nrows;                            // (uniform)
     const rsrc_t wp = w.window(u), wn = u + UN_NW < w.parts ? w.window(u + UN_NW) : next;
     pre(cb, row0);
@@ -171,15 +173,15 @@ __global__ __launch_bounds__(UN_NT, 2) void unit_kernel(const ConvArgs a) {
     const int tid = thread_here(), lane = tid & 63, l31 = lane & 31, lhalf = lane >> 5;
     const int pg = by_cgs(tid), cg = tid - pg * cgs;
     const bool dw_on = pg < pgs;
-    const int n = uniform_div(t, tiles_sp), rr = t - n * tiles_sp, ty = uniform_div(rr, a.tiles_x), tx = rr - ty * a.tiles_x;
+    const int n = tile_div(t, tiles_sp, a.q_sp), rr = t - n * tiles_sp, ty = tile_div(rr, a.tiles_x, a.q_tx), tx = rr - ty * a.tiles_x;
     const int oy0 = ty * a.th, ox0 = tx * a.tw;
     const int iy0 = oy0 * s - 1, ix0 = ox0 * s - 1;                // map position of block position (0, 0)
     const int y_lo = iy0 > 0 ? iy0 : 0, y_hi = iy0 + PH < a.dw_H ? iy0 + PH : a.dw_H;
     const int x_lo = ix0 > 0 ? ix0 : 0, x_hi = ix0 + PWd < a.dw_W ? ix0 + PWd : a.dw_W;
     const int wv = x_hi - x_lo, npos = (y_hi - y_lo) * wv;          // the part of the block inside the map (never empty)
     const SmallDiv by_wv(wv);
-    const UnitWeights w1(a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, (C + 31) / 32, npos);
-    const UnitWeights w2(a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, (a.K + 31) / 32, npx);
+    const UnitWeights w1(a.fire_w[0], a.unit_kred * ESZ / 32, (C1 * ESZ + 31) / 32, (C + 31) / 32, a.q_c, npos);
+    const UnitWeights w2(a.w, a.Kred_pad * ESZ / 32, (C * ESZ + 31) / 32, (a.K + 31) / 32, a.q_k, npx);
 
     // ---- the input block, all channels; k-groups are filled up with zeros ---------------------------------
     {
@@ -392,7 +394,9 @@ static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
   static std::atomic<bool> raised{false};
   const hipError_t e = raise_lds_limit(unit_kernel<T>, raised);
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL((unit_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(UN_NT), lds, st, a);
+  ConvArgs b = a;
+  b.set_quotients();
+  hipLaunchKernelGGL((unit_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(UN_NT), lds, st, b);
   return (int)hipGetLastError();
 }
 
