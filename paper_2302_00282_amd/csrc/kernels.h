@@ -90,6 +90,7 @@ static const int kUnitCfg = 11;
 // shared out over the wavefronts of its workgroup
 static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;
+static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64 (bf16)
 static const int kFcWgPerCu = 1;
 static const int kFcDirectSteps = 16;   // reductions of at most this many 64-element steps are not shared out (no summing pass)    // workgroups per compute unit the reduction split of such a chain aims at
 static const int kPairChannels = 64, kPairRed = 48;
@@ -292,9 +293,9 @@ inline bool pwdw_wave_takes(const ConvArgs& a, int esz) {
 int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream);
 size_t pwdw_wave_lds(const ConvArgs& a, int esz);
 constexpr int wave_mid_pitch(int esz) { return 32 * esz + 16; }
-int launch_conv_wave(const ConvArgs& a, int dtype, void* stream);
-size_t conv_wave_lds(int stages);
-int conv_wave_stages(int steps, int tiles);   // for shares of `steps` reduction steps of `tiles` tiles
+int launch_conv_wave(const ConvArgs& a, int dtype, int edge, void* stream);
+size_t conv_wave_lds(int edge, int stages);
+int conv_wave_stages(int edge, int steps, int tiles);   // for shares of `steps` reduction steps of `tiles` tiles
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

@@ -28,16 +28,15 @@ __device__ __forceinline__ void load_to_lds(rsrc_t w, unsigned char* dst, unsign
   __builtin_amdgcn_raw_ptr_buffer_load_lds(w, (lds_ptr_t)dst, 16, (int)off, (int)soff, 0, 0);
 }
 
-// A wavefront's share of a tile of 32 * RB rows x 32 channels (transposed: accumulator rows are channels, columns the tile's rows).
-template <typename T, int RB>
+// A wavefront's share of a tile of 32 * NB rows x 32 * NB channels (transposed: accumulator rows are channels, columns the tile's rows).
+template <typename T, int NB>
 struct WaveTile {
-  static constexpr int ROWS = 32 * RB + 32;            // pixel rows, then channel rows, of a step
-  static constexpr int STAGE = ROWS * ROWB;            // LDS of a step
-  static constexpr int LOADS = ROWS / 8;               // requests of a step
-  static constexpr int MAX_STAGES = 4;
-  static constexpr int SUM_PITCH = 36;                 // floats of a row of the partial tile in LDS
-  static constexpr int SUM_BYTES = 32 * RB * SUM_PITCH * 4;
-  static_assert(SUM_BYTES <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
+  static constexpr int EDGE = 32 * NB;
+  static constexpr int STAGE = 2 * EDGE * ROWB;        // LDS of a step: pixel rows, then channel rows
+  static constexpr int LOADS = 2 * EDGE / 8;           // requests of a step
+  static constexpr int MAX_STAGES = NB == 1 ? 4 : 2;
+  static constexpr int SLOTS = EDGE / 4;               // four channels each, of a row of the partial tile in LDS
+  static_assert(EDGE * EDGE * 4 <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
 
   // n steps, `stages` (1 .. MAX_STAGES) of them on their way at a time; request(i, dst) issues LOADS requests for step i of this wavefront
   template <typename Request>
@@ -46,57 +45,71 @@ struct WaveTile {
     for (int d = 0; d < stages && d < n; ++d) request(d, s_w + d * STAGE);
   }
   template <typename Request>
-  __device__ __forceinline__ static void finish(int n, int stages, unsigned char* s_w, Request request, f32x16_t (&acc)[RB]) {
+  __device__ __forceinline__ static void finish(int n, int stages, unsigned char* s_w, Request request) {
     const int lane = threadIdx.x & 63, l31 = lane & 31, lhalf = lane >> 5;
     // (row l31 of every block of 32 has the same swizzle; k-group kg is chunks 2 kg and 2 kg + 1, the lane's half chooses)
     int slot[KG];
 #pragma unroll
     for (int kg = 0; kg < KG; ++kg) slot[kg] = l31 * ROWB + (((2 * kg + lhalf) ^ wave_swizzle(l31)) * 16);
+    f32x16_t acc[NB][NB];                                              // [pixel block][channel block]
+#pragma unroll
+    for (int r = 0; r < NB; ++r)
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[r][c][e] = 0.f;
     unsigned char* s = s_w;
     int st = 0;
+    // (the fragments of a step are read behind the multiplications of the step before it: requested ahead of them, in twice the registers, they
+    // cost 4 to 7 % of the chains' time)
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
       const int behind = n - 1 - i < stages - 1 ? n - 1 - i : stages - 1;   // (uniform) steps requested behind this one
-      if (behind >= 3) wait_requests<3 * LOADS>();
-      else if (behind == 2) wait_requests<2 * LOADS>();
+      if (MAX_STAGES > 3 && behind >= 3) wait_requests<(MAX_STAGES > 3 ? 3 : 0) * LOADS>();
+      else if (MAX_STAGES > 2 && behind == 2) wait_requests<(MAX_STAGES > 2 ? 2 : 0) * LOADS>();
       else if (behind == 1) wait_requests<LOADS>();
       else wait_requests<0>();
-      u32x4_t fa[RB][KG], fb[KG];
+      u32x4_t fa[NB][KG], fb[NB][KG];
 #pragma unroll
-      for (int kg = 0; kg < KG; ++kg) {
+      for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) fa[r][kg] = *(const u32x4_t*)(s + r * 32 * ROWB + slot[kg]);
-        fb[kg] = *(const u32x4_t*)(s + RB * 32 * ROWB + slot[kg]);
-      }
+        for (int r = 0; r < NB; ++r) {
+          fa[r][kg] = *(const u32x4_t*)(s + r * 32 * ROWB + slot[kg]);
+          fb[r][kg] = *(const u32x4_t*)(s + (NB + r) * 32 * ROWB + slot[kg]);
+        }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // the stage has been read: it may be written again
       if (i + stages < n) request(i + stages, s);
 #pragma unroll
       for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-          if constexpr (sizeof(T) == 2) {
-            acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[kg]), __builtin_bit_cast(bf16x8_t, fa[r][kg]), acc[r], 0, 0, 0);
-          } else {
+        for (int r = 0; r < NB; ++r)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[r] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[kg][e]), __uint_as_float(fa[r][kg][e]), acc[r], 0, 0, 0);
+          for (int c = 0; c < NB; ++c) {
+            if constexpr (sizeof(T) == 2) {
+              acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[c][kg]), __builtin_bit_cast(bf16x8_t, fa[r][kg]), acc[r][c], 0, 0, 0);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[c][kg][e]), __uint_as_float(fa[r][kg][e]), acc[r][c], 0, 0, 0);
+            }
           }
-        }
       if (++st == stages) { st = 0; s = s_w; } else { s += STAGE; }
     }
-    // the partial tile, [row][channel], in this wavefront's own LDS
-    float* part = (float*)s_w;
+    // the partial tile, [row][channel], in this wavefront's own LDS; four channels of row r lie in slot (their number ^ r)
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
+    for (int r = 0; r < NB; ++r)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(f32x4_t*)(part + (r * 32 + l31) * SUM_PITCH + g * 8 + lhalf * 4) = f32x4_t{acc[r][4 * g], acc[r][4 * g + 1], acc[r][4 * g + 2], acc[r][4 * g + 3]};
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *(f32x4_t*)(s_w + (r * 32 + l31) * EDGE * 4 + (((c * 8 + g * 2 + lhalf) ^ l31) & (SLOTS - 1)) * 16) =
+              f32x4_t{acc[r][c][4 * g], acc[r][c][4 * g + 1], acc[r][c][4 * g + 2], acc[r][c][4 * g + 3]};
   }
-  // four channels of a row, the wavefronts' partial tiles (wave_bytes apart) added in their order
-  __device__ __forceinline__ static f32x4_t sum(const unsigned char* s, int wave_bytes, int row, int c) {
+  // channels 4 c4 .. 4 c4 + 3 of a row, the wavefronts' partial tiles (wave_bytes apart) added in their order
+  __device__ __forceinline__ static f32x4_t sum(const unsigned char* s, int wave_bytes, int row, int c4) {
     f32x4_t v[4];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + (row * SUM_PITCH + c) * 4);
+    for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + row * EDGE * 4 + ((c4 ^ row) & (SLOTS - 1)) * 16);
     return ((v[0] + v[1]) + v[2]) + v[3];
   }
 };

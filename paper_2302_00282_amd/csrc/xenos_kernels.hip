@@ -2647,9 +2647,9 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
     if (scalar_loader) return (int)hipErrorInvalidValue;
     return dtype == DT_BF16 ? launch_conv3x3_t<bf16_t>(a, st) : launch_conv3x3_t<float>(a, st);
   }
-  if (cfg == kWaveCfg) {
+  if (cfg == kWaveCfg || cfg == kWave64Cfg) {
     if (scalar_loader) return (int)hipErrorInvalidValue;
-    return launch_conv_wave(a, dtype, st);
+    return launch_conv_wave(a, dtype, cfg == kWave64Cfg ? 64 : kWaveRows, st);
   }
   if (cfg == kStemCfg) return dtype == DT_BF16 ? launch_stem_t<bf16_t>(a, st) : launch_stem_t<float>(a, st);
   return dtype == DT_BF16 ? launch_conv_t<bf16_t>(a, cfg, scalar_loader, st) : launch_conv_t<float>(a, cfg, scalar_loader, st);

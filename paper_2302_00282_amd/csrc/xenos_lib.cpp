@@ -791,23 +791,23 @@ struct Planner {
     st.cfg = best;
     set_grid(c, best);
     st.lds = conv_lds_bytes(best, c.mode);
-    if (wave_wanted(st)) {
-      c.tiles_m = (c.M_total + kWaveRows - 1) / kWaveRows; c.tiles_n = (c.K + kWaveChannels - 1) / kWaveChannels; c.ntiles = c.tiles_m * c.tiles_n;
+    if (const int edge = wave_edge(st)) {
+      c.tiles_m = (c.M_total + edge - 1) / edge; c.tiles_n = (c.K + edge - 1) / edge; c.ntiles = c.tiles_m * c.tiles_n;
       c.xcd_m = 1;
       c.grid = p.opts.split ? c.ntiles : 1;
-      st.cfg = kWaveCfg;
-      st.lds = conv_wave_lds(conv_wave_stages(c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
-      st.cands.push_back(Step::Cand{kWaveCfg, c, st.lds});
+      st.cfg = edge == 64 ? kWave64Cfg : kWaveCfg;
+      st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
+      st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
     }
     return XENOS_OK;
   }
 
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
   // chain only: the order of its sums then does not depend on how many units there are.
-  bool wave_wanted(const Step& st) const {
+  int wave_edge(const Step& st) const {
     const ConvArgs& c = st.conv;
     if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res) || !conv_wave_takes(c, p.esz))
-      return false;
+      return 0;
     const long long tiles = (long long)((c.M_total + kWaveRows - 1) / kWaveRows) * ((c.K + kWaveChannels - 1) / kWaveChannels);
     // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 and eight in fp32 0.65 to 1; where units
     // get more the larger tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36)
@@ -817,10 +817,19 @@ struct Planner {
       // Layers that the halo kernel shares out: those of maps up to eight wide and the longest reductions of more than two tiles per unit stay
       // there (512 channels 14x14 batch 9, 896 tiles: bf16 79 us there, 94 here; the small maps would be faster here, 256 channels 7x7 batch 32
       // 34 us against 65, but their plans are part of what the planner's tests fix)
-      if (c.W <= 8) return false;
+      if (c.W <= 8) return 0;
       if (c.Kred > 4096) most = 512;
     }
-    return tiles <= most && conv_wave_lds(conv_wave_stages(c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu;
+    // bf16, more than two 32 x 32 tiles per unit: 64 x 64 ones, at most two per unit, where a share has steps enough (3x3 layers, four in a row:
+    // 256 channels 14x14 batch 16 56.8 -> 47.2 us, batch 32 75.3 on the halo kernel -> 61.9, 128 channels 28x28 batch 8 38.7 -> 35.1, 48 -> 192
+    // channels 27x27 batch 32 69.0 on the gather tiles -> 62.8; 1x1 512 channels 7x7 batch 32 27.8 -> 31.2, which is why eight steps are too few;
+    // 784 tiles of 64 x 64 take 75.9 us against the halo kernel's 53.3).  In fp32, whose MFMAs cover the smaller tile's loads, they gain nothing
+    const long long tiles64 = (long long)((c.M_total + 63) / 64) * ((c.K + 63) / 64);
+    const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
+    if (p.dt == DT_BF16 && tiles > 512 && tiles64 <= 512 && nsteps >= (tiles <= 1024 ? 16 : 9) && most > 512 &&
+        conv_wave_lds(64, conv_wave_stages(64, nsteps, (int)tiles64)) <= p.hw.lds_bytes_per_cu)
+      return 64;
+    return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
   // Shares of a wave chain's reduction (1 = none)
   int wave_shares(const ConvArgs& c) const {
@@ -1986,7 +1995,7 @@ struct Planner {
         }
         xenos_status rc = split_conv(st);
         if (rc != XENOS_OK) return rc;
-        if (st.cfg == kWaveCfg) hsplit.ks = 0;
+        if (st.cfg == kWaveCfg || st.cfg == kWave64Cfg) hsplit.ks = 0;
         if (hsplit.ks >= 2) a.kchunk = 1;                          // (the order of the halo kernel, which runs the chain whatever split_conv chose)
         pack_weights();
         if (a.dw_panel > 0) st.lds = dwpw_lds_bytes(a.dw_panel, p.esz);
@@ -2050,7 +2059,7 @@ struct Planner {
             a.ksplit = ks; a.steps_per_split = (nsteps + ks - 1) / ks;
             a.part_ld = a.tiles_n * kWaveChannels;
             a.grid = a.ntiles * ks;
-            st.lds = conv_wave_lds(conv_wave_stages(a.steps_per_split, a.ntiles * ks));
+            st.lds = conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, a.steps_per_split, a.ntiles * ks));
             st.cands.clear();                                      // the plan's structure now depends on this split
             return emit_with_summing_pass();
           }
@@ -2432,7 +2441,8 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg stem_lds_tc{kStemLdsTh * kStemLdsTw, c.K, 32, c.K};
       const TileCfg pwdw_tc{64, kPwDwChannels, 32, 32};
       const TileCfg wave_tc{kWaveRows, kWaveChannels, 32, 32};
-      const TileCfg& tc = s.cfg == kWaveCfg ? wave_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
+      const TileCfg wave64_tc{64, 64, 64, 64};
+      const TileCfg& tc = s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
                "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d",

@@ -1,6 +1,6 @@
 // gfx950 (CDNA4) kernel of small dense convolution chains:
 //
-//  conv_wave_kernel   implicit-GEMM convolution chain (any kernel size and stride) in tiles of 32 pixels x 32 channels, the reduction of a tile shared out over the four wavefronts of its workgroup
+//  conv_wave_kernel   implicit-GEMM convolution chain (any kernel size and stride) in tiles of 32 pixels x 32 channels (or 64 x 64), the reduction of a tile shared out over the four wavefronts of its workgroup
 //                     (wave_gemm.h); scale / shift, shortcut and ReLU in the sum of the partial tiles, or raw sums for a reduction
 //                     that is split over workgroups too.
 #include "wave_gemm.h"
@@ -28,12 +28,12 @@ struct WaveConvArgs {
 // UNI: the tap of a step is the same for all lanes (1x1, or the taps of a channel chunk in consecutive steps); otherwise every 16 bytes of
 // a step have a tap of their own (fewer channels than a step, or a ragged number).
 // DIRECT = false: the input lies at an address that is no multiple of 16 bytes (a tensor of the caller's); it then passes through registers
-template <typename T, bool UNI, bool DIRECT>
-__global__ __launch_bounds__(NT, 4) void conv_wave_kernel(const WaveConvArgs a) {
+template <typename T, int NB, bool UNI, bool DIRECT>
+__global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const WaveConvArgs a) {
   FETCH_ARGS(WaveConvArgs);
   using tr = Tr<T>;
-  using tile = WaveTile<T, 1>;
-  constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T);
+  using tile = WaveTile<T, NB>;
+  constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T), EDGE = tile::EDGE;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lrow = lane >> 3, lslot = lane & 7;                    // a request is 8 rows of 8 slots
@@ -52,20 +52,20 @@ __global__ __launch_bounds__(NT, 4) void conv_wave_kernel(const WaveConvArgs a) 
     // the lane's pixel row, handed on to the lanes that load it
     int off, yx;
     {
-      const int m = (int)tm * 32 + (lane & 31);
+      const int m = (int)tm * EDGE + (lane & (EDGE - 1));
       const int img = small_quotient(m, a.r_ohw), p = m - img * a.OHW, oh = small_quotient(p, a.r_ow), ow = p - oh * a.OW;
       const int ih = m < a.M ? oh * a.stride - a.pad : -0x4000, iw = ow * a.stride - a.pad;
       off = (int)((unsigned)img * a.sN + (unsigned)ih * a.sH + (unsigned)iw * a.sW);
       yx = (int)(((unsigned)ih << 16) | ((unsigned)iw & 0xffffu));
     }
-    int aoff[4], ayx[4];
+    int aoff[4 * NB], ayx[4 * NB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < 4 * NB; ++j) {
       aoff[j] = __builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, off) + (UNI ? ch[j & 1] * 16 : 0);
       ayx[j] = __builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, yx);
     }
     const unsigned woff[2] = {lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
-    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * 32 * a.wpitch, kWindow);
+    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * EDGE * a.wpitch, kWindow);
     auto request = [&](int i, unsigned char* dst) __attribute__((always_inline)) {
       const uint32_t s = (uint32_t)(s_begin + wave + 4 * i);
       // row and column of the kernel, offset and validity of the two chunks that the lane loads of a row
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(NT, 4) void conv_wave_kernel(const WaveConvArgs a) 
         }
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < 4 * NB; ++j) {
         const int y = (ayx[j] >> 16) + kr[j & 1], x = (int)(short)ayx[j] + kc[j & 1];
         const bool ok = ((unsigned)y < (unsigned)a.H) & ((unsigned)x < (unsigned)a.W) & kok[j & 1];
         unsigned o = ok ? (unsigned)aoff[j] + koff[j & 1] : kNoLoad;
@@ -99,54 +99,60 @@ __global__ __launch_bounds__(NT, 4) void conv_wave_kernel(const WaveConvArgs a) 
         else *(u32x4_t*)(dst + j * 1024 + lane * 16) = load_window(wa, o);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) load_to_lds(wb, dst + 4096 + j * 1024, woff[j & 1], j * 8 * a.wpitch + s * ROWB);
+      for (int j = 0; j < 4 * NB; ++j) load_to_lds(wb, dst + (4 * NB + j) * 1024, woff[j & 1], j * 8 * a.wpitch + s * ROWB);
     };
     tile::begin(n, a.stages, s_w, request);
 
-    // what the epilogue reads: on its way during the reduction.  The thread finishes channels k .. k + 3 of pixel row m
-    const int row = tid >> 3, c = (tid & 7) * 4, m = (int)tm * 32 + row, k = (int)tn * 32 + c;
-    const bool live = m < a.M && k < a.K;
-    const int img = small_quotient(m, a.r_ohw), p = m - img * a.OHW;
+    // what the epilogue reads: on its way during the reduction.  The thread finishes channels k .. k + 3 of every RS-th pixel row
+    constexpr int RS = NT / tile::SLOTS, U = EDGE / RS;
+    const int c4 = tid % tile::SLOTS, k = (int)tn * EDGE + c4 * 4, m0 = (int)tm * EDGE + tid / tile::SLOTS;
     f32x4_t sc = {}, sh = {};
-    u32x4_t res = {};                                              // (as they lie in memory: converted behind the reduction)
     if (!(a.flags & WF_PARTIAL)) {
       sc = *(const f32x4_t*)(a.scale + k);
       sh = *(const f32x4_t*)(a.shift + k);
     }
+    u32x4_t res[U];                                                // (as they lie in memory: converted behind the reduction)
+#pragma unroll
+    for (int u = 0; u < U; ++u) res[u] = u32x4_t{0u, 0u, 0u, 0u};
     if (a.res) {                                                   // (uniform)
-      unsigned o = live ? (unsigned)img * a.res_sN + (unsigned)p * a.res_sP + k * ESZ : kNoLoad;
-      asm volatile("" : "+v"(o));
       const rsrc_t wr = make_window(a.res, kWindow);
-      if constexpr (ESZ == 2) {
-        const uint2 r = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(wr, (int)o, 0, 0));
-        res[0] = r.x; res[1] = r.y;
-      } else {
-        res = load_window(wr, o);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int m = m0 + u * RS, img = small_quotient(m, a.r_ohw), p = m - img * a.OHW;
+        unsigned o = (m < a.M) & (k < a.K) ? (unsigned)img * a.res_sN + (unsigned)p * a.res_sP + k * ESZ : kNoLoad;
+        asm volatile("" : "+v"(o));
+        if constexpr (ESZ == 2) {
+          const uint2 r = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(wr, (int)o, 0, 0));
+          res[u][0] = r.x; res[u][1] = r.y;
+        } else {
+          res[u] = load_window(wr, o);
+        }
       }
     }
-    f32x16_t acc[1];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[0][e] = 0.f;
-    tile::finish(n, a.stages, s_w, request, acc);
+    tile::finish(n, a.stages, s_w, request);
     __syncthreads();
-    f32x4_t v = tile::sum(smem, wave_bytes, row, c);
-    if (live) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = m0 + u * RS;
+      f32x4_t v = tile::sum(smem, wave_bytes, tid / tile::SLOTS + u * RS, c4);
+      if (m >= a.M || k >= a.K) continue;
       if (a.flags & WF_PARTIAL) {
         *(f32x4_t*)((float*)a.out + ((size_t)z * a.M + m) * a.part_ld + k) = v;
-      } else {
-        v = v * sc + sh;
-        if (a.res) {
-          if constexpr (ESZ == 2) v += f32x4_t{bf2f((uint16_t)res[0]), __uint_as_float(res[0] & 0xffff0000u), bf2f((uint16_t)res[1]), __uint_as_float(res[1] & 0xffff0000u)};
-          else v += __builtin_bit_cast(f32x4_t, res);
-        }
-        if (a.flags & WF_RELU) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = fmx(v[e], 0.f);
-        }
-        unsigned char* dst = (unsigned char*)a.out + (size_t)((unsigned)img * a.out_sN + (unsigned)p * a.out_sP);
-        if (ESZ == 4 || (a.flags & WF_OUT_F32)) *(f32x4_t*)(dst + k * 4) = v;
-        else *(uint2*)(dst + k * 2) = uint2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
+        continue;
       }
+      v = v * sc + sh;
+      if (a.res) {
+        if constexpr (ESZ == 2) v += f32x4_t{bf2f((uint16_t)res[u][0]), __uint_as_float(res[u][0] & 0xffff0000u), bf2f((uint16_t)res[u][1]), __uint_as_float(res[u][1] & 0xffff0000u)};
+        else v += __builtin_bit_cast(f32x4_t, res[u]);
+      }
+      if (a.flags & WF_RELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmx(v[e], 0.f);
+      }
+      const int img = small_quotient(m, a.r_ohw), p = m - img * a.OHW;
+      unsigned char* dst = (unsigned char*)a.out + (size_t)((unsigned)img * a.out_sN + (unsigned)p * a.out_sP);
+      if (ESZ == 4 || (a.flags & WF_OUT_F32)) *(f32x4_t*)(dst + k * 4) = v;
+      else *(uint2*)(dst + k * 2) = uint2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
     }
     __syncthreads();                                               // the partial tiles are rewritten
   }
@@ -237,14 +243,11 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
       const u32x4_t z = {0u, 0u, 0u, 0u};
       for (int i = tid; i < PH * PWd * (MP / 16); i += NT) *(u32x4_t*)(s_mid + i * 16) = z;
     }
-    f32x16_t acc[1];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[0][e] = 0.f;
-    tile::finish(n_w, a.stages, s_w, request, acc);
+    tile::finish(n_w, a.stages, s_w, request);
     __syncthreads();
     if (const int m = tid >> 3; m < npos) {
       const int py = small_quotient(m, r_wv), px = m - py * wv;
-      f32x4_t v = tile::sum(smem, wave_bytes, m, c4) * psc + psh;
+      f32x4_t v = tile::sum(smem, wave_bytes, m, tid & 7) * psc + psh;
       const float lo = relu_floor(a.flags & WF_RELU);
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = fmx_floor(v[e], lo);
@@ -285,34 +288,35 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
   }
 }
 
-size_t conv_wave_lds(int stages) { return (size_t)4 * stages * WaveTile<float, 1>::STAGE; }
+size_t conv_wave_lds(int edge, int stages) { return (size_t)4 * stages * 2 * edge * ROWB; }
 
 // Steps of a wavefront that are on their way at a time: up to four where a unit has one workgroup, two where it has two, one where it has
 // more, which then hide each other's latency (3x3 layers in bf16, four in a row: 128 channels 28x28 batch 4, 392 tiles, four 36.8 us, two
 // 25.9; 256 channels 14x14 batch 16, 784 tiles, two 60.8, one 56.2; 400 tiles of 144 steps, two 51.8, one 58.5)
-int conv_wave_stages(int steps, int tiles) {
-  const int n = (steps + 3) / 4, most = tiles <= 256 ? 4 : tiles <= 512 ? 2 : 1;
+// (64 x 64 tiles: a stage is 64 KB.  256 channels 14x14, 196 tiles, one 49.9, two 47.2; 392 tiles, two workgroups to a unit, one 61.9, two 85.3)
+int conv_wave_stages(int edge, int steps, int tiles) {
+  const int n = (steps + 3) / 4, most = edge > kWaveRows ? (tiles <= 256 ? 2 : 1) : tiles <= 256 ? 4 : tiles <= 512 ? 2 : 1;
   return n < 1 ? 1 : n < most ? n : most;
 }
 
-template <typename T, bool UNI, bool DIRECT>
+template <typename T, int NB, bool UNI, bool DIRECT>
 static int launch_conv_wave_inst(const WaveConvArgs& w, int grid, int lds, hipStream_t st) {
   static std::atomic<bool> raised{false};
-  const hipError_t e = raise_lds_limit(conv_wave_kernel<T, UNI, DIRECT>, raised);
+  const hipError_t e = raise_lds_limit(conv_wave_kernel<T, NB, UNI, DIRECT>, raised);
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL((conv_wave_kernel<T, UNI, DIRECT>), dim3(std::min((uint32_t)grid, w.tiles)), dim3(NT), lds, st, w);
+  hipLaunchKernelGGL((conv_wave_kernel<T, NB, UNI, DIRECT>), dim3(std::min((uint32_t)grid, w.tiles)), dim3(NT), lds, st, w);
   return (int)hipGetLastError();
 }
 
-template <typename T>
+template <typename T, int NB>
 static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
-  constexpr int ESZ = (int)sizeof(T), BKE = Tr<T>::BKE;
+  constexpr int ESZ = (int)sizeof(T), BKE = Tr<T>::BKE, EDGE = 32 * NB;
   const bool partial = a.ksplit >= 1;
   const int ks = partial ? a.ksplit : 1;
   // what the kernel assumes, checked again on the host
-  if (!conv_wave_takes(a, ESZ) || a.dw_w || a.pair || a.ileave || a.pool != POOL_NONE || a.tiles_m != (a.M_total + 31) / 32 || a.tiles_n != (a.K + 31) / 32 ||
+  if (!conv_wave_takes(a, ESZ) || a.dw_w || a.pair || a.ileave || a.pool != POOL_NONE || a.tiles_m != (a.M_total + EDGE - 1) / EDGE || a.tiles_n != (a.K + EDGE - 1) / EDGE ||
       (!partial && (a.out_sK != 1 || (a.has_res && (!a.vec_res || !a.res)))) ||
-      (partial && (!a.part || a.part_ld < a.tiles_n * 32 || a.steps_per_split < 1)) || a.grid < 1)
+      (partial && (!a.part || a.part_ld < a.tiles_n * EDGE || a.steps_per_split < 1)) || a.grid < 1)
     return (int)hipErrorInvalidValue;
   WaveConvArgs w{};
   w.in = a.in; w.w = a.w; w.scale = a.scale; w.shift = a.shift; w.res = !partial && a.has_res ? a.res : nullptr; w.out = partial ? (void*)a.part : a.out;
@@ -326,18 +330,18 @@ static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
   w.K = a.K; w.part_ld = a.part_ld; w.flags = (a.relu ? WF_RELU : 0) | (partial ? WF_PARTIAL : 0) | (a.out_f32 ? WF_OUT_F32 : 0);
     const int osz = a.out_f32 ? 4 : ESZ;
   w.out_sN = (uint32_t)(a.out_sN * osz); w.out_sP = (uint32_t)(a.out_sP * osz); w.res_sN = (uint32_t)(a.res_sN * ESZ); w.res_sP = (uint32_t)(a.res_sP * ESZ);
-  w.stages = conv_wave_stages(w.steps_per_share, (int)w.tiles);
-  const int lds = (int)conv_wave_lds(w.stages);
+  w.stages = conv_wave_stages(EDGE, w.steps_per_share, (int)w.tiles);
+  const int lds = (int)conv_wave_lds(EDGE, w.stages);
   const bool direct = ((uintptr_t)a.in & 15) == 0;
   if (a.R * a.S == 1 || a.kchunk)
-    return direct ? launch_conv_wave_inst<T, true, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, true, false>(w, a.grid, lds, st);
-  return direct ? launch_conv_wave_inst<T, false, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, false, false>(w, a.grid, lds, st);
+    return direct ? launch_conv_wave_inst<T, NB, true, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, NB, true, false>(w, a.grid, lds, st);
+  return direct ? launch_conv_wave_inst<T, NB, false, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, NB, false, false>(w, a.grid, lds, st);
 }
 
-static int pwdw_wave_stages(const ConvArgs& a, int esz) { return conv_wave_stages(a.Kred_pad * esz / ROWB, a.tiles_m * ((a.K + 31) / 32)); }
+static int pwdw_wave_stages(const ConvArgs& a, int esz) { return conv_wave_stages(kWaveRows, a.Kred_pad * esz / ROWB, a.tiles_m * ((a.K + 31) / 32)); }
 size_t pwdw_wave_lds(const ConvArgs& a, int esz) {
   const int s = a.dw_stride;
-  return conv_wave_lds(pwdw_wave_stages(a, esz)) + (size_t)((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3) * wave_mid_pitch(esz);
+  return conv_wave_lds(kWaveRows, pwdw_wave_stages(a, esz)) + (size_t)((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3) * wave_mid_pitch(esz);
 }
 
 template <typename T, bool DIRECT>
@@ -382,8 +386,10 @@ int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream) {
   return dtype == DT_BF16 ? launch_pwdw_wave_t<bf16_t>(a, (hipStream_t)stream) : launch_pwdw_wave_t<float>(a, (hipStream_t)stream);
 }
 
-int launch_conv_wave(const ConvArgs& a, int dtype, void* stream) {
-  return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t>(a, (hipStream_t)stream) : launch_conv_wave_t<float>(a, (hipStream_t)stream);
+int launch_conv_wave(const ConvArgs& a, int dtype, int edge, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  if (edge == 64) return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t, 2>(a, st) : (int)hipErrorInvalidValue;
+  return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t, 1>(a, st) : launch_conv_wave_t<float, 1>(a, st);
 }
 
 }  // namespace xenos
