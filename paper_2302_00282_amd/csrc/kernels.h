@@ -154,6 +154,7 @@ struct ConvArgs {
   const void* fire_w[2]; const float* fire_scale[2]; const float* fire_shift[2];
   void* fire_out[2]; long long fire_sN[2], fire_sP[2];
   int fire_E[2], fire_relu[2];
+  int fire_skip;         // 64-channel tiles of the 3x3 part modulo the shares: share fire_skip takes the 1x1 part's first
   // linked unit (unit_kernel): this chain is the second pointwise convolution of pointwise -> depthwise 3x3 -> pointwise; `in` is
   // the input of the first (unit_C channels, weights fire_w[0] in fragment order with a reduction padded to unit_kred, epilogue
   // fire_scale / fire_shift / fire_relu[0]), C the channels of the depthwise convolution (dw_*) over the dw_H x dw_W map,

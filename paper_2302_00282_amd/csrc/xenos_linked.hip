@@ -449,8 +449,8 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     u32x4_t w0[KGS > 0 ? KGS : 1];
     auto load_w = [&](int which, int j, auto& w, auto F0, auto F1) __attribute__((always_inline)) {   // fragments F0 .. F1
       constexpr int NF = sizeof(w) / sizeof(u32x4_t);
-      if (a.fire_E[which] > 0) {
-        const u32x4_t* src = (const u32x4_t*)a.fire_w[which] + (j * 64 < a.fire_E[which] ? j * 2 + wave_n : 0) * NF * 64 + lane;
+      if (j * 64 < a.fire_E[which]) {                              // (uniform)
+        const u32x4_t* src = (const u32x4_t*)a.fire_w[which] + (j * 2 + wave_n) * NF * 64 + lane;
 #pragma unroll
         for (int f = F0(); f < F1(); ++f) w[f] = src[f * 64];
       } else {                                                     // (not left undefined: the registers would be kept over the whole kernel)
@@ -462,7 +462,9 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
     constexpr std::integral_constant<int, KGS> f_end1;
     constexpr std::integral_constant<int, 9 * KGS> f_end9;
     constexpr std::integral_constant<int, (KGS == 4 ? 5 : 9) * KGS> f_ahead9;   // of a 3x3 tile: requested before the 1x1 tiles
-    if constexpr (KGS > 0) load_w(0, gz, w0, f_begin, f_end1);
+    // first tile of either part: the 3x3 part's tiles and then the 1x1 part's are dealt to the shares one by one
+    const int j_first[2] = {gz >= a.fire_skip ? gz - a.fire_skip : gz - a.fire_skip + a.tiles_n, gz};
+    if constexpr (KGS > 0) load_w(0, j_first[0], w0, f_begin, f_end1);
 
     // ---- phase 1: the squeeze chain of the block, into LDS -------------------------------------------------
     // (scale and shift of this lane's channels are the same for every chunk: requested once)
@@ -622,12 +624,12 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       return s_sq + ((py + (which ? 0 : ring)) * PWd + px + (which ? 0 : ring)) * SQP + lhalf * 16;
     };
     if constexpr (KGS > 0) {
-      // the tiles gz, gz + tiles_n, ... of one part; w holds the fragments of the first
+      // this share's tiles of one part, tiles_n apart; w holds the fragments of the first
       auto tiles = [&](int which, auto& w) __attribute__((always_inline)) {
         constexpr int TAPS = sizeof(w) / sizeof(u32x4_t) / KGS;
-        if (gz * 64 >= a.fire_E[which]) return;
+        if (j_first[which] * 64 >= a.fire_E[which]) return;
 #pragma unroll 1
-        for (int j = gz;;) {
+        for (int j = j_first[which];;) {
 #pragma unroll 1
           for (int mc = 0; mc * 64 < npix; ++mc) {
             f32x4_t esc[4], esh[4];
@@ -677,7 +679,7 @@ __global__ __launch_bounds__(NT, 2) void fire_kernel(const ConvArgs a) {
       const int taps = which ? 9 : 1, E = a.fire_E[which];
       const int WP = fire_w_pitch(taps, S, ESZ), wrow_b = taps * S * ESZ;   // LDS pitch and bytes of a channel's weights
 #pragma unroll 1
-      for (int j = gz; j * 64 < E; j += a.tiles_n) {
+      for (int j = which ? j_first[1] : j_first[0]; j * 64 < E; j += a.tiles_n) {
         {   // the tile's weights: 64 channels x taps x S, contiguous in memory (rows beyond E are zero)
           const unsigned char* src = (const unsigned char*)a.fire_w[which] + (long long)j * 64 * wrow_b;
           const int cpr = wrow_b / 16, total = 64 * cpr;
@@ -769,7 +771,7 @@ static int launch_fire_t(const ConvArgs& a, hipStream_t st) {
       a.C % CE != 0 || a.C < CE || a.Kred_pad % BKE != 0 ||
       a.K < 1 || a.K > 64 || (a.K * ESZ) % 32 != 0 || a.OH != a.H || a.OW != a.W ||
       (a.fire_E[0] < 1 && a.fire_E[1] < 1) ||
-      a.tiles_n < 1 || a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
+      a.tiles_n < 1 || a.fire_skip != (a.fire_E[1] + 63) / 64 % a.tiles_n || a.tiles_m != a.N * a.tiles_y * a.tiles_x || a.ntiles != a.tiles_m * a.tiles_n || a.grid < 1 ||
       a.in_sN < 0 || a.in_sH < 0 || a.in_sW < a.C)
     return (int)hipErrorInvalidValue;
   for (int e = 0; e < 2; ++e) {   // a part with no channels does not exist (a ConvX -> ConvY pair instead of a module)
