@@ -809,9 +809,11 @@ struct Planner {
     if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res) || !conv_wave_takes(c, p.esz))
       return 0;
     const long long tiles = (long long)((c.M_total + kWaveRows - 1) / kWaveRows) * ((c.K + kWaveChannels - 1) / kWaveChannels);
-    // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 and eight in fp32 0.65 to 1; where units
-    // get more the larger tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36)
-    int most = p.dt == DT_BF16 ? 1024 : 2048;
+    // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 0.65 to 1; where units get more the larger
+    // tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36.  In fp32, whose MFMAs cover the
+    // loads, up to 32: 48 -> 192 channels 27x27 batch 32, 4374 tiles, 196 us against 231 for four layers, 16 -> 64 channels 55x55, 6050
+    // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329; 1x1 64 -> 256 channels there, 25088 tiles, 251 against 221)
+    int most = p.dt == DT_BF16 ? 1024 : 8192;
     ConvArgs t = c;
     if (halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
       // Layers that the halo kernel shares out: those of maps up to eight wide and the longest reductions of more than two tiles per unit stay
@@ -1511,8 +1513,8 @@ struct Planner {
           const double longest = 1.4 + sq_longest + ex_longest;
           const double rounds = std::ceil(wgs / num_cu) / occ;
           // (more shares than the larger part has tiles, SqueezeNet batch 1 bf16 75.3 -> 65.5 us, fp32 180.7 -> 140.5, batch 8 98.0 -> 93.4 and
-          // 279 -> 224; where the model sees no more than 3 % in them, one module at batch 32, they cost 1 % of the network)
-          const double t = (p.opts.split ? std::max(std::max(rounds, 1.0) * all / wgs, longest) + all / (8.0 * num_cu) : all) * (shares > std::max(nt[0], nt[1]) ? 1.03 : 1.0);
+          // 279 -> 224; where the model sees less than 10 % in them they are not worth the squeeze tiles they repeat)
+          const double t = (p.opts.split ? std::max(std::max(rounds, 1.0) * all / wgs, longest) + all / (8.0 * num_cu) : all) * (shares > std::max(nt[0], nt[1]) ? 1.1 : 1.0);
           if (t < best - 1e-9) {
             best = t;
             if (pool) { c.pph = th; c.ppw = tw; c.th = CH; c.tw = CW; } else { c.th = th; c.tw = tw; }
