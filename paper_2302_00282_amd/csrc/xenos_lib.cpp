@@ -833,14 +833,16 @@ struct Planner {
       return 64;
     return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
-  // Shares of a wave chain's reduction (1 = none)
+  // Shares of a wave chain's reduction over workgroups (1 = none).  Cycles: what a tile takes around its steps, a step (bf16: the 8 KB it loads,
+  // fp32: its MFMAs), the launch of the summing pass and its reads (four 3x3 layers of 512 channels 7x7 batch 1, one share 38.3 us, eight 26.3;
+  // 256 channels 14x14 25.0 with one, 25.8 with four; fp32 118.0 and 37.2, 65.2 and 36.4)
   int wave_shares(const ConvArgs& c) const {
     const int nsteps = c.Kred_pad / (kRowBytes / p.esz), num_cu = std::max(1, p.hw.num_cu);
     double best = 1e300;
     int r = 1;
     for (int ks = 1; ks <= 32 && ks <= std::max(1, nsteps / 4); ++ks) {
       const int spk = (nsteps + ks - 1) / ks;
-      if ((nsteps + spk - 1) / spk != ks) continue;
+      if ((nsteps + spk - 1) / spk != ks || c.ntiles * (double)ks >= kHostDiv) continue;
       const double rounds = std::ceil(c.ntiles * (double)ks / num_cu);
       const double t = rounds * (5000 + spk * (p.dt == DT_BF16 ? 150.0 : 270.0)) + (ks > 1 ? 4500 + 100.0 * ks : 0);
       if (t < best) { best = t; r = ks; }
@@ -1654,8 +1656,8 @@ struct Planner {
         const int l2 = pool_node < 0 ? last : absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
         const int c2 = l2 + 1;
         // The kernel that stages the input block in LDS (fp32 NCHW input with unit stride along W, square kernel, stride 1 or 2; bf16 path:
-        // at most 4 channels, 4x4 to 7x7, 3x3 with a pooling; measured at batch 32: 7x7 / 2 on 224x224 0.043 ms against 0.077 ms for
-        // the gather form, while 3x3 kernels without a pooling, 9 gathers per pixel and channel, were faster on the gather form)
+        // at most 4 channels, 3x3 to 7x7; measured at batch 32: 7x7 / 2 on 224x224 0.043 ms against 0.077 ms for the gather form; 3x3 without a
+        // pooling, MobileNet batch 1 75.6 -> 74.8 us, batch 32 273.3 -> 270.1, VGG-16 at link level 2 178.2 -> 177.3)
         // takes a linked max-pooling of 2 or 3 wide windows at stride 2: 3 x 8 windows per tile, their convolution block
         // recomputed per tile.
         const View& gv = p.views[tview[0]];
@@ -1683,9 +1685,6 @@ struct Planner {
         // inputs of up to 100000 pixels: 68 such graphs 0.94 to 1.27 times the time, 1.09 on average; 92 others, which are staged, 0.60 to
         // 1.08, 0.93 on average.
         if (f32 && stem_lds && padded && in_gather && K > 32 && (desc(nodes[pool_node]).kh == 2 || (d.kh >= 4 && is.c * d.kh * d.kw <= 32))) stem_lds = keep_pool = false;
-        // (a 3x3 layer takes the LDS-staged form only for its linked pooling, one launch for two; without pooling the gather form was faster
-        // than that kernel with a single buffer, and has not been compared with the present one)
-        if (stem_lds && d.kh < 4 && !keep_pool) stem_lds = false;
         // (the gather's offsets inside a window are 32 bits: a larger image is imported)
         const bool gathers = is.c * d.kh * d.kw <= kStemRed && conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu &&
                              (is.c - 1) * gv.sK + ((d.kh - 1ll) * is.w + d.kw - 1) * gv.sP < (1ll << 31);
