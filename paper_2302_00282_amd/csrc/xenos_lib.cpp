@@ -2057,13 +2057,14 @@ struct Planner {
           return emit_with_summing_pass();
         }
         const int nsteps = a.Kred_pad / (kRowBytes / p.esz);
-        if (st.cfg == kWaveCfg && !st.fc_stream) {
-          const int ks = p.opts.split ? wave_shares(a) : 1;
+        if ((st.cfg == kWaveCfg || st.cfg == kWave64Cfg) && !st.fc_stream) {
+          const int edge = st.cfg == kWaveCfg ? kWaveRows : 64;
+          const int ks = p.opts.split && edge == kWaveRows ? wave_shares(a) : 1;
           if (ks > 1 || st.gap_finish) {
             a.ksplit = ks; a.steps_per_split = (nsteps + ks - 1) / ks;
-            a.part_ld = a.tiles_n * kWaveChannels;
-            a.grid = a.ntiles * ks;
-            st.lds = conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, a.steps_per_split, a.ntiles * ks));
+            a.part_ld = a.tiles_n * edge;
+            a.grid = p.opts.split ? a.ntiles * ks : 1;
+            st.lds = conv_wave_lds(edge, conv_wave_stages(edge, a.steps_per_split, a.ntiles * ks));
             st.cands.clear();                                      // the plan's structure now depends on this split
             return emit_with_summing_pass();
           }

@@ -555,20 +555,22 @@ def test_reduction_shared_out_over_wavefronts(n, c, h, w, k, ksz, stride, kind, 
 @pytest.mark.parametrize("n,c,h,w,k,ksz,stride,res", [
     (32, 64, 17, 13, 152, 3, 1, True),       # nine steps, channel-chunk order; ragged channel tile, tiles over the borders of images
     (16, 72, 24, 18, 136, 3, 1, False),      # taps inside a step, ragged last step
+    (1, 64, 95, 96, 128, 3, 1, "gap"),       # one image: raw sums, the average in the summing pass
     (24, 48, 31, 33, 72, 7, 2, True)])       # 37 steps
 def test_reduction_shared_out_over_wavefronts_in_larger_tiles(n, c, h, w, k, ksz, stride, res):
     b = wg.builder("wave64", (n, c, h, w), 97, nonzero_bias=True)
     x = b.cbr(0, c, 1, name="pre")
-    t = b.cbr(x, k, ksz, stride, ksz // 2, name="a", relu=not res)
-    g = b.finish(b.relu(b.add(t, b.cbr(x, k, 1, stride, 0, name="side"))) if res else t)
+    t = b.cbr(x, k, ksz, stride, ksz // 2, name="a", relu=(res is not True))
+    g = b.finish(b.gap(t) if res == "gap" else b.relu(b.add(t, b.cbr(x, k, 1, stride, 0, name="side"))) if res else t)
     fmt = dict(out_layout=1, out_dtype=1)
     y, info = check(g, compute=1, **fmt)
     assert [(ch["bm"], ch["bn"]) for ch in info["chains"] if ch["kind"] == "conv" and ch["R"] == ksz] == [(64, 64)], info["chains"]
     assert any(ch["kind"] == "conv" and ch["R"] == ksz and ch["lds"] in (65536, 131072) for ch in info["chains"])      # (a stage is 64 KB)
     check_chains(g, 1, **fmt)
-    y1, _ = run_gpu(g, compute=1, split=0, **fmt)
-    y8, _ = run_gpu(g, compute=1, hw=dict(X_small=True), **fmt)
-    assert np.array_equal(y, y1) and np.array_equal(y, y8)
+    if res != "gap":                                              # (where the average is taken is another question of the split)
+        y1, _ = run_gpu(g, compute=1, split=0, **fmt)
+        y8, _ = run_gpu(g, compute=1, hw=dict(X_small=True), **fmt)
+        assert np.array_equal(y, y1) and np.array_equal(y, y8)
 
 
 @pytest.mark.parametrize("compute", [0, 1])
