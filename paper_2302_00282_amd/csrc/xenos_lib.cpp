@@ -815,10 +815,10 @@ struct Planner {
     // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329; 1x1 64 -> 256 channels there, 25088 tiles, 251 against 221)
     int most = p.dt == DT_BF16 ? 1024 : 8192;
     ConvArgs t = c;
-    if (halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
-      // Layers that the halo kernel shares out: those of maps up to eight wide and the longest reductions of more than two tiles per unit stay
-      // there (512 channels 14x14 batch 9, 896 tiles: bf16 79 us there, 94 here; the small maps would be faster here, 256 channels 7x7 batch 32
-      // 34 us against 65, but their plans are part of what the planner's tests fix)
+    if (p.opts.link < 3 && halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
+      // Link level 2 keeps what the planner's tests fix of its plans: the layers of maps up to eight wide and the longest reductions that the halo
+      // kernel shares out.  They are slower there: 256 channels 7x7 batch 32, four layers, bf16 64.7 us against 34.1, fp32 199.5 against 108;
+      // 512 channels 14x14 batch 8 78.4 against 73.5, fp32 355 against 342
       if (c.W <= 8) return 0;
       if (c.Kred > 4096) most = 512;
     }
