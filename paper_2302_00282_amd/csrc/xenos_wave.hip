@@ -1,13 +1,14 @@
-// gfx950 (CDNA4) kernel of small dense convolution chains:
+// gfx950 (CDNA4) kernels of the chains of few pixels:
 //
-//  conv_wave_kernel   implicit-GEMM convolution chain (any kernel size and stride) in tiles of 32 pixels x 32 channels (or 64 x 64), the reduction of a tile shared out over the four wavefronts of its workgroup
-//                     (wave_gemm.h); scale / shift, shortcut and ReLU in the sum of the partial tiles, or raw sums for a reduction
-//                     that is split over workgroups too.
+//  conv_wave_kernel   implicit-GEMM convolution chain (any kernel size and stride) in tiles of 32 pixels x 32 channels (or 64 x 64), the
+//                     reduction of a tile shared out over the four wavefronts of its workgroup (wave_gemm.h); scale / shift, shortcut
+//                     and ReLU in the sum of the partial tiles, or raw sums for a reduction that is split over workgroups too.
+//  pwdw_wave_kernel   pointwise -> depthwise chain in tiles of at most 32 map positions x 32 channels on the same GEMM.
 #include "wave_gemm.h"
 
 namespace xenos {
 
-// What the kernel needs, in the order and form it needs it: four lines of the constant cache, read at once, where the general
+// What the kernel needs, in the order and form it needs it: three lines of the constant cache, read at once, where the general
 // arguments are ten and lead to quotients and products before the first address is known (2800 cycles from the arguments to the
 // first request of a 64 x 64 tile).  Byte strides in 32 bits, quotients by multipliers made on the host.
 enum { WF_RELU = 1, WF_PARTIAL = 2, WF_OUT_F32 = 4 };
