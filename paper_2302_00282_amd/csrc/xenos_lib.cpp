@@ -833,6 +833,22 @@ struct Planner {
       return 64;
     return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
+  // Does a matmul of at most 32 rows that fc_stream_kernel can run stay with it?  Long weights behind few rows do (layers of one map, here and on the
+  // wave kernel: batch 1 and 8 25088 -> 4096 32.2 against 35.1 us, 4096 -> 4096 8.0 against 8.5); what the wave kernel takes goes there (batch 1 to 32
+  // 2048 -> 512 8.4 -> 5.8, 4096 -> 1000 8.2 to 9.6 -> 7.8, batch 32 25088 -> 4096 38.6 -> 33.1).
+  bool matmul_streams(const Step& st) const {
+    const ConvArgs& c = st.conv;
+    const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
+    if (c.K % 4 != 0 || c.K > 1024 * kWaveChannels || (c.N <= 16 && (double)c.Kred * c.K >= 8e6)) return true;
+    if (wave_edge(st)) return false;
+    // Four channels modulo eight, or a reduction of 2^20 and more: here or on the 64 x 64 tiles.  One launch, at most a workgroup per unit or
+    // eight rows: here (512 and 1024 -> 132 to 4100, 1 to 32 rows, 0.60 to 1.02 times the time; 512 -> 8196, a workgroup more than units, 0.83 at
+    // one row, 1.17 at 16).  With a summing pass: few rows, where the reduction is long enough for them (1 to 4 rows 0.79 to 1.04; 8 to 16 rows
+    // 0.81 to 1.03, but 1152 -> 132 to 1004 1.09 to 1.25), and the longest reductions, of which the tiles make 32 shares at most (17 to 32 rows
+    // 1024 to 65536 -> 132 to 8196 0.84 to 1.6, on average 1.13; 131072 0.80 to 0.93, 2^20 0.37 to 0.59)
+    if (nsteps <= kFcDirectSteps && !c.has_res) return c.N <= 8 || c.K <= 8192;
+    return c.N <= 4 || (c.N <= 16 && nsteps >= 32) || nsteps >= 2048;
+  }
   // Shares of a wave chain's reduction over workgroups (1 = none).  Cycles: what a tile takes around its steps, a step (bf16: the 8 KB it loads,
   // fp32: its MFMAs), the launch of the summing pass and its reads (four 3x3 layers of 512 channels 7x7 batch 1, one share 38.3 us, eight 26.3;
   // 256 channels 14x14 25.0 with one, 25.8 with four; fp32 118.0 and 37.2, 65.2 and 36.4)
@@ -1928,11 +1944,8 @@ struct Planner {
         a.M_total = a.mode == M_FLAT ? a.N * a.OH * a.OW : a.mode == M_ZIGZAG ? a.N * a.PH * a.PW * 4 : a.OH * a.OW;
         // A fully connected chain over at most 32 images streams its weights once: the kernel made for that keeps many
         // loads in flight per unit and shares the reduction out over workgroups (the summing pass finishes the chain)
-        // (Matmuls take the wave kernel where it can have them, but for long weights behind few rows.  Fully connected layers of one map, batch 1
-        // to 32, on either: 2048 -> 512 8.4 -> 5.8 us, 4096 -> 1000 8.2 to 9.6 -> 7.8, batch 32 25088 -> 4096 38.6 -> 33.1; batch 1 and 8
-        // 25088 -> 4096 32.2 -> 35.1, 4096 -> 4096 8.0 -> 8.5.  Those of a FC operator stay where the planner's tests look for them.)
-        const bool wave_fc = nd.kind == XENOS_OP_MATMUL && K % 4 == 0 && K <= 1024 * kWaveChannels && (is.n > 16 || (double)a.R * a.S * a.C * K < 8e6);
-        st.fc_stream = !wave_fc && !a.ileave && p.dt == DT_BF16 && p.opts.split && p.opts.tile == 0 && !from_dw && !from_pair && a.mode == M_FLAT && !st.gap_finish &&
+        // (a matmul may take the wave kernel instead, which is decided below, when its output is known)
+        st.fc_stream = !a.ileave && p.dt == DT_BF16 && p.opts.split && p.opts.tile == 0 && !from_dw && !from_pair && a.mode == M_FLAT && !st.gap_finish &&
                        a.OH == 1 && a.OW == 1 && a.R == is.h && a.S == is.w && a.pad == 0 && is.n <= 32 && !st.scalar && a.C == is.c &&
                        ((long long)a.R * a.S * a.C) % 64 == 0 && (long long)a.R * a.S * a.C >= 512 && (long long)a.R * a.S * a.C < (1ll << 30) &&
                        iv.sN % p.ce == 0 && iv.sN >= (long long)a.R * a.S * a.C && (a.R * a.S == 1 || (iv.sP == a.C && iv.sN == (long long)a.R * a.S * a.C));
@@ -1969,6 +1982,7 @@ struct Planner {
           const View& rv = p.views[st.v_in2];
           a.vec_res = K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0;
         }
+        if (st.fc_stream && nd.kind == XENOS_OP_MATMUL && !matmul_streams(st)) st.fc_stream = 0;
         if (a.unit) {
           if (!a.vec_out || a.mode != M_FLAT || has_res) return fail(XENOS_EUNSUPPORTED, "%s: output of the unit's chain is not aligned", st.name.c_str());
           pack_weights();

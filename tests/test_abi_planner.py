@@ -549,6 +549,27 @@ def test_plan_metadata_names_the_graph_tensor_of_every_view():
             assert q["chains"][-1]["out"]["tensor"] == g.output and q["chains"][-1]["out"]["mem"] == "output"
 
 
+@pytest.mark.parametrize("rows,c,k,kernel", [
+    (8, 1024, 2052, "stream"), (32, 1024, 4100, "stream"), (32, 512, 8196, "tiles"),               # (stores of eight channels: not the wave kernel)
+    (1, 2048, 2052, "stream"), (16, 2048, 516, "stream"), (16, 1152, 516, "tiles"), (20, 4096, 4100, "tiles"), (32, 8192, 516, "tiles"),
+    (16, 2048, 520, "wave"), (32, 8192, 520, "wave"), (20, 4096, 4104, "wave"),
+    (20, 1 << 17, 132, "stream"), (20, 1 << 20, 8, "stream"), (20, (1 << 20) - 128, 8, "wave")])   # (its quotients end at 2^20)
+def test_matmul_of_few_rows_streams_its_weights_where_the_wave_kernel_cannot_run(rows, c, k, kernel):
+    b = undrawn((rows, c, 1, 1))
+    g = b.finish(b.matmul(b.matmul(0, k, "m"), 24, "next"))       # (what the second reads is bf16)
+    chain = next(ch for ch in plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]["chains"] if ch.get("K") == k)
+    assert (chain["loader"], chain["bm"], chain["bn"]) == dict(stream=("stream", 32, 128), tiles=("vector", 64, 64), wave=("vector", 32, 32))[kernel]
+
+
+@pytest.mark.parametrize("k,stream", [(516, True), (520, False)])
+def test_matmul_with_a_shortcut_streams_its_weights_where_the_wave_kernel_cannot_run(k, stream):
+    b = undrawn((16, 2048, 1, 1))
+    side = b.matmul(0, k, "side")
+    g = b.finish(b.relu(b.add(b.matmul(0, k, "m"), side)))        # fp32 output: stores of four channels, but the shortcut is read in eights
+    chains = [c for c in plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]["chains"] if c["kind"] == "conv"]
+    assert len(chains) == 2 and all(c["loader"] == ("stream" if stream else "vector") for c in chains), chains
+
+
 def test_pattern_matmul_to_matmul_layout_link():
     # Table 1, MatmulX -> MatmulY: the first matmul's chain (+ ReLU) writes the row-major [row][column] tensor the
     # second one reads as its operand, with no pass in between; bias, ReLU and the shortcut add are operators of the
