@@ -833,6 +833,13 @@ struct Planner {
       return 64;
     return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
+  // Shares of the reduction of a chain on fc_stream_kernel, for that many units (two workgroups per unit, each with at least 4 steps = 32 KB of
+  // weights to stream)
+  int fc_shares(const ConvArgs& c, int units) const {
+    const int nsteps = c.Kred_pad / (kRowBytes / p.esz), tiles = (c.K + kFcChannels - 1) / kFcChannels;
+    const int ks = std::max(1, std::min((kFcWgPerCu * units + tiles - 1) / tiles, nsteps / 4)), spk = (nsteps + ks - 1) / ks;
+    return (nsteps + spk - 1) / spk;
+  }
   // Does a matmul of at most 32 rows that fc_stream_kernel can run stay with it?  Long weights behind few rows do (layers of one map, here and on the
   // wave kernel: batch 1 and 8 25088 -> 4096 32.2 against 35.1 us, 4096 -> 4096 8.0 against 8.5); what the wave kernel takes goes there (batch 1 to 32
   // 2048 -> 512 8.4 -> 5.8, 4096 -> 1000 8.2 to 9.6 -> 7.8, batch 32 25088 -> 4096 38.6 -> 33.1).
@@ -840,6 +847,16 @@ struct Planner {
     const ConvArgs& c = st.conv;
     const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     if (c.K % 4 != 0 || c.K > 1024 * kWaveChannels || (c.N <= 16 && (double)c.Kred * c.K >= 8e6)) return true;
+    // Weights of 64 MB and more whose rows lie 16 or 32 KB apart, or next to that: the 32 rows that a wavefront of the wave kernel asks for at a
+    // time come from the same few channels of the memory.  Here where that is at most one workgroup per unit (17 to 32 rows, wave kernel / here:
+    // 8192 -> 8192 29.5 to 30.2 / 24.4 to 26.6 us, 16384 -> 4096 33 to 36 / 25 to 28; 8064 and 8320 -> 8192 23 / 24 to 28, 16640 -> 4096 25.5 / 26 to
+    // 29; 8192 -> 4880, two rounds of workgroups, 21 / 26 to 31; 24576 -> 2048 19.5 / 21 to 23)
+    const double pitch = (double)c.Kred_pad * p.esz;
+    const int fc_tiles = (c.K + kFcChannels - 1) / kFcChannels;
+    if ((double)c.Kred * c.K >= 3.2e7 && (std::fabs(pitch - 16384) < 164 || std::fabs(pitch - 32768) < 328) && fc_tiles * fc_shares(c, 256) <= 256) return true;
+    // Up to four rows and 13 to 16 steps, a fourth step for the wave kernel's wavefronts: one launch either way (1024 -> 64 to 4096, 1 to 4 rows, 4.0
+    // to 4.3 us here, 4.2 to 4.4 there; 640 -> 1000 4.0 and 3.8)
+    if (nsteps > 12 && nsteps <= kFcDirectSteps && c.N <= 4 && !c.has_res) return true;
     if (wave_edge(st)) return false;
     // Four channels modulo eight, or a reduction of 2^20 and more: here or on the 64 x 64 tiles.  One launch, at most a workgroup per unit or
     // eight rows: here (512 and 1024 -> 132 to 4100, 1 to 32 rows, 0.60 to 1.02 times the time; 512 -> 8196, a workgroup more than units, 0.83 at
@@ -2089,8 +2106,7 @@ struct Planner {
           if (st.gap_finish) ks = std::max(ks, 1);
           if (from_dw) ks = 1;                                     // the depthwise-panel kernel hands over one share
           const int fc_tiles = (K + kFcChannels - 1) / kFcChannels;
-          // (two workgroups per unit, each with at least 4 steps = 32 KB of weights to stream)
-          if (st.fc_stream) ks = std::max(1, std::min((kFcWgPerCu * std::max(1, p.hw.num_cu) + fc_tiles - 1) / fc_tiles, nsteps / 4));
+          if (st.fc_stream) ks = fc_shares(a, std::max(1, p.hw.num_cu));
           if (st.fc_stream && nsteps <= kFcDirectSteps && !has_res) {
             // short reduction: one share per channel tile, epilogue in the streaming kernel, no summing pass (one launch
             // fewer where launches are what a pass costs: the classifier of a batch-1 network)

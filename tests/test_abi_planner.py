@@ -561,6 +561,17 @@ def test_matmul_of_few_rows_streams_its_weights_where_the_wave_kernel_cannot_run
     assert (chain["loader"], chain["bm"], chain["bn"]) == dict(stream=("stream", 32, 128), tiles=("vector", 64, 64), wave=("vector", 32, 32))[kernel]
 
 
+@pytest.mark.parametrize("rows,c,k,stream", [
+    (20, 8192, 8192, True), (32, 16384, 4096, True), (32, 16256, 4096, True), (24, 8128, 8192, True), (20, 8192, 4096, True),
+    (20, 8192, 4880, False), (32, 8320, 8192, False), (32, 24576, 2048, False), (24, 8192, 2048, False), (32, 4096, 16384, False),
+    (4, 1024, 1000, True), (1, 832, 1000, True), (6, 1024, 1000, False), (1, 768, 1000, False), (1, 512, 1000, False)])
+def test_matmul_of_few_rows_streams_its_weights_where_the_wave_kernel_is_slower(rows, c, k, stream):
+    b = undrawn((rows, c, 1, 1))
+    g = b.finish(b.matmul(b.matmul(0, k, "m"), 24, "next"))
+    chain = next(ch for ch in plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]["chains"] if ch.get("K") == k)
+    assert (chain["loader"], chain["bm"], chain["bn"]) == (("stream", 32, 128) if stream else ("vector", 32, 32))
+
+
 @pytest.mark.parametrize("k,stream", [(516, True), (520, False)])
 def test_matmul_with_a_shortcut_streams_its_weights_where_the_wave_kernel_cannot_run(k, stream):
     b = undrawn((16, 2048, 1, 1))
