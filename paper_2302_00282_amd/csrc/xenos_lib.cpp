@@ -802,6 +802,24 @@ struct Planner {
     return XENOS_OK;
   }
 
+  // fp32 1x1 layers have a ninth of a 3x3 layer's products for the bytes of a step, and against the larger tiles what counts is how much of their last
+  // round those leave idle.  Times of conv_wave_kernel over theirs, four layers of as many channels in a row, 200 to 8000 tiles of 32 x 32:
+  //   up to 672 tiles 0.52 to 1.02; up to 992 of eight steps or more 0.67 to 0.93 (of two to six 0.87 to 1.19); expansions to twice the channels or
+  //   more, in turns with their inverse or as the 1x1 part of a Fire module, up to 1400, 0.70 to 1.08
+  //   just above one 64 x 64 tile per unit, 1024 tiles, 0.67 to 1.02 up to 1184, of eight steps or more up to 1344; of twelve or more all to 1600, 0.83
+  //   to 0.94, and just above two, up to 2400, 0.85 to 0.93; the others up to 2800 0.82 to 1.31, on average 1.07
+  //   above 2800, where the larger ones are 128 x 64, of two steps or more: 0.76 to 1.03 where those leave four tenths of a round, 1.0 to 1.25
+  //   otherwise, and 1.02 to 1.43 against whole 128 x 128 ones from 6912 tiles on
+  //   channels that fill three quarters of the larger tiles or less 0.58 to 0.96, but 1.08 to 1.20 for 1024 to 1700 tiles; half of them 0.54 to 0.84
+  static bool wave_pays_1x1_f32(const ConvArgs& c, int nsteps, int tiles) {
+    const int padded = (c.K + 63) / 64 * 64;
+    if (2 * c.K <= padded || tiles <= (2 * c.C <= c.K ? 1400 : 672)) return true;
+    if (4 * c.K <= 3 * padded) return tiles <= 1024 || tiles > 1700;
+    if (tiles <= 1024) return nsteps >= 12 || (nsteps >= 8 && tiles <= 992);
+    if (tiles <= 2800) return nsteps >= 12 ? tiles <= 1600 || (tiles > 2048 && tiles <= 2400) : tiles <= (nsteps >= 8 ? 1344 : nsteps >= 4 ? 1184 : 0);
+    const double rounds = ((c.M_total + 127) / 128) * (double)(padded / 64) / 256;
+    return nsteps >= 2 && std::ceil(rounds) - rounds >= 0.4 && (tiles <= 6912 || c.K % 128 != 0);
+  }
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
   // chain only: the order of its sums then does not depend on how many units there are.
   int wave_edge(const Step& st) const {
@@ -812,8 +830,10 @@ struct Planner {
     // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 0.65 to 1; where units get more the larger
     // tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36.  In fp32, whose MFMAs cover the
     // loads, up to 32: 48 -> 192 channels 27x27 batch 32, 4374 tiles, 196 us against 231 for four layers, 16 -> 64 channels 55x55, 6050
-    // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329; 1x1 64 -> 256 channels there, 25088 tiles, 251 against 221)
+    // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329)
+    const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     int most = p.dt == DT_BF16 ? 1024 : 8192;
+    if (p.dt == DT_F32 && c.R * c.S == 1 && !wave_pays_1x1_f32(c, nsteps, (int)std::min<long long>(tiles, 8193))) return 0;
     ConvArgs t = c;
     if (p.opts.link < 3 && halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
       // Link level 2 keeps what the planner's tests fix of its plans: the layers of maps up to eight wide and the longest reductions that the halo
@@ -827,11 +847,10 @@ struct Planner {
     // channels 27x27 batch 32 69.0 on the gather tiles -> 62.8; 1x1 512 channels 7x7 batch 32 27.8 -> 31.2, which is why eight steps are too few;
     // 784 tiles of 64 x 64 take 75.9 us against the halo kernel's 53.3).  In fp32, whose MFMAs cover the smaller tile's loads, they gain nothing
     const long long tiles64 = (long long)((c.M_total + 63) / 64) * ((c.K + 63) / 64);
-    const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     if (p.dt == DT_BF16 && tiles > 512 && tiles64 <= 512 && nsteps >= (tiles <= 1024 ? 16 : 9) && most > 512 &&
         conv_wave_lds(64, conv_wave_stages(64, nsteps, (int)tiles64)) <= p.hw.lds_bytes_per_cu)
       return 64;
-    return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, c.Kred_pad / (kRowBytes / p.esz), (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
+    return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, nsteps, (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
   // Shares of the reduction of a chain on fc_stream_kernel, for that many units (two workgroups per unit, each with at least 4 steps = 32 KB of
   // weights to stream)

@@ -549,6 +549,21 @@ def test_plan_metadata_names_the_graph_tensor_of_every_view():
             assert q["chains"][-1]["out"]["tensor"] == g.output and q["chains"][-1]["out"]["mem"] == "output"
 
 
+@pytest.mark.parametrize("n,hw,c,k,wave", [
+    (16, 30, 32, 512, False), (166, 13, 64, 256, False), (4, 56, 64, 192, False),                  # 7200, 7016 and 2352 tiles
+    (42, 8, 192, 256, True), (44, 8, 192, 256, False), (44, 8, 256, 256, True),                    # 672 of six steps, 704 of six and of eight
+    (87, 8, 64, 256, True), (88, 8, 64, 256, False),                                               # expansions, 1392 and 1408
+    (31, 13, 192, 192, False), (16, 16, 192, 288, True),                                           # 984 and 1152 of six steps
+    (13, 13, 512, 704, True), (25, 13, 512, 416, False),                                           # 1518 and 1729 of sixteen
+    (102, 14, 256, 256, True), (102, 14, 32, 256, False), (41, 28, 256, 128, False),               # 5000 of eight steps and of one, 4020
+    (166, 13, 256, 256, False), (40, 55, 64, 32, True), (58, 35, 96, 96, True)])                   # 7016; half and three quarters of 64 channels
+def test_fp32_pointwise_layers_of_many_tiles_keep_the_larger_ones(n, hw, c, k, wave):
+    b = undrawn((n, c, hw, hw))
+    g = b.finish(b.cbr(b.cbr(b.cbr(0, c, 1, name="pre"), k, 1, name="a"), 8, 1, name="post"))
+    chain = [ch for ch in plan_json(g, link=2, compute=X.XENOS_F32)["plan"]["chains"] if ch["kind"] == "conv"][1]
+    assert (chain["C"], chain["K"]) == (c, k) and ((chain["bm"], chain["bn"]) == (32, 32)) == wave, chain
+
+
 @pytest.mark.parametrize("rows,c,k,kernel", [
     (8, 1024, 2052, "stream"), (32, 1024, 4100, "stream"), (32, 512, 8196, "tiles"),               # (stores of eight channels: not the wave kernel)
     (1, 2048, 2052, "stream"), (16, 2048, 516, "stream"), (16, 1152, 516, "tiles"), (20, 4096, 4100, "tiles"), (32, 8192, 516, "tiles"),
