@@ -820,6 +820,16 @@ struct Planner {
     const double rounds = ((c.M_total + 127) / 128) * (double)(padded / 64) / 256;
     return nsteps >= 2 && std::ceil(rounds) - rounds >= 0.4 && (tiles <= 6912 || c.K % 128 != 0);
   }
+  // fp32 layers of wider kernels: not where 128 x 64 tiles fill two rounds (3x3, 3800 to 4096 tiles of 32 x 32, four layers in a row, 64 to 512 channels
+  // 1.08 to 1.09 times their time; 3000 0.61 to 0.87, 5500 0.76 to 0.84) or four (7400 and more, 1.05 to 1.22), and not reductions of 200 steps and more
+  // that 64 x 64 tiles share out over just two workgroups per unit (5x5, 256 channels 8x8 batch 16, four layers, 162.8 us against 146.6, 512
+  // channels 10x10 batch 5 78.5 against 65.0, 7x7 batch 5 43.0 against 37.9; 4x the tiles 0.69, half a round more 0.80)
+  static bool wave_pays_f32(const ConvArgs& c, int nsteps, int tiles, bool halo) {
+    if (4 * c.K <= 3 * ((c.K + 63) / 64 * 64)) return true;
+    const int tiles64 = (c.M_total + 63) / 64 * ((c.K + 63) / 64);
+    if (nsteps >= 200 && !halo && tiles64 >= 28 && tiles64 <= 128 && (512 + tiles64 - 1) / tiles64 * tiles64 <= 528) return false;
+    return tiles < 7400 && (tiles < 3800 || tiles > 4096);
+  }
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
   // chain only: the order of its sums then does not depend on how many units there are.
   int wave_edge(const Step& st) const {
@@ -833,7 +843,7 @@ struct Planner {
     // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329)
     const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     int most = p.dt == DT_BF16 ? 1024 : 8192;
-    if (p.dt == DT_F32 && c.R * c.S == 1 && !wave_pays_1x1_f32(c, nsteps, (int)std::min<long long>(tiles, 8193))) return 0;
+    if (p.dt == DT_F32 && tiles <= most && !(c.R * c.S == 1 ? wave_pays_1x1_f32(c, nsteps, (int)tiles) : wave_pays_f32(c, nsteps, (int)tiles, halo_input_ok(st)))) return 0;
     ConvArgs t = c;
     if (p.opts.link < 3 && halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
       // Link level 2 keeps what the planner's tests fix of its plans: the layers of maps up to eight wide and the longest reductions that the halo

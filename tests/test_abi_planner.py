@@ -564,6 +564,18 @@ def test_fp32_pointwise_layers_of_many_tiles_keep_the_larger_ones(n, hw, c, k, w
     assert (chain["C"], chain["K"]) == (c, k) and ((chain["bm"], chain["bn"]) == (32, 32)) == wave, chain
 
 
+@pytest.mark.parametrize("n,hw,c,k,ksz,stride,wave", [
+    (75, 14, 128, 256, 3, 1, True), (78, 14, 64, 256, 3, 1, False), (84, 14, 64, 256, 3, 1, True),  # 3680, 3824 and 4120 tiles
+    (20, 56, 32, 128, 3, 1, False), (163, 28, 128, 256, 3, 2, False), (75, 56, 32, 32, 3, 1, True), # 7840, 7992; half of 64 channels
+    (5, 10, 512, 512, 5, 1, False), (5, 7, 512, 512, 5, 1, False), (3, 14, 512, 512, 5, 1, True),  # 64, 32 and 80 tiles of 64 x 64
+    (16, 8, 256, 256, 5, 1, False), (16, 8, 192, 256, 5, 1, True), (20, 14, 1024, 256, 3, 2, False)])   # 200 and 150 steps, 288
+def test_fp32_layers_keep_the_larger_tiles_where_those_fill_their_rounds(n, hw, c, k, ksz, stride, wave):
+    b = undrawn((n, c, hw, hw))
+    g = b.finish(b.cbr(b.cbr(b.cbr(0, c, 1, name="pre"), k, ksz, stride, ksz // 2, name="a"), 8, 1, name="post"))
+    chain = [ch for ch in plan_json(g, link=2, compute=X.XENOS_F32)["plan"]["chains"] if ch["kind"] == "conv"][1]
+    assert (chain["C"], chain["K"]) == (c, k) and ((chain["bm"], chain["bn"]) == (32, 32)) == wave, chain
+
+
 @pytest.mark.parametrize("rows,c,k,kernel", [
     (8, 1024, 2052, "stream"), (32, 1024, 4100, "stream"), (32, 512, 8196, "tiles"),               # (stores of eight channels: not the wave kernel)
     (1, 2048, 2052, "stream"), (16, 2048, 516, "stream"), (16, 1152, 516, "tiles"), (20, 4096, 4100, "tiles"), (32, 8192, 516, "tiles"),
