@@ -830,6 +830,28 @@ struct Planner {
     if (nsteps >= 200 && !halo && tiles64 >= 28 && tiles64 <= 128 && (512 + tiles64 - 1) / tiles64 * tiles64 <= 528) return false;
     return tiles < 7400 && (tiles < 3800 || tiles > 4096);
   }
+  // bf16, where the wave kernel is slower than the others:
+  //   1x1 layers of few steps that 64 x 64 tiles nearly give every unit one of: four layers of as many channels in a row, 192 channels 846 tiles of
+  //   32 x 32 22.0 us against 19.1, 256 channels 1000 tiles 25.7 against 20.1, 512 channels 1024 tiles 29.3 against 25.1 (600 tiles 0.89 to 1.00 times
+  //   the time; two steps, 900 tiles, 0.96; eight, 912, 0.93; nine and more 0.86 to 1.08, one 0.98 with any number).  Not so where they expand, to twice the channels or more (0.64 to 0.98 up to
+  //   1000 tiles), or fill three quarters of the larger tiles' channels or less
+  //   1x1 in 64 x 64 wave tiles of less than sixteen steps, 0.95 to 1.16 (sixteen and 24: 0.77 to 0.98), and to an eighth of the channels or less
+  //   behind 32 steps and more, 0.9 to 1.31 (4096 -> 256 8x8 batch 128 43.1 us against 32.9)
+  //   256 steps and more of a wider kernel, whose operands come from the caches twice as often as those of larger tiles: against the halo kernel's
+  //   shares 2048 -> 128 channels 56x56 45.7 us against 28.1, -> 384 55x55 89.6 against 62.0, and against two workgroups per unit of the 64 x 64
+  //   tiles (/ 2, 8x8 batch 128 -> 256 51.3 against 39.1, 55x55 30.1 against 25.9; up to 100 tiles 0.77, above 512 0.50 to 0.72)
+  bool wave_pays_bf16(const ConvArgs& c, int nsteps, int tiles, bool halo) const {
+    if (c.R * c.S > 1) {
+      ConvArgs t = c;
+      if (nsteps < 256 || tiles < 100) return true;
+      return !(halo && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) && tiles > 512;
+    }
+    if (tiles > 768 && nsteps >= 32 && c.C >= 8 * c.K) return false;
+    if (nsteps >= 16) return true;
+    if (tiles > (nsteps >= 9 ? 1056 : 1024)) return false;
+    if (2 * c.C <= c.K || 4 * c.K <= 3 * ((c.K + 63) / 64 * 64)) return true;
+    return tiles <= (nsteps >= 9 ? 1056 : nsteps >= 7 ? 928 : nsteps >= 3 ? 600 : nsteps == 2 ? 900 : 1024);
+  }
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
   // chain only: the order of its sums then does not depend on how many units there are.
   int wave_edge(const Step& st) const {
@@ -844,6 +866,7 @@ struct Planner {
     const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     int most = p.dt == DT_BF16 ? 1024 : 8192;
     if (p.dt == DT_F32 && tiles <= most && !(c.R * c.S == 1 ? wave_pays_1x1_f32(c, nsteps, (int)tiles) : wave_pays_f32(c, nsteps, (int)tiles, halo_input_ok(st)))) return 0;
+    if (p.dt == DT_BF16 && tiles <= 2048 && !wave_pays_bf16(c, nsteps, (int)tiles, halo_input_ok(st))) return 0;
     ConvArgs t = c;
     if (p.opts.link < 3 && halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
       // Link level 2 keeps what the planner's tests fix of its plans: the layers of maps up to eight wide and the longest reductions that the halo

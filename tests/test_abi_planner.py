@@ -576,6 +576,21 @@ def test_fp32_layers_keep_the_larger_tiles_where_those_fill_their_rounds(n, hw, 
     assert (chain["C"], chain["K"]) == (c, k) and ((chain["bm"], chain["bn"]) == (32, 32)) == wave, chain
 
 
+@pytest.mark.parametrize("n,hw,c,k,ksz,stride,bm", [
+    (16, 10, 192, 384, 1, 1, 32), (16, 10, 256, 416, 1, 1, 0), (16, 10, 192, 416, 1, 1, 32),      # 600 tiles of three steps, 650 of four, an expansion
+    (40, 10, 256, 256, 1, 1, 0), (40, 10, 128, 256, 1, 1, 32), (32, 8, 512, 384, 1, 1, 32),       # 1000 of four and, an expansion, of two, 768 of eight
+    (17, 15, 512, 512, 1, 1, 0), (12, 14, 640, 448, 1, 1, 64), (27, 7, 576, 1152, 1, 1, 0),       # 1920 of eight, 1036 of ten, 1512 of nine
+    (27, 7, 1024, 1152, 1, 1, 64), (128, 8, 4096, 256, 1, 1, 0),                                   # sixteen steps; to a sixteenth of the channels
+    (1, 56, 2048, 128, 3, 1, 0), (1, 55, 2048, 384, 3, 1, 0), (1, 56, 1024, 128, 3, 1, 32),       # the halo kernel's shares
+    (128, 8, 2048, 256, 3, 2, 0), (128, 10, 2048, 256, 3, 2, 64), (16, 8, 2048, 256, 3, 2, 32)])   # 512, 800 and 64 tiles
+def test_bf16_layers_that_other_kernels_run_faster(n, hw, c, k, ksz, stride, bm):
+    b = undrawn((n, c, hw, hw))
+    g = b.finish(b.cbr(b.cbr(b.cbr(0, c, 1, name="pre"), k, ksz, stride, ksz // 2, name="a"), 8, 1, name="post"))
+    chain = [ch for ch in plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]["chains"] if ch["kind"] == "conv"][1]
+    wave = chain["halo"] == 0 and chain["bm"] == chain["bn"] and chain["lds"] % (chain["bm"] * 1024) == 0   # (stages of whole tiles, without padding)
+    assert (chain["C"], chain["K"]) == (c, k) and chain["bm"] * wave == bm, chain
+
+
 @pytest.mark.parametrize("rows,c,k,kernel", [
     (8, 1024, 2052, "stream"), (32, 1024, 4100, "stream"), (32, 512, 8196, "tiles"),               # (stores of eight channels: not the wave kernel)
     (1, 2048, 2052, "stream"), (16, 2048, 516, "stream"), (16, 1152, 516, "tiles"), (20, 4096, 4100, "tiles"), (32, 8192, 516, "tiles"),
