@@ -164,11 +164,11 @@ __device__ __forceinline__ int uniform_div(int n, int d) {
 }
 
 // n / d of wavefront-uniform values by the host's multiplier, one scalar multiplication (the reciprocal on the vector unit, its conversions and
-// the way back were some 90 cycles each, three of them in a row before a tile's first request); mul = 0: by division
+// the way back were some 90 cycles each, three of them in a row before a tile's first request); mul = 0: by the reciprocal all the same
 __device__ __forceinline__ int tile_div(int n, int d, unsigned mul) {
   if (mul) return (int)host_quotient((unsigned)n, mul);
   asm volatile("" : "+s"(d));                          // (nothing of the division is worked out ahead, for calls that need none)
-  return n / d;
+  return uniform_div(n, d);
 }
 
 // Dynamic LDS of a kernel whose launches differ in their need: its limit is raised once, to all of a unit's memory.  (Raised to what

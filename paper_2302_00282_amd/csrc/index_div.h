@@ -20,10 +20,14 @@ __attribute__((always_inline)) constexpr int any_quotient(int n, int d, float r)
   return (int)(rem < 0 ? q - 1 : rem >= d ? q + 1 : q);
 }
 
-// n / d for 0 <= n < 2^15 and 1 <= d < 2^15 by a multiplier that the host has made, one scalar multiplication: 2 n * multiplier / 2^32 is
-// n / d and less than n / 2^31 above it, and n / d is at least 1 / d below the next integer.
-constexpr unsigned kHostDiv = 1u << 15;
+// n / d for n d < 2^31 by a multiplier that the host has made, one scalar multiplication: the multiplier is less than 1 above 2^31 / d, so that
+// 2 n multiplier / 2^32 is n / d and less than n / 2^31 <= 1 / d above it, and n / d is at least 1 / d below the next integer.
+constexpr unsigned kHostDiv = 1u << 15;                // (numbers and divisors that need no other look)
 __attribute__((always_inline)) constexpr unsigned host_multiplier(unsigned d) { return (unsigned)((0x80000000ull + d - 1) / d); }
 __attribute__((always_inline)) constexpr unsigned host_quotient(unsigned n, unsigned mul) { return (unsigned)((2ull * n * mul) >> 32); }
+// The multiplier for numbers below `end`: one whose quotients are all 0 where they are, and 0 where there is none
+constexpr unsigned host_multiplier(long long end, long long d) {
+  return end <= d ? 1u : (end - 1) * d < (1ll << 31) ? host_multiplier((unsigned)d) : 0u;
+}
 
 }  // namespace xenos

@@ -58,11 +58,11 @@ __device__ __forceinline__ u32x4_t ld16(gptr_t base, unsigned off) { return *(co
 struct UnitWeights {
   const void* w;
   int kgs, nkg, ncb, parts;
-  unsigned mul;                                        // multiplier of quotients by ncb (0: division)
+  unsigned mul;                                        // multiplier of quotients by ncb (never 0: a block of all channels is in LDS)
   __device__ __forceinline__ UnitWeights(const void* w_, int kgs_, int nkg_, int ncb_, unsigned mul_, int nrows)
       : w(w_), kgs(kgs_), nkg(nkg_), ncb(ncb_), parts(ncb_ * ((nrows + 63) / 64)), mul(mul_) {}
   __device__ __forceinline__ rsrc_t window(int u) const {
-    const int cb = u - tile_div(u, ncb, mul) * ncb;
+    const int cb = u - (int)host_quotient((unsigned)u, mul) * ncb;
     return make_window((const unsigned char*)w + (long long)cb * kgs * 1024, u < parts ? nkg * 1024u : 0u);
   }
 };
@@ -85,7 +85,7 @@ __device__ __forceinline__ void unit_gemm(const UnitWeights& w, u32x4_t (&rb)[UN
   if (NEXT && wave >= w.parts) unit_request(next, rb);
 #pragma unroll 1
   for (int u = wave; u < w.parts; u += UN_NW) {
-    const int rg = tile_div(u, ncb, w.mul), cb = u - rg * ncb, row0 = rg * 64;
+    const int rg = (int)host_quotient((unsigned)u, w.mul), cb = u - rg * ncb, row0 = rg * 64;
     const bool two = row0 + 32 < nrows;                            // (uniform)
     const rsrc_t wp = w.window(u), wn = u + UN_NW < w.parts ? w.window(u + UN_NW) : next;
     pre(cb, row0);
@@ -396,6 +396,7 @@ static int launch_unit_t(const ConvArgs& a, hipStream_t st) {
   if (e != hipSuccess) return (int)e;
   ConvArgs b = a;
   b.set_quotients();
+  if (!b.q_c || !b.q_k) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL((unit_kernel<T>), dim3(a.grid < a.ntiles ? a.grid : a.ntiles), dim3(UN_NT), lds, st, b);
   return (int)hipGetLastError();
 }

@@ -662,6 +662,40 @@ def test_linked_chains_of_images_beyond_2_gb(pattern, compute):
         part.close()
 
 
+@pytest.mark.parametrize("pattern,compute,n", [("pwdw", 0, 30002), ("pwdw", 1, 30002), ("pwdw", 1, 47005), ("fire", 1, 47005), ("unit", 1, 33005)])
+def test_linked_chains_of_more_tiles_than_2_15(pattern, compute, n):
+    # 60004 tiles, whose numbers the multiplier still takes apart, and 94010, where it cannot: seven images over and over
+    X = _xenos()
+
+    def session(n):
+        b = wg._Builder("many", (1, 1, 1, 1), 91, True, True)
+        side = 7 if pattern == "unit" else 3
+        b.g.input_shape, b.g.x, b._shapes = (n, 16, side, side), None, [(n, 16, side, side)]
+        t = b.cbr(0, 16, 1, name="a")
+        if pattern == "fire":
+            q = b.cbr(t, 16, 1, name="sq")
+            t = b.concat([b.cbr(q, 32, 1, name="e1"), b.cbr(q, 80, 3, 1, 1, name="e3")])
+        else:
+            c = 72 if pattern == "pwdw" else 96
+            t = b.cbr(b.cbr(t, c, 1, name="pw"), c, 3, 1, 1, groups=c, name="dw")
+            t = b.cbr(t, 96, 3 if pattern == "pwdw" else 1, 1, int(pattern == "pwdw"), name="z")   # (a 3x3 layer ends the linked chain)
+        return X.Session(b.finish(t), link=3, compute=compute, in_dtype=compute, in_layout=1, out_dtype=compute, out_layout=1)
+
+    big, part = session(n), session(7)
+    try:
+        tested, = [ch for ch in big.info["chains"] if ch.get("loader") == pattern]
+        assert tested["grid"] < tested["tiles_m"] and tested["tiles_m"] % n == 0, tested
+        part.x.uniform_(-1, 1)
+        big.x.copy_(part.x.repeat(n // 7, 1, 1, 1))
+        big.run()
+        part.run()
+        got, ref = big.y.reshape(n // 7, *part.y.shape).double(), part.y.double()
+        assert float((got - ref).abs().max()) <= TOL[compute] * float(ref.abs().max()) and float(ref.abs().max()) > 0.1
+    finally:
+        big.close()
+        part.close()
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("stride,h,w", [(1, 1, 1), (1, 7, 9), (2, 8, 5)])
 def test_depthwise_padding_does_not_meet_infinite_weights(stride, h, w, compute):

@@ -58,6 +58,7 @@ def test_index_quotients_are_exact_over_their_ranges(tmp_path):
 
 
 HOST_PROGRAM = r"""
+#include <initializer_list>
 #include <stdint.h>
 #include <stdio.h>
 #include "index_div.h"
@@ -71,6 +72,18 @@ int main() {
     for (unsigned m = 0; m < kHostDiv + d; m += d) { if (m) check(m - 1); check(m); }
     check(kHostDiv - 1);
   }
+  // any number whose product with the divisor is below 2^31: every boundary of a divisor, or 200 of them spread evenly and the last, and the ends
+  for (int64_t d = 1; d < (1ll << 31); d += d < 70000 ? 1 : d / 211 + 1)
+    for (int64_t end : {(int64_t)1, d, d + 1, 3 * d / 2 + 1, (INT32_MAX - d) / d / 3 + 1, INT32_MAX / d + 1}) {
+      const unsigned mul = host_multiplier((long long)end, (long long)d);
+      const bool none = end > d && (end - 1) * d > INT32_MAX;
+      if ((mul == 0) != none && ++bad < 9) printf("multiplier %lld / %lld\n", (long long)end, (long long)d);
+      auto check = [&](int64_t n) { ++seen; if (n >= 0 && n < end && n <= INT32_MAX && host_quotient((unsigned)n, mul) != n / d && ++bad < 9) printf("%lld / %lld\n", (long long)n, (long long)d); };
+      if (none) continue;
+      const int64_t kmax = (end - 1) / d, step = kmax / 200 + 1;
+      for (int64_t k = 0; k <= kmax; k += step) { check(k * d - 1); check(k * d); }
+      for (int64_t n : {kmax * d - 1, kmax * d, end - 2, end - 1}) check(n);
+    }
   printf("%lld quotients, %lld wrong\n", seen, bad);
   return bad != 0;
 }
