@@ -70,9 +70,10 @@ constexpr size_t stem_lds_bytes(int taps, int channels, int esz) {
 // launched, so that none starts, with its weights and tables, behind another, and none is missing to hide the others' latencies.
 // Batch 8 to 32, one fewer and one more than this: 32 channels 3x3 bf16 1.05 times the time, fp32 1.05 / 1.12; 5x5 bf16 1.07 / 1.13,
 // fp32 1.06 / 1.12; 64 channels 3x3 bf16 1.02, 5x5 1.02 / 1.08, 7x7 1.22 with one more.
+// 3x3 bf16 without a pooling, 24 and 32 channels, batch 8 to 64: five instead of four 0.97 to 1.015, 0.99 on average.
 constexpr int stem_lds_resident(int taps, int channels, int esz, bool pool) {
   if (esz == 4) return channels > 32 ? 2 : 3;
-  return taps <= 12 ? 4 : taps <= 28 ? (channels > 32 || pool ? 3 : 4) : channels > 32 || pool ? 2 : 3;
+  return taps <= 12 ? (channels > 32 || pool ? 4 : 5) : taps <= 28 ? (channels > 32 || pool ? 3 : 4) : channels > 32 || pool ? 2 : 3;
 }
 // Configuration index of the kernel that links a pointwise (1x1) convolution chain with the depthwise 3x3 chain that consumes
 // it: a TH x TW block of depthwise output pixels x kPwDwChannels channels per workgroup, the pointwise output of the block

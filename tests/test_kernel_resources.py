@@ -65,7 +65,7 @@ def test_wave_kernels_keep_everything_in_registers(kernels, kernel, most):
 
 
 # first layers that take stem_lds_kernel: (compute type, output channels, kernel size, behind it a pooling)
-FIRST_LAYERS = [(1, 32, 3, 1), (1, 64, 3, 1), (1, 24, 5, 1), (1, 32, 5, 0), (1, 64, 4, 0), (1, 64, 5, 1), (1, 32, 7, 1), (1, 32, 7, 0), (1, 48, 7, 1), (1, 64, 7, 0),
+FIRST_LAYERS = [(1, 32, 3, 1), (1, 64, 3, 1), (1, 24, 3, 0), (1, 32, 3, 0), (1, 48, 3, 0), (1, 64, 3, 0), (1, 24, 5, 1), (1, 32, 5, 0), (1, 64, 4, 0), (1, 64, 5, 1), (1, 32, 7, 1), (1, 32, 7, 0), (1, 48, 7, 1), (1, 64, 7, 0),
                 (0, 32, 3, 1), (0, 64, 3, 1), (0, 24, 5, 1), (0, 64, 5, 1)]
 
 
