@@ -188,6 +188,8 @@ def chain_label(c):
         return c["kind"]
     if c.get("halo"):
         return "conv3x3_kernel"
+    if c.get("wave"):
+        return "pwdw_wave_kernel" if c["loader"] == "pwdw" else "conv_wave_kernel"
     return {"stem": "stem kernel", "pair": "conv_pair_kernel", "stream": "fc_stream_kernel", "pwdw": "pwdw_kernel", "unit": "unit_kernel", "fire": "fire_kernel",
             "vector": "dwpw_kernel" if c.get("dw_linked") else "conv_kernel", "scalar": "conv_kernel"}.get(c.get("loader"), "conv_kernel")
 

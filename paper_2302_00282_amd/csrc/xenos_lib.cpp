@@ -794,7 +794,7 @@ struct Planner {
     if (const int edge = wave_edge(st)) {
       c.tiles_m = (c.M_total + edge - 1) / edge; c.tiles_n = (c.K + edge - 1) / edge; c.ntiles = c.tiles_m * c.tiles_n;
       c.xcd_m = 1;
-      c.grid = p.opts.split ? c.ntiles : 1;
+      c.grid = wave_grid(c.ntiles);
       st.cfg = edge == 64 ? kWave64Cfg : kWaveCfg;
       st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
       st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
@@ -852,8 +852,11 @@ struct Planner {
     if (2 * c.C <= c.K || 4 * c.K <= 3 * ((c.K + 63) / 64 * 64)) return true;
     return tiles <= (nsteps >= 9 ? 1056 : nsteps >= 7 ? 928 : nsteps >= 3 ? 600 : nsteps == 2 ? 900 : 1024);
   }
+  // Workgroups of a wave kernel: one per tile.  (A machine of a few units walks them: no more wait than thirty-two per unit, which is what the
+  // rules above leave 256 units at most)
+  int wave_grid(int tiles) const { return p.opts.split ? std::min(tiles, 32 * std::max(1, p.hw.num_cu)) : 1; }
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
-  // chain only: the order of its sums then does not depend on how many units there are.
+  // chain only: where its reduction is not split over workgroups too (wave_shares), the order of its sums does not depend on how many units there are.
   int wave_edge(const Step& st) const {
     const ConvArgs& c = st.conv;
     if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res) || !conv_wave_takes(c, p.esz))
@@ -2146,7 +2149,7 @@ struct Planner {
           if (ks > 1 || st.gap_finish) {
             a.ksplit = ks; a.steps_per_split = (nsteps + ks - 1) / ks;
             a.part_ld = a.tiles_n * edge;
-            a.grid = p.opts.split ? a.ntiles * ks : 1;
+            a.grid = wave_grid(a.ntiles * ks);
             st.lds = conv_wave_lds(edge, conv_wave_stages(edge, a.steps_per_split, a.ntiles * ks));
             st.cands.clear();                                      // the plan's structure now depends on this split
             return emit_with_summing_pass();
@@ -2236,7 +2239,7 @@ struct Planner {
     a.tiles_n = (K + kPwDwChannels - 1) / kPwDwChannels;
     a.ntiles = a.tiles_m * a.tiles_n;
     a.xcd_m = 8;
-    a.grid = !p.opts.split ? 1 : a.pwdw == 2 ? 2 * a.ntiles : std::max(1, std::min(a.ntiles, 4 * std::max(1, p.hw.num_cu)));
+    a.grid = a.pwdw == 2 ? wave_grid(a.tiles_m * ((K + kWaveChannels - 1) / kWaveChannels)) : p.opts.split ? std::max(1, std::min(a.ntiles, 4 * std::max(1, p.hw.num_cu))) : 1;
     st.cfg = kPwDwCfg;
     st.lds = a.pwdw == 2 ? pwdw_wave_lds(a, p.esz) : pwdw_lds_bytes(a.th, a.tw, a.dw_stride, p.esz);
     st.flops = 2.0 * is.n * is.h * is.w * (double)K * is.c + 2.0 * os.n * os.h * os.w * (double)K * 9;
@@ -2529,13 +2532,14 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg pwdw_tc{64, kPwDwChannels, 32, 32};
       const TileCfg wave_tc{kWaveRows, kWaveChannels, 32, 32};
       const TileCfg wave64_tc{64, 64, 64, 64};
+      const bool wave = s.cfg == kWaveCfg || s.cfg == kWave64Cfg || c.pwdw == 2;
       const TileCfg& tc = s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
-               "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d",
+               "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d,\"wave\":%d",
                kModeNames[c.mode], s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.unit ? "unit" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
                c.PH, c.PW, c.pool, c.relu, c.has_res, tc.bm, tc.bn, c.tiles_m, c.tiles_n, c.grid, s.lds, c.pph, c.ppw, c.patch_h,
-               c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave);
+               c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave, wave);
       j += buf;
     }
     // where the chain's tensors lie (byte offset into the workspace / the caller's input or output buffer, element

@@ -329,7 +329,7 @@ static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
   w.stride = a.stride; w.pad = a.pad; w.H = a.H; w.W = a.W; w.C = a.C;
   w.sN = (uint32_t)(a.in_sN * ESZ); w.sH = (uint32_t)(a.in_sH * ESZ); w.sW = (uint32_t)(a.in_sW * ESZ); w.wpitch = (uint32_t)(a.Kred_pad * ESZ);
   w.K = a.K; w.part_ld = a.part_ld; w.flags = (a.relu ? WF_RELU : 0) | (partial ? WF_PARTIAL : 0) | (a.out_f32 ? WF_OUT_F32 : 0);
-    const int osz = a.out_f32 ? 4 : ESZ;
+  const int osz = a.out_f32 ? 4 : ESZ;
   w.out_sN = (uint32_t)(a.out_sN * osz); w.out_sP = (uint32_t)(a.out_sP * osz); w.res_sN = (uint32_t)(a.res_sN * ESZ); w.res_sP = (uint32_t)(a.res_sP * ESZ);
   w.stages = conv_wave_stages(EDGE, w.steps_per_share, (int)w.tiles);
   const int lds = (int)conv_wave_lds(EDGE, w.stages);
@@ -379,8 +379,7 @@ static int launch_pwdw_wave_t(const ConvArgs& a, hipStream_t st) {
   w.stages = pwdw_wave_stages(a, ESZ);
   if (lds > kLdsPerUnit) return (int)hipErrorInvalidValue;
   const bool direct = ((uintptr_t)a.in & 15) == 0;
-  const int grid = a.grid == 1 ? 1 : (int)w.tiles;
-  return direct ? launch_pwdw_wave_inst<T, true>(w, grid, lds, st) : launch_pwdw_wave_inst<T, false>(w, grid, lds, st);
+  return direct ? launch_pwdw_wave_inst<T, true>(w, a.grid, lds, st) : launch_pwdw_wave_inst<T, false>(w, a.grid, lds, st);
 }
 
 int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream) {

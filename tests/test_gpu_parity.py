@@ -527,6 +527,7 @@ def test_reductions_of_every_length(c, compute):
     (5, 192, 6, 6, 96, 3, 1, "plain"),       # 27 and 54 steps
     (1, 128, 8, 8, 256, 7, 3, "plain"),      # padding of three pixels
     (1, 640, 7, 7, 64, 3, 1, "res"),         # reduction shared out over workgroups too
+    (3, 64, 17, 19, 104, 3, 1, "res"),       # 124 tiles
     (2, 264, 10, 10, 40, 1, 1, "gap"),       # raw sums, the average in the summing pass
     (40, 512, 1, 1, 72, 1, 1, "fc")])        # rows of a fully connected operator
 def test_reduction_shared_out_over_wavefronts(n, c, h, w, k, ksz, stride, kind, compute):
@@ -545,11 +546,14 @@ def test_reduction_shared_out_over_wavefronts(n, c, h, w, k, ksz, stride, kind, 
     y, info = check(g, compute=compute, **fmt)
     tested = [ch for ch in info["chains"] if ch["kind"] == "conv" and ch["in"]["mem"] == "workspace"]
     assert tested and all((ch["bm"], ch["bn"]) == (32, 32) for ch in tested), tested
+    assert c != 640 or any(ch["ksplit"] > 1 for ch in tested), tested
     check_chains(g, compute, **fmt)
-    y8, _ = run_gpu(g, compute=compute, hw=dict(X_small=True), **fmt)
+    few, info_few = run_gpu(g, compute=compute, hw=dict(_xenos().MI355X, num_cu=1), **fmt)
     if all(ch["ksplit"] == 1 for ch in tested) and kind != "gap":
+        for ch in info_few["chains"]:                             # (thirty-two workgroups at most)
+            assert not ch.get("wave") or (ch["grid"] == min(32, ch["tiles_m"] * ch["tiles_n"]) and ch["ksplit"] == 1), ch
         y1, _ = run_gpu(g, compute=compute, split=0, **fmt)
-        assert np.array_equal(y, y1) and np.array_equal(y, y8)    # one workgroup, or any number, walking the tiles: same bits
+        assert np.array_equal(y, y1) and np.array_equal(y, few)   # one workgroup, a few, or one per tile: same bits
 
 
 @pytest.mark.parametrize("n,c,h,w,k,ksz,stride,res", [
@@ -569,8 +573,9 @@ def test_reduction_shared_out_over_wavefronts_in_larger_tiles(n, c, h, w, k, ksz
     check_chains(g, 1, **fmt)
     if res != "gap":                                              # (where the average is taken is another question of the split)
         y1, _ = run_gpu(g, compute=1, split=0, **fmt)
-        y8, _ = run_gpu(g, compute=1, hw=dict(X_small=True), **fmt)
-        assert np.array_equal(y, y1) and np.array_equal(y, y8)
+        few, info = run_gpu(g, compute=1, hw=dict(_xenos().MI355X, num_cu=1), **fmt)
+        assert [ch["grid"] for ch in info["chains"] if (ch.get("bm"), ch.get("bn")) == (64, 64) and ch["wave"]] == [32]
+        assert np.array_equal(y, y1) and np.array_equal(y, few)
 
 
 @pytest.mark.parametrize("compute", [0, 1])
@@ -589,12 +594,39 @@ def test_pointwise_depthwise_of_few_pixels(n, c, h, w, k, stride, compute):
     fmt = dict(out_layout=1, out_dtype=compute)
     y, info = check(g, compute=compute, link=3, **fmt)
     tested, = [ch for ch in info["chains"] if ch.get("loader") == "pwdw"]
-    assert tested["grid"] == 2 * tested["tiles_m"] * tested["tiles_n"], tested      # (a workgroup takes 32 channels)
+    assert tested["wave"] and tested["grid"] == tested["tiles_m"] * -(-k // 32), tested
     check_chains(g, compute, link=3, **fmt)
     y1, _ = run_gpu(g, compute=compute, link=3, split=0, **fmt)
-    y8, _ = run_gpu(g, compute=compute, link=3, hw=dict(X_small=True), **fmt)
+    few, info_few = run_gpu(g, compute=compute, link=3, hw=dict(_xenos().MI355X, num_cu=1), **fmt)
+    walks, = [ch for ch in info_few["chains"] if ch.get("loader") == "pwdw"]
+    assert walks["wave"] and walks["grid"] == min(32, tested["grid"])
     if all(ch.get("ksplit", 1) == 1 for ch in info["chains"]):    # (or the chain before it sums in another order)
-        assert np.array_equal(y, y1) and np.array_equal(y, y8)
+        assert np.array_equal(y, y1) and np.array_equal(y, few)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
+def test_pointwise_depthwise_of_few_pixels_at_any_address(compute):
+    # the pair reads channels 8 .. 135 of the caller's tensor, which lies at no multiple of 16 bytes: through registers, same bits
+    X = _xenos()
+    b = wg.builder("pwdwat", (2, 136, 9, 7), 89, nonzero_bias=True)
+    g = b.finish(b.cbr(b.cbr(b.slice(0, 8, 128), 72, 1, name="pw"), 72, 3, 1, 1, groups=72, name="dw"))
+    fmt = dict(in_layout=1, in_dtype=compute, out_layout=1, out_dtype=compute)
+    y, _ = check(g, compute=compute, link=3, **fmt)
+    s = X.Session(g, link=3, compute=compute, **fmt)
+    try:
+        chain, = s.info["chains"]
+        assert chain["loader"] == "pwdw" and chain["wave"] and chain["in"]["mem"] == "input"
+        s.set_input(g.x)
+        n = s.x.numel()
+        buf = s.torch.full((n + 64,), float("nan"), dtype=s.x.dtype, device=s.device)
+        for off in (1, 6, 8):
+            buf[:] = float("nan")
+            buf[off:off + n] = s.x.reshape(-1)
+            s.y.zero_()
+            X.xenos_run(s.plan, buf[off:].data_ptr(), s.y.data_ptr(), s.stream())
+            assert np.array_equal(s.output(), y)
+    finally:
+        s.close()
 
 
 @pytest.mark.parametrize("compute", [0, 1])
