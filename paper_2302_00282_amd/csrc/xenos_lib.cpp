@@ -874,7 +874,8 @@ struct Planner {
     if (p.opts.link < 3 && halo_input_ok(st) && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) {
       // Link level 2 keeps what the planner's tests fix of its plans: the layers of maps up to eight wide and the longest reductions that the halo
       // kernel shares out.  They are slower there: 256 channels 7x7 batch 32, four layers, bf16 64.7 us against 34.1, fp32 199.5 against 108;
-      // 512 channels 14x14 batch 8 78.4 against 73.5, fp32 355 against 342
+      // 512 channels 14x14 batch 8, 9, 12, 16 and 20 91.2, 92.9, 109.1, 121.3 and 129.4 against 78.3, 78.5, 102.1, 104.9 and 112.0, fp32 batch 8 363
+      // against 347
       if (c.W <= 8) return 0;
       if (c.Kred > 4096) most = 512;
     }
@@ -1602,8 +1603,8 @@ struct Planner {
           const double all = ((double)shares * sq_total + (double)ty * tx * ex_total) * c.N + 1.4 * wgs;
           const double longest = 1.4 + sq_longest + ex_longest;
           const double rounds = std::ceil(wgs / num_cu) / occ;
-          // (more shares than the larger part has tiles, SqueezeNet batch 1 bf16 75.3 -> 65.5 us, fp32 180.7 -> 140.5, batch 8 98.0 -> 93.4 and
-          // 279 -> 224; where the model sees less than 10 % in them they are not worth the squeeze tiles they repeat)
+          // (more shares than the larger part has tiles, SqueezeNet batch 1 bf16 71.7 -> 65.8 us, fp32 152.4 -> 142.2, batch 8 102.2 -> 98.6 and
+          // 232.9 -> 227.9; where the model sees less than 10 % in them they are not worth the squeeze tiles they repeat)
           const double t = (p.opts.split ? std::max(std::max(rounds, 1.0) * all / wgs, longest) + all / (8.0 * num_cu) : all) * (shares > std::max(nt[0], nt[1]) ? 1.1 : 1.0);
           if (t < best - 1e-9) {
             best = t;
@@ -1745,7 +1746,7 @@ struct Planner {
         const int c2 = l2 + 1;
         // The kernel that stages the input block in LDS (fp32 NCHW input with unit stride along W, square kernel, stride 1 or 2; bf16 path:
         // at most 4 channels, 3x3 to 7x7; measured at batch 32: 7x7 / 2 on 224x224 0.043 ms against 0.077 ms for the gather form; 3x3 without a
-        // pooling, MobileNet batch 1 75.6 -> 74.8 us, batch 32 273.3 -> 270.1, VGG-16 at link level 2 178.2 -> 177.3)
+        // pooling and the chain behind it, 32 and 64 channels, 32x32 to 224x224, stride 1 and 2, batch 1 to 32, 0.84 to 0.97 times the time, 60 graphs)
         // takes a linked max-pooling of 2 or 3 wide windows at stride 2: 3 x 8 windows per tile, their convolution block
         // recomputed per tile.
         const View& gv = p.views[tview[0]];
