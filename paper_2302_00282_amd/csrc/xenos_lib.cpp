@@ -807,27 +807,29 @@ struct Planner {
   //   up to 672 tiles 0.52 to 1.02; up to 992 of eight steps or more 0.67 to 0.93 (of two to six 0.87 to 1.19); expansions to twice the channels or
   //   more, in turns with their inverse or as the 1x1 part of a Fire module, up to 1400, 0.70 to 1.08
   //   just above one 64 x 64 tile per unit, 1024 tiles, 0.67 to 1.02 up to 1184, of eight steps or more up to 1344; of twelve or more all to 1600, 0.83
-  //   to 0.94, and just above two, up to 2400, 0.85 to 0.93; the others up to 2800 0.82 to 1.31, on average 1.07
+  //   to 0.94; just above two, up to 2400, of eight or more 0.85 to 1.04; the others up to 2800 0.82 to 1.31, on average 1.07
   //   above 2800, where the larger ones are 128 x 64, of two steps or more: 0.76 to 1.03 where those leave four tenths of a round, 1.0 to 1.25
   //   otherwise, and 1.02 to 1.43 against whole 128 x 128 ones from 6912 tiles on
-  //   channels that fill three quarters of the larger tiles or less 0.58 to 0.96, but 1.08 to 1.20 for 1024 to 1700 tiles; half of them 0.54 to 0.84
+  //   channels that fill three quarters of the larger tiles 0.58 to 0.96, but 1.08 to 1.20 for 1024 to 1700 tiles; less 0.54 to 0.87
   static bool wave_pays_1x1_f32(const ConvArgs& c, int nsteps, int tiles) {
     const int padded = (c.K + 63) / 64 * 64;
-    if (2 * c.K <= padded || tiles <= (2 * c.C <= c.K ? 1400 : 672)) return true;
-    if (4 * c.K <= 3 * padded) return tiles <= 1024 || tiles > 1700;
+    if (4 * c.K < 3 * padded || tiles <= (2 * c.C <= c.K ? 1400 : 672)) return true;
+    if (4 * c.K == 3 * padded) return tiles <= 1024 || tiles > 1700;
     if (tiles <= 1024) return nsteps >= 12 || (nsteps >= 8 && tiles <= 992);
-    if (tiles <= 2800) return nsteps >= 12 ? tiles <= 1600 || (tiles > 2048 && tiles <= 2400) : tiles <= (nsteps >= 8 ? 1344 : nsteps >= 4 ? 1184 : 0);
+    if (nsteps >= 8 && tiles > 2048 && tiles <= 2400) return true;
+    if (tiles <= 2800) return tiles <= (nsteps >= 12 ? 1600 : nsteps >= 8 ? 1344 : nsteps >= 4 ? 1184 : 0);
     const double rounds = ((c.M_total + 127) / 128) * (double)(padded / 64) / 256;
     return nsteps >= 2 && std::ceil(rounds) - rounds >= 0.4 && (tiles <= 6912 || c.K % 128 != 0);
   }
   // fp32 layers of wider kernels: not where 128 x 64 tiles fill two rounds (3x3, 3800 to 4096 tiles of 32 x 32, four layers in a row, 64 to 512 channels
   // 1.08 to 1.09 times their time; 3000 0.61 to 0.87, 5500 0.76 to 0.84) or four (7400 and more, 1.05 to 1.22), and not reductions of 200 steps and more
   // that 64 x 64 tiles share out over just two workgroups per unit (5x5, 256 channels 8x8 batch 16, four layers, 162.8 us against 146.6, 512
-  // channels 10x10 batch 5 78.5 against 65.0, 7x7 batch 5 43.0 against 37.9; 4x the tiles 0.69, half a round more 0.80)
+  // channels 10x10 batch 5 78.5 against 65.0; fully connected 25088 -> 4096, 40 rows, 167 against 137; up to 32 rows, which half fill the larger tiles,
+  // 0.65 to 0.95 times the time, and where they make a few workgroups more than two per unit, 0.80)
   static bool wave_pays_f32(const ConvArgs& c, int nsteps, int tiles, bool halo) {
     if (4 * c.K <= 3 * ((c.K + 63) / 64 * 64)) return true;
     const int tiles64 = (c.M_total + 63) / 64 * ((c.K + 63) / 64);
-    if (nsteps >= 200 && !halo && tiles64 >= 28 && tiles64 <= 128 && (512 + tiles64 - 1) / tiles64 * tiles64 <= 528) return false;
+    if (nsteps >= 200 && c.M_total > kWaveRows && !halo && tiles64 >= 28 && tiles64 <= 128 && 512 % tiles64 == 0) return false;
     return tiles < 7400 && (tiles < 3800 || tiles > 4096);
   }
   // bf16, where the wave kernel is slower than the others:
@@ -839,11 +841,12 @@ struct Planner {
   //   behind 32 steps and more, 0.9 to 1.31 (4096 -> 256 8x8 batch 128 43.1 us against 32.9)
   //   256 steps and more of a wider kernel, whose operands come from the caches twice as often as those of larger tiles: against the halo kernel's
   //   shares 2048 -> 128 channels 56x56 45.7 us against 28.1, -> 384 55x55 89.6 against 62.0, and against two workgroups per unit of the 64 x 64
-  //   tiles (/ 2, 8x8 batch 128 -> 256 51.3 against 39.1, 55x55 30.1 against 25.9; up to 100 tiles 0.77, above 512 0.50 to 0.72)
+  //   tiles (/ 2, 8x8 batch 128 -> 256 51.3 against 39.1, 55x55 30.1 against 25.9; up to 100 tiles 0.77, above 512 0.50 to 0.72; fewer pixels than
+  //   channels, fully connected 25088 -> 1024 at 160 to 256 rows 0.92 to 0.94)
   bool wave_pays_bf16(const ConvArgs& c, int nsteps, int tiles, bool halo) const {
     if (c.R * c.S > 1) {
       ConvArgs t = c;
-      if (nsteps < 256 || tiles < 100) return true;
+      if (nsteps < 256 || tiles < 100 || c.M_total <= c.K) return true;
       return !(halo && c.OH == c.H && c.OW == c.W && choose_halo_tile(c, 1, t) && t.tiles_y * t.tiles_x >= kHaloSplitTiles) && tiles > 512;
     }
     if (tiles > 768 && nsteps >= 32 && c.C >= 8 * c.K) return false;

@@ -555,6 +555,7 @@ def test_plan_metadata_names_the_graph_tensor_of_every_view():
     (87, 8, 64, 256, True), (88, 8, 64, 256, False),                                               # expansions, 1392 and 1408
     (31, 13, 192, 192, False), (16, 16, 192, 288, True),                                           # 984 and 1152 of six steps
     (13, 13, 512, 704, True), (25, 13, 512, 416, False),                                           # 1518 and 1729 of sixteen
+    (16, 28, 88, 88, True), (12, 28, 256, 256, True), (12, 28, 192, 256, False),                    # 1176 of 88 channels; 2352 of eight steps and of six
     (102, 14, 256, 256, True), (102, 14, 32, 256, False), (41, 28, 256, 128, False),               # 5000 of eight steps and of one, 4020
     (166, 13, 256, 256, False), (40, 55, 64, 32, True), (58, 35, 96, 96, True)])                   # 7016; half and three quarters of 64 channels
 def test_fp32_pointwise_layers_of_many_tiles_keep_the_larger_ones(n, hw, c, k, wave):
@@ -589,6 +590,16 @@ def test_bf16_layers_that_other_kernels_run_faster(n, hw, c, k, ksz, stride, bm)
     chain = [ch for ch in plan_json(g, link=3, compute=X.XENOS_BF16)["plan"]["chains"] if ch["kind"] == "conv"][1]
     wave = chain["halo"] == 0 and chain["bm"] == chain["bn"] and chain["lds"] % (chain["bm"] * 1024) == 0   # (stages of whole tiles, without padding)
     assert (chain["C"], chain["K"]) == (c, k) and chain["bm"] * wave == bm, chain
+
+
+@pytest.mark.parametrize("compute,rows,hw,c,k,wave", [
+    (X.XENOS_F32, 32, 7, 512, 4096, True), (X.XENOS_F32, 40, 7, 512, 4096, False), (X.XENOS_F32, 100, 7, 512, 4096, False), (X.XENOS_F32, 160, 7, 512, 1024, True),
+    (X.XENOS_BF16, 160, 7, 512, 1024, True), (X.XENOS_BF16, 256, 7, 512, 1024, True)])
+def test_fully_connected_layers_of_many_steps(compute, rows, hw, c, k, wave):
+    b = undrawn((rows, c, hw, hw))
+    g = b.finish(b.fc(b.fc(b.cbr(0, c, 1, name="pre"), k, "fc"), 8, "post"))
+    chain = [ch for ch in plan_json(g, link=3, compute=compute)["plan"]["chains"] if ch["kind"] == "conv"][1]
+    assert (chain["C"], chain["K"], bool(chain["wave"])) == (c, k, wave), chain
 
 
 @pytest.mark.parametrize("rows,c,k,kernel", [
