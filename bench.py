@@ -188,6 +188,8 @@ def chain_label(c):
         return c["kind"]
     if c.get("halo"):
         return "conv3x3_kernel"
+    if c.get("frag3"):
+        return "conv3x3_frag_kernel"
     if c.get("wave"):
         return "pwdw_wave_kernel" if c["loader"] == "pwdw" else "conv_wave_kernel"
     return {"stem": "stem kernel", "pair": "conv_pair_kernel", "stream": "fc_stream_kernel", "pwdw": "pwdw_kernel", "unit": "unit_kernel", "fire": "fire_kernel",
@@ -235,7 +237,7 @@ def run_workload(name, steps, warmup, links=(3,), chains=False, wg=None, X=None,
                                   ms_between_events=float(raw[c["i"]]), gflop=c["flops"] / 1e9,
                                   mb=(c["bytes_in"] + c["bytes_w"] + c["bytes_out"] + c["bytes_res"]) / 1e6,
                                   mode=c.get("mode"), tile=[c.get("bm"), c.get("bn")] if c["kind"] == "conv" else None,
-                                  loader=c.get("loader"), halo=c.get("halo", 0), ksplit=c.get("ksplit", 1))
+                                  loader=c.get("loader"), halo=c.get("halo", 0), frag3=c.get("frag3", 0), ksplit=c.get("ksplit", 1))
                              for c in s.info["chains"]]
         out[LINK_NAMES[link]] = rec
         s.close()
@@ -353,7 +355,7 @@ def measure_traffic(workload, link):
             n = info["kernel_launches_of_the_passes"]
             last = rows[-n:]
             nc = info["n_chains"]
-            dom = [i for i, c in enumerate(info["chains"]) if c["kernel"] == "conv3x3_kernel"] or list(range(nc))
+            dom = next((d for d in ([i for i, c in enumerate(info["chains"]) if c["kernel"] == k] for k in ("conv3x3_frag_kernel", "conv3x3_kernel")) if d), list(range(nc)))
             n_dom = len(dom)
             per[counter] = sum(last[p * nc + i][1] for p in range(passes) for i in dom) / passes * 1024.0 * scale[counter]
         total = (per["FETCH_SIZE"] + per["WRITE_SIZE"]) / n_dom
@@ -500,11 +502,11 @@ def main():
     head, g = run_workload(name, args.steps, args.warmup, links, chains=True, wg=wg, X=X, torch=torch)
     lk = head[LINK_NAMES[HEADLINE_LINK]]
 
-    # Roofline of the dominant kernel: conv3x3_kernel (halo-staged 3x3 convolution chains on MFMA), over all its
+    # Roofline of the dominant kernel: conv3x3_frag_kernel (3x3 convolution chains on MFMA; conv3x3_kernel where no chain takes it), over all its
     # launches in one step.  achieved = algorithmic flops of those chains / their summed launch durations, measured
     # with HIP events around every launch on the launch stream.  The other chains are in `per_layer`.
     conv = [c for c in lk["chains"] if c["kind"] == "conv"]
-    dom = [c for c in conv if c.get("halo")] or conv
+    dom = [c for c in conv if c.get("frag3")] or [c for c in conv if c.get("halo")] or conv
     dom_ms, dom_gf = sum(c["ms"] for c in dom), sum(c["gflop"] for c in dom)
     conv_ms, conv_gf = sum(c["ms"] for c in conv), sum(c["gflop"] for c in conv)
     step_ms = sum(c["ms"] for c in lk["chains"])

@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxenos.so")
-SOURCES = ["xenos_kernels.hip", "xenos_linked.hip", "xenos_unit.hip", "xenos_wave.hip", "xenos_lib.cpp"]
+SOURCES = ["xenos_kernels.hip", "xenos_conv3.hip", "xenos_linked.hip", "xenos_unit.hip", "xenos_wave.hip", "xenos_lib.cpp"]
 HEADERS = ["kernels.h", "device_common.h", "wave_gemm.h", "index_div.h", os.path.join("..", "..", "include", "xenos.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -92,6 +92,15 @@ static const int kUnitCfg = 11;
 static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;
 static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64 (bf16)
+// Configuration index of the 3x3 kernel whose weights go from the cache into registers (bf16): kFrag3Pixels blocks of 16 pixels per wavefront
+static const int kFrag3Cfg = 14;
+constexpr int kFrag3Pitch = 80;        // LDS bytes of a patch position: 32 channels and an odd number of 16-byte slots
+// positions of the patch in LDS, for blocks per wavefront x pixel groups; row pitch of the patch
+constexpr int frag3_positions(int pb, int wp) { return wp == 2 ? 384 : pb > 7 ? 320 : pb > 4 ? 192 : 128; }
+constexpr int frag3_pitch(int tw) { return (tw + 2 + 1) / 4 * 4 + 2; }
+constexpr size_t frag3_lds(int pb, int wp, int ks) {
+  return (size_t)ks * 2 * frag3_positions(pb, wp) * kFrag3Pitch + wp * pb * 16 * 4 + (ks > 1 ? 4 / (wp * ks) * pb * 2048 : 0);
+}
 static const int kFcWgPerCu = 1;
 static const int kFcDirectSteps = 16;   // reductions of at most this many 64-element steps are not shared out (no summing pass)    // workgroups per compute unit the reduction split of such a chain aims at
 static const int kPairChannels = 64, kPairRed = 48;
@@ -169,6 +178,7 @@ struct ConvArgs {
   int halo_bn;           // halo kernel: output channels per tile (128 or 64)
   int halo_mgroup;       // halo kernel: an XCD walks its pixel tiles in groups of this many, every output-channel tile of a group
                          // before the next group (>= 1; a value of at least the XCD's tile count = one sweep per channel tile)
+  int frag3, frag3_wp, frag3_ks;   // conv3x3_frag_kernel: blocks of 16 pixels per wavefront, groups of pixels and shares of the reduction among its wavefronts
   int halo_plin;         // halo kernel: patch-linear rows (GEMM row = patch position, pitch TW + 2; pixel-major chains only)
   int M_total;           // rows enumerated over the whole problem (FLAT, ZIGZAG); per-image rows for GAP
   int tiles_m, tiles_n, ntiles;
@@ -277,6 +287,14 @@ inline bool conv_wave_takes(const ConvArgs& a, int esz) {
          a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && ((double)a.N * a.in_sN + a.C) * esz < lim && 128.0 * a.Kred_pad * esz < lim &&
          ((double)a.N * a.out_sN + a.K) * 4 < lim && ((double)a.N * a.res_sN + a.K) * esz < lim;
 }
+// Do a 3x3 chain's sizes fit the indices of conv3x3_frag_kernel (byte offsets of 32 bits)?
+inline bool frag3_takes(const ConvArgs& a) {
+  const double lim = 4294967040.0;
+  return a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.OH == a.H && a.OW == a.W && a.C % 32 == 0 && a.C >= 32 && a.K % 8 == 0 &&
+         a.in_sN >= 0 && a.in_sH >= 0 && a.in_sW >= 0 && ((double)a.N * a.in_sN + a.C) * 2 < lim && ((double)a.N * a.out_sN + a.K) * 2 < lim &&
+         ((double)a.N * a.res_sN + a.K) * 2 < lim && (double)((a.K + 127) / 128) * 128 * a.C * 18 < lim;
+}
+int launch_frag3(const ConvArgs& a, int dtype, void* stream);
 // Pixels of the map that the windows of a tile of th x tw depthwise outputs cover, at most
 inline int wave_block_positions(const ConvArgs& a, int th, int tw) {
   auto most = [&](int out, int t, int in) {

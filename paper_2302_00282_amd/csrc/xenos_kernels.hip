@@ -2651,6 +2651,10 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
     if (scalar_loader) return (int)hipErrorInvalidValue;
     return launch_conv_wave(a, dtype, cfg == kWave64Cfg ? 64 : kWaveRows, st);
   }
+  if (cfg == kFrag3Cfg) {
+    if (scalar_loader) return (int)hipErrorInvalidValue;
+    return launch_frag3(a, dtype, st);
+  }
   if (cfg == kStemCfg) return dtype == DT_BF16 ? launch_stem_t<bf16_t>(a, st) : launch_stem_t<float>(a, st);
   return dtype == DT_BF16 ? launch_conv_t<bf16_t>(a, cfg, scalar_loader, st) : launch_conv_t<float>(a, cfg, scalar_loader, st);
 }

@@ -799,7 +799,121 @@ struct Planner {
       st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
       st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
     }
+    ConvArgs f = c;
+    if (choose_frag3(st, f)) {
+      c = f;
+      st.cfg = kFrag3Cfg;
+      st.lds = frag3_lds(c.frag3, c.frag3_wp, c.frag3_ks);
+      st.cands.clear();                                            // (its weights lie in an order of their own)
+    }
     return XENOS_OK;
+  }
+
+  // conv3x3_frag_kernel's variants.  Microseconds of a chunk (32 channels, nine taps) of a work item that has a unit to itself and of two that share
+  // one, of what an item or two take around their chunks, and of a launch: fitted to 559 graphs of three layers (batch 1 to 32, 32 to 512
+  // channels, maps of 4x4 to 256x256), whose times they give to within 4 to 6 %.  By them the fastest variant or one 0.7 % slower is taken.
+  // (slots: workgroups that a unit holds; the fourth variant needs more than half of its LDS)
+  struct Frag3Variant { int pb, wp, ks, slots; double alone, pair, around1, around2, launch; };
+  static constexpr Frag3Variant kFrag3Variants[] = {
+    {13, 1, 1, 2, 2.50, 4.64, 1.8, 2.3, 5.6},
+    {7, 1, 1, 2, 1.34, 2.66, 0.8, 1.5, 4.5},
+    {7, 2, 1, 2, 1.40, 2.69, 1.4, 2.1, 4.6},
+    {7, 1, 2, 1, 1.59, 0.00, 1.8, 0.0, 3.6},
+    {4, 1, 2, 2, 1.34, 1.91, 0.0, 1.1, 3.5},
+  };
+  // Does a 3x3 chain take conv3x3_frag_kernel, and in which variant and tile?  (bf16, link level 3.)  Chains of up to 1024 tiles of 32 x 32 stay with the
+  // wave kernel, which has a workgroup for each of them (1.0 to 3.3 times its time here); all others go: 559 such graphs 0.735 times the time of
+  // the kernels they had, halo, 64 x 64 wave tiles and gather tiles alike, 0.39 to 1.03 (32x56x56 256 channels 114 -> 87 us, 28x28 512 channels
+  // 108 -> 84, 14x14 512 channels 37 -> 29, 56x56 64 channels 17.1 -> 14.8, 28x28 128 channels 14.0 -> 11.0, 7x7 512 channels 18.8 -> 14.3).
+  bool choose_frag3(const Step& st, ConvArgs& out) const {
+    const ConvArgs& c = st.conv;
+    const bool zig = c.mode == M_ZIGZAG;
+    if (p.dt != DT_BF16 || p.opts.link < 3 || !p.opts.split || p.opts.tile != 0 || st.scalar || st.cfg == kWaveCfg || c.ileave || c.dw_w || c.pair ||
+        (!st.gap_finish && (!c.vec_out || (c.has_res && !c.vec_res))) || (c.mode != M_FLAT && !(zig && c.H % 2 == 0 && c.W % 2 == 0)) || !frag3_takes(c))
+      return false;
+    const int num_cu = std::max(1, p.hw.num_cu);
+    double best = 1e300;
+    for (const Frag3Variant& v : kFrag3Variants) {
+      const int rows = v.pb * v.wp * 16, bn = 128 / (v.wp * v.ks), step = zig ? 2 : 1;
+      if (c.C % (32 * v.ks) || frag3_lds(v.pb, v.wp, v.ks) > p.hw.lds_bytes_per_cu) continue;
+      // the tile that wastes the fewest rows, the squarest of those (th * ceil(tw / 2): either parity of columns has half of the rows)
+      ConvArgs t = c;
+      double fill = 0;
+      for (int tw = step; tw < c.W + step && tw <= 32; tw += step) {
+        const int pw = frag3_pitch(tw);
+        int th = std::min({rows / tw, rows / 2 / ((tw + 1) / 2), frag3_positions(v.pb, v.wp) / pw - 2, (c.H + step - 1) / step * step}) / step * step;
+        if (th < step) continue;
+        const int ty = (c.H + th - 1) / th, tx = (c.W + tw - 1) / tw;
+        const double f = (double)c.H * c.W / ((double)ty * tx * rows) - 1e-4 * std::abs(th - tw);
+        if (f > fill) { fill = f; t.th = th; t.tw = tw; t.tiles_y = ty; t.tiles_x = tx; }
+      }
+      const long long items = (long long)c.N * t.tiles_y * t.tiles_x * ((c.K + bn - 1) / bn);
+      if (fill <= 0 || items >= kHostDiv) continue;
+      const int chunks = c.C / (32 * v.ks);
+      const long long round = (long long)v.slots * num_cu, full = items / round, rest = items % round;
+      const double alone = chunks * v.alone + v.around1, pair = v.slots == 2 ? chunks * v.pair + v.around2 : alone;
+      const double us = v.launch + full * pair + (rest == 0 ? 0 : rest <= num_cu ? alone : pair);
+      if (us >= best) continue;
+      best = us;
+      t.frag3 = v.pb; t.frag3_wp = v.wp; t.frag3_ks = v.ks; t.halo_bn = bn;
+      t.tiles_m = c.N * t.tiles_y * t.tiles_x; t.tiles_n = (c.K + bn - 1) / bn; t.ntiles = t.tiles_m * t.tiles_n;
+      // (as many workgroups for every XCD as the largest of their ranges has items)
+      t.grid = std::min((t.ntiles + 7) / 8 * 8, std::max(8, v.slots * num_cu / 8 * 8));
+      out = t;
+    }
+    return best < 1e300;
+  }
+  // Which pixel of a tile row r of block b of conv3x3_frag_kernel is: (ty << 8) | tx, 0xffff none.  A fragment read serves rows 0 - 3 and 12 - 15 of one
+  // 16-byte chunk and rows 4 - 11 of the chunk two further on at a time; at a pitch of five slots these sixteen lanes hit sixteen of them where the first eight
+  // pixels lie at even positions of the patch that differ mod 16 and the others at odd ones.  Pooling windows are kept together: two rows of either kind.
+  std::vector<uint16_t> frag3_table(const ConvArgs& c) const {
+    const int blocks = c.frag3 * c.frag3_wp, pw = frag3_pitch(c.tw);
+    const bool zig = c.mode == M_ZIGZAG;
+    static const int even[8] = {0, 1, 2, 3, 12, 13, 14, 15}, odd[8] = {7, 6, 5, 4, 11, 10, 9, 8};
+    std::vector<uint16_t> tab((size_t)blocks * 16, 0xffff);
+    if (!zig) {
+      for (int par = 0; par < 2; ++par) {
+        std::vector<int> cls[16], rest;
+        for (int y = 0; y < c.th; ++y)
+          for (int x = par; x < c.tw; x += 2) cls[(y * pw + x) & 15].push_back(y << 8 | x);
+        std::vector<int> fill(blocks, 0);
+        for (int b = 0; b < blocks; ++b)
+          for (int r = par; r < 16; r += 2)
+            if (b < (int)cls[r].size() && fill[b] < 8) tab[(size_t)b * 16 + (par ? odd : even)[fill[b]++]] = (uint16_t)cls[r][b];
+        for (int r = par; r < 16; r += 2)
+          for (size_t i = blocks; i < cls[r].size(); ++i) rest.push_back(cls[r][i]);
+        for (int v : rest) {
+          int b = 0;
+          while (b < blocks && fill[b] == 8) ++b;
+          if (b == blocks) return {};
+          tab[(size_t)b * 16 + (par ? odd : even)[fill[b]++]] = (uint16_t)v;
+        }
+      }
+      return tab;
+    }
+    // windows by where their first pixel lies mod 16; four to a block whose even pixels (first column) lie at eight different places
+    std::vector<int> cls[16];
+    for (int y = 0; y < c.th; y += 2)
+      for (int x = 0; x < c.tw; x += 2) cls[(y * pw + x) & 15].push_back(y << 8 | x);
+    size_t left = (size_t)(c.th / 2) * (c.tw / 2);
+    for (int b = 0; b < blocks && left; ++b) {
+      unsigned used = 0;
+      for (int w = 0; w < 4 && left; ++w, --left) {
+        int pick = -1;
+        for (int r = 0; r < 16; r += 2) {
+          const bool free = !(used >> r & 1) && !(used >> ((r + pw) & 15) & 1);
+          if (!cls[r].empty() && (pick < 0 || (free && cls[r].size() > cls[pick].size()) || (free && (used >> pick & 1)))) pick = r;
+        }
+        const int v = cls[pick].back();
+        cls[pick].pop_back();
+        used |= 1u << pick | 1u << ((pick + pw) & 15);
+        for (int dy = 0; dy < 2; ++dy) {
+          tab[(size_t)b * 16 + even[2 * w + dy]] = (uint16_t)(v + (dy << 8));
+          tab[(size_t)b * 16 + odd[2 * w + dy]] = (uint16_t)(v + (dy << 8) + 1);
+        }
+      }
+    }
+    return left ? std::vector<uint16_t>{} : tab;
   }
 
   // fp32 1x1 layers have a ninth of a 3x3 layer's products for the bytes of a step, and against the larger tiles what counts is how much of their last
@@ -970,6 +1084,23 @@ struct Planner {
     auto kidx = [&](int c, int rs) -> size_t {
       return kchunk ? ((size_t)(c / bke) * R * S + rs) * bke + c % bke : (size_t)rs * C + c;
     };
+    if (st.cfg == kFrag3Cfg) {
+      // [32 channels][chunk of 32 input channels][tap][block of 16 channels][lane = 16 * (k-group) + row][16 bytes]; row r of block j is channel
+      // 8 (r / 4) + 4 j + r % 4, so that a lane ends with eight channels in a row of a pixel; k-group g is the chunk's 16 bytes 0, 2, 1, 3
+      const size_t chunks = C / 32;
+      for (int k = 0; k < K; ++k) {
+        const float* src = o.weight.data() + (size_t)k * Csrc * R * S;
+        const int q = k % 32, blk = q >> 2 & 1, row = (q >> 3) * 4 + (q & 3);
+        for (int c8 = 0; c8 < Csrc; c8 += 8) {
+          const int c16 = c8 % 32 / 8, kg = (c16 & 1) << 1 | c16 >> 1;
+          uint16_t* dst = (uint16_t*)base + (((((size_t)(k / 32) * chunks + c8 / 32) * 9) * 2 + blk) * 64 + kg * 16 + row) * 8;
+          for (int rs = 0; rs < 9; ++rs, dst += 2 * 64 * 8)
+            for (int c = c8; c < std::min(c8 + 8, Csrc); ++c) dst[c - c8] = f2bf_host(src[wch(c) * 9 + rs]);
+        }
+      }
+      st.bytes_w = (long long)K * R * S * Csrc * p.esz;
+      return;
+    }
     if (st.fc_stream || st.conv.wfrag) {
       // Fragment order: the operands of a 32-channel block are stored as a wavefront loads them, [block][128-byte step]
       // [k-group of 32 bytes][lane = 32 * (half of the k-group) + channel][16 bytes], so every load instruction reads 1 KB of
@@ -2089,7 +2220,11 @@ struct Planner {
         }
         xenos_status rc = split_conv(st);
         if (rc != XENOS_OK) return rc;
-        if (st.cfg == kWaveCfg || st.cfg == kWave64Cfg) hsplit.ks = 0;
+        if (st.cfg == kWaveCfg || st.cfg == kWave64Cfg || st.cfg == kFrag3Cfg) hsplit.ks = 0;
+        if (st.cfg == kFrag3Cfg) {
+          const std::vector<uint16_t> tab = frag3_table(a);
+          st.ktab_off = (long long)wpush(tab.data(), tab.size() * 2);
+        }
         if (hsplit.ks >= 2) a.kchunk = 1;                          // (the order of the halo kernel, which runs the chain whatever split_conv chose)
         pack_weights();
         if (a.dw_panel > 0) st.lds = dwpw_lds_bytes(a.dw_panel, p.esz);
@@ -2144,6 +2279,10 @@ struct Planner {
           a.ksplit = hsplit.ks; a.steps_per_split = a.C / (kRowBytes / p.esz) / hsplit.ks;
           a.part_ld = a.tiles_n * a.halo_bn;
           set_grid(a, kHaloCfg);
+          return emit_with_summing_pass();
+        }
+        if (st.cfg == kFrag3Cfg && st.gap_finish) {                // raw sums for the pass that averages
+          a.ksplit = 1; a.steps_per_split = a.C / 32; a.part_ld = a.tiles_n * a.halo_bn;
           return emit_with_summing_pass();
         }
         const int nsteps = a.Kred_pad / (kRowBytes / p.esz);
@@ -2537,13 +2676,14 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg wave_tc{kWaveRows, kWaveChannels, 32, 32};
       const TileCfg wave64_tc{64, 64, 64, 64};
       const bool wave = s.cfg == kWaveCfg || s.cfg == kWave64Cfg || c.pwdw == 2;
-      const TileCfg& tc = s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
+      const TileCfg frag3_tc{c.frag3 * c.frag3_wp * 16, c.halo_bn, c.frag3 * 16, 32};
+      const TileCfg& tc = s.cfg == kFrag3Cfg ? frag3_tc : s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
-               "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d,\"wave\":%d",
+               "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d,\"wave\":%d,\"frag3\":%d",
                kModeNames[c.mode], s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.unit ? "unit" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
                c.PH, c.PW, c.pool, c.relu, c.has_res, tc.bm, tc.bn, c.tiles_m, c.tiles_n, c.grid, s.lds, c.pph, c.ppw, c.patch_h,
-               c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave, wave);
+               c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave, wave, s.cfg == kFrag3Cfg ? c.frag3 : 0);
       j += buf;
     }
     // where the chain's tensors lie (byte offset into the workspace / the caller's input or output buffer, element

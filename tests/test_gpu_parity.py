@@ -578,6 +578,45 @@ def test_reduction_shared_out_over_wavefronts_in_larger_tiles(n, c, h, w, k, ksz
         assert np.array_equal(y, y1) and np.array_equal(y, few)
 
 
+@pytest.mark.parametrize("kind,n,c,h,w,k,num_cu,bm,bn", [
+    ("plain", 1, 32, 97, 95, 256, 8, 208, 128),     # one chunk a tile; tiles clipped at two borders, twelve of them walked by a workgroup
+    ("max", 3, 32, 30, 44, 256, 8, 208, 128),
+    ("res", 3, 96, 97, 95, 72, 8, 208, 128),        # an odd number of chunks, a ragged channel tile
+    ("gap", 2, 32, 97, 95, 72, 8, 208, 128),        # raw sums, the average in the summing pass
+    ("res", 5, 32, 30, 44, 256, 256, 112, 128),     # fewer items than units, their number no multiple of the XCDs
+    ("avg", 1, 64, 64, 66, 256, 8, 112, 128),
+    ("gap", 5, 32, 30, 44, 256, 256, 112, 128),
+    ("plain", 2, 32, 97, 95, 136, 8, 224, 64),      # two groups of pixels
+    ("max", 2, 64, 64, 66, 136, 8, 224, 64),
+    ("plain", 6, 192, 28, 28, 256, 256, 112, 64),   # two shares of the reduction, three chunks each
+    ("max", 6, 192, 28, 28, 256, 256, 112, 64),
+    ("gap", 6, 192, 28, 28, 256, 256, 112, 64),
+    ("res", 2, 64, 97, 95, 64, 256, 64, 64),        # a chunk for either share
+    ("plain", 40, 64, 13, 17, 136, 256, 64, 64),    # more items than workgroups
+    ("avg", 3, 64, 30, 44, 256, 256, 64, 64),
+    ("gap", 2, 64, 64, 66, 136, 256, 64, 64)])
+def test_3x3_weights_from_the_cache_into_registers(kind, n, c, h, w, k, num_cu, bm, bn):
+    # link level 3, conv3x3_frag_kernel: every variant with every epilogue it has
+    b = wg.builder("frag", (n, 24, h, w), 101, nonzero_bias=True)
+    x = b.cbr(0, c, 1, name="pre")
+    t = b.cbr(x, k, 3, 1, 1, name="a", relu=(kind != "res"))
+    if kind == "res":
+        t = b.relu(b.add(t, b.cbr(x, k, 1, name="side")))
+    elif kind == "gap":
+        t = b.gap(t)
+    elif kind != "plain":
+        t = (b.maxpool if kind == "max" else b.avgpool)(t, 2, 2, 0)
+    g = b.finish(t)
+    fmt = dict(link=3, out_layout=1, out_dtype=1)
+    hw = dict(_xenos().MI355X, num_cu=num_cu)
+    y, info = check(g, compute=1, hw=hw, **fmt)
+    tested, = [ch for ch in info["chains"] if ch.get("frag3")]
+    assert (tested["bm"], tested["bn"]) == (bm, bn) and tested["th"] * tested["tw"] <= bm, tested
+    check_chains(g, 1, hw=hw, **fmt)
+    again, _ = run_gpu(g, compute=1, hw=hw, **fmt)
+    assert np.array_equal(y, again)
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("n,c,h,w,k,stride", [
     (1, 136, 1, 1, 8, 1),        # one pixel, eight channels
