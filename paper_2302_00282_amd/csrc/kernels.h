@@ -91,6 +91,7 @@ static const int kUnitCfg = 11;
 // shared out over the wavefronts of its workgroup
 static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;
+constexpr int kWaveStageF32 = 32 * 128 + 3 * 32 * 64;   // fp32: LDS of a step, 32 pixel rows and the three bf16 parts of 32 channel rows
 static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64 (bf16)
 // Configuration index of the 3x3 kernel whose weights go from the cache into registers (bf16): kFrag3Pixels blocks of 16 pixels per wavefront
 static const int kFrag3Cfg = 14;
@@ -314,8 +315,8 @@ int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream);
 size_t pwdw_wave_lds(const ConvArgs& a, int esz);
 constexpr int wave_mid_pitch(int esz) { return 32 * esz + 16; }
 int launch_conv_wave(const ConvArgs& a, int dtype, int edge, void* stream);
-size_t conv_wave_lds(int edge, int stages);
-int conv_wave_stages(int edge, int steps, int tiles);   // for shares of `steps` reduction steps of `tiles` tiles
+size_t conv_wave_lds(int edge, int stages, int esz);
+int conv_wave_stages(int edge, int steps, int tiles, int esz);   // for shares of `steps` reduction steps of `tiles` tiles
 bool conv_cfg_has_scalar_loader(int cfg);
 bool conv_cfg_has_dw_prologue(int cfg, int mode);
 size_t dwpw_lds_bytes(int panel_channels, int esz);   // LDS of the depthwise-panel kernel for a panel of that many channels

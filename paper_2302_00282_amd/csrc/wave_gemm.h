@@ -114,4 +114,108 @@ struct WaveTile {
   }
 };
 
+// Three bf16 values whose sum is x (each rounds what the ones before it leave; the third is exact, eight of the 24 bits).  Infinite values, and finite ones
+// that round to infinity, leave NaN.
+struct Split8 { bf16x8_t hi, mid, lo; };
+__device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
+  u32x4_t p[3];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float x0 = __uint_as_float(i < 2 ? a[2 * i] : b[2 * i - 4]), x1 = __uint_as_float(i < 2 ? a[2 * i + 1] : b[2 * i - 3]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t u = f2bf2(x0, x1);
+      p[q][i] = u;
+      x0 -= __uint_as_float(u << 16);
+      x1 -= __uint_as_float(u & 0xffff0000u);
+    }
+  }
+  return Split8{__builtin_bit_cast(bf16x8_t, p[0]), __builtin_bit_cast(bf16x8_t, p[1]), __builtin_bit_cast(bf16x8_t, p[2])};
+}
+
+// fp32 tiles on the bf16 MFMAs, which multiply at sixteen times the rate of the fp32 ones: both operands are split into three bf16 values whose sum they
+// are, the weights when they are packed, the pixels as fragments are read, and six of the nine products are summed in fp32 (the three left out are below
+// 2^-24 of the product).  The five small ones have sums of their own, so that the large ones are rounded once in sixteen products: against 64 bits dot products
+// of 16 to 4608 random numbers are off by 3.2e-8 to 4.2e-7 of their norm, half or less of the fp32 MFMAs' 5.5e-8 to 1.2e-6.  A step is twelve MFMAs of 32
+// cycles instead of sixteen of 64.  The image of a step of the weights lies in memory as in LDS: [hi, mid, lo][32 channels][64 bytes], 16-byte slot s of
+// row r holds chunk s ^ (r / 4 % 4).  Sums that are not finite are for the caller to work out again (an infinite value is no sum of three).
+template <>
+struct WaveTile<float, 1> {
+  static constexpr int EDGE = 32, ROWS_A = EDGE * ROWB, PLANE = EDGE * 64;
+  static constexpr int STAGE = (int)kWaveStageF32;      // pixel rows, then the three planes of the channel rows
+  static constexpr int LOADS = ROWS_A / 1024 + 3 * PLANE / 1024;
+  static constexpr int MAX_STAGES = 3, SLOTS = EDGE / 4;
+  static_assert(STAGE == ROWS_A + 3 * PLANE && EDGE * EDGE * 4 <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
+
+  template <typename Request>
+  __device__ __forceinline__ static void begin(int n, int stages, unsigned char* s_w, Request request) {
+#pragma unroll 1
+    for (int d = 0; d < stages && d < n; ++d) request(d, s_w + d * STAGE);
+  }
+  template <typename Request>
+  __device__ __forceinline__ static void finish(int n, int stages, unsigned char* s_w, Request request) {
+    const int lane = threadIdx.x & 63, l31 = lane & 31, lhalf = lane >> 5;
+    // the lane's eight values of pixels in either half of a step, 16 bytes at a time, and of weights: chunks 4 g + 2 lhalf + 0 and 1, and 2 g + lhalf
+    // (their slots differ in one bit of the address, stages being multiples of 1 KB; worked out by step, for want of registers)
+    const uint32_t aslot = (uint32_t)(uintptr_t)(lds_ptr_t)s_w + l31 * ROWB + ((2 * lhalf) ^ wave_swizzle(l31)) * 16;
+    const uint32_t wslot = (uint32_t)(uintptr_t)(lds_ptr_t)s_w + ROWS_A + l31 * 64 + (lhalf ^ ((l31 >> 2) & 3)) * 16;
+    typedef const __attribute__((address_space(3))) u32x4_t* lds_vec_t;
+    f32x16_t acc, small;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = small[e] = 0.f;
+    unsigned char* s = s_w;
+    int st = 0;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int behind = n - 1 - i < stages - 1 ? n - 1 - i : stages - 1;   // (uniform) steps requested behind this one
+      if (behind == 2) wait_requests<2 * LOADS>();
+      else if (behind == 1) wait_requests<LOADS>();
+      else wait_requests<0>();
+      u32x4_t a[4], w[2][3];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = *(lds_vec_t)(uintptr_t)((aslot + (uint32_t)(s - s_w)) ^ (uint32_t)((q >> 1) * 64 + (q & 1) * 16));
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) w[g][q] = *(lds_vec_t)(uintptr_t)(((wslot + (uint32_t)(s - s_w)) ^ (uint32_t)(g * 32)) + q * PLANE);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // the stage has been read: it may be written again
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        if (g == 1 && i + stages < n) request(i + stages, s);          // (here, where fewer registers hold what was read)
+        const Split8 x = split8(a[2 * g], a[2 * g + 1]);
+        const bf16x8_t hi = __builtin_bit_cast(bf16x8_t, w[g][0]), mid = __builtin_bit_cast(bf16x8_t, w[g][1]), lo = __builtin_bit_cast(bf16x8_t, w[g][2]);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, x.hi, small, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.hi, acc, 0, 0, 0);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x.hi, small, 0, 0, 0);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x.mid, small, 0, 0, 0);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.mid, small, 0, 0, 0);
+        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.lo, small, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (++st == stages) { st = 0; s = s_w; } else { s += STAGE; }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(f32x4_t*)(s_w + l31 * EDGE * 4 + (((g * 2 + lhalf) ^ l31) & (SLOTS - 1)) * 16) =
+          f32x4_t{acc[4 * g] + small[4 * g], acc[4 * g + 1] + small[4 * g + 1], acc[4 * g + 2] + small[4 * g + 2], acc[4 * g + 3] + small[4 * g + 3]};
+  }
+  __device__ __forceinline__ static f32x4_t sum(const unsigned char* s, int wave_bytes, int row, int c4) {
+    f32x4_t v[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + row * EDGE * 4 + ((c4 ^ row) & (SLOTS - 1)) * 16);
+    return ((v[0] + v[1]) + v[2]) + v[3];
+  }
+  // element i of a step of channel row `row`, out of the packed image of that step
+  __device__ static float weight(const unsigned char* step, int row, int i) {
+    const uint16_t* p = (const uint16_t*)(step + row * 64 + (((i >> 3) ^ ((row >> 2) & 3)) * 16)) + (i & 7);
+    return (bf2f(p[0]) + bf2f(p[PLANE / 2])) + bf2f(p[PLANE]);
+  }
+};
+__device__ __forceinline__ bool all_finite(const f32x4_t& v) {
+  uint32_t e = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e |= (__float_as_uint(v[i]) & 0x7f800000u) == 0x7f800000u ? 1u : 0u;
+  return e == 0;
+}
+
 }  // namespace xenos

@@ -796,8 +796,9 @@ struct Planner {
       c.xcd_m = 1;
       c.grid = wave_grid(c.ntiles);
       st.cfg = edge == 64 ? kWave64Cfg : kWaveCfg;
-      st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles));
-      st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
+      st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles, p.esz), p.esz);
+      if (p.dt == DT_F32) st.cands.clear();                        // (its weights lie in an order of their own)
+      else st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
     }
     ConvArgs f = c;
     if (choose_frag3(st, f)) {
@@ -1002,9 +1003,9 @@ struct Planner {
     // 784 tiles of 64 x 64 take 75.9 us against the halo kernel's 53.3).  In fp32, whose MFMAs cover the smaller tile's loads, they gain nothing
     const long long tiles64 = (long long)((c.M_total + 63) / 64) * ((c.K + 63) / 64);
     if (p.dt == DT_BF16 && tiles > 512 && tiles64 <= 512 && nsteps >= (tiles <= 1024 ? 16 : 9) && most > 512 &&
-        conv_wave_lds(64, conv_wave_stages(64, nsteps, (int)tiles64)) <= p.hw.lds_bytes_per_cu)
+        conv_wave_lds(64, conv_wave_stages(64, nsteps, (int)tiles64, p.esz), p.esz) <= p.hw.lds_bytes_per_cu)
       return 64;
-    return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, nsteps, (int)tiles)) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
+    return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, nsteps, (int)tiles, p.esz), p.esz) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
   // Shares of the reduction of a chain on fc_stream_kernel, for that many units (two workgroups per unit, each with at least 4 steps = 32 KB of
   // weights to stream)
@@ -1073,10 +1074,10 @@ struct Planner {
     const int kred_pad = st.conv.Kred_pad;
     const bool kchunk = st.conv.kchunk;
     const int kout_pad = (K + 127) / 128 * 128;
-    const size_t bytes = (size_t)kout_pad * kred_pad * p.esz;
+    const bool wave_f32 = p.dt == DT_F32 && (st.cfg == kWaveCfg || st.conv.pwdw == 2);
+    const size_t bytes = wave_f32 ? (size_t)((K + 31) / 32) * (kred_pad / bke) * (6 * 1024) : (size_t)kout_pad * kred_pad * p.esz;
     st.w_off = (long long)wpush(nullptr, bytes);
-    unsigned char* base = p.wimage.data() + st.w_off;
-    memset(base, 0, bytes);
+    unsigned char* base = p.wimage.data() + st.w_off;               // (zeros)
     // source [K][C][R][S] -> destination [K][reduction index]; channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
     // folded shuffle of g groups (tensor channel j * m + i is the operator's channel i * g + j), its shuffled position
     const int shg = pack_shuffle_groups, shm = shg ? Csrc / shg : 1;
@@ -1084,6 +1085,40 @@ struct Planner {
     auto kidx = [&](int c, int rs) -> size_t {
       return kchunk ? ((size_t)(c / bke) * R * S + rs) * bke + c % bke : (size_t)rs * C + c;
     };
+    if (wave_f32) {
+      // [32 channels][step][upper, middle and lower eight bits][channel][64 bytes], 16-byte slot s of channel r holds chunk s ^ (r / 4 % 4): a step as it
+      // lies in LDS
+      const size_t nsteps = kred_pad / bke;
+      for (int k = 0; k < K; ++k) {
+        const float* src = o.weight.data() + (size_t)k * Csrc * R * S;
+        const int row = k % 32, group = C % 8 == 0 ? 8 : 4;        // (channels that lie behind one another)
+        for (int c0 = 0; c0 < Csrc; c0 += group)
+          for (int rs = 0; rs < R * S; ++rs) {
+            const size_t at = kidx(c0, rs), i = at % bke;
+            uint16_t* dst = (uint16_t*)(base + ((size_t)(k / 32) * nsteps + at / bke) * (6 * 1024) + row * 64 + ((i / 8) ^ (row / 4 % 4)) * 16) + i % 8;
+            const int cn = std::min(group, Csrc - c0);
+            float v[8] = {};
+            uint16_t h[8];
+            if (shg) for (int c = 0; c < cn; ++c) v[c] = src[wch(c0 + c) * R * S + rs];
+            else if (R * S == 1 && cn == 8) memcpy(v, src + c0, 8 * sizeof(float));
+            else for (int c = 0; c < cn; ++c) v[c] = src[(size_t)(c0 + c) * R * S + rs];
+            for (int part = 0; part < 3; ++part, dst += 1024) {
+              for (int c = 0; c < 8; ++c) {
+                uint32_t u;
+                memcpy(&u, &v[c], 4);
+                u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+                h[c] = (uint16_t)(u >> 16);
+                float f;
+                memcpy(&f, &u, 4);
+                v[c] -= f;
+              }
+              if (cn == 8) memcpy(dst, h, 16); else memcpy(dst, h, cn * sizeof(uint16_t));
+            }
+          }
+      }
+      st.bytes_w = (long long)K * R * S * Csrc * p.esz;
+      return;
+    }
     if (st.cfg == kFrag3Cfg) {
       // [32 channels][chunk of 32 input channels][tap][block of 16 channels][lane = 16 * (k-group) + row][16 bytes]; row r of block j is channel
       // 8 (r / 4) + 4 j + r % 4, so that a lane ends with eight channels in a row of a pixel; k-group g is the chunk's 16 bytes 0, 2, 1, 3
@@ -1139,6 +1174,10 @@ struct Planner {
     p.dt = p.opts.compute == XENOS_BF16 ? DT_BF16 : DT_F32;
     p.esz = p.dt == DT_BF16 ? 2 : 4;
     p.ce = 16 / p.esz;
+    // (room for every weight, padded, in its widest form: growing step by step the image would be copied again and again)
+    size_t room = 1 << 16;
+    for (const GOp& o : g.ops) room += o.weight.size() * (p.dt == DT_F32 ? 6 : 2) * 5 / 4 + 4096;
+    p.wimage.reserve(room);
     p.zero_off = wpush(nullptr, 256);      // (new bytes of the image are zero)
     build_nodes();
     const int nn = (int)nodes.size();
@@ -2293,7 +2332,7 @@ struct Planner {
             a.ksplit = ks; a.steps_per_split = (nsteps + ks - 1) / ks;
             a.part_ld = a.tiles_n * edge;
             a.grid = wave_grid(a.ntiles * ks);
-            st.lds = conv_wave_lds(edge, conv_wave_stages(edge, a.steps_per_split, a.ntiles * ks));
+            st.lds = conv_wave_lds(edge, conv_wave_stages(edge, a.steps_per_split, a.ntiles * ks, p.esz), p.esz);
             st.cands.clear();                                      // the plan's structure now depends on this split
             return emit_with_summing_pass();
           }
@@ -2367,10 +2406,6 @@ struct Planner {
     a.pwdw = 1; a.dw_k = 3; a.dw_stride = dd.stride_h; a.dw_pad = 1; a.dw_relu = w2.relu; a.dw_H = is.h; a.dw_W = is.w;
     a.M_total = a.N * a.OH * a.OW;
     set_reduction(st, a.C, 1, 1);
-    pack_dense(st, go, is.c, a.C, 1, 1, K);
-    push_affine(w1.af, (K + 127) / 128 * 128, &st.scale_off, &st.shift_off);
-    st.dw_w_off = pack_depthwise(g.ops[dnode.src], K, 9);
-    push_affine(w2.af, (K + 63) / 64 * 64, &st.dw_scale_off, &st.dw_shift_off);
     st.v_out = out_view_for(w2.cur, true);
     const View& ov = p.views[st.v_out];
     a.out_sN = ov.sN; a.out_sP = ov.sP; a.out_sK = ov.sK; a.out_f32 = ov.f32;
@@ -2378,6 +2413,10 @@ struct Planner {
     if (!a.vec_out) return fail(XENOS_EUNSUPPORTED, "%s: output of the pointwise -> depthwise chain is not aligned", st.name.c_str());
     if (!choose_pwdw_tile(a)) return fail(XENOS_EUNSUPPORTED, "%s: no tile of the pointwise -> depthwise kernel fits", st.name.c_str());
     if (choose_pwdw_wave_tile(a)) a.pwdw = 2;
+    pack_dense(st, go, is.c, a.C, 1, 1, K);
+    push_affine(w1.af, (K + 127) / 128 * 128, &st.scale_off, &st.shift_off);
+    st.dw_w_off = pack_depthwise(g.ops[dnode.src], K, 9);
+    push_affine(w2.af, (K + 63) / 64 * 64, &st.dw_scale_off, &st.dw_shift_off);
     a.tiles_m = a.N * a.tiles_y * a.tiles_x;
     a.tiles_n = (K + kPwDwChannels - 1) / kPwDwChannels;
     a.ntiles = a.tiles_m * a.tiles_n;

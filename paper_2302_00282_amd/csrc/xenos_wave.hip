@@ -35,7 +35,7 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
   using tr = Tr<T>;
   using tile = WaveTile<T, NB>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T), EDGE = tile::EDGE;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(128) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lrow = lane >> 3, lslot = lane & 7;                    // a request is 8 rows of 8 slots
   const int wave_bytes = a.stages * tile::STAGE;
@@ -65,8 +65,8 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
       aoff[j] = __builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, off) + (UNI ? ch[j & 1] * 16 : 0);
       ayx[j] = __builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, yx);
     }
-    const unsigned woff[2] = {lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
-    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * EDGE * a.wpitch, kWindow);
+    const unsigned woff[2] = {ESZ == 4 ? lane * 16u : lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
+    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * (ESZ == 4 ? 1 : EDGE) * a.wpitch, kWindow);
     auto request = [&](int i, unsigned char* dst) __attribute__((always_inline)) {
       const uint32_t s = (uint32_t)(s_begin + wave + 4 * i);
       // row and column of the kernel, offset and validity of the two chunks that the lane loads of a row
@@ -99,8 +99,13 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
         if constexpr (DIRECT) load_to_lds(wa, dst + j * 1024, o, 0);
         else *(u32x4_t*)(dst + j * 1024 + lane * 16) = load_window(wa, o);
       }
+      if constexpr (ESZ == 4) {
 #pragma unroll
-      for (int j = 0; j < 4 * NB; ++j) load_to_lds(wb, dst + (4 * NB + j) * 1024, woff[j & 1], j * 8 * a.wpitch + s * ROWB);
+        for (int j = 0; j < 6; ++j) load_to_lds(wb, dst + (4 + j) * 1024, woff[0], (s * 6 + j) * 1024u);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) load_to_lds(wb, dst + (4 * NB + j) * 1024, woff[j & 1], j * 8 * a.wpitch + s * ROWB);
+      }
     };
     tile::begin(n, a.stages, s_w, request);
 
@@ -137,6 +142,26 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
       const int m = m0 + u * RS;
       f32x4_t v = tile::sum(smem, wave_bytes, tid / tile::SLOTS + u * RS, c4);
       if (m >= a.M || k >= a.K) continue;
+      if constexpr (ESZ == 4) {
+        if (!all_finite(v)) {                                      // with the products of the operands themselves
+          const int img = small_quotient(m, a.r_ohw), p = m - img * a.OHW, oh = small_quotient(p, a.r_ow), ow = p - oh * a.OW;
+          const unsigned char* const px = (const unsigned char*)a.in + (size_t)((unsigned)img * a.sN);
+          v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int i = s_begin * BKE; i < (s_begin + share) * BKE; ++i) {
+            const int s = i / BKE;
+            int tap, c;
+            if constexpr (UNI) { const int cc = (int)host_quotient((uint32_t)s, a.m_rs); tap = s - cc * (int)a.rs; c = cc * BKE + i % BKE; }
+            else { tap = small_quotient(i, a.r_C); c = i - tap * a.C; }
+            const int r = small_quotient(tap, a.r_S), y = oh * a.stride - a.pad + r, x = ow * a.stride - a.pad + tap - r * (int)a.S;
+            if (c >= a.C || tap >= (int)a.rs || (unsigned)y >= (unsigned)a.H || (unsigned)x >= (unsigned)a.W) continue;
+            const float f = *(const float*)(px + ((unsigned)y * a.sH + (unsigned)x * a.sW + (unsigned)c * 4u));
+            const unsigned char* const wst = (const unsigned char*)a.w + (size_t)tn * a.wpitch + (size_t)s * (6 * 1024);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, WaveTile<float, 1>::weight(wst, c4 * 4 + e, i % BKE), v[e]);
+          }
+        }
+      }
       if (a.flags & WF_PARTIAL) {
         *(f32x4_t*)((float*)a.out + ((size_t)z * a.M + m) * a.part_ld + k) = v;
         continue;
@@ -184,7 +209,7 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
   using tr = Tr<T>;
   using tile = WaveTile<T, 1>;
   constexpr int CE = tr::CE, BKE = tr::BKE, ESZ = (int)sizeof(T), MP = wave_mid_pitch(ESZ), CG = 32 / CE;
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(128) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lrow = lane >> 3, lslot = lane & 7;
   const int wave_bytes = a.stages * tile::STAGE;
@@ -208,13 +233,18 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
 #pragma unroll
       for (int j = 0; j < 4; ++j) aoff[j] = (unsigned)__builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, (int)off);
     }
-    const unsigned woff[2] = {lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
-    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)nh * 32 * a.wpitch, kWindow);
+    const unsigned woff[2] = {ESZ == 4 ? lane * 16u : lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
+    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)nh * (ESZ == 4 ? 1 : 32) * a.wpitch, kWindow);
     auto request = [&](int i, unsigned char* dst) __attribute__((always_inline)) {
       const uint32_t st = (uint32_t)(wave + 4 * i);
       const int left = a.C - (int)st * BKE;                        // (the padding of the reduction)
+      if constexpr (ESZ == 4) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) load_to_lds(wb, dst + 4096 + j * 1024, woff[j & 1], j * 8 * a.wpitch + st * ROWB);
+        for (int j = 0; j < 6; ++j) load_to_lds(wb, dst + 4096 + j * 1024, woff[0], (st * 6 + j) * 1024u);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_to_lds(wb, dst + 4096 + j * 1024, woff[j & 1], j * 8 * a.wpitch + st * ROWB);
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         unsigned o = (aoff[j] != kNoLoad) & (ch[j & 1] * CE < left) ? aoff[j] + ch[j & 1] * 16u + st * ROWB : kNoLoad;
@@ -247,12 +277,26 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
     tile::finish(n_w, a.stages, s_w, request);
     __syncthreads();
     if (const int m = tid >> 3; m < npos) {
-      const int py = small_quotient(m, r_wv), px = m - py * wv;
-      f32x4_t v = tile::sum(smem, wave_bytes, m, tid & 7) * psc + psh;
+      const int py = small_quotient(m, r_wv), px_ = m - py * wv;
+      f32x4_t v = tile::sum(smem, wave_bytes, m, tid & 7);
+      if constexpr (ESZ == 4) {
+        if (!all_finite(v)) {                                      // with the products of the operands themselves
+          const unsigned char* const px = (const unsigned char*)a.in + (size_t)(n * a.sN + (unsigned)(y_lo + py) * a.sH + (unsigned)(x_lo + px_) * a.sW);
+          v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int i = 0; i < a.C; ++i) {
+            const float f = *(const float*)(px + (unsigned)i * 4u);
+            const unsigned char* const wst = (const unsigned char*)a.w + (size_t)nh * a.wpitch + (size_t)(i / BKE) * (6 * 1024);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, WaveTile<float, 1>::weight(wst, c4 + e, i % BKE), v[e]);
+          }
+        }
+      }
+      v = v * psc + psh;
       const float lo = relu_floor(a.flags & WF_RELU);
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = fmx_floor(v[e], lo);
-      unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px - ix0)) * MP + c4 * ESZ;
+      unsigned char* dst = s_mid + ((y_lo + py - iy0) * PWd + (x_lo + px_ - ix0)) * MP + c4 * ESZ;
       if constexpr (ESZ == 2) *(uint2*)dst = uint2{f2bf2(v[0], v[1]), f2bf2(v[2], v[3])};
       else *(f32x4_t*)dst = v;
     }
@@ -289,14 +333,15 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
   }
 }
 
-size_t conv_wave_lds(int edge, int stages) { return (size_t)4 * stages * 2 * edge * ROWB; }
+size_t conv_wave_lds(int edge, int stages, int esz) { return (size_t)4 * stages * (esz == 4 ? kWaveStageF32 : 2 * edge * ROWB); }
 
 // Steps of a wavefront that are on their way at a time: up to four where a unit has one workgroup, two where it has two, one where it has
 // more, which then hide each other's latency (3x3 layers in bf16, four in a row: 128 channels 28x28 batch 4, 392 tiles, four 36.8 us, two
 // 25.9; 256 channels 14x14 batch 16, 784 tiles, two 60.8, one 56.2; 400 tiles of 144 steps, two 51.8, one 58.5)
 // (64 x 64 tiles: a stage is 64 KB.  256 channels 14x14, 196 tiles, one 49.9, two 47.2; 392 tiles, two workgroups to a unit, one 61.9, two 85.3)
-int conv_wave_stages(int edge, int steps, int tiles) {
-  const int n = (steps + 3) / 4, most = edge > kWaveRows ? (tiles <= 256 ? 2 : 1) : tiles <= 256 ? 4 : tiles <= 512 ? 2 : 1;
+// (fp32: a stage is 40 KB, and three of them leave room for the block of a depthwise convolution)
+int conv_wave_stages(int edge, int steps, int tiles, int esz) {
+  const int n = (steps + 3) / 4, most = edge > kWaveRows ? (tiles <= 256 ? 2 : 1) : tiles <= 256 ? (esz == 4 ? 3 : 4) : tiles <= 512 ? 2 : 1;
   return n < 1 ? 1 : n < most ? n : most;
 }
 
@@ -327,22 +372,22 @@ static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
   w.rs = (uint32_t)(a.R * a.S); w.m_rs = host_multiplier(w.rs); w.S = (uint32_t)a.S; w.m_S = host_multiplier(w.S); w.r_C = 1.f / (float)a.C; w.r_S = 1.f / (float)a.S;
   w.M = a.M_total; w.OHW = a.OH * a.OW; w.OW = a.OW; w.r_ohw = 1.f / (float)w.OHW; w.r_ow = 1.f / (float)w.OW;
   w.stride = a.stride; w.pad = a.pad; w.H = a.H; w.W = a.W; w.C = a.C;
-  w.sN = (uint32_t)(a.in_sN * ESZ); w.sH = (uint32_t)(a.in_sH * ESZ); w.sW = (uint32_t)(a.in_sW * ESZ); w.wpitch = (uint32_t)(a.Kred_pad * ESZ);
+  w.sN = (uint32_t)(a.in_sN * ESZ); w.sH = (uint32_t)(a.in_sH * ESZ); w.sW = (uint32_t)(a.in_sW * ESZ); w.wpitch = (uint32_t)(ESZ == 4 ? a.Kred_pad / BKE * (6 * 1024) : a.Kred_pad * ESZ);   // (of a row, or of a block of 32)
   w.K = a.K; w.part_ld = a.part_ld; w.flags = (a.relu ? WF_RELU : 0) | (partial ? WF_PARTIAL : 0) | (a.out_f32 ? WF_OUT_F32 : 0);
   const int osz = a.out_f32 ? 4 : ESZ;
   w.out_sN = (uint32_t)(a.out_sN * osz); w.out_sP = (uint32_t)(a.out_sP * osz); w.res_sN = (uint32_t)(a.res_sN * ESZ); w.res_sP = (uint32_t)(a.res_sP * ESZ);
-  w.stages = conv_wave_stages(EDGE, w.steps_per_share, (int)w.tiles);
-  const int lds = (int)conv_wave_lds(EDGE, w.stages);
+  w.stages = conv_wave_stages(EDGE, w.steps_per_share, (int)w.tiles, ESZ);
+  const int lds = (int)conv_wave_lds(EDGE, w.stages, ESZ);
   const bool direct = ((uintptr_t)a.in & 15) == 0;
   if (a.R * a.S == 1 || a.kchunk)
     return direct ? launch_conv_wave_inst<T, NB, true, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, NB, true, false>(w, a.grid, lds, st);
   return direct ? launch_conv_wave_inst<T, NB, false, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, NB, false, false>(w, a.grid, lds, st);
 }
 
-static int pwdw_wave_stages(const ConvArgs& a, int esz) { return conv_wave_stages(kWaveRows, a.Kred_pad * esz / ROWB, a.tiles_m * ((a.K + 31) / 32)); }
+static int pwdw_wave_stages(const ConvArgs& a, int esz) { return conv_wave_stages(kWaveRows, a.Kred_pad * esz / ROWB, a.tiles_m * ((a.K + 31) / 32), esz); }
 size_t pwdw_wave_lds(const ConvArgs& a, int esz) {
   const int s = a.dw_stride;
-  return conv_wave_lds(kWaveRows, pwdw_wave_stages(a, esz)) + (size_t)((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3) * wave_mid_pitch(esz);
+  return conv_wave_lds(kWaveRows, pwdw_wave_stages(a, esz), esz) + (size_t)((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3) * wave_mid_pitch(esz);
 }
 
 template <typename T, bool DIRECT>
@@ -372,7 +417,7 @@ static int launch_pwdw_wave_t(const ConvArgs& a, hipStream_t st) {
   w.nh = (uint32_t)((a.K + 31) / 32); w.m_nh = host_multiplier(w.nh); w.tiles = (uint32_t)a.tiles_m * w.nh;
   w.tiles_sp = (uint32_t)(a.tiles_y * a.tiles_x); w.m_sp = host_multiplier(w.tiles_sp); w.tiles_x = (uint32_t)a.tiles_x; w.m_tx = host_multiplier(w.tiles_x);
   w.nsteps = a.Kred_pad / BKE; w.C = a.C; w.K = a.K; w.H = a.H; w.W = a.W; w.OH = a.OH; w.OW = a.OW; w.th = a.th; w.tw = a.tw; w.r_tw = 1.f / (float)a.tw;
-  w.sN = (uint32_t)(a.in_sN * ESZ); w.sH = (uint32_t)(a.in_sH * ESZ); w.sW = (uint32_t)(a.in_sW * ESZ); w.wpitch = (uint32_t)(a.Kred_pad * ESZ);
+  w.sN = (uint32_t)(a.in_sN * ESZ); w.sH = (uint32_t)(a.in_sH * ESZ); w.sW = (uint32_t)(a.in_sW * ESZ); w.wpitch = (uint32_t)(ESZ == 4 ? a.Kred_pad / BKE * (6 * 1024) : a.Kred_pad * ESZ);   // (of a row, or of a block of 32)
   w.out_sN = (uint32_t)(a.out_sN * ESZ); w.out_sP = (uint32_t)(a.out_sP * ESZ);
   w.stride = s; w.flags = (a.relu ? WF_RELU : 0) | (a.dw_relu ? WF_DW_RELU : 0);
   const int lds = (int)pwdw_wave_lds(a, ESZ);

@@ -578,6 +578,33 @@ def test_reduction_shared_out_over_wavefronts_in_larger_tiles(n, c, h, w, k, ksz
         assert np.array_equal(y, y1) and np.array_equal(y, few)
 
 
+@pytest.mark.parametrize("kind,c,ksz,stride", [("conv", 40, 1, 1), ("conv", 64, 3, 2), ("conv", 24, 3, 1), ("split", 640, 3, 1), ("pwdw", 72, 1, 1)])
+def test_fp32_products_in_three_parts_keep_infinite_and_largest_values(kind, c, ksz, stride):
+    # fp32 wave kernels multiply bf16 parts of their operands, which an infinite value and one that rounds to infinity in bf16 do not have
+    b = wg.builder("parts", (2, c, 9, 8), 103, nonzero_bias=True)
+    t = b.cbr(0, 40, ksz, stride, ksz // 2, name="a", bn=False, relu=False)
+    if kind == "pwdw":
+        t = b.cbr(t, 40, 3, 1, 1, groups=40, name="dw", bn=False, relu=False)
+        b.g.ops[t - 1].params["weight"][:] = np.abs(b.g.ops[t - 1].params["weight"]) + 0.1   # (no 0 x infinity, no infinity - infinity)
+    g = b.finish(t)
+    w = g.ops[0].params["weight"]
+    w[:] = np.abs(w) + np.float32(1e-3)
+    w[3] = np.round(w[3] * 64) / 64 + 0.5              # (parts of it are zero)
+    g.x = np.abs(g.x)
+    g.x[0, 3, 2, 2] = np.inf
+    g.x[1, 5, 6, 5] = np.finfo(np.float32).max          # (rounds to infinity in bf16; times the smallest weights it is finite)
+    g.x[1, 7, 1, 1] = 1e-39
+    w[:, 5] = 1e-5
+    fmt = dict(link=3, in_layout=1, out_layout=1)
+    ref = xo.forward(g)
+    y, info = run_gpu(g, compute=0, **fmt)
+    assert any(ch.get("wave") for ch in info["chains"]) and (kind != "split" or any(ch.get("ksplit", 1) > 1 for ch in info["chains"])), info["chains"]
+    fin = np.isfinite(ref)
+    assert not fin.all() and not np.isnan(ref).any() and np.array_equal(y[~fin], ref[~fin].astype(np.float32))
+    big = fin & (np.abs(ref) > 1e20)
+    assert big.any() and rel_err(y[big], ref[big]) <= 1e-5 and rel_err(y[fin & ~big], ref[fin & ~big]) <= 1e-5
+
+
 @pytest.mark.parametrize("kind,n,c,h,w,k,num_cu,bm,bn", [
     ("plain", 1, 32, 97, 95, 256, 8, 208, 128),     # one chunk a tile; tiles clipped at two borders, twelve of them walked by a workgroup
     ("max", 3, 32, 30, 44, 256, 8, 208, 128),
