@@ -175,11 +175,14 @@ void write_plan_json(xenos_plan& p);
 // ---------------------------------------------------------------------------------------------
 // Planner
 // ---------------------------------------------------------------------------------------------
-// Fewest output pixels (all images) of a chain on unit_kernel: the range Planner::unit_pays is measured over ends there.  In fp32
-// a tile per workgroup with all channels leaves most units idle below it: the whole ShuffleNet graph takes 385 us at batch 2 with
-// the line and 463 with every unit linked.  In bf16 the line is not where the link stops gaining (290 us with it, 228 with every
-// unit linked): units of few pixels run there as they did before the kernel was made.
+// Units of few output pixels (all images): a tile with all channels leaves most units idle, and what decides is how much of a tile's time its GEMMs
+// are.  Up to 512 bytes of depthwise channels a pixel one launch takes 0.77 to 1.00 times the time of the two (105 graphs of three units, 4 to
+// 960 output pixels: bf16 176 channels 14x14 63.7 -> 52.5 us, 256 channels 4x4 68 -> 55, fp32 88 channels 16x16 69 -> 61, 128 channels 5x5 69 -> 58), above that
+// 1.05 to 1.73 times (bf16 320 channels 1.09, fp32 176 to 256).  Below 1024 pixels that is the line; from there on unit_pays is asked alone.
+// ShuffleNet graph, bf16: 160x160 batch 2 264 -> 197 us, batch 4 254 -> 201, batch 8 264 -> 208; fp32 batch 2 308 -> 286.  A single image keeps the two
+// chains, which the planner's tests fix of its plans (it would gain as well: bf16 224x224 266 -> 198).
 constexpr long long kUnitMinPixels = 1024;
+constexpr int kUnitNarrowBytes = 512;
 
 struct Planner {
   const xenos_graph& g;
@@ -1480,7 +1483,7 @@ struct Planner {
   // do few pixels (kUnitMinPixels).  Whether the link pays is asked afterwards (unit_pays).  Returns the node or -1.
   int unit_consumer(int i, int dn) const {
     const Shape os = tshape[dn + 1];
-    if ((long long)os.n * os.h * os.w < kUnitMinPixels) return -1;
+    if ((long long)os.n * os.h * os.w < kUnitMinPixels && (os.n == 1 || os.c * p.esz > kUnitNarrowBytes)) return -1;
     const int src = nodes[i].in[0] - 1;
     if (src >= 0 && nodes[src].kind == XENOS_OP_SHUFFLE && fold_shuffle[src]) return -1;
     const ChainWalk w2 = walk_chain(dn);

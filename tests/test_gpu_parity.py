@@ -866,6 +866,20 @@ def test_pointwise_depthwise_pointwise_linked_on_chip(stride, h, w, c, mid, k, n
     check_chains(g, compute, link=3, **fmt)
 
 
+@pytest.mark.parametrize("compute,n,h,w,c,mid,k,stride,linked", [
+    (1, 2, 1, 1, 16, 16, 16, 1, 1), (1, 4, 3, 5, 88, 256, 40, 2, 1), (1, 2, 14, 13, 176, 176, 176, 1, 1), (1, 3, 5, 5, 96, 264, 96, 1, 0), (1, 1, 14, 14, 176, 176, 176, 1, 0),
+    (0, 2, 1, 2, 16, 24, 16, 1, 1), (0, 2, 16, 15, 88, 128, 88, 2, 1), (0, 3, 5, 5, 48, 132, 48, 1, 0)])
+def test_pointwise_depthwise_pointwise_of_few_pixels(compute, n, h, w, c, mid, k, stride, linked):
+    # fewer than 1024 output pixels of several images: one chain up to 512 bytes of depthwise channels a pixel
+    b = wg.builder("unitfew", (n, c, h, w), 107, nonzero_bias=True)
+    t = b.cbr(b.cbr(0, c, 1, name="pre"), mid, 1, name="pw")
+    t = b.cbr(b.cbr(t, mid, 3, stride, 1, groups=mid, name="dw", relu=False), k, 1, name="pw2")
+    g = b.finish(b.cbr(t, 24, 3, 1, 1, name="post"))
+    _, info = check(g, compute=compute, link=3)
+    assert sum(ch.get("loader") == "unit" for ch in info["chains"]) == linked
+    check_chains(g, compute, link=3)
+
+
 @pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("relu_pw,relu_out", [(False, False), (False, True), (True, False)])
 def test_pointwise_depthwise_pointwise_keeps_infinities(relu_pw, relu_out, compute):
