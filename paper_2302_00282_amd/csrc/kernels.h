@@ -279,9 +279,9 @@ inline bool block_window_fits(const ConvArgs& a, int rows, int esz) {
   return (double)a.in_sH * std::min(rows, a.H) * esz < kBlockWindow && 64.0 * a.Kred_pad * esz < 0xffffff00ll;
 }
 // Do a chain's sizes fit the indices of the wave kernel (quotients, packed coordinates and byte offsets of 32 bits)?
-inline bool conv_wave_takes(const ConvArgs& a, int esz) {
+inline bool conv_wave_takes(const ConvArgs& a, int esz, int edge = kWaveRows) {
   const int bke = kRowBytes / esz, ce = 16 / esz;
-  const double lim = 2147483648.0, tiles = std::ceil(a.M_total / (double)kWaveRows) * std::ceil(a.K / (double)kWaveChannels) * (a.ksplit > 1 ? a.ksplit : 1);
+  const double lim = 2147483648.0, tiles = std::ceil(a.M_total / (double)edge) * std::ceil(a.K / (double)edge) * (a.ksplit > 1 ? a.ksplit : 1);
   return a.mode == M_FLAT && a.C % ce == 0 && a.K % 4 == 0 && a.Kred_pad % bke == 0 && a.Kred_pad / bke + 4 < (int)kHostDiv && a.Kred_pad + bke < kSmallDiv &&
          a.M_total + kWaveRows < kSmallDiv && tiles < kHostDiv && a.R * a.S < (int)kHostDiv && a.H + a.pad < 0x4000 && a.W + a.pad < 0x4000 && a.R < 0x1000 && a.S < 0x1000 && a.stride < 0x1000 &&
          (a.OH - 1) * (double)a.stride < 0x4000 && (a.OW - 1) * (double)a.stride < 0x4000 && a.pad < 0x1000 &&

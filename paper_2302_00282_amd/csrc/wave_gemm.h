@@ -139,13 +139,13 @@ __device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
 // of 16 to 4608 random numbers are off by 3.2e-8 to 4.2e-7 of their norm, half or less of the fp32 MFMAs' 5.5e-8 to 1.2e-6.  A step is twelve MFMAs of 32
 // cycles instead of sixteen of 64.  The image of a step of the weights lies in memory as in LDS: [hi, mid, lo][32 channels][64 bytes], 16-byte slot s of
 // row r holds chunk s ^ (r / 4 % 4).  Sums that are not finite are for the caller to work out again (an infinite value is no sum of three).
-template <>
-struct WaveTile<float, 1> {
-  static constexpr int EDGE = 32, ROWS_A = EDGE * ROWB, PLANE = EDGE * 64;
-  static constexpr int STAGE = (int)kWaveStageF32;      // pixel rows, then the three planes of the channel rows
-  static constexpr int LOADS = ROWS_A / 1024 + 3 * PLANE / 1024;
-  static constexpr int MAX_STAGES = 3, SLOTS = EDGE / 4;
-  static_assert(STAGE == ROWS_A + 3 * PLANE && EDGE * EDGE * 4 <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
+template <int NB>
+struct WaveTile<float, NB> {
+  static constexpr int EDGE = 32 * NB, ROWS_A = EDGE * ROWB, PLANE = 32 * 64, BLOCK = 3 * PLANE;
+  static constexpr int STAGE = NB * (int)kWaveStageF32; // pixel rows, then the three planes of the rows of each 32 channels
+  static constexpr int LOADS = (ROWS_A + NB * BLOCK) / 1024;
+  static constexpr int MAX_STAGES = NB == 1 ? 3 : 2, SLOTS = EDGE / 4;
+  static_assert(STAGE == ROWS_A + NB * BLOCK && EDGE * EDGE * 4 <= STAGE && LOADS * (MAX_STAGES - 1) < 64, "the partial tile takes the place of a stage; waits can count the requests");
 
   template <typename Request>
   __device__ __forceinline__ static void begin(int n, int stages, unsigned char* s_w, Request request) {
@@ -155,49 +155,78 @@ struct WaveTile<float, 1> {
   template <typename Request>
   __device__ __forceinline__ static void finish(int n, int stages, unsigned char* s_w, Request request) {
     const int lane = threadIdx.x & 63, l31 = lane & 31, lhalf = lane >> 5;
-    // the lane's eight values of pixels in either half of a step, 16 bytes at a time, and of weights: chunks 4 g + 2 lhalf + 0 and 1, and 2 g + lhalf
+    // the lane's eight values of a pixel in either half of a step, 16 bytes at a time, and of weights: chunks 4 g + 2 lhalf + 0 and 1, and 2 g + lhalf
     // (their slots differ in one bit of the address, stages being multiples of 1 KB; worked out by step, for want of registers)
     const uint32_t aslot = (uint32_t)(uintptr_t)(lds_ptr_t)s_w + l31 * ROWB + ((2 * lhalf) ^ wave_swizzle(l31)) * 16;
     const uint32_t wslot = (uint32_t)(uintptr_t)(lds_ptr_t)s_w + ROWS_A + l31 * 64 + (lhalf ^ ((l31 >> 2) & 3)) * 16;
     typedef const __attribute__((address_space(3))) u32x4_t* lds_vec_t;
-    f32x16_t acc, small;
+    f32x16_t acc[NB][NB], small[NB][NB];                               // [pixel block][channel block]
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = small[e] = 0.f;
+    for (int r = 0; r < NB; ++r)
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[r][c][e] = small[r][c][e] = 0.f;
     unsigned char* s = s_w;
     int st = 0;
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
       const int behind = n - 1 - i < stages - 1 ? n - 1 - i : stages - 1;   // (uniform) steps requested behind this one
-      if (behind == 2) wait_requests<2 * LOADS>();
+      if (MAX_STAGES > 2 && behind == 2) wait_requests<(MAX_STAGES > 2 ? 2 : 0) * LOADS>();
       else if (behind == 1) wait_requests<LOADS>();
       else wait_requests<0>();
-      u32x4_t a[4], w[2][3];
+      u32x4_t a[2][NB][2], w[2][NB][3];
+      auto read = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) a[q] = *(lds_vec_t)(uintptr_t)((aslot + (uint32_t)(s - s_w)) ^ (uint32_t)((q >> 1) * 64 + (q & 1) * 16));
+        for (int r = 0; r < NB; ++r) {
 #pragma unroll
-      for (int g = 0; g < 2; ++g)
+          for (int q = 0; q < 2; ++q) a[g][r][q] = *(lds_vec_t)(uintptr_t)(((aslot + (uint32_t)(s - s_w)) ^ (uint32_t)(g * 64 + q * 16)) + r * 32 * ROWB);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) w[g][q] = *(lds_vec_t)(uintptr_t)(((wslot + (uint32_t)(s - s_w)) ^ (uint32_t)(g * 32)) + q * PLANE);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // the stage has been read: it may be written again
+          for (int q = 0; q < 3; ++q) w[g][r][q] = *(lds_vec_t)(uintptr_t)(((wslot + (uint32_t)(s - s_w)) ^ (uint32_t)(g * 32)) + r * BLOCK + q * PLANE);
+        }
+      };
+      read(0);
+      if constexpr (NB == 1) read(1);
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        if (g == 1 && i + stages < n) request(i + stages, s);          // (here, where fewer registers hold what was read)
-        const Split8 x = split8(a[2 * g], a[2 * g + 1]);
-        const bf16x8_t hi = __builtin_bit_cast(bf16x8_t, w[g][0]), mid = __builtin_bit_cast(bf16x8_t, w[g][1]), lo = __builtin_bit_cast(bf16x8_t, w[g][2]);
-        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, x.hi, small, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.hi, acc, 0, 0, 0);
-        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x.hi, small, 0, 0, 0);
-        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x.mid, small, 0, 0, 0);
-        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.mid, small, 0, 0, 0);
-        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x.lo, small, 0, 0, 0);
+        if (g == 0 && NB == 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (g == 1) {
+          if constexpr (NB > 1) {
+            read(1);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          }
+          // the stage has been read: it may be written again (asked for here, where fewer registers hold what was read)
+          if (i + stages < n) request(i + stages, s);
+        }
+        Split8 x[NB];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) x[r] = split8(a[g][r][0], a[g][r][1]);
+#pragma unroll
+        for (int r = 0; r < NB; ++r)
+#pragma unroll
+          for (int c = 0; c < NB; ++c) {
+            const bf16x8_t hi = __builtin_bit_cast(bf16x8_t, w[g][c][0]), mid = __builtin_bit_cast(bf16x8_t, w[g][c][1]), lo = __builtin_bit_cast(bf16x8_t, w[g][c][2]);
+            small[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, x[r].hi, small[r][c], 0, 0, 0);
+            acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x[r].hi, acc[r][c], 0, 0, 0);
+            small[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x[r].hi, small[r][c], 0, 0, 0);
+            small[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, x[r].mid, small[r][c], 0, 0, 0);
+            small[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x[r].mid, small[r][c], 0, 0, 0);
+            small[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, x[r].lo, small[r][c], 0, 0, 0);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
       if (++st == stages) { st = 0; s = s_w; } else { s += STAGE; }
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *(f32x4_t*)(s_w + l31 * EDGE * 4 + (((g * 2 + lhalf) ^ l31) & (SLOTS - 1)) * 16) =
-          f32x4_t{acc[4 * g] + small[4 * g], acc[4 * g + 1] + small[4 * g + 1], acc[4 * g + 2] + small[4 * g + 2], acc[4 * g + 3] + small[4 * g + 3]};
+    for (int r = 0; r < NB; ++r)
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x16_t &v = acc[r][c], &m = small[r][c];
+          *(f32x4_t*)(s_w + (r * 32 + l31) * EDGE * 4 + (((c * 8 + g * 2 + lhalf) ^ l31) & (SLOTS - 1)) * 16) =
+              f32x4_t{v[4 * g] + m[4 * g], v[4 * g + 1] + m[4 * g + 1], v[4 * g + 2] + m[4 * g + 2], v[4 * g + 3] + m[4 * g + 3]};
+        }
   }
   __device__ __forceinline__ static f32x4_t sum(const unsigned char* s, int wave_bytes, int row, int c4) {
     f32x4_t v[4];
@@ -205,12 +234,12 @@ struct WaveTile<float, 1> {
     for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + row * EDGE * 4 + ((c4 ^ row) & (SLOTS - 1)) * 16);
     return ((v[0] + v[1]) + v[2]) + v[3];
   }
-  // element i of a step of channel row `row`, out of the packed image of that step
-  __device__ static float weight(const unsigned char* step, int row, int i) {
-    const uint16_t* p = (const uint16_t*)(step + row * 64 + (((i >> 3) ^ ((row >> 2) & 3)) * 16)) + (i & 7);
-    return (bf2f(p[0]) + bf2f(p[PLANE / 2])) + bf2f(p[PLANE]);
-  }
 };
+// element i of a step of row `row` of 32 channels, out of the packed image of that step
+__device__ __forceinline__ float wave_weight_f32(const unsigned char* step, int row, int i) {
+  const uint16_t* p = (const uint16_t*)(step + row * 64 + (((i >> 3) ^ ((row >> 2) & 3)) * 16)) + (i & 7);
+  return (bf2f(p[0]) + bf2f(p[1024])) + bf2f(p[2048]);
+}
 __device__ __forceinline__ bool all_finite(const f32x4_t& v) {
   uint32_t e = 0;
 #pragma unroll

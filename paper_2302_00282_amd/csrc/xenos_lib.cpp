@@ -976,12 +976,28 @@ struct Planner {
   // Workgroups of a wave kernel: one per tile.  (A machine of a few units walks them: no more wait than thirty-two per unit, which is what the
   // rules above leave 256 units at most)
   int wave_grid(int tiles) const { return p.opts.split ? std::min(tiles, 32 * std::max(1, p.hw.num_cu)) : 1; }
+  // fp32 at link level 3: every dense chain, since its products are the bf16 MFMAs'.  32 x 32 tiles, or 64 x 64 ones where they are many and long enough for
+  // the operands' reuse to tell, and their channels mostly filled (256 graphs of 1x1 and 3x3 layers, 300 to 32000 tiles: by this line 0.6 % slower than by the
+  // faster of the two, 0.917 times the time of the rules below; 1024 channels 27x27 batch 7, 1x1, 97 us -> 72, 256 -> 128 36x36 batch 24, 3x3, 164 -> 110).
+  // Link level 2 keeps what the planner's tests fix of its plans.
+  static int wave_edge_f32(const ConvArgs& c) {
+    const int nsteps = c.Kred_pad / (kRowBytes / 4);
+    const double tiles = std::ceil(c.M_total / 32.0) * std::ceil(c.K / 32.0);
+    if (4 * c.K <= 3 * ((c.K + 63) / 64 * 64)) return kWaveRows;
+    return (nsteps >= 24 && tiles >= 1600) || (nsteps >= 8 && tiles >= 2400) || (nsteps >= 2 && tiles >= 6000) ? 64 : kWaveRows;
+  }
   // Chains of few pixels take the kernel whose wavefronts share out the reduction (conv_wave_kernel).  The rule knows the sizes of the
   // chain only: where its reduction is not split over workgroups too (wave_shares), the order of its sums does not depend on how many units there are.
   int wave_edge(const Step& st) const {
     const ConvArgs& c = st.conv;
-    if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res) || !conv_wave_takes(c, p.esz))
-      return 0;
+    if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res)) return 0;
+    if (p.dt == DT_F32 && p.opts.link >= 3) {
+      const int edge = wave_edge_f32(c);
+      // (fully connected layers as below)
+      if (c.R * c.S > 1 && c.OH * c.OW == 1 && c.M_total < 8192 && !wave_pays_f32(c, c.Kred_pad / (kRowBytes / p.esz), (c.M_total + 31) / 32 * ((c.K + 31) / 32), false)) return 0;
+      return conv_wave_takes(c, p.esz, edge) && conv_wave_lds(edge, edge == 64 ? 2 : 3, p.esz) <= p.hw.lds_bytes_per_cu ? edge : 0;
+    }
+    if (!conv_wave_takes(c, p.esz)) return 0;
     const long long tiles = (long long)((c.M_total + kWaveRows - 1) / kWaveRows) * ((c.K + kWaveChannels - 1) / kWaveChannels);
     // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 0.65 to 1; where units get more the larger
     // tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36.  In fp32, whose MFMAs cover the
@@ -1077,8 +1093,8 @@ struct Planner {
     const int kred_pad = st.conv.Kred_pad;
     const bool kchunk = st.conv.kchunk;
     const int kout_pad = (K + 127) / 128 * 128;
-    const bool wave_f32 = p.dt == DT_F32 && (st.cfg == kWaveCfg || st.conv.pwdw == 2);
-    const size_t bytes = wave_f32 ? (size_t)((K + 31) / 32) * (kred_pad / bke) * (6 * 1024) : (size_t)kout_pad * kred_pad * p.esz;
+    const bool wave_f32 = p.dt == DT_F32 && (st.cfg == kWaveCfg || st.cfg == kWave64Cfg || st.conv.pwdw == 2);
+    const size_t bytes = wave_f32 ? (size_t)((K + 63) / 64 * 2) * (kred_pad / bke) * (6 * 1024) : (size_t)kout_pad * kred_pad * p.esz;
     st.w_off = (long long)wpush(nullptr, bytes);
     unsigned char* base = p.wimage.data() + st.w_off;               // (zeros)
     // source [K][C][R][S] -> destination [K][reduction index]; channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
@@ -1960,6 +1976,19 @@ struct Planner {
           stem_lds = false;
         }
       }
+      // fp32 at link level 3: a window pooling behind a convolution that the wave kernel can take is a pass of its own.  Linked,
+      // the general kernel computes it on the fp32 MFMAs, the pixels where windows overlap more than once, or in the few tiles of a small map (16 -> 64 channels
+      // 55x55 batch 32, 3x3 with a 3x3 / 2 pooling, 52.9 us -> 25.2 and 7.4; 256 channels 10x10 batch 4 with a 2x2 one, 49.0 -> 9.1, 6.2 with the sums of its
+      // shares, and 6.5).  VGG at half its width, 160x160 batch 4, 368 -> 258 us, SqueezeNet 224x224 batch 32 478 -> 411 with the line above
+      if (p.dt == DT_F32 && link >= 3 && p.opts.split && p.opts.tile == 0 && !dw && !is_fc && !stem && !dwpro.active && pool_node >= 0 &&
+          desc(nodes[pool_node]).kind != XENOS_OP_GLOBAL_AVGPOOL && is.c % p.ce == 0 && K % p.ce == 0 && tview[nd.in[0]] >= 0) {
+        const View& iv0 = p.views[tview[nd.in[0]]];
+        const int l2 = absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
+        if (iv0.internal_nhwc() && !iv0.f32 && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && l2 + 1 != out_tid && !placed.count(l2 + 1)) {
+          absorbed.pop_back();
+          pool_node = -1; last = l2; cur = l2 + 1;
+        }
+      }
       for (int a : absorbed) st.ops.push_back(nodes[a].src);
 
       // link level 3, ConvX -> ConvY: a 3x3 first layer whose only consumer is a 3x3 convolution of the same 64 channels
@@ -2177,8 +2206,10 @@ struct Planner {
         // (a linked depthwise producer needs the depthwise-panel kernel for this, which takes whole channel groups)
         const bool dw_panel_fits = from_dw && a.C % p.ce == 0 && K % p.ce == 0 && !has_res &&
                                    dwpw_lds_bytes(kRowBytes / p.esz, p.esz) <= std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
-        if (a.mode == M_GAP && p.opts.split && (!from_dw || dw_panel_fits) && 2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) &&
-            p.opts.tile == 0) {
+        // (fp32 at link level 3: with any number of images, the convolution's sums being the wave kernel's: 512 -> 1000 channels 13x13 batch 32
+        // 65 us -> 41 and 9)
+        if (a.mode == M_GAP && p.opts.split && (!from_dw || dw_panel_fits) && p.opts.tile == 0 &&
+            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave))) {
           st.gap_finish = 1;
           a.mode = M_FLAT; a.pool = POOL_NONE;
         }

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
       ayx[j] = __builtin_amdgcn_ds_bpermute((j * 8 + lrow) * 4, yx);
     }
     const unsigned woff[2] = {ESZ == 4 ? lane * 16u : lrow * a.wpitch + ch[0] * 16u, lrow * a.wpitch + ch[1] * 16u};
-    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * (ESZ == 4 ? 1 : EDGE) * a.wpitch, kWindow);
+    const rsrc_t wb = make_window((const unsigned char*)a.w + (size_t)tn * (ESZ == 4 ? NB : EDGE) * a.wpitch, kWindow);
     auto request = [&](int i, unsigned char* dst) __attribute__((always_inline)) {
       const uint32_t s = (uint32_t)(s_begin + wave + 4 * i);
       // row and column of the kernel, offset and validity of the two chunks that the lane loads of a row
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
       }
       if constexpr (ESZ == 4) {
 #pragma unroll
-        for (int j = 0; j < 6; ++j) load_to_lds(wb, dst + (4 + j) * 1024, woff[0], (s * 6 + j) * 1024u);
+        for (int j = 0; j < 6 * NB; ++j) load_to_lds(wb, dst + (4 * NB + j) * 1024, woff[0], (j / 6) * a.wpitch + (s * 6 + j % 6) * 1024u);
       } else {
 #pragma unroll
         for (int j = 0; j < 4 * NB; ++j) load_to_lds(wb, dst + (4 * NB + j) * 1024, woff[j & 1], j * 8 * a.wpitch + s * ROWB);
@@ -117,15 +117,16 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
       sc = *(const f32x4_t*)(a.scale + k);
       sh = *(const f32x4_t*)(a.shift + k);
     }
+    constexpr bool EARLY = NB == 1 || ESZ == 2;                    // (64 x 64 tiles in fp32 have no registers for the shortcut)
     u32x4_t res[U];                                                // (as they lie in memory: converted behind the reduction)
 #pragma unroll
     for (int u = 0; u < U; ++u) res[u] = u32x4_t{0u, 0u, 0u, 0u};
-    if (a.res) {                                                   // (uniform)
+    auto load_res = [&]() __attribute__((always_inline)) {
       const rsrc_t wr = make_window(a.res, kWindow);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int m = m0 + u * RS, img = small_quotient(m, a.r_ohw), p = m - img * a.OHW;
-        unsigned o = (m < a.M) & (k < a.K) ? (unsigned)img * a.res_sN + (unsigned)p * a.res_sP + k * ESZ : kNoLoad;
+        unsigned o = ((m < a.M) & (k < a.K)) ? (unsigned)img * a.res_sN + (unsigned)p * a.res_sP + k * ESZ : kNoLoad;
         asm volatile("" : "+v"(o));
         if constexpr (ESZ == 2) {
           const uint2 r = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(wr, (int)o, 0, 0));
@@ -134,8 +135,10 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
           res[u] = load_window(wr, o);
         }
       }
-    }
+    };
+    if (EARLY && a.res) load_res();                                // (uniform)
     tile::finish(n, a.stages, s_w, request);
+    if (!EARLY && a.res) load_res();
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -156,9 +159,9 @@ __global__ __launch_bounds__(NT, NB == 1 ? 4 : 2) void conv_wave_kernel(const Wa
             const int r = small_quotient(tap, a.r_S), y = oh * a.stride - a.pad + r, x = ow * a.stride - a.pad + tap - r * (int)a.S;
             if (c >= a.C || tap >= (int)a.rs || (unsigned)y >= (unsigned)a.H || (unsigned)x >= (unsigned)a.W) continue;
             const float f = *(const float*)(px + ((unsigned)y * a.sH + (unsigned)x * a.sW + (unsigned)c * 4u));
-            const unsigned char* const wst = (const unsigned char*)a.w + (size_t)tn * a.wpitch + (size_t)s * (6 * 1024);
+            const unsigned char* const wst = (const unsigned char*)a.w + (size_t)(NB == 1 ? tn : (unsigned)k / 32) * a.wpitch + (size_t)s * (6 * 1024);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, WaveTile<float, 1>::weight(wst, c4 * 4 + e, i % BKE), v[e]);
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, wave_weight_f32(wst, (k & 31) + e, i % BKE), v[e]);
           }
         }
       }
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        unsigned o = (aoff[j] != kNoLoad) & (ch[j & 1] * CE < left) ? aoff[j] + ch[j & 1] * 16u + st * ROWB : kNoLoad;
+        unsigned o = ((aoff[j] != kNoLoad) & (ch[j & 1] * CE < left)) ? aoff[j] + ch[j & 1] * 16u + st * ROWB : kNoLoad;
         asm volatile("" : "+v"(o));
         if constexpr (DIRECT) load_to_lds(wa, dst + j * 1024, o, 0);
         else *(u32x4_t*)(dst + j * 1024 + lane * 16) = load_window(wa, o);
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
             const float f = *(const float*)(px + (unsigned)i * 4u);
             const unsigned char* const wst = (const unsigned char*)a.w + (size_t)nh * a.wpitch + (size_t)(i / BKE) * (6 * 1024);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, WaveTile<float, 1>::weight(wst, c4 + e, i % BKE), v[e]);
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(f, wave_weight_f32(wst, c4 + e, i % BKE), v[e]);
           }
         }
       }
@@ -333,7 +336,7 @@ __global__ __launch_bounds__(NT, 2) void pwdw_wave_kernel(const WavePwDwArgs a) 
   }
 }
 
-size_t conv_wave_lds(int edge, int stages, int esz) { return (size_t)4 * stages * (esz == 4 ? kWaveStageF32 : 2 * edge * ROWB); }
+size_t conv_wave_lds(int edge, int stages, int esz) { return (size_t)4 * stages * (esz == 4 ? edge / 32 * kWaveStageF32 : 2 * edge * ROWB); }
 
 // Steps of a wavefront that are on their way at a time: up to four where a unit has one workgroup, two where it has two, one where it has
 // more, which then hide each other's latency (3x3 layers in bf16, four in a row: 128 channels 28x28 batch 4, 392 tiles, four 36.8 us, two
@@ -360,7 +363,7 @@ static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
   const bool partial = a.ksplit >= 1;
   const int ks = partial ? a.ksplit : 1;
   // what the kernel assumes, checked again on the host
-  if (!conv_wave_takes(a, ESZ) || a.dw_w || a.pair || a.ileave || a.pool != POOL_NONE || a.tiles_m != (a.M_total + EDGE - 1) / EDGE || a.tiles_n != (a.K + EDGE - 1) / EDGE ||
+  if (!conv_wave_takes(a, ESZ, EDGE) || a.dw_w || a.pair || a.ileave || a.pool != POOL_NONE || a.tiles_m != (a.M_total + EDGE - 1) / EDGE || a.tiles_n != (a.K + EDGE - 1) / EDGE ||
       (!partial && (a.out_sK != 1 || (a.has_res && (!a.vec_res || !a.res)))) ||
       (partial && (!a.part || a.part_ld < a.tiles_n * EDGE || a.steps_per_split < 1)) || a.grid < 1)
     return (int)hipErrorInvalidValue;
@@ -433,7 +436,7 @@ int launch_pwdw_wave(const ConvArgs& a, int dtype, void* stream) {
 
 int launch_conv_wave(const ConvArgs& a, int dtype, int edge, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  if (edge == 64) return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t, 2>(a, st) : (int)hipErrorInvalidValue;
+  if (edge == 64) return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t, 2>(a, st) : launch_conv_wave_t<float, 2>(a, st);
   return dtype == DT_BF16 ? launch_conv_wave_t<bf16_t, 1>(a, st) : launch_conv_wave_t<float, 1>(a, st);
 }
 

@@ -578,6 +578,41 @@ def test_reduction_shared_out_over_wavefronts_in_larger_tiles(n, c, h, w, k, ksz
         assert np.array_equal(y, y1) and np.array_equal(y, few)
 
 
+@pytest.mark.parametrize("kind,n,c,h,w,k,ksz,stride", [
+    ("res", 24, 96, 31, 33, 104, 3, 1),      # 27 steps, a ragged channel tile, tiles over the borders of images
+    ("plain", 8, 40, 63, 61, 256, 1, 1),     # a ragged second step; more tiles than two per unit
+    ("plain", 24, 104, 32, 30, 128, 3, 1),   # taps inside a step
+    ("plain", 14, 128, 61, 63, 120, 3, 2),
+    ("gap", 20, 264, 33, 35, 120, 1, 1),     # raw sums, the average in the summing pass
+    ("pool", 8, 64, 64, 62, 128, 3, 1),      # the pooling a pass of its own
+    ("inf", 8, 64, 64, 62, 256, 1, 1)])
+def test_fp32_products_in_three_parts_in_larger_tiles(kind, n, c, h, w, k, ksz, stride):
+    b = wg.builder("parts64", (n, c, h, w), 109, nonzero_bias=True)
+    x = 0 if kind == "inf" else b.cbr(0, c, 1, name="pre")
+    t = b.cbr(x, k, ksz, stride, ksz // 2, name="a", bn=(kind != "inf"), relu=(kind in ("plain", "gap", "pool")))
+    if kind == "res":
+        t = b.relu(b.add(t, b.cbr(x, k, 1, name="side")))
+    elif kind in ("gap", "pool"):
+        t = b.gap(t) if kind == "gap" else b.maxpool(t, 3, 2, 1)
+    g = b.finish(t)
+    fmt = dict(link=3, in_layout=1, out_layout=1)
+    if kind == "inf":
+        g.ops[0].params["weight"][:] = np.abs(g.ops[0].params["weight"]) + np.float32(1e-3)
+        g.x = np.abs(g.x)
+        g.x[3, 40, 7, 9], g.x[7, 63, 63, 61], g.x[0, 0, 0, 0] = np.inf, np.inf, 3e38
+        g.ops[0].params["weight"][:, 0] = 1e-5
+    ref = xo.forward(g)
+    y, info = run_gpu(g, compute=0, **fmt)
+    tested = [ch for ch in info["chains"] if ch["kind"] == "conv" and (ch["C"], ch["K"], ch["R"]) == (c, k, ksz)]
+    assert tested and all((ch["bm"], ch["bn"], bool(ch["wave"])) == (64, 64, True) for ch in tested[:1]), tested
+    fin = np.isfinite(ref)
+    assert fin.all() == (kind != "inf") and np.array_equal(y[~fin], ref[~fin].astype(np.float32))
+    big = fin & (np.abs(ref) > 1e20)
+    assert big.any() == (kind == "inf") and rel_err(y[fin & ~big], ref[fin & ~big]) <= 1e-5 and (not big.any() or rel_err(y[big], ref[big]) <= 1e-5)
+    if kind != "inf":
+        check_chains(g, 0, **fmt)
+
+
 @pytest.mark.parametrize("kind,c,ksz,stride", [("conv", 40, 1, 1), ("conv", 64, 3, 2), ("conv", 24, 3, 1), ("split", 640, 3, 1), ("pwdw", 72, 1, 1)])
 def test_fp32_products_in_three_parts_keep_infinite_and_largest_values(kind, c, ksz, stride):
     # fp32 wave kernels multiply bf16 parts of their operands, which an infinite value and one that rounds to infinity in bf16 do not have
