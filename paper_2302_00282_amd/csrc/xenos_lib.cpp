@@ -179,6 +179,7 @@ void write_plan_json(xenos_plan& p);
 // are.  Up to 512 bytes of depthwise channels a pixel one launch takes 0.77 to 1.00 times the time of the two (105 graphs of three units, 4 to
 // 960 output pixels: bf16 176 channels 14x14 63.7 -> 52.5 us, 256 channels 4x4 68 -> 55, fp32 88 channels 16x16 69 -> 61, 128 channels 5x5 69 -> 58), above that
 // 1.05 to 1.73 times (bf16 320 channels 1.09, fp32 176 to 256).  Below 1024 pixels that is the line; from there on unit_pays is asked alone.
+// (Measured with as many output channels as the depthwise convolution has, or fewer; 128 -> 256 channels 5x5 batch 30 13 us against 11.5.)
 // ShuffleNet graph, bf16: 160x160 batch 2 264 -> 197 us, batch 4 254 -> 201, batch 8 264 -> 208; fp32 batch 2 308 -> 286.  A single image keeps the two
 // chains, which the planner's tests fix of its plans (it would gain as well: bf16 224x224 266 -> 198).
 constexpr long long kUnitMinPixels = 1024;
@@ -1499,7 +1500,8 @@ struct Planner {
   // do few pixels (kUnitMinPixels).  Whether the link pays is asked afterwards (unit_pays).  Returns the node or -1.
   int unit_consumer(int i, int dn) const {
     const Shape os = tshape[dn + 1];
-    if ((long long)os.n * os.h * os.w < kUnitMinPixels && (os.n == 1 || os.c * p.esz > kUnitNarrowBytes)) return -1;
+    const bool few = (long long)os.n * os.h * os.w < kUnitMinPixels;
+    if (few && (os.n == 1 || os.c * p.esz > kUnitNarrowBytes)) return -1;
     const int src = nodes[i].in[0] - 1;
     if (src >= 0 && nodes[src].kind == XENOS_OP_SHUFFLE && fold_shuffle[src]) return -1;
     const ChainWalk w2 = walk_chain(dn);
@@ -1507,7 +1509,7 @@ struct Planner {
     const int pw = single_consumer(w2.cur);
     if (pw < 0 || nodes[pw].kind != XENOS_OP_CONV || node_step[pw] >= 0) return -1;
     const xenos_op_desc& pd = desc(nodes[pw]);
-    if (pd.groups != 1 || pd.kh != 1 || pd.kw != 1 || pd.stride_h != 1 || pd.pad_h != 0 || pd.out_c % p.ce != 0) return -1;
+    if (pd.groups != 1 || pd.kh != 1 || pd.kw != 1 || pd.stride_h != 1 || pd.pad_h != 0 || pd.out_c % p.ce != 0 || (few && pd.out_c > os.c)) return -1;
     const int next_dw = pwdw_consumer(pw);
     if (next_dw >= 0 && pwdw_wanted(pw, next_dw)) return -1;
     const ChainWalk w3 = walk_chain(pw);
