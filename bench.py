@@ -192,7 +192,7 @@ def chain_label(c):
         return "conv3x3_frag_kernel"
     if c.get("wave"):
         return "pwdw_wave_kernel" if c["loader"] == "pwdw" else "conv_wave_kernel"
-    return {"stem": "stem kernel", "pair": "conv_pair_kernel", "stream": "fc_stream_kernel", "pwdw": "pwdw_kernel", "unit": "unit_kernel", "fire": "fire_kernel",
+    return {"stem": "stem kernel", "first": "conv3x3_first_kernel", "pair": "conv_pair_kernel", "stream": "fc_stream_kernel", "pwdw": "pwdw_kernel", "unit": "unit_kernel", "fire": "fire_kernel",
             "vector": "dwpw_kernel" if c.get("dw_linked") else "conv_kernel", "scalar": "conv_kernel"}.get(c.get("loader"), "conv_kernel")
 
 

@@ -92,8 +92,11 @@ static const int kUnitCfg = 11;
 static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;
 constexpr int kWaveStageF32 = 32 * 128 + 3 * 32 * 64;   // fp32: LDS of a step, 32 pixel rows and the three bf16 parts of 32 channel rows
-static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64 (bf16)
-// Configuration index of the 3x3 kernel whose weights go from the cache into registers (bf16): kFrag3Pixels blocks of 16 pixels per wavefront
+static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64
+// Configuration index of the kernel that computes a first layer's 2x2 pooling windows on the vector unit, a window x kFirstChannels channels per thread
+static const int kFirstCfg = 15;
+constexpr int kFirstChannels = 8;
+// Configuration index of the 3x3 kernel whose weights go from the cache into registers (bf16)
 static const int kFrag3Cfg = 14;
 constexpr int kFrag3Pitch = 80;        // LDS bytes of a patch position: 32 channels and an odd number of 16-byte slots
 // positions of the patch in LDS, for blocks per wavefront x pixel groups; row pitch of the patch
@@ -296,6 +299,7 @@ inline bool frag3_takes(const ConvArgs& a) {
          ((double)a.N * a.res_sN + a.K) * 2 < lim && (double)((a.K + 127) / 128) * 128 * a.C * 18 < lim;
 }
 int launch_frag3(const ConvArgs& a, int dtype, void* stream);
+int launch_first(const ConvArgs& a, int dtype, void* stream);
 // Pixels of the map that the windows of a tile of th x tw depthwise outputs cover, at most
 inline int wave_block_positions(const ConvArgs& a, int th, int tw) {
   auto most = [&](int out, int t, int in) {

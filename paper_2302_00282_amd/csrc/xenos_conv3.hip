@@ -1,7 +1,9 @@
-// gfx950 (CDNA4) kernel of dense 3x3 / stride 1 / pad 1 convolution chains in bf16 whose weights go from the cache straight into registers:
+// gfx950 (CDNA4) kernels of dense 3x3 / stride 1 / pad 1 convolution chains whose weights do not pass through LDS:
 //
-//  conv3x3_frag_kernel   a workgroup of four wavefronts owns a TH x TW block of output pixels of one image; the input patch of a chunk of 32
-//                        channels lies in LDS, every wavefront multiplies all (or half) of its pixels by 32 output channels of its own.
+//  conv3x3_frag_kernel   bf16, weights from the cache straight into the registers that the MFMAs read: a workgroup of four wavefronts owns a TH x TW block
+//                        of output pixels of one image; the input patch of a chunk of 32 channels lies in LDS, every wavefront multiplies all
+//                        (or half) of its pixels by 32 output channels of its own.
+//  conv3x3_first_kernel  a first layer of at most four channels with its 2x2 pooling on the vector unit, the weights in scalar registers.
 #include "device_common.h"
 
 namespace xenos {
@@ -327,6 +329,137 @@ int launch_frag3(const ConvArgs& a, int dtype, void* stream) {
   XENOS_FRAG3(4, 1, 2);
 #undef XENOS_FRAG3
   return (int)hipErrorInvalidValue;
+}
+
+struct FirstArgs {
+  const void* in; const void* w; const float* scale; const float* shift; void* out;
+  long long out_sN, out_sP, out_sK;                                // elements
+  uint32_t sN, sC, sH, sW, bytes;                                  // bytes; `bytes`: from a channel's first element to behind its last
+  int32_t wins, PHW, PW, H, W, blocks, items, groups, wpitch; float r_phw, r_pw;   // pooling windows, blocks of 256 of them, groups of channels, bytes of a channel's weights
+  int32_t flags;
+};
+enum { FF_RELU = 1, FF_MAX = 2, FF_OUT_F32 = 4, FF_VEC = 8 };
+
+// A first layer of few channels in and out (3 -> 16) is neither a matrix product nor bytes: 27 products of a pixel fill a step of 32 or 64 only with an
+// import pass in front or a gather of single elements, and 16 channels half a tile.  Here a thread owns a 2x2 pooling window x eight
+// channels: the 4 x 4 input pixels of it are in registers, read in the caller's layout; the weights are the wavefront's, in scalar registers, so that a
+// product is one instruction; the window is pooled in the thread.  What bounds it is the vector unit's fp32 rate, which without packed instructions is 79 TFLOP/s:
+// 25x206x206, 3 -> 16 channels, 0.92 GFLOP, 155 us on conv_kernel behind an import pass -> 21.5 (12 at that rate), 32x256x256 296 -> 35.4.  The products of bf16 numbers are
+// exact in fp32, sums are fp32 as the MFMAs' are.
+template <typename T, typename TIN, int C>
+__global__ __launch_bounds__(NT) void conv3x3_first_kernel(const FirstArgs a) {
+  FETCH_ARGS(FirstArgs);
+  typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+  typedef const __attribute__((address_space(4))) float* scalar_f32;
+  // the groups of a block behind one another on one XCD, whose L2 then has the input
+  for (int item = (int)blockIdx.x; item < a.items; item += (int)gridDim.x) {
+    const int q = item >> 3, qb = uniform_div(q, a.groups), block = qb * 8 + (item & 7), k0 = (q - qb * a.groups) * kFirstChannels;
+    if (block >= a.blocks) continue;
+    const int win = block * NT + (int)threadIdx.x, w0 = win < a.wins ? win : 0;
+    const int n = any_quotient(w0, a.PHW, a.r_phw), p = w0 - n * a.PHW, ph = any_quotient(p, a.PW, a.r_pw), pw = p - ph * a.PW;
+    constexpr unsigned OUTSIDE = 1u << 30;                           // (plus any offset inside: beyond the window)
+    unsigned ro[4], co[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int y = 2 * ph - 1 + i, x = 2 * pw - 1 + i;
+      ro[i] = (unsigned)y < (unsigned)a.H ? (unsigned)n * a.sN + (unsigned)y * a.sH : OUTSIDE;
+      co[i] = (unsigned)x < (unsigned)a.W ? (unsigned)x * a.sW : OUTSIDE;
+    }
+    float x[C][4][4];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const rsrc_t win_c = make_window((const unsigned char*)a.in + (size_t)c * a.sC, a.bytes);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          if constexpr (sizeof(TIN) == 4) {
+            x[c][r][s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(win_c, (int)(ro[r] + co[s]), 0, 0));
+            if constexpr (sizeof(T) == 2) x[c][r][s] = (float)(__bf16)x[c][r][s];
+          } else {
+            x[c][r][s] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(win_c, (int)(ro[r] + co[s]), 0, 0) << 16);
+          }
+        }
+    }
+    const float lo = a.flags & FF_RELU ? 0.f : __uint_as_float(0x7fc00000u);
+    const bool pmax = a.flags & FF_MAX;
+    float y[kFirstChannels];
+#pragma unroll
+    for (int k = 0; k < kFirstChannels; ++k) {
+      const scalar_ptr wk = (scalar_ptr)((uintptr_t)a.w + (size_t)(k0 + k) * (unsigned)a.wpitch);
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const int e = t * C + c, r = t / 3, s = t % 3;
+          float w;
+          if constexpr (sizeof(T) == 4) w = __uint_as_float(wk[e]);
+          else w = __uint_as_float(e & 1 ? wk[e / 2] & 0xffff0000u : wk[e / 2] << 16);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[j] = fmaf(x[c][r + j / 2][s + j % 2], w, acc[j]);
+        }
+      const float sc = ((scalar_f32)(uintptr_t)a.scale)[k0 + k], sh = ((scalar_f32)(uintptr_t)a.shift)[k0 + k];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = fmaxf(fmaf(acc[j], sc, sh), lo);
+      y[k] = pmax ? fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3])) : ((acc[0] + acc[1]) + (acc[2] + acc[3])) * 0.25f;
+    }
+    if (win >= a.wins) continue;
+    const long long o = (long long)n * a.out_sN + (long long)p * a.out_sP + (long long)k0 * a.out_sK;
+    if (sizeof(T) == 2 && !(a.flags & FF_OUT_F32)) {
+      bf16_t* out = (bf16_t*)a.out + o;
+      if (a.flags & FF_VEC) {
+        *(u32x4_t*)out = u32x4_t{f2bf2(y[0], y[1]), f2bf2(y[2], y[3]), f2bf2(y[4], y[5]), f2bf2(y[6], y[7])};
+      } else {
+#pragma unroll
+        for (int k = 0; k < kFirstChannels; ++k) ((uint16_t*)out)[k * a.out_sK] = f2bf(y[k]);
+      }
+    } else {
+      float* out = (float*)a.out + o;
+      if (a.flags & FF_VEC) {
+        *(f32x4_t*)out = f32x4_t{y[0], y[1], y[2], y[3]};
+        *(f32x4_t*)(out + 4) = f32x4_t{y[4], y[5], y[6], y[7]};
+      } else {
+#pragma unroll
+        for (int k = 0; k < kFirstChannels; ++k) out[k * a.out_sK] = y[k];
+      }
+    }
+  }
+}
+
+template <typename T, typename TIN>
+static int launch_first_t(const FirstArgs& w, int C, int grid, hipStream_t st) {
+  switch (C) {
+    case 1: hipLaunchKernelGGL((conv3x3_first_kernel<T, TIN, 1>), dim3(grid), dim3(NT), 0, st, w); break;
+    case 2: hipLaunchKernelGGL((conv3x3_first_kernel<T, TIN, 2>), dim3(grid), dim3(NT), 0, st, w); break;
+    case 3: hipLaunchKernelGGL((conv3x3_first_kernel<T, TIN, 3>), dim3(grid), dim3(NT), 0, st, w); break;
+    case 4: hipLaunchKernelGGL((conv3x3_first_kernel<T, TIN, 4>), dim3(grid), dim3(NT), 0, st, w); break;
+    default: return (int)hipErrorInvalidValue;
+  }
+  return (int)hipGetLastError();
+}
+
+int launch_first(const ConvArgs& a, int dtype, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  const int esz = dtype == DT_BF16 ? 2 : 4, isz = a.in_f32 ? 4 : esz, osz = a.out_f32 ? 4 : esz;
+  const long long wins = (long long)a.N * a.PH * a.PW, blocks = (wins + NT - 1) / NT, groups = a.K / kFirstChannels;
+  const long long bytes = ((a.N - 1) * a.in_sN + (a.H - 1) * a.in_sH + (a.W - 1) * a.in_sW + 1) * isz;
+  // what the kernel assumes, checked again on the host
+  if (a.C < 1 || a.C > 4 || a.R != 3 || a.S != 3 || a.stride != 1 || a.pad != 1 || a.K < kFirstChannels || a.K % kFirstChannels != 0 || a.mode != M_ZIGZAG || a.pk != 2 || a.ps != 2 ||
+      a.pp != 0 || a.OH != a.H || a.OW != a.W || 2 * a.PH > a.H || 2 * a.PW > a.W || a.PH < 1 || a.PW < 1 || a.N < 1 || a.has_res || a.ileave || a.dw_w || a.pair || a.kchunk ||
+      a.Kred != 9 * a.C || a.Kred_pad < a.Kred || a.Kred_pad % 8 != 0 || a.in_sN < 0 || a.in_sH < 0 || a.in_sW < 0 || a.pair_sC < 0 || a.pair_sC * isz >= (1ll << 32) || bytes > (1ll << 30) ||
+      wins >= (1ll << 30) || (blocks + 7) / 8 * 8 * groups >= (1ll << 30) || a.grid < 1 || a.grid > (blocks + 7) / 8 * 8 * groups || (a.pool != POOL_MAX && a.pool != POOL_AVG))
+    return (int)hipErrorInvalidValue;
+  FirstArgs w{};
+  w.in = a.in; w.w = a.w; w.scale = a.scale; w.shift = a.shift; w.out = a.out;
+  w.out_sN = a.out_sN; w.out_sP = a.out_sP; w.out_sK = a.out_sK;
+  w.sN = (uint32_t)(a.in_sN * isz); w.sC = (uint32_t)(a.pair_sC * isz); w.sH = (uint32_t)(a.in_sH * isz); w.sW = (uint32_t)(a.in_sW * isz); w.bytes = (uint32_t)bytes;
+  w.wins = (int)wins; w.PHW = a.PH * a.PW; w.PW = a.PW; w.H = a.H; w.W = a.W; w.blocks = (int)blocks; w.items = (int)((blocks + 7) / 8 * 8 * groups); w.groups = (int)groups; w.wpitch = a.Kred_pad * esz;
+  w.r_phw = 1.f / (float)w.PHW; w.r_pw = 1.f / (float)w.PW;
+  const bool vec = a.out_sK == 1 && ((uintptr_t)a.out & 15) == 0 && a.out_sN * osz % 16 == 0 && a.out_sP * osz % 16 == 0;
+  w.flags = (a.relu ? FF_RELU : 0) | (a.pool == POOL_MAX ? FF_MAX : 0) | (osz == 4 ? FF_OUT_F32 : 0) | (vec ? FF_VEC : 0);
+  if (dtype != DT_BF16) return launch_first_t<float, float>(w, a.C, a.grid, st);
+  return a.in_f32 ? launch_first_t<bf16_t, float>(w, a.C, a.grid, st) : launch_first_t<bf16_t, bf16_t>(w, a.C, a.grid, st);
 }
 
 }  // namespace xenos

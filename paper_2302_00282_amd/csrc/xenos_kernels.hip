@@ -2655,6 +2655,7 @@ int launch_conv(const ConvArgs& a, int dtype, int cfg, int scalar_loader, void* 
     if (scalar_loader) return (int)hipErrorInvalidValue;
     return launch_frag3(a, dtype, st);
   }
+  if (cfg == kFirstCfg) return launch_first(a, dtype, stream);
   if (cfg == kStemCfg) return dtype == DT_BF16 ? launch_stem_t<bf16_t>(a, st) : launch_stem_t<float>(a, st);
   return dtype == DT_BF16 ? launch_conv_t<bf16_t>(a, cfg, scalar_loader, st) : launch_conv_t<float>(a, cfg, scalar_loader, st);
 }

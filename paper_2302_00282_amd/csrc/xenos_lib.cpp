@@ -106,6 +106,7 @@ struct Step {
   SplitKArgs splitk{};
   int cfg = 0, scalar = 0, stem = 0;
   int stem_lds = 0;            // first-layer chain on the kernel that stages its input block in LDS
+  int first = 0;               // first-layer chain on the vector unit (conv3x3_first_kernel)
   int fc_stream = 0;           // fully connected chain with few rows: weights streamed by fc_stream_kernel, finished by the summing pass
   int gap_finish = 0;          // global average linked through the summing pass of a reduction split (few images)
   // every partition the split planner found legal for this chain (tile shape x kernel), for profiling-driven choice;
@@ -184,6 +185,7 @@ void write_plan_json(xenos_plan& p);
 // chains, which the planner's tests fix of its plans (it would gain as well: bf16 224x224 266 -> 198).
 constexpr long long kUnitMinPixels = 1024;
 constexpr int kUnitNarrowBytes = 512;
+constexpr long long kFirstWindows = 8192;
 
 struct Planner {
   const xenos_graph& g;
@@ -637,6 +639,18 @@ struct Planner {
     return r;
   }
 
+  // Does a first layer with its 2x2 pooling take conv3x3_first_kernel?  Any order of the input (offsets inside a channel of it are 30 bits) and of the
+  // output.  From 8192 windows on: 3 -> 16 channels, 10600 windows 7.2 us -> 6.2 in fp32, 8.1 -> 6.8 and 6.1 in bf16; 4096 windows 5.8 -> 6.2, 6.6 -> 6.7 and
+  // 6.9 -> 6.4, where the launch is all there is; 265000 (25x206x206) 155 -> 21.5, 113 -> 23.3 and 107 -> 21.7.
+  bool first_takes(const Shape& is, const xenos_op_desc& d, int K, const xenos_op_desc& pd, const Shape& cs, const Shape& ps) const {
+    const View& v = p.views[tview[0]];
+    const long long wins = (long long)ps.n * ps.h * ps.w, bytes = ((is.n - 1) * v.sN + ((long long)is.h * is.w - 1) * v.sP + 1) * v.esz;
+    return p.opts.link >= 2 && p.opts.tile == 0 && is.c <= 4 && K % kFirstChannels == 0 && K <= 64 && (v.f32 || v.esz == p.esz) &&
+           d.kh == 3 && d.kw == 3 && d.stride_h == 1 && d.stride_w == 1 && d.pad_h == 1 && d.pad_w == 1 &&
+           (pd.kind == XENOS_OP_MAXPOOL || pd.kind == XENOS_OP_AVGPOOL) && pd.kh == 2 && pd.kw == 2 && pd.stride_h == 2 && pd.stride_w == 2 && pd.pad_h == 0 &&
+           pd.pad_w == 0 && 2 * ps.h <= cs.h && 2 * ps.w <= cs.w && wins >= kFirstWindows && wins < (1ll << 30) / 8 && v.sN >= 0 && v.sP >= 0 && bytes <= (1ll << 30);
+  }
+
   xenos_status split_conv(Step& st) {
     ConvArgs& c = st.conv;
     const int num_cu = std::max(1, p.hw.num_cu);
@@ -651,6 +665,13 @@ struct Planner {
       c.grid = p.opts.split ? std::max(1, std::min(c.tiles_m, stem_lds_resident(c.R * c.S, c.K, p.esz, c.pool != POOL_NONE) * num_cu)) : 1;
       st.cfg = kStemLdsCfg;
       st.lds = stem_lds_bytes(c.R * c.S, c.K, p.esz);
+      return XENOS_OK;
+    }
+    if (st.first) {   // 256 pooling windows x kFirstChannels channels per workgroup
+      c.tiles_m = (int)(((long long)c.N * c.PH * c.PW + 255) / 256); c.tiles_n = c.K / kFirstChannels; c.ntiles = c.tiles_m * c.tiles_n; c.xcd_m = 8;
+      c.grid = p.opts.split ? (c.tiles_m + 7) / 8 * 8 * c.tiles_n : 1;
+      st.cfg = kFirstCfg;
+      st.lds = 0;
       return XENOS_OK;
     }
     if (st.stem) {   // one wavefront = 32 pixels x all channels; workgroups of 4 wavefronts stride over the pixel blocks
@@ -921,7 +942,9 @@ struct Planner {
     return left ? std::vector<uint16_t>{} : tab;
   }
 
-  // fp32 1x1 layers have a ninth of a 3x3 layer's products for the bytes of a step, and against the larger tiles what counts is how much of their last
+  // fp32 at link level 2 (this rule and the next; at level 3 wave_edge_f32 decides): drawn while conv_wave_kernel multiplied on the fp32 MFMAs as the larger tiles
+  // do, so they leave out some chains that it would now gain on.
+  // 1x1 layers have a ninth of a 3x3 layer's products for the bytes of a step, and against the larger tiles what counts is how much of their last
   // round those leave idle.  Times of conv_wave_kernel over theirs, four layers of as many channels in a row, 200 to 8000 tiles of 32 x 32:
   //   up to 672 tiles 0.52 to 1.02; up to 992 of eight steps or more 0.67 to 0.93 (of two to six 0.87 to 1.19); expansions to twice the channels or
   //   more, in turns with their inverse or as the 1x1 part of a Fire module, up to 1400, 0.70 to 1.08
@@ -1001,9 +1024,9 @@ struct Planner {
     if (!conv_wave_takes(c, p.esz)) return 0;
     const long long tiles = (long long)((c.M_total + kWaveRows - 1) / kWaveRows) * ((c.K + kWaveChannels - 1) / kWaveChannels);
     // (a tile per unit takes 0.4 to 0.75 times the time of the 64 x 64 and 256-row tiles, four in bf16 0.65 to 1; where units get more the larger
-    // tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36.  In fp32, whose MFMAs cover the
-    // loads, up to 32: 48 -> 192 channels 27x27 batch 32, 4374 tiles, 196 us against 231 for four layers, 16 -> 64 channels 55x55, 6050
-    // tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329)
+    // tiles' reuse of operands tells: 64 channels 56x56 batch 8, 3x3 in bf16, 1568 tiles, 44 us against 36.  fp32, here at link level 2 only, up
+    // to 32: the line was drawn when both kernels used the fp32 MFMAs, 48 -> 192 channels 27x27 batch 32, 4374 tiles, 196 us against 231 for four
+    // layers, 16 -> 64 channels 55x55, 6050 tiles, 145 against 221, 64 channels 56x56, 6272, 306 against 329; the wave kernel has become faster since)
     const int nsteps = c.Kred_pad / (kRowBytes / p.esz);
     int most = p.dt == DT_BF16 ? 1024 : 8192;
     if (p.dt == DT_F32 && tiles <= most && !(c.R * c.S == 1 ? wave_pays_1x1_f32(c, nsteps, (int)tiles) : wave_pays_f32(c, nsteps, (int)tiles, halo_input_ok(st)))) return 0;
@@ -1020,7 +1043,7 @@ struct Planner {
     // bf16, more than two 32 x 32 tiles per unit: 64 x 64 ones, at most two per unit, where a share has steps enough (3x3 layers, four in a row:
     // 256 channels 14x14 batch 16 56.8 -> 47.2 us, batch 32 75.3 on the halo kernel -> 61.9, 128 channels 28x28 batch 8 38.7 -> 35.1, 48 -> 192
     // channels 27x27 batch 32 69.0 on the gather tiles -> 62.8; 1x1 512 channels 7x7 batch 32 27.8 -> 31.2, which is why eight steps are too few;
-    // 784 tiles of 64 x 64 take 75.9 us against the halo kernel's 53.3).  In fp32, whose MFMAs cover the smaller tile's loads, they gain nothing
+    // 784 tiles of 64 x 64 take 75.9 us against the halo kernel's 53.3)
     const long long tiles64 = (long long)((c.M_total + 63) / 64) * ((c.K + 63) / 64);
     if (p.dt == DT_BF16 && tiles > 512 && tiles64 <= 512 && nsteps >= (tiles <= 1024 ? 16 : 9) && most > 512 &&
         conv_wave_lds(64, conv_wave_stages(64, nsteps, (int)tiles64, p.esz), p.esz) <= p.hw.lds_bytes_per_cu)
@@ -1497,7 +1520,7 @@ struct Planner {
   // The pointwise convolution behind depthwise node dn (= pwdw_consumer(i)) if all three can run as one chain: a plain 1x1
   // chain of its own (no shortcut, no pooling) that stores 16-byte channel groups, or finishes a two-group shuffle whose other
   // part exists already.  A pointwise convolution that hands on to the next depthwise one stays out (see pwdw_wanted), and so
-  // do few pixels (kUnitMinPixels).  Whether the link pays is asked afterwards (unit_pays).  Returns the node or -1.
+  // do wide units of few pixels (kUnitNarrowBytes).  Whether the link of more pays is asked afterwards (unit_pays).  Returns the node or -1.
   int unit_consumer(int i, int dn) const {
     const Shape os = tshape[dn + 1];
     const bool few = (long long)os.n * os.h * os.w < kUnitMinPixels;
@@ -1971,7 +1994,11 @@ struct Planner {
         // (the gather's offsets inside a window are 32 bits: a larger image is imported)
         const bool gathers = is.c * d.kh * d.kw <= kStemRed && conv_lds_bytes(kStemCfg, M_FLAT) <= p.hw.lds_bytes_per_cu &&
                              (is.c - 1) * gv.sK + ((d.kh - 1ll) * is.w + d.kw - 1) * gv.sP < (1ll << 31);
-        if ((stem_lds || gathers) && (keep_pool || (c2 != out_tid && !placed.count(c2) && !(padded && pool_node >= 0)))) {
+        // (where the pooling would become a pass of its own, conv3x3_first_kernel keeps it: 3 -> 64 channels 8x224x224, fp32 99.7 us -> 29.5, bf16 63.9 -> 30.7, 32
+        // channels 31.3 -> 18.8; against the chain with its pooling on chip it takes 0.81 to 1.05 times the time in fp32, 1.1 to 1.45 in bf16)
+        if (!keep_pool && pool_node >= 0 && first_takes(is, d, K, desc(nodes[pool_node]), tshape[i + 1], tshape[pool_node + 1])) {
+          stem_lds = false;
+        } else if ((stem_lds || gathers) && (keep_pool || (c2 != out_tid && !placed.count(c2) && !(padded && pool_node >= 0)))) {
           stem = true;
           if (pool_node >= 0 && !keep_pool) { absorbed.pop_back(); pool_node = -1; cur = c2; last = l2; }
         } else {
@@ -2108,7 +2135,8 @@ struct Planner {
         pairpro.active = false;
         if (!from_dw && nd.in[0] == 0 && in_lazy) {
           st.stem = stem;
-          if (!st.stem && !in_gather) import_input();
+          st.first = !st.stem && !has_res && pool_node >= 0 && first_takes(is, d, K, desc(nodes[pool_node]), tshape[i + 1], tshape[pool_node + 1]);
+          if (!st.stem && !st.first && !in_gather) import_input();
           st.stem_lds = st.stem && stem_lds;
         }
         const int vin = from_dw ? pro.v_in : from_pair ? tview[0] : tview[nd.in[0]];
@@ -2125,6 +2153,7 @@ struct Planner {
         else { a.R = d.kh; a.S = d.kw; a.stride = d.stride_h; a.pad = d.pad_h; a.OH = tshape[i + 1].h; a.OW = tshape[i + 1].w; }
         st.scalar = !(iv.internal_nhwc() && !iv.f32 && iv.esz == p.esz && a.C % p.ce == 0 && iv.off % p.ce == 0 && iv.sP % p.ce == 0);
         a.in_sN = iv.sN; a.in_sH = iv.sP * is.w; a.in_sW = iv.sP; a.in_f32 = iv.f32;
+        if (st.first) a.pair_sC = iv.sK;
         if (from_dw) {
           st.scalar = 0;
           st.dw_w_off = pro.w_off; st.dw_scale_off = pro.scale_off; st.dw_shift_off = pro.shift_off;
@@ -2746,17 +2775,18 @@ void write_plan_json(xenos_plan& p) {
       const TileCfg stem_tc{32, c.K, 32, c.K};
       const TileCfg pair_tc{kPairRows, kPairChannels, 64, kPairChannels / 2};
       const TileCfg fc_tc{32, kFcChannels, 32, 32};
+      const TileCfg first_tc{256, kFirstChannels, 64, kFirstChannels};
       const TileCfg stem_lds_tc{kStemLdsTh * kStemLdsTw, c.K, 32, c.K};
       const TileCfg pwdw_tc{64, kPwDwChannels, 32, 32};
       const TileCfg wave_tc{kWaveRows, kWaveChannels, 32, 32};
       const TileCfg wave64_tc{64, 64, 64, 64};
       const bool wave = s.cfg == kWaveCfg || s.cfg == kWave64Cfg || c.pwdw == 2;
       const TileCfg frag3_tc{c.frag3 * c.frag3_wp * 16, c.halo_bn, c.frag3 * 16, 32};
-      const TileCfg& tc = s.cfg == kFrag3Cfg ? frag3_tc : s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
+      const TileCfg& tc = s.cfg == kFirstCfg ? first_tc : s.cfg == kFrag3Cfg ? frag3_tc : s.cfg == kWaveCfg ? wave_tc : s.cfg == kWave64Cfg ? wave64_tc : s.cfg == kPwDwCfg || s.cfg == kFireCfg || s.cfg == kUnitCfg ? pwdw_tc : s.cfg == kHaloCfg ? halo_tc : s.cfg == kStemCfg ? stem_tc : s.cfg == kStemLdsCfg ? stem_lds_tc : s.cfg == kPairCfg ? pair_tc : s.cfg == kFcCfg ? fc_tc : kTileCfgs[s.cfg];
       snprintf(buf, sizeof buf, ",\"mode\":\"%s\",\"loader\":\"%s\",\"N\":%d,\"C\":%d,\"H\":%d,\"W\":%d,\"K\":%d,\"R\":%d,\"S\":%d,\"stride\":%d,"
                "\"pad\":%d,\"OH\":%d,\"OW\":%d,\"PH\":%d,\"PW\":%d,\"pool\":%d,\"relu\":%d,\"res\":%d,\"bm\":%d,\"bn\":%d,\"tiles_m\":%d,"
                "\"tiles_n\":%d,\"grid\":%d,\"lds\":%zu,\"pph\":%d,\"ppw\":%d,\"patch_h\":%d,\"patch_w\":%d,\"out_c_off\":%lld,\"out_sP\":%lld,\"halo\":%d,\"th\":%d,\"tw\":%d,\"dw_linked\":%d,\"ksplit\":%d,\"candidates\":%d,\"tuned\":%d,\"plin\":%d,\"shuffle_store\":%d,\"wave\":%d,\"frag3\":%d",
-               kModeNames[c.mode], s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.unit ? "unit" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
+               kModeNames[c.mode], s.first ? "first" : s.stem ? "stem" : c.pair ? "pair" : c.pwdw ? "pwdw" : c.unit ? "unit" : c.fire ? "fire" : s.fc_stream ? "stream" : s.scalar ? "scalar" : "vector", c.N, c.C, c.H, c.W, c.K, c.R, c.S, c.stride, c.pad, c.OH, c.OW,
                c.PH, c.PW, c.pool, c.relu, c.has_res, tc.bm, tc.bn, c.tiles_m, c.tiles_n, c.grid, s.lds, c.pph, c.ppw, c.patch_h,
                c.patch_w, p.views[s.v_out].off, c.out_sP, s.cfg == kHaloCfg ? 1 : 0, c.th, c.tw, s.dw_w_off >= 0 ? 1 : 0, c.ksplit > 1 ? c.ksplit : 1, (int)s.cands.size(), s.tuned, s.cfg == kHaloCfg ? c.halo_plin : 0, c.ileave, wave, s.cfg == kFrag3Cfg ? c.frag3 : 0);
       j += buf;

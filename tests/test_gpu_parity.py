@@ -680,6 +680,31 @@ def test_3x3_weights_from_the_cache_into_registers(kind, n, c, h, w, k, num_cu, 
 
 
 @pytest.mark.parametrize("compute", [0, 1])
+@pytest.mark.parametrize("n,c,h,w,k,pool,relu,fmt", [
+    (1, 3, 211, 193, 16, "max", True, {}),                                             # the caller's order in and out; a last row and column that no window has
+    (70, 3, 22, 22, 8, "avg", False, dict(in_layout=1)),                               # one group; windows of many images in a block
+    (2, 4, 2, 8202, 40, "max", False, dict(out_layout=1)),                             # one row of windows
+    (3, 1, 8204, 2, 24, "avg", True, dict(out_layout=1)),                              # one column of them
+    (7, 3, 66, 98, 64, "max", True, dict(in_dtype=1, in_layout=1, out_dtype=1, out_layout=1)),
+    (5, 3, 97, 98, 48, "max", True, dict(in_dtype=1, out_dtype=1))])
+def test_first_layer_windows_on_the_vector_unit(n, c, h, w, k, pool, relu, fmt, compute):
+    # conv3x3_first_kernel against the oracle, and against the general kernel, which the un-linked plan takes
+    if compute == 0:
+        fmt = {key: v for key, v in fmt.items() if not key.endswith("dtype")}
+    b = wg.builder("first", (n, c, h, w), 131, nonzero_bias=True)
+    t = b.cbr(0, k, 3, 1, 1, name="a", relu=relu)
+    g = b.finish((b.maxpool if pool == "max" else b.avgpool)(t, 2, 2, 0))
+    for link in (2, 3):
+        y, info = check(g, compute=compute, link=link, **fmt)
+        assert [ch.get("loader") for ch in info["chains"]] == ["first"], info["chains"]
+        unsplit, info = run_gpu(g, compute=compute, link=link, split=0, **fmt)
+        assert info["chains"][0]["loader"] == "first" and info["chains"][0]["grid"] == 1 and np.array_equal(y, unsplit)
+    general, info = run_gpu(g, compute=compute, link=1, **fmt)
+    # (two bf16 roundings, of the un-linked convolution's output and of the result; fp32: 36 products summed in another order)
+    assert not any(ch.get("loader") == "first" for ch in info["chains"]) and rel_err(y, general) <= (2 ** -7 if compute else 36 * 2 ** -23)
+
+
+@pytest.mark.parametrize("compute", [0, 1])
 @pytest.mark.parametrize("n,c,h,w,k,stride", [
     (1, 136, 1, 1, 8, 1),        # one pixel, eight channels
     (2, 72, 5, 4, 40, 1),        # a ragged last step and a ragged second channel part; a whole image in a tile

@@ -50,7 +50,7 @@ def kernels(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", ["conv_kernel", "fire_kernel", "dwpw_kernel", "pwdw_kernel", "unit_kernel", "dw_kernel", "splitk_finish_kernel", "fc_stream_kernel",
-                                    "stem_lds_kernel", "conv3x3_frag_kernel"])
+                                    "stem_lds_kernel", "conv3x3_frag_kernel", "conv3x3_first_kernel"])
 def test_no_vector_register_is_spilled(kernels, kernel):
     found = {k: v for k, v in kernels.items() if re.search(r"\d" + kernel + r"I|\d" + kernel + r"E", k)}
     assert found, kernel
