@@ -372,6 +372,10 @@ struct Planner {
   bool need_export = false;
 
   // A depthwise chain waiting to be linked into the pointwise convolution that consumes it (link level 3)
+  // fp32 at link level 3 with the plan of level 2's rules, whose poolings and global averages stay linked: less workspace, more time.  (Taken where
+  // xenos_run_static's workspace holds that plan only: 5 to 8 images of VGG at a quarter of its width)
+  bool compact = false;
+  bool sizes_only = false;   // dense weights are not packed: only how much workspace the plan would need
   bool in_lazy = false, in_all_dense = false, in_gather = false;   // graph input not yet imported; see plan()
 
   struct DwPro {
@@ -1015,7 +1019,7 @@ struct Planner {
   int wave_edge(const Step& st) const {
     const ConvArgs& c = st.conv;
     if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res)) return 0;
-    if (p.dt == DT_F32 && p.opts.link >= 3) {
+    if (p.dt == DT_F32 && p.opts.link >= 3 && !compact) {
       const int edge = wave_edge_f32(c);
       // (fully connected layers as below)
       if (c.R * c.S > 1 && c.OH * c.OW == 1 && c.M_total < 8192 && !wave_pays_f32(c, c.Kred_pad / (kRowBytes / p.esz), (c.M_total + 31) / 32 * ((c.K + 31) / 32), false)) return 0;
@@ -1119,6 +1123,7 @@ struct Planner {
     const int kout_pad = (K + 127) / 128 * 128;
     const bool wave_f32 = p.dt == DT_F32 && (st.cfg == kWaveCfg || st.cfg == kWave64Cfg || st.conv.pwdw == 2);
     const size_t bytes = wave_f32 ? (size_t)((K + 63) / 64 * 2) * (kred_pad / bke) * (6 * 1024) : (size_t)kout_pad * kred_pad * p.esz;
+    if (sizes_only) { st.w_off = 0; return; }
     st.w_off = (long long)wpush(nullptr, bytes);
     unsigned char* base = p.wimage.data() + st.w_off;               // (zeros)
     // source [K][C][R][S] -> destination [K][reduction index]; channel of the operator's weights that multiplies channel c of the tensor in memory: the same one, or, behind a
@@ -1220,7 +1225,7 @@ struct Planner {
     // (room for every weight, padded, in its widest form: growing step by step the image would be copied again and again)
     size_t room = 1 << 16;
     for (const GOp& o : g.ops) room += o.weight.size() * (p.dt == DT_F32 ? 6 : 2) * 5 / 4 + 4096;
-    p.wimage.reserve(room);
+    if (!sizes_only) p.wimage.reserve(room);
     p.zero_off = wpush(nullptr, 256);      // (new bytes of the image are zero)
     build_nodes();
     const int nn = (int)nodes.size();
@@ -2009,7 +2014,7 @@ struct Planner {
       // the general kernel computes it on the fp32 MFMAs, the pixels where windows overlap more than once, or in the few tiles of a small map (16 -> 64 channels
       // 55x55 batch 32, 3x3 with a 3x3 / 2 pooling, 52.9 us -> 25.2 and 7.4; 256 channels 10x10 batch 4 with a 2x2 one, 49.0 -> 9.1, 6.2 with the sums of its
       // shares, and 6.5).  VGG at half its width, 160x160 batch 4, 368 -> 258 us, SqueezeNet 224x224 batch 32 478 -> 411 with the line above
-      if (p.dt == DT_F32 && link >= 3 && p.opts.split && p.opts.tile == 0 && !dw && !is_fc && !stem && !dwpro.active && pool_node >= 0 &&
+      if (p.dt == DT_F32 && link >= 3 && !compact && p.opts.split && p.opts.tile == 0 && !dw && !is_fc && !stem && !dwpro.active && pool_node >= 0 &&
           desc(nodes[pool_node]).kind != XENOS_OP_GLOBAL_AVGPOOL && is.c % p.ce == 0 && K % p.ce == 0 && tview[nd.in[0]] >= 0) {
         const View& iv0 = p.views[tview[nd.in[0]]];
         const int l2 = absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
@@ -2240,7 +2245,7 @@ struct Planner {
         // (fp32 at link level 3: with any number of images, the convolution's sums being the wave kernel's: 512 -> 1000 channels 13x13 batch 32
         // 65 us -> 41 and 9)
         if (a.mode == M_GAP && p.opts.split && (!from_dw || dw_panel_fits) && p.opts.tile == 0 &&
-            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave))) {
+            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !compact && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave))) {
           st.gap_finish = 1;
           a.mode = M_FLAT; a.pool = POOL_NONE;
         }
@@ -3097,7 +3102,15 @@ xenos_status xenos_plan_link_split(const xenos_graph* graph, const xenos_hw_info
   p->opts = *opts; p->hw = *hw; p->in = graph->in; p->out = graph->out;
   xenos_status rc;
   try {
+    const auto fits_static = [&](bool compact) {
+      xenos_plan trial;
+      trial.opts = *opts; trial.hw = *hw; trial.in = graph->in; trial.out = graph->out;
+      Planner pl(*graph, trial);
+      pl.compact = compact; pl.sizes_only = true;
+      return pl.run() == XENOS_OK && trial.workspace_bytes <= (size_t)XENOS_STATIC_WORKSPACE_BYTES;
+    };
     Planner pl(*graph, *p);
+    pl.compact = opts->compute == XENOS_F32 && opts->link >= 3 && opts->split && opts->tile == 0 && !fits_static(false) && fits_static(true);
     rc = pl.run();
   } catch (const std::bad_alloc&) {
     rc = fail(XENOS_ENOMEM, "out of host memory");

@@ -659,3 +659,15 @@ def test_pattern_matmul_to_matmul_layout_link():
     with pytest.raises(X.XenosError) as e:
         X.xenos_graph_create(X.TensorDesc(4, 2, 2, 2, X.XENOS_F32, X.XENOS_NCHW), ops, 1)     # not a rows x columns tensor
     assert e.value.status == X.XENOS_ESHAPE
+
+
+def test_fp32_plans_keep_within_the_static_workspace_where_they_can():
+    # the poolings and averages that link level 3 takes apart in fp32 need tensors of their own: not where the linked plan alone fits xenos_run_static
+    needs = []
+    for batch in (1, 6, 16):
+        j = plan_json(wg.vgg16(batch=batch, width=0.25, fc_dim=256, draw=False), link=3, split=1, compute=X.XENOS_F32)
+        needs.append((j["workspace_bytes"], sum(c["kind"] == "pool" for c in j["plan"]["chains"])))
+    (small, apart), (fits, linked), (large, apart_again) = needs
+    assert small <= X.XENOS_STATIC_WORKSPACE_BYTES and apart > 0
+    assert fits <= X.XENOS_STATIC_WORKSPACE_BYTES and linked < apart
+    assert large > X.XENOS_STATIC_WORKSPACE_BYTES and apart_again > 0
