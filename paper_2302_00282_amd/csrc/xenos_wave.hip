@@ -387,7 +387,13 @@ static int launch_conv_wave_t(const ConvArgs& a, hipStream_t st) {
   return direct ? launch_conv_wave_inst<T, NB, false, true>(w, a.grid, lds, st) : launch_conv_wave_inst<T, NB, false, false>(w, a.grid, lds, st);
 }
 
-static int pwdw_wave_stages(const ConvArgs& a, int esz) { return conv_wave_stages(kWaveRows, a.Kred_pad * esz / ROWB, a.tiles_m * ((a.K + 31) / 32), esz); }
+// (fp32 beyond 256 tiles: two stages of 40 KB and the block of the depthwise convolution leave a unit room for one workgroup, one stage for three.  256 channels
+// 15x15 batch 3, 480 tiles, a launch of five in a row: with two 7.7 us, MobileNet graph 112.8, with one 5.8 and 103.4; batch 1 224x224 97.4 -> 95.4)
+static int pwdw_wave_stages(const ConvArgs& a, int esz) {
+  const int tiles = a.tiles_m * ((a.K + 31) / 32);
+  if (esz == 4 && tiles > 256) return 1;
+  return conv_wave_stages(kWaveRows, a.Kred_pad * esz / ROWB, tiles, esz);
+}
 size_t pwdw_wave_lds(const ConvArgs& a, int esz) {
   const int s = a.dw_stride;
   return conv_wave_lds(kWaveRows, pwdw_wave_stages(a, esz), esz) + (size_t)((a.th - 1) * s + 3) * ((a.tw - 1) * s + 3) * wave_mid_pitch(esz);
