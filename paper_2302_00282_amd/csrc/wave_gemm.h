@@ -114,14 +114,14 @@ struct WaveTile {
   }
 };
 
-// Three bf16 values whose sum is x (each rounds what the ones before it leave; the third is exact, eight of the 24 bits).  Infinite values, and finite ones
-// that round to infinity, leave NaN.
+// Three bf16 values whose sum is x * kWavePartScale (each rounds what the ones before it leave; the third is exact, eight of the 24 bits), whatever x is
+// below kWavePartMost.  Infinite values, and finite ones that become so, leave NaN.
 struct Split8 { bf16x8_t hi, mid, lo; };
 __device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
   u32x4_t p[3];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float x0 = __uint_as_float(i < 2 ? a[2 * i] : b[2 * i - 4]), x1 = __uint_as_float(i < 2 ? a[2 * i + 1] : b[2 * i - 3]);
+    float x0 = __uint_as_float(i < 2 ? a[2 * i] : b[2 * i - 4]) * kWavePartScale, x1 = __uint_as_float(i < 2 ? a[2 * i + 1] : b[2 * i - 3]) * kWavePartScale;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const uint32_t u = f2bf2(x0, x1);
@@ -138,7 +138,9 @@ __device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
 // 2^-24 of the product).  The five small ones have sums of their own, so that the large ones are rounded once in sixteen products: against 64 bits dot products
 // of 16 to 4608 random numbers are off by 3.2e-8 to 4.2e-7 of their norm, half or less of the fp32 MFMAs' 5.5e-8 to 1.2e-6.  A step is twelve MFMAs of 32
 // cycles instead of sixteen of 64.  The image of a step of the weights lies in memory as in LDS: [hi, mid, lo][32 channels][64 bytes], 16-byte slot s of
-// row r holds chunk s ^ (r / 4 % 4).  Sums that are not finite are for the caller to work out again (an infinite value is no sum of three).
+// row r holds chunk s ^ (r / 4 % 4).  Sums that are not finite are for the caller to work out again: those of an infinite operand or one that is not a number, and,
+products being 2^48 times too large, any beyond 2^79 and of a pixel or weight from 2^103 on.  (The scale costs a multiplication a pixel value: SqueezeNet batch 32
+426 -> 432 us, MobileNet batch 1 95.5 -> 96.7; without it operands below 2^-110 had fewer than 24 bits, 1e-38 ten.)
 template <int NB>
 struct WaveTile<float, NB> {
   static constexpr int EDGE = 32 * NB, ROWS_A = EDGE * ROWB, PLANE = 32 * 64, BLOCK = 3 * PLANE;
@@ -232,13 +234,14 @@ struct WaveTile<float, NB> {
     f32x4_t v[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w) v[w] = *(const f32x4_t*)(s + w * wave_bytes + row * EDGE * 4 + ((c4 ^ row) & (SLOTS - 1)) * 16);
-    return ((v[0] + v[1]) + v[2]) + v[3];
+    return (((v[0] + v[1]) + v[2]) + v[3]) * (1.f / (kWavePartScale * kWavePartScale));
   }
 };
 // element i of a step of row `row` of 32 channels, out of the packed image of that step
 __device__ __forceinline__ float wave_weight_f32(const unsigned char* step, int row, int i) {
   const uint16_t* p = (const uint16_t*)(step + row * 64 + (((i >> 3) ^ ((row >> 2) & 3)) * 16)) + (i & 7);
-  return (bf2f(p[0]) + bf2f(p[1024])) + bf2f(p[2048]);
+  if (p[0] == kWaveWholeWeight) return __uint_as_float((uint32_t)p[1024] << 16 | p[2048]);
+  return ((bf2f(p[0]) + bf2f(p[1024])) + bf2f(p[2048])) * (1.f / kWavePartScale);
 }
 __device__ __forceinline__ bool all_finite(const f32x4_t& v) {
   uint32_t e = 0;

@@ -1135,7 +1135,8 @@ struct Planner {
     };
     if (wave_f32) {
       // [32 channels][step][upper, middle and lower eight bits][channel][64 bytes], 16-byte slot s of channel r holds chunk s ^ (r / 4 % 4): a step as it
-      // lies in LDS
+      // lies in LDS.  A weight that the parts don't hold, infinite, not a number or beyond 2^103, is there itself, behind a mark that makes its sums NaN,
+      // whereupon they are worked out again
       const size_t nsteps = kred_pad / bke;
       for (int k = 0; k < K; ++k) {
         const float* src = o.weight.data() + (size_t)k * Csrc * R * S;
@@ -1145,22 +1146,36 @@ struct Planner {
             const size_t at = kidx(c0, rs), i = at % bke;
             uint16_t* dst = (uint16_t*)(base + ((size_t)(k / 32) * nsteps + at / bke) * (6 * 1024) + row * 64 + ((i / 8) ^ (row / 4 % 4)) * 16) + i % 8;
             const int cn = std::min(group, Csrc - c0);
-            float v[8] = {};
-            uint16_t h[8];
+            float v[8] = {}, whole[8];
+            uint16_t h[3][8];
             if (shg) for (int c = 0; c < cn; ++c) v[c] = src[wch(c0 + c) * R * S + rs];
             else if (R * S == 1 && cn == 8) memcpy(v, src + c0, 8 * sizeof(float));
             else for (int c = 0; c < cn; ++c) v[c] = src[(size_t)(c0 + c) * R * S + rs];
-            for (int part = 0; part < 3; ++part, dst += 1024) {
+            bool parts = true;
+            for (int c = 0; c < 8; ++c) {
+              whole[c] = v[c];
+              parts &= std::fabs(v[c]) < kWavePartMost;            // (false for NaN)
+              v[c] *= kWavePartScale;
+            }
+            for (int part = 0; part < 3; ++part)
               for (int c = 0; c < 8; ++c) {
                 uint32_t u;
                 memcpy(&u, &v[c], 4);
                 u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-                h[c] = (uint16_t)(u >> 16);
+                h[part][c] = (uint16_t)(u >> 16);
                 float f;
                 memcpy(&f, &u, 4);
                 v[c] -= f;
               }
-              if (cn == 8) memcpy(dst, h, 16); else memcpy(dst, h, cn * sizeof(uint16_t));
+            if (!parts)
+              for (int c = 0; c < 8; ++c) {
+                if (std::fabs(whole[c]) < kWavePartMost) continue;
+                uint32_t u;
+                memcpy(&u, &whole[c], 4);
+                h[0][c] = kWaveWholeWeight; h[1][c] = (uint16_t)(u >> 16); h[2][c] = (uint16_t)u;
+              }
+            for (int part = 0; part < 3; ++part, dst += 1024) {
+              if (cn == 8) memcpy(dst, h[part], 16); else memcpy(dst, h[part], cn * sizeof(uint16_t));
             }
           }
       }

@@ -640,6 +640,52 @@ def test_fp32_products_in_three_parts_keep_infinite_and_largest_values(kind, c, 
     assert big.any() and rel_err(y[big], ref[big]) <= 1e-5 and rel_err(y[fin & ~big], ref[fin & ~big]) <= 1e-5
 
 
+@pytest.mark.parametrize("kind,n,c,h,w,k,ksz,stride", [
+    ("conv", 2, 40, 9, 8, 40, 1, 1), ("conv", 2, 24, 9, 8, 40, 3, 1), ("split", 2, 640, 9, 8, 40, 3, 1), ("pwdw", 2, 72, 9, 8, 40, 1, 1),
+    ("conv64", 8, 64, 63, 62, 128, 3, 1)])
+def test_fp32_products_in_three_parts_hold_every_weight_and_pixel(kind, n, c, h, w, k, ksz, stride):
+    # the whole range of fp32, where one part alone may be out of bf16's: infinite, largest, not a number, and down to the smallest
+    def graph():
+        b = wg.builder("range", (n, c, h, w), 113)
+        t = b.cbr(0, k, ksz, stride, ksz // 2, name="a", bn=False, relu=False)
+        if kind == "pwdw":
+            t = b.cbr(t, k, 3, 1, 1, groups=k, name="dw", bn=False, relu=False)
+            b.g.ops[t - 1].params["weight"][:] = np.abs(b.g.ops[t - 1].params["weight"]) + 0.1
+        g = b.finish(t)
+        g.x = np.abs(g.x) + np.float32(0.1)
+        return g, g.ops[0].params["weight"]
+
+    def run(g):
+        y, info = run_gpu(g, compute=0, link=3, in_layout=1, out_layout=1)
+        assert info["chains"][0]["wave"] and (kind == "conv64") == (info["chains"][0]["bm"] == 64), info["chains"]
+        assert kind != "split" or info["chains"][0]["ksplit"] > 1
+        return y
+
+    most = np.finfo(np.float32).max
+    g, wt = graph()
+    wt[0, 1], wt[1, 2], wt[2, 3], wt[3, 4] = most, np.inf, -np.inf, np.float32(3.3962e38)     # (the last rounds to infinity in bf16)
+    wt[4, 5] = np.array(0x7fffffff, np.uint32).view(np.float32)
+    wt[5, 6], wt[6, 7] = 1e32, -most
+    g.x[:, [1, 4, 7]] *= np.float32(1e-3)                      # (finite sums of the largest weights)
+    ref = xo.forward(g)
+    y = run(g)
+    assert np.isnan(ref[:, 4]).all() and np.isinf(ref[:, 1:3]).all() and np.isfinite(ref[:, [0, 3, 5, 6]]).all()
+    fin = np.isfinite(ref)
+    assert np.array_equal(y[~fin], ref[~fin].astype(np.float32), equal_nan=True)
+    for ch in range(k):
+        if fin[:, ch].all():
+            assert rel_err(y[:, ch], ref[:, ch]) <= 1e-5, ch
+    # (weights, pixels): 24 bits of either whatever their size, while the result itself is a normal number
+    for ws, xs in ((1, 1e-35), (1e-38, 100), (1e-42, 1e8), (1e-18, 1e-17), (1e28, 1e-42), (1e33, 1e-36), (1e-36, 1e36), (1e-3, 1e31)):
+        g, wt = graph()
+        wt *= np.float32(ws)
+        g.x *= np.float32(xs)
+        ref = xo.forward(g)
+        y = run(g)
+        for ch in range(k):
+            assert np.abs(ref[:, ch]).max() > 1e-37 and float(np.abs(y[:, ch] - ref[:, ch]).max() / np.abs(ref[:, ch]).max()) <= 1e-5, (ws, xs, ch)
+
+
 @pytest.mark.parametrize("kind,n,c,h,w,k,num_cu,bm,bn", [
     ("plain", 1, 32, 97, 95, 256, 8, 208, 128),     # one chunk a tile; tiles clipped at two borders, twelve of them walked by a workgroup
     ("max", 3, 32, 30, 44, 256, 8, 208, 128),
