@@ -139,8 +139,8 @@ __device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
 // of 16 to 4608 random numbers are off by 3.2e-8 to 4.2e-7 of their norm, half or less of the fp32 MFMAs' 5.5e-8 to 1.2e-6.  A step is twelve MFMAs of 32
 // cycles instead of sixteen of 64.  The image of a step of the weights lies in memory as in LDS: [hi, mid, lo][32 channels][64 bytes], 16-byte slot s of
 // row r holds chunk s ^ (r / 4 % 4).  Sums that are not finite are for the caller to work out again: those of an infinite operand or one that is not a number, and,
-products being 2^48 times too large, any beyond 2^79 and of a pixel or weight from 2^103 on.  (The scale costs a multiplication a pixel value: SqueezeNet batch 32
-426 -> 432 us, MobileNet batch 1 95.5 -> 96.7; without it operands below 2^-110 had fewer than 24 bits, 1e-38 ten.)
+// products being 2^48 times too large, any beyond 2^79 and of a pixel or weight from 2^103 on.  (The scale costs a multiplication a pixel value: SqueezeNet batch 32
+// 426 -> 432 us, MobileNet batch 1 95.5 -> 96.7; without it operands below 2^-110 had fewer than 24 bits, 1e-38 ten.)
 template <int NB>
 struct WaveTile<float, NB> {
   static constexpr int EDGE = 32 * NB, ROWS_A = EDGE * ROWB, PLANE = 32 * 64, BLOCK = 3 * PLANE;
