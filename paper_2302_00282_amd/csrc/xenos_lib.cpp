@@ -1054,6 +1054,27 @@ struct Planner {
       return 64;
     return tiles <= most && conv_wave_lds(kWaveRows, conv_wave_stages(kWaveRows, nsteps, (int)tiles, p.esz), p.esz) <= p.hw.lds_bytes_per_cu ? kWaveRows : 0;
   }
+  // Does the wave kernel run a convolution of `iv` once the window pooling behind it is a pass of its own, its output a tensor by itself?  (Where it refuses, more
+  // than 2^20 - 32 pixels for instance, the chain keeps its pooling: the same kernel would write the whole map for the pass to read again.  VGG-16 fp32 batch 32
+  // has 411 MB more to move in its second layer and 822 MB of workspace instead of 514.)
+  bool wave_takes_apart(const View& iv, const Shape& is, const xenos_op_desc& d, const Shape& os, int res_tid) const {
+    Step t;
+    ConvArgs& a = t.conv;
+    if ((long long)os.n * os.h * os.w >= kSmallDiv) return false;
+    a.N = is.n; a.C = std::max(is.c, iv.cphys); a.H = is.h; a.W = is.w; a.K = d.out_c;
+    a.R = d.kh; a.S = d.kw; a.stride = d.stride_h; a.pad = d.pad_h; a.OH = os.h; a.OW = os.w;
+    a.in_sN = iv.sN; a.in_sH = iv.sP * is.w; a.in_sW = iv.sP;
+    a.out_sN = (long long)os.h * os.w * a.K; a.out_sP = a.K; a.out_sK = 1; a.vec_out = 1;
+    if (res_tid >= 0) {
+      if (tview[res_tid] < 0) return false;
+      const View& rv = p.views[tview[res_tid]];
+      a.has_res = 1; a.res_sN = rv.sN; a.res_sP = rv.sP; a.vec_res = aligned_res(rv, a.K);
+    }
+    a.mode = M_FLAT; a.M_total = a.N * a.OH * a.OW;
+    set_reduction(t, a.C, a.R, a.S);
+    return wave_edge(t) != 0;
+  }
+  bool aligned_res(const View& rv, int K) const { return K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0; }
   // Shares of the reduction of a chain on fc_stream_kernel, for that many units (two workgroups per unit, each with at least 4 steps = 32 KB of
   // weights to stream)
   int fc_shares(const ConvArgs& c, int units) const {
@@ -2025,7 +2046,7 @@ struct Planner {
           stem_lds = false;
         }
       }
-      // fp32 at link level 3: a window pooling behind a convolution that the wave kernel can take is a pass of its own.  Linked,
+      // fp32 at link level 3: a window pooling behind a convolution that the wave kernel takes is a pass of its own.  Linked,
       // the general kernel computes it on the fp32 MFMAs, the pixels where windows overlap more than once, or in the few tiles of a small map (16 -> 64 channels
       // 55x55 batch 32, 3x3 with a 3x3 / 2 pooling, 52.9 us -> 25.2 and 7.4; 256 channels 10x10 batch 4 with a 2x2 one, 49.0 -> 9.1, 6.2 with the sums of its
       // shares, and 6.5).  VGG at half its width, 160x160 batch 4, 368 -> 258 us, SqueezeNet 224x224 batch 32 478 -> 411 with the line above
@@ -2033,7 +2054,8 @@ struct Planner {
           desc(nodes[pool_node]).kind != XENOS_OP_GLOBAL_AVGPOOL && is.c % p.ce == 0 && K % p.ce == 0 && tview[nd.in[0]] >= 0) {
         const View& iv0 = p.views[tview[nd.in[0]]];
         const int l2 = absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
-        if (iv0.internal_nhwc() && !iv0.f32 && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && l2 + 1 != out_tid && !placed.count(l2 + 1)) {
+        if (iv0.internal_nhwc() && !iv0.f32 && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && l2 + 1 != out_tid && !placed.count(l2 + 1) &&
+            wave_takes_apart(iv0, is, d, tshape[i + 1], has_res ? res_tid : -1)) {
           absorbed.pop_back();
           pool_node = -1; last = l2; cur = l2 + 1;
         }
@@ -2222,6 +2244,7 @@ struct Planner {
         if (has_res) {
           st.v_in2 = tview[res_tid];
           a.res_sN = p.views[st.v_in2].sN; a.res_sP = p.views[st.v_in2].sP;
+          a.vec_res = aligned_res(p.views[st.v_in2], K);
         }
         const auto fit = fin.find(cur);
         if (fit != fin.end()) {
@@ -2309,10 +2332,6 @@ struct Planner {
         a.vec_out = ov.sK == 1 && (!ov.f32 || p.dt == DT_F32) && ov.esz == p.esz && K % p.ce == 0 && ov.off % p.ce == 0 &&
                     ov.sP % p.ce == 0 && ov.sN % p.ce == 0;
         if (a.ileave && !a.vec_out) return fail(XENOS_EUNSUPPORTED, "%s: shuffled concat buffer is not aligned", st.name.c_str());
-        if (has_res) {
-          const View& rv = p.views[st.v_in2];
-          a.vec_res = K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0;
-        }
         if (st.fc_stream && nd.kind == XENOS_OP_MATMUL && !matmul_streams(st)) st.fc_stream = 0;
         if (a.unit) {
           if (!a.vec_out || a.mode != M_FLAT || has_res) return fail(XENOS_EUNSUPPORTED, "%s: output of the unit's chain is not aligned", st.name.c_str());

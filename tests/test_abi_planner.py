@@ -671,3 +671,16 @@ def test_fp32_plans_keep_within_the_static_workspace_where_they_can():
     assert small <= X.XENOS_STATIC_WORKSPACE_BYTES and apart > 0
     assert fits <= X.XENOS_STATIC_WORKSPACE_BYTES and linked < apart
     assert large > X.XENOS_STATIC_WORKSPACE_BYTES and apart_again > 0
+
+
+@pytest.mark.parametrize("n,c,hw,k,ksz,pool,apart", [
+    (31, 64, 184, 64, 3, 2, 0), (31, 64, 183, 64, 3, 2, 1),                                        # 2^20 pixels and more than the wave kernel's indices hold, and fewer
+    (32, 64, 224, 64, 3, 2, 0), (16, 16, 300, 32, 1, 3, 0), (8, 64, 56, 64, 3, 2, 1), (2, 16, 55, 64, 1, 3, 1)])
+def test_fp32_window_pooling_stays_linked_where_the_wave_kernel_refuses_the_convolution(n, c, hw, k, ksz, pool, apart):
+    b = undrawn((n, 8, hw, hw))
+    t = b.cbr(b.cbr(0, c, 1, name="a"), k, ksz, 1, ksz // 2, name="b")
+    g = b.finish(b.cbr(b.maxpool(t, pool, 2), 8, 1, name="c"))
+    chains = plan_json(g, link=3, compute=X.XENOS_F32)["plan"]["chains"]
+    conv, = [ch for ch in chains if ch["kind"] == "conv" and (ch["C"], ch["K"]) == (c, k)]
+    assert (conv["pool"] == 0) == bool(apart) and sum(ch["kind"] == "pool" for ch in chains) == apart, chains
+    assert conv["wave"] or not apart
