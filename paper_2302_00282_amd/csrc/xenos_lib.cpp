@@ -1074,6 +1074,16 @@ struct Planner {
     set_reduction(t, a.C, a.R, a.S);
     return wave_edge(t) != 0;
   }
+  // The same of a chain whose global average moves to the summing pass.  (32x200x200, 64 -> 512 channels, on the general kernel: 2.6 GB of sums.)
+  bool wave_takes_average(const Step& st) const {
+    Step t = st;
+    ConvArgs& a = t.conv;
+    if ((long long)a.N * a.OH * a.OW >= kSmallDiv) return false;
+    t.gap_finish = 1;
+    a.mode = M_FLAT; a.pool = POOL_NONE; a.M_total = a.N * a.OH * a.OW;
+    set_reduction(t, a.C, a.R, a.S);
+    return wave_edge(t) != 0;
+  }
   bool aligned_res(const View& rv, int K) const { return K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0; }
   // Shares of the reduction of a chain on fc_stream_kernel, for that many units (two workgroups per unit, each with at least 4 steps = 32 KB of
   // weights to stream)
@@ -2280,10 +2290,10 @@ struct Planner {
         // (a linked depthwise producer needs the depthwise-panel kernel for this, which takes whole channel groups)
         const bool dw_panel_fits = from_dw && a.C % p.ce == 0 && K % p.ce == 0 && !has_res &&
                                    dwpw_lds_bytes(kRowBytes / p.esz, p.esz) <= std::min<size_t>(p.hw.lds_bytes_per_cu, 160 * 1024);
-        // (fp32 at link level 3: with any number of images, the convolution's sums being the wave kernel's: 512 -> 1000 channels 13x13 batch 32
+        // (fp32 at link level 3: with any number of images where the convolution's sums are the wave kernel's: 512 -> 1000 channels 13x13 batch 32
         // 65 us -> 41 and 9)
         if (a.mode == M_GAP && p.opts.split && (!from_dw || dw_panel_fits) && p.opts.tile == 0 &&
-            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !compact && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave))) {
+            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !compact && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave && wave_takes_average(st)))) {
           st.gap_finish = 1;
           a.mode = M_FLAT; a.pool = POOL_NONE;
         }
