@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
@@ -372,9 +373,11 @@ struct Planner {
   bool need_export = false;
 
   // A depthwise chain waiting to be linked into the pointwise convolution that consumes it (link level 3)
-  // fp32 at link level 3 with the plan of level 2's rules, whose poolings and global averages stay linked: less workspace, more time.  (Taken where
-  // xenos_run_static's workspace holds that plan only: 5 to 8 images of VGG at a quarter of its width)
-  bool compact = false;
+  // fp32 at link level 3 in less workspace and more time, where xenos_run_static's workspace holds no faster plan: window poolings and the global averages
+  // of many images stay linked behind maps of more than that many bytes (5 to 8 images of VGG at a quarter of its width, whose first map is 16 to 26 MB), and, if
+  // that is not enough, dense chains go by level 2's rules, which share out fewer reductions
+  long long apart_most = std::numeric_limits<long long>::max();
+  bool level2_rules = false;
   bool sizes_only = false;   // dense weights are not packed: only how much workspace the plan would need
   bool in_lazy = false, in_all_dense = false, in_gather = false;   // graph input not yet imported; see plan()
 
@@ -1019,7 +1022,7 @@ struct Planner {
   int wave_edge(const Step& st) const {
     const ConvArgs& c = st.conv;
     if (p.opts.tile != 0 || st.scalar || c.dw_w || c.ileave || (!st.gap_finish && (c.out_sK != 1 || (!c.out_f32 && !c.vec_out))) || (c.has_res && !c.vec_res)) return 0;
-    if (p.dt == DT_F32 && p.opts.link >= 3 && !compact) {
+    if (p.dt == DT_F32 && p.opts.link >= 3 && !level2_rules) {
       const int edge = wave_edge_f32(c);
       // (fully connected layers as below)
       if (c.R * c.S > 1 && c.OH * c.OW == 1 && c.M_total < 8192 && !wave_pays_f32(c, c.Kred_pad / (kRowBytes / p.esz), (c.M_total + 31) / 32 * ((c.K + 31) / 32), false)) return 0;
@@ -1060,7 +1063,7 @@ struct Planner {
   bool wave_takes_apart(const View& iv, const Shape& is, const xenos_op_desc& d, const Shape& os, int res_tid) const {
     Step t;
     ConvArgs& a = t.conv;
-    if ((long long)os.n * os.h * os.w >= kSmallDiv) return false;
+    if ((long long)os.n * os.h * os.w >= kSmallDiv || (long long)os.n * os.h * os.w * d.out_c * p.esz > apart_most) return false;
     a.N = is.n; a.C = std::max(is.c, iv.cphys); a.H = is.h; a.W = is.w; a.K = d.out_c;
     a.R = d.kh; a.S = d.kw; a.stride = d.stride_h; a.pad = d.pad_h; a.OH = os.h; a.OW = os.w;
     a.in_sN = iv.sN; a.in_sH = iv.sP * is.w; a.in_sW = iv.sP;
@@ -1078,7 +1081,7 @@ struct Planner {
   bool wave_takes_average(const Step& st) const {
     Step t = st;
     ConvArgs& a = t.conv;
-    if ((long long)a.N * a.OH * a.OW >= kSmallDiv) return false;
+    if ((long long)a.N * a.OH * a.OW >= kSmallDiv || (long long)a.N * a.OH * a.OW * a.K * p.esz > apart_most) return false;
     t.gap_finish = 1;
     a.mode = M_FLAT; a.pool = POOL_NONE; a.M_total = a.N * a.OH * a.OW;
     set_reduction(t, a.C, a.R, a.S);
@@ -2060,7 +2063,7 @@ struct Planner {
       // the general kernel computes it on the fp32 MFMAs, the pixels where windows overlap more than once, or in the few tiles of a small map (16 -> 64 channels
       // 55x55 batch 32, 3x3 with a 3x3 / 2 pooling, 52.9 us -> 25.2 and 7.4; 256 channels 10x10 batch 4 with a 2x2 one, 49.0 -> 9.1, 6.2 with the sums of its
       // shares, and 6.5).  VGG at half its width, 160x160 batch 4, 368 -> 258 us, SqueezeNet 224x224 batch 32 478 -> 411 with the line above
-      if (p.dt == DT_F32 && link >= 3 && !compact && p.opts.split && p.opts.tile == 0 && !dw && !is_fc && !stem && !dwpro.active && pool_node >= 0 &&
+      if (p.dt == DT_F32 && link >= 3 && p.opts.split && p.opts.tile == 0 && !dw && !is_fc && !stem && !dwpro.active && pool_node >= 0 &&
           desc(nodes[pool_node]).kind != XENOS_OP_GLOBAL_AVGPOOL && is.c % p.ce == 0 && K % p.ce == 0 && tview[nd.in[0]] >= 0) {
         const View& iv0 = p.views[tview[nd.in[0]]];
         const int l2 = absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
@@ -2293,7 +2296,7 @@ struct Planner {
         // (fp32 at link level 3: with any number of images where the convolution's sums are the wave kernel's: 512 -> 1000 channels 13x13 batch 32
         // 65 us -> 41 and 9)
         if (a.mode == M_GAP && p.opts.split && (!from_dw || dw_panel_fits) && p.opts.tile == 0 &&
-            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !compact && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave && wave_takes_average(st)))) {
+            (2 * a.N * ((K + 63) / 64) <= std::max(1, p.hw.num_cu) || (p.dt == DT_F32 && link >= 3 && !from_dw && !from_pair && !is_fc && !st.stem && !st.scalar && !a.ileave && wave_takes_average(st)))) {
           st.gap_finish = 1;
           a.mode = M_FLAT; a.pool = POOL_NONE;
         }
@@ -3146,15 +3149,19 @@ xenos_status xenos_plan_link_split(const xenos_graph* graph, const xenos_hw_info
   p->opts = *opts; p->hw = *hw; p->in = graph->in; p->out = graph->out;
   xenos_status rc;
   try {
-    const auto fits_static = [&](bool compact) {
+    struct Limit { long long apart_most; bool level2_rules; };
+    static const Limit limits[] = {{std::numeric_limits<long long>::max(), false}, {16 << 20, false}, {8 << 20, false}, {0, false}, {0, true}};
+    const auto fits_static = [&](const Limit& l) {
       xenos_plan trial;
       trial.opts = *opts; trial.hw = *hw; trial.in = graph->in; trial.out = graph->out;
       Planner pl(*graph, trial);
-      pl.compact = compact; pl.sizes_only = true;
+      pl.apart_most = l.apart_most; pl.level2_rules = l.level2_rules; pl.sizes_only = true;
       return pl.run() == XENOS_OK && trial.workspace_bytes <= (size_t)XENOS_STATIC_WORKSPACE_BYTES;
     };
     Planner pl(*graph, *p);
-    pl.compact = opts->compute == XENOS_F32 && opts->link >= 3 && opts->split && opts->tile == 0 && !fits_static(false) && fits_static(true);
+    if (opts->compute == XENOS_F32 && opts->link >= 3 && opts->split && opts->tile == 0)
+      for (const Limit& l : limits)
+        if (fits_static(l)) { pl.apart_most = l.apart_most; pl.level2_rules = l.level2_rules; break; }   // (none: nothing is gained, and the plan is the first)
     rc = pl.run();
   } catch (const std::bad_alloc&) {
     rc = fail(XENOS_ENOMEM, "out of host memory");

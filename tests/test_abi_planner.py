@@ -694,3 +694,16 @@ def test_fp32_global_average_stays_linked_where_the_wave_kernel_refuses_the_conv
     chains = plan_json(b.finish(b.gap(t)), link=3, compute=X.XENOS_F32)["plan"]["chains"]
     conv, = [ch for ch in chains if ch["kind"] == "conv" and (ch["C"], ch["K"]) == (64, 512)]
     assert (conv["mode"] != "gap") == bool(apart) and bool(conv["wave"]) == bool(apart) and sum(ch["kind"] == "splitk_finish" for ch in chains) == apart
+
+
+@pytest.mark.parametrize("batch", [5, 6, 8])
+def test_fp32_plans_within_the_static_workspace_link_only_the_poolings_of_large_maps(batch):
+    # VGG at a quarter of its width: the maps in front of the first two poolings are 16 to 26 MB and half of that; all other layers are planned as for any other number of images
+    def chains(n):
+        return plan_json(wg.vgg16(batch=n, width=0.25, fc_dim=256, draw=False), link=3, compute=X.XENOS_F32)
+    j = chains(batch)
+    conv = [c for c in j["plan"]["chains"] if c["kind"] == "conv"]
+    assert j["workspace_bytes"] <= X.XENOS_STATIC_WORKSPACE_BYTES
+    linked = [c["OH"] for c in conv if c["pool"]]
+    assert linked in ([224], [224, 112]) and all(c["wave"] for c in conv if not c["pool"])
+    assert sum(c["kind"] == "pool" for c in j["plan"]["chains"]) == sum(c["kind"] == "pool" for c in chains(4)["plan"]["chains"]) - len(linked)
