@@ -675,7 +675,7 @@ def test_fp32_plans_keep_within_the_static_workspace_where_they_can():
 
 @pytest.mark.parametrize("n,c,hw,k,ksz,pool,apart", [
     (31, 64, 184, 64, 3, 2, 0), (31, 64, 183, 64, 3, 2, 1),                                        # 2^20 pixels and more than the wave kernel's indices hold, and fewer
-    (32, 64, 224, 64, 3, 2, 0), (16, 16, 300, 32, 1, 3, 0), (8, 64, 56, 64, 3, 2, 1), (2, 16, 55, 64, 1, 3, 1)])
+    (32, 64, 224, 64, 3, 2, 0), (16, 16, 300, 32, 1, 3, 0), (8, 64, 56, 64, 3, 2, 1), (2, 128, 55, 64, 1, 3, 1)])
 def test_fp32_window_pooling_stays_linked_where_the_wave_kernel_refuses_the_convolution(n, c, hw, k, ksz, pool, apart):
     b = undrawn((n, 8, hw, hw))
     t = b.cbr(b.cbr(0, c, 1, name="a"), k, ksz, 1, ksz // 2, name="b")
@@ -698,12 +698,29 @@ def test_fp32_global_average_stays_linked_where_the_wave_kernel_refuses_the_conv
 
 @pytest.mark.parametrize("batch", [5, 6, 8])
 def test_fp32_plans_within_the_static_workspace_link_only_the_poolings_of_large_maps(batch):
-    # VGG at a quarter of its width: the maps in front of the first two poolings are 16 to 26 MB and half of that; all other layers are planned as for any other number of images
-    def chains(n):
-        return plan_json(wg.vgg16(batch=n, width=0.25, fc_dim=256, draw=False), link=3, compute=X.XENOS_F32)
-    j = chains(batch)
+    # VGG at a quarter of its width: the maps in front of the first two poolings are 16 to 26 MB and half of that; the other three are passes of their own
+    # and every layer without one on the wave kernel, as for any other number of images
+    j = plan_json(wg.vgg16(batch=batch, width=0.25, fc_dim=256, draw=False), link=3, compute=X.XENOS_F32)
     conv = [c for c in j["plan"]["chains"] if c["kind"] == "conv"]
-    assert j["workspace_bytes"] <= X.XENOS_STATIC_WORKSPACE_BYTES
     linked = [c["OH"] for c in conv if c["pool"]]
+    assert j["workspace_bytes"] <= X.XENOS_STATIC_WORKSPACE_BYTES
     assert linked in ([224], [224, 112]) and all(c["wave"] for c in conv if not c["pool"])
-    assert sum(c["kind"] == "pool" for c in j["plan"]["chains"]) == sum(c["kind"] == "pool" for c in chains(4)["plan"]["chains"]) - len(linked)
+    assert sum(c["kind"] == "pool" for c in j["plan"]["chains"]) == 5 - len(linked)
+
+
+@pytest.mark.parametrize("n,c,hw,k,ksz,pool,last,nhwc,apart", [
+    # disjoint windows: four steps of 32 channels and taps, five to nine by the number of 32 x 32 tiles, ten
+    (2, 128, 32, 64, 1, 2, 0, 1, 0), (2, 160, 32, 64, 1, 2, 0, 1, 1), (2, 288, 80, 64, 1, 2, 0, 1, 0), (2, 288, 80, 48, 1, 2, 0, 1, 1), (2, 320, 80, 64, 1, 2, 0, 1, 1), (2, 160, 160, 64, 1, 2, 0, 1, 1),
+    # overlapping ones
+    (2, 64, 33, 64, 1, 3, 0, 1, 0), (2, 96, 33, 64, 1, 3, 0, 1, 1), (8, 64, 80, 64, 1, 3, 0, 1, 1),
+    # the graph's output, in the caller's order and in the pooling pass's
+    (2, 288, 32, 64, 1, 2, 1, 0, 0), (2, 320, 32, 64, 1, 2, 1, 0, 1), (2, 288, 32, 64, 1, 2, 1, 1, 1), (2, 192, 33, 64, 1, 3, 1, 0, 0), (2, 224, 33, 64, 1, 3, 1, 0, 1)])
+def test_fp32_window_pooling_behind_a_short_reduction_stays_linked(n, c, hw, k, ksz, pool, last, nhwc, apart):
+    b = undrawn((n, 8, hw, hw))
+    t = b.maxpool(b.cbr(b.cbr(0, c, 1, name="a"), k, ksz, 1, ksz // 2, name="b"), pool, 2)
+    G = X.graph_from_workload(b.finish(t if last else b.cbr(t, 8, 1, name="c")), out_layout=X.XENOS_NHWC if nhwc else X.XENOS_NCHW)
+    P = X.xenos_plan_link_split(G, link=3, compute=X.XENOS_F32)
+    chains = X.xenos_plan_query(P)["plan"]["chains"]
+    X.xenos_destroy(P)
+    X.xenos_destroy(G)
+    assert sum(ch["kind"] == "pool" for ch in chains) == apart, chains
