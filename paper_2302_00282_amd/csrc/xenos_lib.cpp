@@ -2078,7 +2078,7 @@ struct Planner {
         const View& iv0 = p.views[tview[nd.in[0]]];
         const int l2 = absorbed.size() >= 2 ? absorbed[absorbed.size() - 2] : i;
         if (iv0.internal_nhwc() && !iv0.f32 && iv0.off % p.ce == 0 && iv0.sP % p.ce == 0 && l2 + 1 != out_tid && !placed.count(l2 + 1) &&
-            wave_takes_apart(iv0, is, d, tshape[i + 1], has_res ? res_tid : -1)) {
+            wave_takes_apart(iv0, is, d, tshape[i + 1], has_res ? res_tid : -1, desc(nodes[pool_node]), cur == out_tid && !ext_is_internal(p.out))) {
           absorbed.pop_back();
           pool_node = -1; last = l2; cur = l2 + 1;
         }
