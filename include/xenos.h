@@ -193,8 +193,9 @@ xenos_status xenos_run_graph(xenos_plan* plan, const void* d_input, void* d_outp
  * each candidate is launched `reps` times on hip_stream and the fastest replaces the cost model's choice.  One full
  * pass runs first so that every buffer holds finite values of the real shapes; since workspace blocks are reused
  * along the pass, a chain is not guaranteed to be timed on its own input (the kernels' run time does not depend on
- * the values), and the call ends with a full pass that leaves d_output valid.  Chains whose plan structure depends on the choice (reduction
- * split, first-layer kernel, linked depthwise producer) keep it.  d_output is overwritten; the JSON of
+ * the values), and the call ends with a full pass that leaves d_output valid.  A chain whose kernel has a weight order of its own (the
+ * 3x3 kernel of link level 3 in bf16, the fp32 wave kernel) chooses among that kernel's tiles.  Chains whose plan structure depends on the
+ * choice (reduction split, first-layer kernels, linked producers) keep it.  d_output is overwritten; the JSON of
  * xenos_plan_query reflects the result ("tuned":1); *n_changed (may be NULL) = chains whose choice changed.
  * Synchronises hip_stream.  Allocates no device memory. */
 xenos_status xenos_plan_tune(xenos_plan* plan, const void* d_input, void* d_output, void* hip_stream,

@@ -112,7 +112,7 @@ struct Step {
   int gap_finish = 0;          // global average linked through the summing pass of a reduction split (few images)
   // every partition the split planner found legal for this chain (tile shape x kernel), for profiling-driven choice;
   // empty when the choice is forced or tied to the structure of the plan (reduction split, stem, linked depthwise)
-  struct Cand { int cfg; ConvArgs a; size_t lds; };
+  struct Cand { int cfg; ConvArgs a; size_t lds; long long ktab_off = -1; };   // (ktab_off: a table of the partition's own, conv3x3_frag_kernel's)
   std::vector<Cand> cands;
   int tuned = 0;               // chosen by measurement (xenos_plan_tune)
   int v_in = -1, v_in2 = -1, v_out = -1;
@@ -173,6 +173,17 @@ uint16_t f2bf_host(float f) {
 }
 
 void write_plan_json(xenos_plan& p);
+
+static bool same_partition(const Step& s, const Step::Cand& c) {
+  const ConvArgs &a = s.conv, &b = c.a;
+  return c.cfg == s.cfg && a.tiles_m == b.tiles_m && a.tiles_n == b.tiles_n && a.halo_bn == b.halo_bn && a.halo_plin == b.halo_plin && a.frag3 == b.frag3 &&
+         a.frag3_wp == b.frag3_wp && a.frag3_ks == b.frag3_ks;
+}
+// a chain's step in the partition of one of its candidates
+static void take_partition(Step& s, const Step::Cand& c) {
+  s.cfg = c.cfg; s.conv = c.a; s.lds = c.lds;
+  if (c.ktab_off >= 0) s.ktab_off = c.ktab_off;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Planner
@@ -829,15 +840,27 @@ struct Planner {
       c.grid = wave_grid(c.ntiles);
       st.cfg = edge == 64 ? kWave64Cfg : kWaveCfg;
       st.lds = conv_wave_lds(edge, conv_wave_stages(edge, c.Kred_pad / (kRowBytes / p.esz), c.ntiles, p.esz), p.esz);
-      if (p.dt == DT_F32) st.cands.clear();                        // (its weights lie in an order of their own)
-      else st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
+      if (p.dt == DT_F32) {                                        // (its weights lie in an order of their own: tiles of either size)
+        st.cands.clear();
+        for (int e : {kWaveRows, 64}) {
+          ConvArgs t = c;
+          t.tiles_m = (c.M_total + e - 1) / e; t.tiles_n = (c.K + e - 1) / e; t.ntiles = t.tiles_m * t.tiles_n;
+          t.grid = wave_grid(t.ntiles);
+          const size_t lds = conv_wave_lds(e, conv_wave_stages(e, c.Kred_pad / (kRowBytes / p.esz), t.ntiles, p.esz), p.esz);
+          if (conv_wave_takes(t, p.esz, e) && lds <= p.hw.lds_bytes_per_cu) st.cands.push_back(Step::Cand{e == 64 ? kWave64Cfg : kWaveCfg, t, lds});
+        }
+      } else {
+        st.cands.push_back(Step::Cand{st.cfg, c, st.lds});
+      }
     }
-    ConvArgs f = c;
-    if (choose_frag3(st, f)) {
-      c = f;
+    std::vector<ConvArgs> variants;
+    const int v = choose_frag3(st, variants);
+    if (v >= 0) {
+      c = variants[v];
       st.cfg = kFrag3Cfg;
       st.lds = frag3_lds(c.frag3, c.frag3_wp, c.frag3_ks);
-      st.cands.clear();                                            // (its weights lie in an order of their own)
+      st.cands.clear();                                            // (its weights lie in an order of their own: its variants)
+      for (const ConvArgs& t : variants) st.cands.push_back(Step::Cand{kFrag3Cfg, t, frag3_lds(t.frag3, t.frag3_wp, t.frag3_ks)});
     }
     return XENOS_OK;
   }
@@ -854,18 +877,19 @@ struct Planner {
     {7, 1, 2, 1, 1.59, 0.00, 1.8, 0.0, 3.6},
     {4, 1, 2, 2, 1.34, 1.91, 0.0, 1.1, 3.5},
   };
-  // Does a 3x3 chain take conv3x3_frag_kernel, and in which variant and tile?  (bf16, link level 3.)  Chains of up to 1024 tiles of 32 x 32 stay with the
+  // Does a 3x3 chain take conv3x3_frag_kernel, in which variants and tiles, and in which of them (the index; -1: it does not)?  (bf16, link level 3.)  Chains of up to 1024 tiles of 32 x 32 stay with the
   // wave kernel, which has a workgroup for each of them (1.0 to 3.3 times its time here); all others go: 559 such graphs 0.735 times the time of
   // the kernels they had, halo, 64 x 64 wave tiles and gather tiles alike, 0.39 to 1.03 (32x56x56 256 channels 114 -> 87 us, 28x28 512 channels
   // 108 -> 84, 14x14 512 channels 37 -> 29, 56x56 64 channels 17.1 -> 14.8, 28x28 128 channels 14.0 -> 11.0, 7x7 512 channels 18.8 -> 14.3).
-  bool choose_frag3(const Step& st, ConvArgs& out) const {
+  int choose_frag3(const Step& st, std::vector<ConvArgs>& variants) const {
     const ConvArgs& c = st.conv;
     const bool zig = c.mode == M_ZIGZAG;
     if (p.dt != DT_BF16 || p.opts.link < 3 || !p.opts.split || p.opts.tile != 0 || st.scalar || st.cfg == kWaveCfg || c.ileave || c.dw_w || c.pair ||
         (!st.gap_finish && (!c.vec_out || (c.has_res && !c.vec_res))) || (c.mode != M_FLAT && !(zig && c.H % 2 == 0 && c.W % 2 == 0)) || !frag3_takes(c))
-      return false;
+      return -1;
     const int num_cu = std::max(1, p.hw.num_cu);
     double best = 1e300;
+    int chosen = -1;
     for (const Frag3Variant& v : kFrag3Variants) {
       const int rows = v.pb * v.wp * 16, bn = 128 / (v.wp * v.ks), step = zig ? 2 : 1;
       if (c.C % (32 * v.ks) || frag3_lds(v.pb, v.wp, v.ks) > p.hw.lds_bytes_per_cu) continue;
@@ -886,15 +910,14 @@ struct Planner {
       const long long round = (long long)v.slots * num_cu, full = items / round, rest = items % round;
       const double alone = chunks * v.alone + v.around1, pair = v.slots == 2 ? chunks * v.pair + v.around2 : alone;
       const double us = v.launch + full * pair + (rest == 0 ? 0 : rest <= num_cu ? alone : pair);
-      if (us >= best) continue;
-      best = us;
       t.frag3 = v.pb; t.frag3_wp = v.wp; t.frag3_ks = v.ks; t.halo_bn = bn;
       t.tiles_m = c.N * t.tiles_y * t.tiles_x; t.tiles_n = (c.K + bn - 1) / bn; t.ntiles = t.tiles_m * t.tiles_n;
       // (as many workgroups for every XCD as the largest of their ranges has items)
       t.grid = std::min((t.ntiles + 7) / 8 * 8, std::max(8, v.slots * num_cu / 8 * 8));
-      out = t;
+      if (us < best) { best = us; chosen = (int)variants.size(); }
+      variants.push_back(t);
     }
-    return best < 1e300;
+    return chosen;
   }
   // Which pixel of a tile row r of block b of conv3x3_frag_kernel is: (ty << 8) | tx, 0xffff none.  A fragment read serves rows 0 - 3 and 12 - 15 of one
   // 16-byte chunk and rows 4 - 11 of the chunk two further on at a time; at a pitch of five slots these sixteen lanes hit sixteen of them where the first eight
@@ -2388,8 +2411,16 @@ struct Planner {
         if (rc != XENOS_OK) return rc;
         if (st.cfg == kWaveCfg || st.cfg == kWave64Cfg || st.cfg == kFrag3Cfg) hsplit.ks = 0;
         if (st.cfg == kFrag3Cfg) {
-          const std::vector<uint16_t> tab = frag3_table(a);
-          st.ktab_off = (long long)wpush(tab.data(), tab.size() * 2);
+          const auto push_table = [&](const ConvArgs& t) {
+            const std::vector<uint16_t> tab = frag3_table(t);
+            return (long long)wpush(tab.data(), tab.size() * 2);
+          };
+          if (st.gap_finish) st.cands.clear();                     // (the plan's structure depends on the variant)
+          for (Step::Cand& cand : st.cands) {
+            cand.ktab_off = push_table(cand.a);
+            if (same_partition(st, cand)) st.ktab_off = cand.ktab_off;
+          }
+          if (st.cands.empty()) st.ktab_off = push_table(a);
         }
         if (hsplit.ks >= 2) a.kchunk = 1;                          // (the order of the halo kernel, which runs the chain whatever split_conv chose)
         pack_weights();
@@ -3310,7 +3341,7 @@ xenos_status xenos_plan_tune(xenos_plan* plan, const void* d_input, void* d_outp
     float best_ms = 0.f, incumbent_ms = 0.f;
     for (size_t ci = 0; ci < s.cands.size() && rc == XENOS_OK; ++ci) {
       Step trial = s;
-      trial.cfg = s.cands[ci].cfg; trial.conv = s.cands[ci].a; trial.lds = s.cands[ci].lds;
+      take_partition(trial, s.cands[ci]);
       if (launch_step(*plan, trial, d_input, d_output, hip_stream) != XENOS_OK) continue;   // warm-up; a candidate that cannot launch is skipped
       if (hipEventRecord(e0, st) != hipSuccess) { rc = fail(XENOS_EDEVICE, "xenos_plan_tune: event record failed"); break; }
       for (int r = 0; r < reps; ++r) (void)launch_step(*plan, trial, d_input, d_output, hip_stream);
@@ -3320,18 +3351,16 @@ xenos_status xenos_plan_tune(xenos_plan* plan, const void* d_input, void* d_outp
         break;
       }
       if (best < 0 || ms < best_ms) { best = (int)ci; best_ms = ms; }
-      const Step::Cand& cc = s.cands[ci];
-      if (cc.cfg == s.cfg && cc.a.tiles_m == s.conv.tiles_m && cc.a.tiles_n == s.conv.tiles_n && cc.a.halo_bn == s.conv.halo_bn &&
-          cc.a.halo_plin == s.conv.halo_plin) { incumbent = (int)ci; incumbent_ms = ms; }
+      if (same_partition(s, s.cands[ci])) { incumbent = (int)ci; incumbent_ms = ms; }
     }
     if (rc != XENOS_OK) break;
     // a few short trials time a chain to 2-3 %: the cost model's choice is given up only for a clear win
     if (best >= 0 && incumbent >= 0 && best != incumbent && best_ms > 0.96f * incumbent_ms) { best = incumbent; best_ms = incumbent_ms; }
     if (best >= 0) {
       const Step::Cand& c = s.cands[best];
-      const bool same = c.cfg == s.cfg && c.a.tiles_m == s.conv.tiles_m && c.a.tiles_n == s.conv.tiles_n && c.a.halo_bn == s.conv.halo_bn && c.a.halo_plin == s.conv.halo_plin;
-      if (!same) ++changed;
-      s.cfg = c.cfg; s.conv = c.a; s.lds = c.lds; s.tuned = 1;
+      if (!same_partition(s, c)) ++changed;
+      take_partition(s, c);
+      s.tuned = 1;
       // the last trial may not have been the winner: leave the winner's output in the workspace for the next chain
       if (launch_step(*plan, s, d_input, d_output, hip_stream) != XENOS_OK) { rc = fail(XENOS_EDEVICE, "xenos_plan_tune: launch failed"); break; }
     }

@@ -336,6 +336,17 @@ def test_partition_candidates_and_tune_argument_checks():
         X.xenos_destroy(G)
 
 
+def test_kernels_with_a_weight_order_of_their_own_have_candidates_in_it():
+    # the variants of the 3x3 kernel whose weights go into registers, and either tile of the fp32 wave kernel
+    q = plan_json(wg.build(3, 32, draw=False), link=3, compute=X.XENOS_BF16)["plan"]
+    frag = [c for c in q["chains"] if c.get("frag3")]
+    assert len(frag) > 6 and all(c["candidates"] == 5 for c in frag)
+    wave = [c for c in plan_json(wg.build(4, 32, draw=False), link=3, compute=X.XENOS_F32)["plan"]["chains"] if c.get("wave") and c["loader"] == "vector"]
+    assert {c["bm"] for c in wave} == {32, 64}
+    for c in wave:                                                     # (raw sums for a summing pass: the plan depends on the tile)
+        assert c["candidates"] == (0 if c["out"]["tensor"] < 0 else 2), c
+
+
 def test_run_entry_points_reject_bad_arguments_before_any_launch():
     # xenos_run / xenos_run_with / xenos_run_static / xenos_run_graph / xenos_run_chain on a plan that is not bound, and
     # null pointers: XENOS_EINVAL with a message, nothing touches the device (there is none here)

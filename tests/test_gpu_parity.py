@@ -1593,6 +1593,29 @@ def test_table4_micro_benchmark_operators(name, compute):
         assert np.array_equal(y, y0)
 
 
+@pytest.mark.parametrize("num_cu", [8, 256])
+@pytest.mark.parametrize("compute", [0, 1])
+def test_profiled_partitions_of_kernels_with_a_weight_order_of_their_own(compute, num_cu):
+    # the plan for eight units takes variants that the device has faster ones for; a tuned chain keeps its weights and brings its pixel table
+    b = wg.builder("tuned", (4, 24, 58, 60), 57, nonzero_bias=True)
+    t = b.cbr(0, 64, 1, name="pre")
+    t = b.cbr(b.cbr(t, 128, 3, 1, 1, name="a"), 192, 3, 1, 1, name="b")
+    t = b.cbr(b.maxpool(t, 2, 2), 128, 3, 1, 1, name="c")
+    g = b.finish(b.cbr(t, 64, 1, name="d"))
+    ref = xo.forward(g)
+    X = _xenos()
+    s = X.Session(g, link=3, compute=compute, hw=dict(X.MI355X, num_cu=num_cu))
+    try:
+        assert rel_err(s.forward(g.x), ref) <= TOL[compute]
+        tun = [c["i"] for c in s.info["chains"] if c["kind"] == "conv" and c["candidates"] >= 2]
+        assert any(c.get("frag3") if compute else c["wave"] for c in s.info["chains"] if c["i"] in tun)
+        print("changed", s.tune(reps=3), flush=True)
+        assert all(c["tuned"] == 1 for c in s.info["chains"] if c["i"] in tun)
+        assert rel_err(s.forward(g.x), ref) <= TOL[compute]
+    finally:
+        s.close()
+
+
 @pytest.mark.parametrize("net,compute", [("resnet", 1), ("squeezenet", 0), ("vgg", 1)])
 def test_profiling_driven_partition_choice(net, compute):
     # xenos_plan_tune: every legal partition of every tunable chain is profiled on the device and the fastest kept
