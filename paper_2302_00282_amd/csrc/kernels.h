@@ -93,8 +93,9 @@ static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;
 constexpr int kWaveStageF32 = 32 * 128 + 3 * 32 * 64;   // fp32: LDS of a step, 32 pixel rows and the three bf16 parts of 32 channel rows
 // fp32 operands of the wave kernels are taken apart as multiples of 2^-24: the smallest number of fp32, 2^-149, then is a normal number of bf16 (2^-126 and
-// more), so that three parts hold every number below kWavePartMost, and its products what fp32 would hold of them and more
-constexpr float kWavePartScale = 16777216.f, kWavePartMost = 0x1p103f;
+// more), so that three parts hold every number below 2^103, and its products what fp32 would hold of them and more
+constexpr float kWavePartScale = 16777216.f;
+constexpr unsigned kWavePartMostBits = (127u + 103u) << 23;      // 2^103
 constexpr unsigned short kWaveWholeWeight = 0x7fc0;   // in the place of a weight's upper part: the other two are the halves of the fp32 number itself
 static const int kWave64Cfg = 13;      // the same in tiles of 64 x 64
 // Configuration index of the kernel that computes a first layer's 2x2 pooling windows on the vector unit, a window x kFirstChannels channels per thread

@@ -115,7 +115,7 @@ struct WaveTile {
 };
 
 // Three bf16 values whose sum is x * kWavePartScale (each rounds what the ones before it leave; the third is exact, eight of the 24 bits), whatever x is
-// below kWavePartMost.  Infinite values, and finite ones that become so, leave NaN.
+// below 2^103.  Infinite values, and finite ones that become so, leave NaN.
 struct Split8 { bf16x8_t hi, mid, lo; };
 __device__ __forceinline__ Split8 split8(const u32x4_t& a, const u32x4_t& b) {
   u32x4_t p[3];
