@@ -1110,7 +1110,9 @@ struct Planner {
     if (disjoint ? nsteps <= 4 || (nsteps <= 9 && filled && (to_caller || (tiles >= 400 && tiles <= 2400))) : nsteps <= (to_caller ? 6 : 2) && (to_caller || tiles <= 2400)) return false;
     return wave_edge(t) != 0;
   }
-  // The same of a chain whose global average moves to the summing pass.  (32x200x200, 64 -> 512 channels, on the general kernel: 2.6 GB of sums.)
+  // The same of a chain whose global average moves to the summing pass.  (32x200x200, 64 -> 512 channels, on the general kernel: 2.6 GB of sums.)  Short reductions keep the
+  // average in their tiles: what they would save is less than the raw sums cost.  Times apart over linked, 300 graphs of more images than two workgroups a
+  // unit, 4x4 to 60x60: one and two steps 1.3 (up to 2.0), three to six 1.16 on maps of less than 150 pixels and 0.88 on larger ones, seven and more 0.70.
   bool wave_takes_average(const Step& st) const {
     Step t = st;
     ConvArgs& a = t.conv;
@@ -1118,6 +1120,8 @@ struct Planner {
     t.gap_finish = 1;
     a.mode = M_FLAT; a.pool = POOL_NONE; a.M_total = a.N * a.OH * a.OW;
     set_reduction(t, a.C, a.R, a.S);
+    const int nsteps = a.Kred_pad / (kRowBytes / p.esz);
+    if (nsteps < 7 && (nsteps < 3 || a.OH * a.OW < 150)) return false;
     return wave_edge(t) != 0;
   }
   bool aligned_res(const View& rv, int K) const { return K % p.ce == 0 && rv.off % p.ce == 0 && rv.sP % p.ce == 0 && rv.sN % p.ce == 0; }

@@ -697,13 +697,17 @@ def test_fp32_window_pooling_stays_linked_where_the_wave_kernel_refuses_the_conv
     assert conv["wave"] or not apart
 
 
-@pytest.mark.parametrize("n,hw,apart", [(32, 200, 0), (31, 184, 0), (31, 100, 0), (20, 100, 1), (32, 13, 1), (1, 13, 1)])
-def test_fp32_global_average_stays_linked_where_the_wave_kernel_refuses_the_convolution(n, hw, apart):
-    # 2^20 pixels or 2^15 tiles and more (31x100x100: 4844 times 8 of 64 x 64): no sums of every pixel for a pass to read
+@pytest.mark.parametrize("n,hw,c,apart", [
+    (32, 200, 256, 0), (31, 184, 256, 0), (31, 100, 256, 0), (20, 100, 256, 1), (32, 13, 256, 1),
+    # steps of 32 channels: six on a map of 144 and of 169 pixels, seven; two and three
+    (32, 12, 192, 0), (32, 13, 192, 1), (32, 12, 224, 1), (32, 20, 64, 0), (32, 20, 96, 1), (1, 13, 64, 1)])
+def test_fp32_global_average_stays_linked_where_that_is_faster(n, hw, c, apart):
+    # 2^20 pixels or 2^15 tiles and more, which the wave kernel refuses (31x100x100: 4844 times 8 of 64 x 64): no sums of every pixel for a pass to read.
+    # Short reductions of many images neither
     b = undrawn((n, 8, hw, hw))
-    t = b.cbr(b.cbr(0, 64, 1, name="a"), 512, 1, name="b")
+    t = b.cbr(b.cbr(0, c, 1, name="a"), 512, 1, name="b")
     chains = plan_json(b.finish(b.gap(t)), link=3, compute=X.XENOS_F32)["plan"]["chains"]
-    conv, = [ch for ch in chains if ch["kind"] == "conv" and (ch["C"], ch["K"]) == (64, 512)]
+    conv, = [ch for ch in chains if ch["kind"] == "conv" and (ch["C"], ch["K"]) == (c, 512)]
     assert (conv["mode"] != "gap") == bool(apart) and bool(conv["wave"]) == bool(apart) and sum(ch["kind"] == "splitk_finish" for ch in chains) == apart
 
 
