@@ -87,7 +87,7 @@ static const int kFireMaxPositions = 400;
 // Configuration index of the kernel that runs pointwise -> depthwise 3x3 -> pointwise as one chain, a tile of output pixels x all
 // channels per workgroup
 static const int kUnitCfg = 11;
-// Configuration index of the kernel for chains of few pixels: tiles of kWaveRows pixels x kWaveChannels channels, the reduction of a tile
+// Configuration index of the kernel for chains of few pixels (fp32 at link level 3: of any number): tiles of kWaveRows pixels x kWaveChannels channels, the reduction of a tile
 // shared out over the wavefronts of its workgroup
 static const int kWaveCfg = 12;
 static const int kWaveRows = 32, kWaveChannels = 32;

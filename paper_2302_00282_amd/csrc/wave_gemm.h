@@ -1,4 +1,5 @@
-// The reduction of a small chain shared out over the wavefronts of a workgroup (device code of the wave kernels).
+// The reduction of a tile shared out over the wavefronts of a workgroup (device code of the wave kernels): the chains of few pixels in bf16, and
+// every dense chain in fp32, whose products are made on the bf16 MFMAs here.
 //
 // At batch 1 a chain is 30 to 250 workgroups whose time is a chain of latencies, not bytes or MFMAs.  With all four wavefronts on one
 // tile step by step (request into registers, write to LDS, barrier, read fragments, multiply) a step of 128 bytes per row takes 690
@@ -28,9 +29,10 @@ __device__ __forceinline__ void load_to_lds(rsrc_t w, unsigned char* dst, unsign
   __builtin_amdgcn_raw_ptr_buffer_load_lds(w, (lds_ptr_t)dst, 16, (int)off, (int)soff, 0, 0);
 }
 
-// A wavefront's share of a tile of 32 * NB rows x 32 * NB channels (transposed: accumulator rows are channels, columns the tile's rows).
+// A wavefront's share of a tile of 32 * NB rows x 32 * NB channels (transposed: accumulator rows are channels, columns the tile's rows).  This is bf16; fp32 below
 template <typename T, int NB>
 struct WaveTile {
+  static_assert(sizeof(T) == 2, "fp32 has a form of its own");
   static constexpr int EDGE = 32 * NB;
   static constexpr int STAGE = 2 * EDGE * ROWB;        // LDS of a step: pixel rows, then channel rows
   static constexpr int LOADS = 2 * EDGE / 8;           // requests of a step
@@ -84,15 +86,8 @@ struct WaveTile {
 #pragma unroll
         for (int r = 0; r < NB; ++r)
 #pragma unroll
-          for (int c = 0; c < NB; ++c) {
-            if constexpr (sizeof(T) == 2) {
-              acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[c][kg]), __builtin_bit_cast(bf16x8_t, fa[r][kg]), acc[r][c], 0, 0, 0);
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[c][kg][e]), __uint_as_float(fa[r][kg][e]), acc[r][c], 0, 0, 0);
-            }
-          }
+          for (int c = 0; c < NB; ++c)
+            acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fb[c][kg]), __builtin_bit_cast(bf16x8_t, fa[r][kg]), acc[r][c], 0, 0, 0);
       if (++st == stages) { st = 0; s = s_w; } else { s += STAGE; }
     }
     // the partial tile, [row][channel], in this wavefront's own LDS; four channels of row r lie in slot (their number ^ r)

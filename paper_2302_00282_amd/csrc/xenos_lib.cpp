@@ -877,7 +877,8 @@ struct Planner {
     {7, 1, 2, 1, 1.59, 0.00, 1.8, 0.0, 3.6},
     {4, 1, 2, 2, 1.34, 1.91, 0.0, 1.1, 3.5},
   };
-  // Does a 3x3 chain take conv3x3_frag_kernel, in which variants and tiles, and in which of them (the index; -1: it does not)?  (bf16, link level 3.)  Chains of up to 1024 tiles of 32 x 32 stay with the
+  // Does a 3x3 chain take conv3x3_frag_kernel, in which variants and tiles, and in which of them (the index; -1: it does not)?  (bf16, link level 3;
+  // link level 2 keeps the kernels that the planner's tests fix of its plans.)  Chains of up to 1024 tiles of 32 x 32 stay with the
   // wave kernel, which has a workgroup for each of them (1.0 to 3.3 times its time here); all others go: 559 such graphs 0.735 times the time of
   // the kernels they had, halo, 64 x 64 wave tiles and gather tiles alike, 0.39 to 1.03 (32x56x56 256 channels 114 -> 87 us, 28x28 512 channels
   // 108 -> 84, 14x14 512 channels 37 -> 29, 56x56 64 channels 17.1 -> 14.8, 28x28 128 channels 14.0 -> 11.0, 7x7 512 channels 18.8 -> 14.3).

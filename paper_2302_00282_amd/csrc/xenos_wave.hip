@@ -1,4 +1,4 @@
-// gfx950 (CDNA4) kernels of the chains of few pixels:
+// gfx950 (CDNA4) kernels of the chains of few pixels (bf16) and of every dense chain (fp32 at link level 3):
 //
 //  conv_wave_kernel   implicit-GEMM convolution chain (any kernel size and stride) in tiles of 32 pixels x 32 channels (or 64 x 64), the
 //                     reduction of a tile shared out over the four wavefronts of its workgroup (wave_gemm.h); scale / shift, shortcut
