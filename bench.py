@@ -374,7 +374,7 @@ def pmc_traffic(workload):
     """HBM bytes per launch of the dominant kernel.  rocprofv3 counters cannot be read from inside the timed process,
     so this is the value of the committed counter summary (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script
     on the same workload, link level and partition policy), returned with the file it comes from; None if there is none."""
-    rel = os.path.join("profiles", "conv3x3_kernel_%s_pmc.txt" % workload)
+    rel = os.path.join("profiles", "conv3x3_frag_kernel_%s_pmc.txt" % workload)
     val, plan = None, ""
     try:
         for ln in open(os.path.join(ROOT, rel)):
