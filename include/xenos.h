@@ -105,10 +105,13 @@ typedef struct {
  *        1 = fused CBR only; pooling / add / concat stay separate passes (the "HO baseline")
  *        2 = operator linking on (Section 4.1): CBR + pool, shortcut add, concat-by-offset
  *        3 = 2 plus the chains whose intermediate tensor stays on chip (Table 1, ConvX -> ConvY): depthwise -> pointwise
- *            and pointwise -> depthwise (Section 2.2 example), from 1024 output pixels on pointwise -> depthwise -> pointwise where
- *            the planner expects one chain to be faster than two,
+ *            and pointwise -> depthwise (Section 2.2 example), pointwise -> depthwise -> pointwise where the planner expects one chain to
+ *            be faster than two (below 1024 output pixels: more images than one and at most 512 bytes of depthwise channels a pixel),
  *            a 1x1 squeeze convolution -> its 1x1 and 3x3 expand
- *            convolutions -> concat (-> max-pool), and, on the bf16 path, a first-layer 3x3 -> 3x3 convolution pair
+ *            convolutions -> concat (-> max-pool), and, on the bf16 path, a first-layer 3x3 -> 3x3 convolution pair.  On the fp32
+ *            path poolings and global averages are taken apart again where the convolution alone is faster on another kernel: a plan may
+ *            need up to twice the workspace of level 2's (not more than XENOS_STATIC_WORKSPACE_BYTES where the linked plan needs no more);
+ *            packed fp32 weights take up to 1.5 times the parameters' bytes at any level
  * split: 0 = every chain runs on ONE compute unit (no operator split; for tests)
  *        1 = DSP-aware operator split (Section 4.2): output channels first, then H/W, then (layers whose output tiles
  *            leave most units idle) the reduction, whose shares a summing pass adds in index order
