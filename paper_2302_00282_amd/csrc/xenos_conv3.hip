@@ -51,9 +51,10 @@ __device__ constexpr int patch_store_at(int it) { return PB > 7 ? (it < HALF ? 4
 // Rows are a pitch of five 16-byte slots apart, an odd number, so that a tap is an added offset.  Requests lie between pairs of MFMAs one at a time: two
 // in a row hold a wavefront up (43 cycles a tap).
 // VGG-16 batch 32: 128 channels 112x112 114 -> 98 us, 256 56x56 115 -> 88 (1340 TFLOP/s), 512 28x28 108 -> 85 (1390), 512 14x14 38 -> 29.5; by the counters MFMA
-// pipes are 57 to 66 % busy in the first three at 2.1 to 2.2 GHz, 38 in the last, and 8 to 30 % of the LDS cycles are bank conflicts (most in the pooled forms).  A workgroup alone on its unit takes 2950 cycles for a chunk of 126 MFMAs: without its weight requests 2600, without its fragment
-// reads 2750.  Three patch buffers with the barrier in the middle of a chunk and fragments that run on across chunks took 1 to 10 % longer (they
-// spill, or the barrier waits for more reads), fragments nine ahead instead of six the same.
+// pipes are 57 to 66 % busy in the first three at 2.1 to 2.2 GHz, 38 in the last, and 8 to 30 % of the LDS cycles are bank conflicts (most in the pooled forms).
+// A workgroup alone on its unit takes 2950 cycles for a chunk of 126 MFMAs: without its weight requests 2600, without its fragment reads 2750.  Three patch
+// buffers with the barrier in the middle of a chunk and fragments that run on across chunks took 1 to 10 % longer (they spill, or the barrier waits for more
+// reads), fragments nine ahead instead of six the same.
 // PB blocks of 16 pixels per wavefront; the four wavefronts are WP groups of pixels x KS shares of the reduction x groups of 32 channels.
 template <int PB, int WP, int KS, bool ZIG>
 __global__ __launch_bounds__(NT, 2) void conv3x3_frag_kernel(const Frag3Args a) {
