@@ -1084,11 +1084,12 @@ struct Planner {
   // Does the wave kernel run a convolution of `iv` once the window pooling behind it is a pass of its own, its output a tensor by itself?  (Where it refuses, more
   // than 2^20 - 32 pixels for instance, the chain keeps its pooling: the same kernel would write the whole map for the pass to read again.  VGG-16 fp32 batch 32
   // has 411 MB more to move in its second layer and 822 MB of workspace instead of 514.)
-  // Short reductions keep it too, whose linked chain costs less than the second launch and the bytes of the map.  Times apart over linked, 900 graphs of a
+  // Short reductions keep it too, whose linked chain costs less than the second launch and the bytes of the map.  Times apart over linked, 1200 graphs of a
   // convolution and a max-pooling, 128-byte steps of the reduction: 2x2 windows, which share no pixel, one to four steps 1.15 on average (0.89 to 1.69), five to
-  // nine 1.14 from 400 to 2400 tiles of 32 x 32 whose channels mostly fill 64 (0.98 to 1.40), 0.73 to 1.08 in others; ten to fourteen 0.82.  Other windows one
+  // nine 1.1 from 400 to 2400 tiles of 32 x 32 whose channels fill three quarters of 64 (0.90 to 1.40), 0.73 to 1.08 in others; ten to fourteen 0.82.  Other windows one
   // and two 1.00 (0.71 to 1.47; then linked, without the map in memory), five to nine 0.82.  In front of an output in the caller's order, which the pooling pass doesn't
-  // write, up to nine steps 1.35 and up to six 1.2; 3x3 layers of 64 channels and more 0.44 to 0.8 in all of them.
+  // write, 2x2 windows up to nine steps 1.35, up to eighteen 1.16 from 700 to 2400 tiles (1.00 to 1.31) and 0.83 in others; other windows up to six 1.2, up to nine 1.12
+  // from 400 to 2400 tiles.  Longer reductions 0.36 to 1.1, on average 0.7.
   bool wave_takes_apart(const View& iv, const Shape& is, const xenos_op_desc& d, const Shape& os, int res_tid, const xenos_op_desc& pd, bool to_caller) const {
     Step t;
     ConvArgs& a = t.conv;
@@ -1107,8 +1108,12 @@ struct Planner {
     const int nsteps = a.Kred_pad / (kRowBytes / p.esz);
     const long long tiles = (long long)((a.M_total + 31) / 32) * ((a.K + 31) / 32);
     const bool disjoint = pd.kh == 2 && pd.kw == 2 && pd.stride_h == 2 && pd.pad_h == 0;
-    const bool filled = 4 * a.K > 3 * ((a.K + 63) / 64 * 64);
-    if (disjoint ? nsteps <= 4 || (nsteps <= 9 && filled && (to_caller || (tiles >= 400 && tiles <= 2400))) : nsteps <= (to_caller ? 6 : 2) && (to_caller || tiles <= 2400)) return false;
+    const bool filled = 4 * a.K >= 3 * ((a.K + 63) / 64 * 64), middle = filled && tiles >= 400 && tiles <= 2400;
+    if (disjoint) {
+      if (nsteps <= 4 || (nsteps <= 9 && (to_caller ? filled : middle)) || (to_caller && nsteps <= 18 && middle && tiles >= 700)) return false;
+    } else if (to_caller ? nsteps <= 6 || (nsteps <= 9 && middle) : nsteps <= 2 && tiles <= 2400) {
+      return false;
+    }
     return wave_edge(t) != 0;
   }
   // The same of a chain whose global average moves to the summing pass.  (32x200x200, 64 -> 512 channels, on the general kernel: 2.6 GB of sums.)  Short reductions keep the

@@ -725,11 +725,13 @@ def test_fp32_plans_within_the_static_workspace_link_only_the_poolings_of_large_
 
 @pytest.mark.parametrize("n,c,hw,k,ksz,pool,last,nhwc,apart", [
     # disjoint windows: four steps of 32 channels and taps, five to nine by the number of 32 x 32 tiles, ten
-    (2, 128, 32, 64, 1, 2, 0, 1, 0), (2, 160, 32, 64, 1, 2, 0, 1, 1), (2, 288, 80, 64, 1, 2, 0, 1, 0), (2, 288, 80, 48, 1, 2, 0, 1, 1), (2, 320, 80, 64, 1, 2, 0, 1, 1), (2, 160, 160, 64, 1, 2, 0, 1, 1),
+    (2, 128, 32, 64, 1, 2, 0, 1, 0), (2, 160, 32, 64, 1, 2, 0, 1, 1), (2, 288, 80, 64, 1, 2, 0, 1, 0), (2, 288, 80, 48, 1, 2, 0, 1, 0), (2, 288, 80, 40, 1, 2, 0, 1, 1), (2, 320, 80, 64, 1, 2, 0, 1, 1), (2, 160, 160, 64, 1, 2, 0, 1, 1),
     # overlapping ones
     (2, 64, 33, 64, 1, 3, 0, 1, 0), (2, 96, 33, 64, 1, 3, 0, 1, 1), (8, 64, 80, 64, 1, 3, 0, 1, 1),
     # the graph's output, in the caller's order and in the pooling pass's
-    (2, 288, 32, 64, 1, 2, 1, 0, 0), (2, 320, 32, 64, 1, 2, 1, 0, 1), (2, 288, 32, 64, 1, 2, 1, 1, 1), (2, 192, 33, 64, 1, 3, 1, 0, 0), (2, 224, 33, 64, 1, 3, 1, 0, 1)])
+    (2, 288, 32, 64, 1, 2, 1, 0, 0), (2, 288, 32, 40, 1, 2, 1, 0, 1), (2, 320, 32, 64, 1, 2, 1, 0, 1), (2, 288, 32, 64, 1, 2, 1, 1, 1),
+    (3, 576, 64, 64, 1, 2, 1, 0, 0), (3, 608, 64, 64, 1, 2, 1, 0, 1), (3, 576, 60, 64, 1, 2, 1, 0, 1), (8, 64, 56, 64, 3, 2, 1, 0, 0),
+    (2, 192, 33, 64, 1, 3, 1, 0, 0), (2, 224, 33, 64, 1, 3, 1, 0, 1), (4, 288, 64, 64, 1, 3, 1, 0, 0), (4, 320, 64, 64, 1, 3, 1, 0, 1)])
 def test_fp32_window_pooling_behind_a_short_reduction_stays_linked(n, c, hw, k, ksz, pool, last, nhwc, apart):
     b = undrawn((n, 8, hw, hw))
     t = b.maxpool(b.cbr(b.cbr(0, c, 1, name="a"), k, ksz, 1, ksz // 2, name="b"), pool, 2)
